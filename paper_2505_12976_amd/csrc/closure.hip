@@ -31,11 +31,13 @@
 // wait ends;
 // a bounded spin turns anything else into a device error instead of a hang.
 //
-// uint16 matrices run two columns per 32-bit lane with v_pk_min_u16 and
-// v_pk_max_u16 (one instruction per update); int32 matrices use v_min_i32
-// and v_max3_i32 over pairs of k.  The matrix is padded with zero rows and
-// columns to a multiple of B; padded vertices have no edges and change
-// nothing.
+// uint16 matrices run two columns per 32-bit lane, as half-precision keys
+// with v_pk_minimum3_f16 and v_pk_maximum3_f16 over pairs of k (0.75 lane
+// operations per update; fw_tiles.h), or with v_pk_min_u16 and v_pk_max_u16
+// (one) when a value has no key of its own order; int32 matrices use
+// v_min_i32 and v_max3_i32 over pairs of k (1.5).  The matrix is padded with
+// zero rows and columns to a multiple of B; padded vertices have no edges
+// and change nothing.
 #include "fw_tiles.h"
 #include "tile_io.h"
 
@@ -53,11 +55,14 @@ __device__ inline bool gated_off(const int32_t *gate, int32_t want) { return gat
 // ------------------------------------------------------------------ weights
 // P[i][j] = edge weight from d (winning votes or margin); zero padding.  A
 // workgroup takes the pair of 64 x 64 tiles (I, J) and (J, I), I <= J: both
-// need the same two blocks of d, so every count is read once.
+// need the same two blocks of d, so every count is read once.  With `wide`
+// (uint16 only) the weights are stored as half-precision keys, and *wide is
+// set when one of them is above KEY_MAX.
 template <typename E>
 __global__ __launch_bounds__(256) void k_weights(const E *__restrict__ d, int64_t ldd, int32_t m, int mode,
                                                  E *__restrict__ P, int64_t ld, int32_t mp, int dvec,
-                                                 const int32_t *gate = nullptr, int32_t want = 0) {
+                                                 int32_t *wide = nullptr, const int32_t *gate = nullptr,
+                                                 int32_t want = 0) {
     __shared__ E a[64][65];  // a[r][c] = d[I0 + r][J0 + c]
     __shared__ E b[64][65];  // b[r][c] = d[J0 + r][I0 + c]
     if (blockIdx.y > blockIdx.x || gated_off(gate, want)) return;
@@ -65,25 +70,51 @@ __global__ __launch_bounds__(256) void k_weights(const E *__restrict__ d, int64_
     tio::load<E>(a, d, ldd, I0, J0, m, m, dvec != 0);
     tio::load<E>(b, d, ldd, J0, I0, m, m, dvec != 0);
     __syncthreads();
+    bool above = false;
     auto weight = [&](E x, E y, bool diag) -> E {  // edge weight given d[i][j] = x, d[j][i] = y
-        if (diag || x <= y) return (E)0;
-        return mode == SCHULZE_MARGIN ? (E)(x - y) : x;
+        const E w = diag || x <= y ? (E)0 : mode == SCHULZE_MARGIN ? (E)(x - y) : x;
+        if constexpr (sizeof(E) == 2) {
+            if (wide) {
+                above |= w > KEY_MAX;
+                return key_of(w);
+            }
+        }
+        return w;
     };
     // the workspace matrix is 16-byte aligned with a pitch that is a multiple of 64
     tio::store<E>(P, ld, I0, J0, mp, mp, true, [&](int r, int c) { return weight(a[r][c], b[c][r], I0 + r == J0 + c); });
     if (I0 != J0)  // the mirrored tile (J, I)
         tio::store<E>(P, ld, J0, I0, mp, mp, true, [&](int r, int c) { return weight(b[r][c], a[c][r], false); });
+    if (above) *wide = 1;
 }
 
 // p[i][j] = P[i][j] for i != j, 0 on the diagonal; one workgroup per row.
+// With `wide` (uint16 only) P holds half-precision keys unless *wide is set.
 template <typename E>
 __global__ __launch_bounds__(256) void k_fw_store(const E *__restrict__ P, int64_t ld, int32_t m, E *__restrict__ p,
-                                                  int64_t ldp, const int32_t *gate, int32_t want) {
+                                                  int64_t ldp, const int32_t *wide, const int32_t *gate,
+                                                  int32_t want) {
     if (gated_off(gate, want)) return;
     const int32_t i = blockIdx.x;
     const E *src = P + (int64_t)i * ld;
     E *dst = p + (int64_t)i * ldp;
+    if constexpr (sizeof(E) == 2) {
+        if (wide && !*wide) {
+            for (int32_t j = threadIdx.x; j < m; j += 256) dst[j] = i == j ? (E)0 : key_value(src[j]);
+            return;
+        }
+    }
     for (int32_t j = threadIdx.x; j < m; j += 256) dst[j] = i == j ? (E)0 : src[j];
+}
+
+// A matrix of keys back to values, and *wide set (only when the persistent
+// launch that takes keys was refused).
+__global__ __launch_bounds__(256) void k_fw_decode(uint16_t *__restrict__ P, int64_t count, int32_t *wide,
+                                                   const int32_t *gate, int32_t want) {
+    if (gated_off(gate, want)) return;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
+        P[i] = key_value(P[i]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *wide = 1;
 }
 
 // ------------------------------------------------------------------ persistent launch
@@ -100,6 +131,7 @@ struct PersistArgs {
     int32_t early_panels; // run round r+1's panels ahead of round r's last tiles when possible
     const int32_t *gate;  // run only if *gate == gate_want (nullptr: always)
     int32_t gate_want;
+    const int32_t *wide;  // uint16 only: P holds half-precision keys, closed as such unless *wide is set
 };
 
 constexpr int MAX_OWNED = 512;
@@ -184,36 +216,14 @@ __device__ inline void acc_store_agent(const Acc<E, B> &a, E *dst, int64_t ld) {
     }
 }
 
+// What one workgroup of the persistent launch does: lds and owned are the
+// kernel's shared memory, owned[0 .. no-1] the workgroup's tiles.
 template <typename E, int B>
-__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : (B < 128 ? 2 : 1)) void k_fw_persist(PersistArgs<E> a) {
-    using C = Cfg<E, B>;
+__device__ __forceinline__ void persist_run(const PersistArgs<E> &a, E *lds, const int32_t *owned, int32_t no,
+                                            int32_t &probe_seen) {
     constexpr int DS = diag_steps<E, B>();
-    constexpr int DIAG_LDS = diag_lds_elems<E, B, DS, true>();
-    __shared__ __attribute__((aligned(16))) E lds[C::LDS_ELEMS > DIAG_LDS ? C::LDS_ELEMS : DIAG_LDS];
-    __shared__ int32_t owned[MAX_OWNED];
-    __shared__ int32_t n_owned;
     const int32_t nb = a.nb, G = gridDim.x, w = blockIdx.x;
     const int64_t tile_elems = (int64_t)B * B;
-    if (gated_off(a.gate, a.gate_want)) return;  // uniform over the grid: every workgroup leaves
-
-    // Tiles this workgroup owns, in ascending tile number: the numbers
-    // k = w, w + G, w + 2G, ... stand for block row I = k / nb and column
-    // J = (k mod nb - I) mod nb (the inverse of the owner map below).
-    if (threadIdx.x == 0) n_owned = (int32_t)((nb * nb - w + G - 1) / G);
-    __syncthreads();
-    const int32_t no = n_owned;
-    for (int32_t q = threadIdx.x; q < no && q < MAX_OWNED; q += 256) {
-        const int32_t k = w + q * G, I = k / nb;
-        owned[q] = I * nb + ((k % nb) - I + nb) % nb;
-    }
-    __syncthreads();
-    if (no > MAX_OWNED) {  // the host sizes the grid so that this cannot happen
-        if (threadIdx.x == 0) {
-            set_device_error(a.err, SCHULZE_EDEVICE);
-            __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return;
-    }
 
     // owned[q] through a scalar register: tile numbers are uniform, and
     // everything derived from them (tile addresses, flags) then stays in
@@ -243,7 +253,6 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : (B < 128 ? 2 : 1)) void k
     // A rest tile of round r.  When `probe` is given, thread 0 also reads
     // that flag (issued before the product, so its latency hides behind the
     // tile) and the workgroup learns whether it was raised.
-    __shared__ int32_t probe_seen;
     auto do_rest = [&](int32_t r, int32_t I, int32_t J, const int32_t *probe) -> bool {
         if (!wait_flags(flag(r, 1 + J), flag(r, 1 + nb + I), a.abort, a.spin_limit)) return false;
         int32_t seen = 0;
@@ -363,6 +372,65 @@ stuck:
     if (threadIdx.x == 0) set_device_error(a.err, SCHULZE_EDEVICE);
 }
 
+template <typename E, int B>
+__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : (B < 128 ? 2 : 1)) void k_fw_persist(PersistArgs<E> a) {
+    using C = Cfg<E, B>;
+    constexpr int DIAG_LDS = diag_lds_elems<E, B, diag_steps<E, B>(), true>();
+    __shared__ __attribute__((aligned(16))) E lds[C::LDS_ELEMS > DIAG_LDS ? C::LDS_ELEMS : DIAG_LDS];
+    __shared__ int32_t owned[MAX_OWNED];
+    __shared__ int32_t n_owned, probe_seen;
+    const int32_t nb = a.nb, G = gridDim.x, w = blockIdx.x;
+    if (gated_off(a.gate, a.gate_want)) return;  // uniform over the grid: every workgroup leaves
+
+    // Tiles this workgroup owns, in ascending tile number: the numbers
+    // k = w, w + G, w + 2G, ... stand for block row I = k / nb and column
+    // J = (k mod nb - I) mod nb (the inverse of the owner map below).
+    if (threadIdx.x == 0) n_owned = (int32_t)((nb * nb - w + G - 1) / G);
+    __syncthreads();
+    const int32_t no = n_owned;
+    for (int32_t q = threadIdx.x; q < no && q < MAX_OWNED; q += 256) {
+        const int32_t k = w + q * G, I = k / nb;
+        owned[q] = I * nb + ((k % nb) - I + nb) % nb;
+    }
+    __syncthreads();
+    if (no > MAX_OWNED) {  // the host sizes the grid so that this cannot happen
+        if (threadIdx.x == 0) {
+            set_device_error(a.err, SCHULZE_EDEVICE);
+            __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
+
+    if constexpr (sizeof(E) == 2) {
+        if (!*a.wide) {  // (uniform over the grid)
+            const PersistArgs<_Float16> h{reinterpret_cast<_Float16 *>(a.P),
+                                          a.ld,
+                                          a.nb,
+                                          reinterpret_cast<_Float16 *>(a.ring),
+                                          a.flags,
+                                          a.abort,
+                                          a.err,
+                                          a.spin_limit,
+                                          a.early_panels,
+                                          nullptr,
+                                          0,
+                                          nullptr};
+            persist_run<_Float16, B>(h, reinterpret_cast<_Float16 *>(lds), owned, no, probe_seen);
+            return;
+        }
+        // a value without a key in order: the owned tiles back to integers
+        for (int32_t q = 0; q < no; ++q) {
+            E *t = a.P + (int64_t)(owned[q] / nb) * B * a.ld + (int64_t)(owned[q] % nb) * B;
+            for (int i = threadIdx.x; i < B * B; i += 256) {
+                E *x = t + (int64_t)(i / B) * a.ld + i % B;
+                *x = key_value(*x);
+            }
+        }
+        __syncthreads();
+    }
+    persist_run<E, B>(a, lds, owned, no, probe_seen);
+}
+
 // ------------------------------------------------------------------ per-phase launches
 // Used when a cooperative launch is not available: three launches per round.
 template <typename E, int B>
@@ -418,7 +486,21 @@ template <typename E, int B>
 size_t ring_bytes(int32_t nb) {
     return sizeof(E) * (size_t)nb * (2 * (size_t)nb + 1) * B * B;
 }
-inline size_t flag_bytes(int32_t nb) { return sizeof(int32_t) * ((size_t)nb * (2 * (size_t)nb + 1) + 64); }
+inline size_t flag_words(int32_t nb) { return (size_t)nb * (2 * (size_t)nb + 1) + 64; }
+
+// Whether close_padded starts the persistent launch: its uint16 matrices are
+// written as half-precision keys.
+inline bool persistent(const schulze_ctx *ctx, int32_t nb) { return nb > 1 && !ctx->force_phased; }
+
+// Workspace of the persistent launch, its flags (words of them) zeroed on
+// the stream; the words after the round flags are the abort word and, for a
+// uint16 closure, its `wide` word.
+inline int persist_prepare(schulze_ctx *ctx, hipStream_t s, size_t ring, size_t words) {
+    int rc;
+    if ((rc = ws_reserve(ctx, WS_RING, ring)) != SCHULZE_OK) return rc;
+    if ((rc = ws_reserve(ctx, WS_FLAGS, sizeof(int32_t) * words)) != SCHULZE_OK) return rc;
+    return fill_u32(ctx, s, static_cast<uint32_t *>(ctx->ws[WS_FLAGS]), words, 0u);
+}
 
 // Launch the persistent kernel.  Outside stream capture it is a cooperative
 // launch (all workgroups resident).  Under capture it is captured as a
@@ -440,13 +522,14 @@ inline hipError_t launch_persistent(const void *fn, unsigned G, void **args, hip
 // Close the padded matrix P (pitch ld, nb x nb tiles of B) in place: one
 // persistent dataflow launch, or three launches per round when the device
 // refuses a cooperative launch or the phased schedule is forced.  Every
-// launch is gated on (gate, want) (see gated_off).
+// launch is gated on (gate, want) (see gated_off).  `wide` (uint16 only):
+// P holds half-precision keys unless *wide is set when the kernels run;
+// afterwards too.  The persistent launch needs persist_prepare before it.
 template <typename E, int B>
-int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, const int32_t *gate = nullptr,
-                 int32_t want = 0) {
-    int rc;
+int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, int32_t *wide = nullptr,
+                 const int32_t *gate = nullptr, int32_t want = 0) {
     bool done = false;
-    if (nb > 1 && !ctx->force_phased) {
+    if (persistent(ctx, nb)) {
         // persistent dataflow launch
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_fw_persist<E, B>, 256, 0) != hipSuccess)
@@ -456,18 +539,14 @@ int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, 
         const int64_t tiles_per_wg = ceil_div((int64_t)nb * nb, G > 0 ? G : 1);
         if (G >= 1 && tiles_per_wg <= MAX_OWNED) {
             const int64_t nslots = (int64_t)nb * (2 * nb + 1);
-            if ((rc = ws_reserve(ctx, WS_RING, ring_bytes<E, B>(nb))) != SCHULZE_OK) return rc;
-            if ((rc = ws_reserve(ctx, WS_FLAGS, flag_bytes(nb))) != SCHULZE_OK) return rc;
             int32_t *flags = static_cast<int32_t *>(ctx->ws[WS_FLAGS]);
-            if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(flags), (size_t)(nslots + 64), 0u)) != SCHULZE_OK)
-                return rc;
             // early panels and the two-rounds-ahead diagonal while each workgroup
             // has few tiles per round: at most 20 (uint16) or 8 (int32); measured
             // on one MI355X: uint16 m = 12288 66.1 -> 62.1 ms, m = 14187 112.8 ->
             // 111.6 ms, m = 16384 146.4 -> 148 ms (hence off there)
             const int32_t early = (int64_t)nb * nb <= (sizeof(E) == 2 ? 20 : 8) * G ? 1 : 0;
             PersistArgs<E> pa{P,     ld,    nb, static_cast<E *>(ctx->ws[WS_RING]), flags, flags + nslots, ctx->err,
-                              (int64_t)1 << 22, early, gate, want};
+                              (int64_t)1 << 22, early, gate, want, wide};
             void *args[] = {&pa};
             int tok;
             timing_begin(ctx, K_FW_PERSIST, s, &tok);
@@ -481,6 +560,12 @@ int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, 
         }
     }
     if (!done) {
+        if constexpr (sizeof(E) == 2) {
+            if (wide)
+                SCHULZE_LAUNCH(ctx, K_FW_STORE, s,
+                               k_fw_decode<<<dim3((unsigned)(ctx->num_cus * 8)), dim3(256), 0, s>>>(
+                                   P, ld * (int64_t)nb * B, wide, gate, want));
+        }
         for (int32_t r = 0; r < nb; ++r) {
             SCHULZE_LAUNCH(ctx, K_FW_DIAG, s, k_fw_diag<E, B><<<dim3(1), dim3(256), 0, s>>>(P, ld, r, gate, want));
             if (nb > 1) {
@@ -504,12 +589,17 @@ int run_closure(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_
     int rc = ws_reserve(ctx, WS_CLOSURE, sizeof(E) * (size_t)mp * mp);
     if (rc != SCHULZE_OK) return rc;
     E *P = static_cast<E *>(ctx->ws[WS_CLOSURE]);
+    int32_t *wide = nullptr;
+    if (persistent(ctx, nb)) {
+        if ((rc = persist_prepare(ctx, s, ring_bytes<E, B>(nb), flag_words(nb))) != SCHULZE_OK) return rc;
+        if (sizeof(E) == 2) wide = static_cast<int32_t *>(ctx->ws[WS_FLAGS]) + (flag_words(nb) - 1);
+    }
     dim3 wgrid((unsigned)ceil_div(mp, 64), (unsigned)ceil_div(mp, 64));
     SCHULZE_LAUNCH(ctx, K_WEIGHTS, s, k_weights<E><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp,
-                                                                          tio::vec_ok<E>(d, ldd) ? 1 : 0));
-    if ((rc = close_padded<E, B>(ctx, s, P, ld, nb)) != SCHULZE_OK) return rc;
+                                                                          tio::vec_ok<E>(d, ldd) ? 1 : 0, wide));
+    if ((rc = close_padded<E, B>(ctx, s, P, ld, nb, wide)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FW_STORE, s,
-                   k_fw_store<E><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, nullptr, 0));
+                   k_fw_store<E><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, wide, nullptr, 0));
     ctx->closure_bits = sizeof(E) * 8;
     return SCHULZE_OK;
 }
@@ -554,7 +644,9 @@ __global__ __launch_bounds__(256) void k_rank_blocks(const uint32_t *__restrict_
 
 // Exclusive scan of the block sums (one workgroup); flags[1] = number of
 // distinct nonzero values; flags[2] = 1 if the closure runs on ranks (no
-// value at or above RANK_CAP, at most 65535 distinct values), else 0.
+// value at or above RANK_CAP, at most 65535 distinct values), else 0;
+// flags[3] = 1 if a rank is above KEY_MAX (then the ranks are closed as
+// integers, else as half-precision keys).
 __global__ __launch_bounds__(256) void k_rank_top(uint32_t *__restrict__ block_sum, int32_t *__restrict__ flags) {
     __shared__ uint32_t part[256];
     constexpr int PER = RANK_BLOCKS / 256;
@@ -580,6 +672,7 @@ __global__ __launch_bounds__(256) void k_rank_top(uint32_t *__restrict__ block_s
     if (threadIdx.x == 255) {
         flags[1] = (int32_t)part[255];
         flags[2] = (flags[0] == 0 && part[255] <= 65535u) ? 1 : 0;
+        flags[3] = part[255] > KEY_MAX ? 1 : 0;
     }
 }
 
@@ -699,14 +792,15 @@ __global__ __launch_bounds__(256) void k_weights_mark(const int32_t *__restrict_
         if (local[i]) atomicOr(&bitmap[i], local[i]);
 }
 
-// P16 = rank of the weights of d (0 for 0), straight from d: one workgroup
+// P16 = rank of the weights of d (0 for 0), as a half-precision key when
+// `keys` is set, straight from d: one workgroup
 // per pair of 64 x 64 blocks (I, J), (J, I) of the padded mp x mp matrix
 // (zero past m); the table lookups of a thread's 32 elements are issued
 // together before the ranks are formed.
 __global__ __launch_bounds__(256) void k_rank_apply_d(const int32_t *__restrict__ d, int64_t ldd, int32_t m,
                                                       int mode, int dvec, const uint32_t *__restrict__ bitmap,
                                                       const uint32_t *__restrict__ word_rank,
-                                                      uint16_t *__restrict__ P16, int64_t ld, int32_t mp,
+                                                      uint16_t *__restrict__ P16, int64_t ld, int32_t mp, int keys,
                                                       const int32_t *gate) {
     __shared__ int32_t a[64][65];
     __shared__ int32_t b[64][65];
@@ -741,8 +835,8 @@ __global__ __launch_bounds__(256) void k_rank_apply_d(const int32_t *__restrict_
             uint16_t k[8];
             for (int u = 0; u < 8; ++u) {
                 const int32_t v = w[t][h][u];
-                k[u] = v == 0 ? (uint16_t)0
-                              : (uint16_t)(wr[t][h][u] + __popc(bw[t][h][u] & ((1u << (v & 31)) - 1u)) + 1u);
+                const uint32_t rank = v == 0 ? 0u : wr[t][h][u] + __popc(bw[t][h][u] & ((1u << (v & 31)) - 1u)) + 1u;
+                k[u] = keys ? key_of(rank) : (uint16_t)rank;
             }
             // mp and ld are multiples of 64 and P16 is 16-byte aligned: eight columns are one store
             *reinterpret_cast<uint4 *>(P16 + (int64_t)row * ld + C0 + c8) = tio::pack<uint16_t>(k);
@@ -751,11 +845,14 @@ __global__ __launch_bounds__(256) void k_rank_apply_d(const int32_t *__restrict_
 }
 
 // p[i][j] = value_of[P16[i][j]] for i != j, 0 on the diagonal; one
-// workgroup per row, four columns per thread and step (ld is a multiple of 64).
+// workgroup per row, four columns per thread and step (ld is a multiple of
+// 64).  With `wide`, P16 holds half-precision keys of the ranks unless *wide
+// is set.
 __global__ __launch_bounds__(256) void k_rank_store(const uint16_t *__restrict__ P16, int64_t ld, int32_t m,
                                                     const int32_t *__restrict__ value_of, int32_t *__restrict__ p,
-                                                    int64_t ldp, const int32_t *gate) {
+                                                    int64_t ldp, const int32_t *wide, const int32_t *gate) {
     if (gated_off(gate, 1)) return;
+    const bool keys = wide && !*wide;
     const int32_t i = blockIdx.x;
     int32_t *row = p + (int64_t)i * ldp;
     // STORE_STEP groups of four columns per thread and step; every load and
@@ -768,6 +865,9 @@ __global__ __launch_bounds__(256) void k_rank_store(const uint16_t *__restrict__
         for (int u = 0; u < STORE_STEP; ++u)
             r[u] = *reinterpret_cast<const ushort4 *>(P16 + (int64_t)i * ld + min(jb + 1024 * u, (int32_t)ld - 4));
         int32_t v[STORE_STEP][4];
+        if (keys)
+            for (int u = 0; u < STORE_STEP; ++u)
+                r[u] = make_ushort4(key_value(r[u].x), key_value(r[u].y), key_value(r[u].z), key_value(r[u].w));
         for (int u = 0; u < STORE_STEP; ++u) {
             v[u][0] = value_of[r[u].x];
             v[u][1] = value_of[r[u].y];
@@ -807,10 +907,11 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
     int rc = ws_reserve(ctx, WS_CLOSURE, sizeof(int32_t) * (size_t)count);
     if (rc != SCHULZE_OK) return rc;
     if ((rc = ws_reserve(ctx, WS_RANKED, head + sizeof(uint16_t) * (size_t)count)) != SCHULZE_OK) return rc;
-    if ((rc = ws_reserve(ctx, WS_RING, std::max(ring_bytes<int32_t, BI>(mp / BI), ring_bytes<uint16_t, BU>(mp / BU)))) !=
-        SCHULZE_OK)
+    // (one set of cleared flags: only one of the two closures runs)
+    const bool persist = persistent(ctx, mp / B);
+    if (persist && (rc = persist_prepare(ctx, s, std::max(ring_bytes<int32_t, BI>(mp / BI), ring_bytes<uint16_t, BU>(mp / BU)),
+                                         std::max(flag_words(mp / BI), flag_words(mp / BU)))) != SCHULZE_OK)
         return rc;
-    if ((rc = ws_reserve(ctx, WS_FLAGS, std::max(flag_bytes(mp / BI), flag_bytes(mp / BU)))) != SCHULZE_OK) return rc;
     int32_t *P = static_cast<int32_t *>(ctx->ws[WS_CLOSURE]);
     const int dvec = tio::vec_ok<int32_t>(d, ldd) ? 1 : 0;
 
@@ -823,7 +924,7 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
     uint16_t *P16 = reinterpret_cast<uint16_t *>(q + head);
     if ((rc = fill_u32(ctx, s, bitmap, RANK_WORDS, 0u)) != SCHULZE_OK) return rc;
     if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(value_of), 1, 0u)) != SCHULZE_OK) return rc;
-    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(flags), 3, 0u)) != SCHULZE_OK) return rc;
+    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(flags), 4, 0u)) != SCHULZE_OK) return rc;
     // The weights' values are marked straight from d (the weights are not
     // written here): four marking workgroups per CU, each merging its LDS
     // bitmap once.
@@ -838,23 +939,25 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
     SCHULZE_LAUNCH(ctx, K_RANK, s, k_rank_top<<<dim3(1), dim3(256), 0, s>>>(block_off, flags));
     // flags[2] decides on the device; both variants are queued, each gated
     const int32_t *ranked = flags + 2;
+    int32_t *wide = persist ? flags + 3 : nullptr;
     const dim3 wgrid((unsigned)ceil_div(mp, 64), (unsigned)ceil_div(mp, 64));
     // values too wide or too many: the weights, then the int32 closure on them
     SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
-                   k_weights<int32_t><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp, dvec, ranked, 0));
-    if ((rc = close_padded<int32_t, BI>(ctx, s, P, ld, mp / BI, ranked, 0)) != SCHULZE_OK) return rc;
+                   k_weights<int32_t><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp, dvec, nullptr, ranked, 0));
+    if ((rc = close_padded<int32_t, BI>(ctx, s, P, ld, mp / BI, nullptr, ranked, 0)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FW_STORE, s,
-                   k_fw_store<int32_t><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, ranked, 0));
+                   k_fw_store<int32_t><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, nullptr, ranked,
+                                                                               0));
     // otherwise the ranks of the weights (straight from d) and the uint16 closure on them
     SCHULZE_LAUNCH(ctx, K_RANK, s,
                    k_rank_words<<<dim3(RANK_BLOCKS), dim3(256), 0, s>>>(bitmap, block_off, word_rank, value_of,
                                                                         ranked));
     SCHULZE_LAUNCH(ctx, K_RANK, s,
                    k_rank_apply_d<<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, dvec, bitmap, word_rank, P16, ld, mp,
-                                                              ranked));
-    if ((rc = close_padded<uint16_t, BU>(ctx, s, P16, ld, mp / BU, ranked, 1)) != SCHULZE_OK) return rc;
+                                                              persist ? 1 : 0, ranked));
+    if ((rc = close_padded<uint16_t, BU>(ctx, s, P16, ld, mp / BU, wide, ranked, 1)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_RANK, s,
-                   k_rank_store<<<dim3((unsigned)m), dim3(256), 0, s>>>(P16, ld, m, value_of, p, ldp, ranked));
+                   k_rank_store<<<dim3((unsigned)m), dim3(256), 0, s>>>(P16, ld, m, value_of, p, ldp, wide, ranked));
     ctx->closure_bits = 0;
     ctx->closure_ranked_flag = ranked;
     return SCHULZE_OK;

@@ -9,6 +9,7 @@
 namespace fw {
 
 typedef __attribute__((ext_vector_type(2))) unsigned short us2;
+typedef __attribute__((ext_vector_type(2))) _Float16 hf2;
 
 // Tile operands in device memory may be plain pointers or pointers qualified
 // with the global address space (then every access is a global_* instruction
@@ -35,6 +36,7 @@ struct Lane<int32_t> {
     static constexpr int PER = 1;
     __device__ static W splat(int32_t v) { return v; }
     __device__ static W relax(W c, W a, W b) { return max(c, min(a, b)); }
+    __device__ static int32_t relax1(int32_t c, int32_t a, int32_t b) { return max(c, min(a, b)); }
 };
 template <>
 struct Lane<uint16_t> {
@@ -44,8 +46,47 @@ struct Lane<uint16_t> {
     __device__ static W relax(W c, W a, W b) {
         return __builtin_elementwise_max(c, __builtin_elementwise_min(a, b));
     }
+    __device__ static uint16_t relax1(uint16_t c, uint16_t a, uint16_t b) { return max(c, min(a, b)); }
 };
 
+// 16-bit values as half-precision keys.  gfx950 has a packed three-operand
+// maximum for halves (v_pk_maximum3_f16) and none for 16-bit integers, so
+// two k of the recurrence take two packed minima and one packed maximum3
+// where integers take two of each: 0.75 lane operations per update instead
+// of 1 (all of them issue at the same rate, 36.7-37.9 T lane operations/s
+// measured).  Minima and maxima only compare, and the map from value to key
+// is increasing over 0 .. KEY_MAX, so the recurrence on keys is exact:
+//   0 .. 31743      -inf .. the negative denormal nearest to zero
+//   31744 .. 63488  +0 .. +inf
+// (-0 is not used: no two keys compare equal).  The values above KEY_MAX
+// take the patterns left (-0 and the NaNs), so that every 16-bit value has
+// a key to be stored as, but a matrix that holds one of them is closed on
+// integers.
+constexpr uint32_t KEY_MAX = 63488;
+__host__ __device__ inline uint16_t key_of(uint32_t v) {
+    if (v <= KEY_MAX) return (uint16_t)(v >= 31744u ? v - 31744u : 0x8000u + (31744u - v));
+    const uint32_t i = v - (KEY_MAX + 1);  // 0 .. 2046
+    return (uint16_t)(i == 0 ? 0x8000u : (i < 1024u ? 0x7C00u + i : 0xFC00u + (i - 1023u)));
+}
+__host__ __device__ inline uint16_t key_value(uint32_t k) {
+    const uint32_t mag = k & 0x7FFFu;
+    if (mag <= 0x7C00u)
+        return (uint16_t)((k & 0x8000u) == 0 ? 31744u + mag : (mag ? 31744u - mag : KEY_MAX + 1));
+    return (uint16_t)(KEY_MAX + 1 + (mag - 0x7C00u) + ((k & 0x8000u) ? 1023u : 0u));
+}
+
+template <>
+struct Lane<_Float16> {
+    using W = hf2;  // two elements per 32-bit lane
+    static constexpr int PER = 2;
+    __device__ static W splat(_Float16 v) { return hf2{v, v}; }
+    __device__ static W relax(W c, W a, W b) {
+        return __builtin_elementwise_maximum(c, __builtin_elementwise_minimum(a, b));
+    }
+    __device__ static _Float16 relax1(_Float16 c, _Float16 a, _Float16 b) {
+        return __builtin_elementwise_maximum(c, __builtin_elementwise_minimum(a, b));
+    }
+};
 
 // ------------------------------------------------------------------ tile product
 // 256 threads as 16 x 16; thread (ty, tx) owns rows ty*TM .. and columns
@@ -126,39 +167,73 @@ __device__ inline void acc_store(const Acc<E, B> &a, DstP dst, int64_t ld) {
     }
 }
 
+// Element e (0 or 1) of a 32-bit word.
+template <typename E>
+__device__ __forceinline__ E half_of(uint32_t word, int e) {
+    return __builtin_bit_cast(E, e ? (unsigned short)(word >> 16) : (unsigned short)word);
+}
+
 // The four k of one step of the 16-bit product: A values av (four k per
 // row, one 8-byte read each), B rows at bs (pitch ldb elements, this
-// thread's columns).  The B row of step k+1 is read before the products of
-// step k (the scheduling barrier keeps it there), so that only the first
-// read of each step waits.
-template <int B>
-__device__ __forceinline__ void step4_16(Acc<uint16_t, B> &a, const v2u32 (&av)[Cfg<uint16_t, B>::TM],
-                                         const FW_LDS uint16_t *bs, int ldb) {
-    using C = Cfg<uint16_t, B>;
-    using L = Lane<uint16_t>;
+// thread's columns).  The B rows of the next k (uint16) or pair of k (half
+// keys) are read before the products of this one (the scheduling barrier
+// keeps them there), so that only the first read of each step waits.
+template <typename E, int B>
+__device__ __forceinline__ void step4_16(Acc<E, B> &a, const v2u32 (&av)[Cfg<E, B>::TM], const FW_LDS E *bs,
+                                         int ldb) {
+    using C = Cfg<E, B>;
+    using L = Lane<E>;
     using W = typename L::W;
     constexpr int TM = C::TM, WN = C::WN;
-    W bq[2][WN];
-    const FW_LDS W *b0 = (const FW_LDS W *)bs;
-    for (int jj = 0; jj < WN; ++jj) bq[0][jj] = b0[jj];
+    if constexpr (__is_same(E, _Float16)) {
+        // c = maximum3(c, minimum(a_k, b_k), minimum(a_k+1, b_k+1))
+        W bq[4][WN];
+        auto rows = [&](int k) {
+            for (int q = k; q < k + 2; ++q) {
+                const FW_LDS W *bn = (const FW_LDS W *)(bs + q * ldb);
+                for (int jj = 0; jj < WN; ++jj) bq[q][jj] = bn[jj];
+            }
+        };
+        rows(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        if (kk + 1 < 4) {
-            const FW_LDS W *bn = (const FW_LDS W *)(bs + (kk + 1) * ldb);
-            for (int jj = 0; jj < WN; ++jj) bq[(kk + 1) & 1][jj] = bn[jj];
+        for (int kk = 0; kk < 4; kk += 2) {
+            if (kk == 0) rows(2);
+            __builtin_amdgcn_sched_barrier(0);
+            for (int ii = 0; ii < TM; ++ii) {
+                const uint32_t word = kk == 0 ? av[ii].x : av[ii].y;
+                const W a0 = L::splat(half_of<E>(word, 0)), a1 = L::splat(half_of<E>(word, 1));
+                // (all minima of the row before its maxima, as below)
+                W t0[WN], t1[WN];
+                for (int jj = 0; jj < WN; ++jj) {
+                    t0[jj] = __builtin_elementwise_minimum(a0, bq[kk][jj]);
+                    t1[jj] = __builtin_elementwise_minimum(a1, bq[kk + 1][jj]);
+                }
+                for (int jj = 0; jj < WN; ++jj)
+                    a.c[ii][jj] =
+                        __builtin_elementwise_maximum(__builtin_elementwise_maximum(a.c[ii][jj], t0[jj]), t1[jj]);
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        const W *bp = bq[kk & 1];
-        for (int ii = 0; ii < TM; ++ii) {
-            const uint32_t word = kk < 2 ? av[ii].x : av[ii].y;
-            const unsigned short av16 = (kk & 1) ? (unsigned short)(word >> 16) : (unsigned short)word;
-            const W aa = L::splat(av16);
-            // all mins of the row before its maxes: a max right after the
-            // min it reads needs a wait state when that min takes the high
-            // half of its operand (the compiler inserts an s_nop there)
-            W t[WN];
-            for (int jj = 0; jj < WN; ++jj) t[jj] = __builtin_elementwise_min(aa, bp[jj]);
-            for (int jj = 0; jj < WN; ++jj) a.c[ii][jj] = __builtin_elementwise_max(a.c[ii][jj], t[jj]);
+    } else {
+        W bq[2][WN];
+        const FW_LDS W *b0 = (const FW_LDS W *)bs;
+        for (int jj = 0; jj < WN; ++jj) bq[0][jj] = b0[jj];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            if (kk + 1 < 4) {
+                const FW_LDS W *bn = (const FW_LDS W *)(bs + (kk + 1) * ldb);
+                for (int jj = 0; jj < WN; ++jj) bq[(kk + 1) & 1][jj] = bn[jj];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const W *bp = bq[kk & 1];
+            for (int ii = 0; ii < TM; ++ii) {
+                const W aa = L::splat(half_of<E>(kk < 2 ? av[ii].x : av[ii].y, kk & 1));
+                // all mins of the row before its maxes: a max right after the
+                // min it reads needs a wait state when that min takes the high
+                // half of its operand (the compiler inserts an s_nop there)
+                W t[WN];
+                for (int jj = 0; jj < WN; ++jj) t[jj] = __builtin_elementwise_min(aa, bp[jj]);
+                for (int jj = 0; jj < WN; ++jj) a.c[ii][jj] = __builtin_elementwise_max(a.c[ii][jj], t[jj]);
+            }
         }
     }
 }
@@ -176,9 +251,9 @@ struct Dma128 {
     static constexpr int LDS_ELEMS = 2 * (AS + BS);    // two buffers
 };
 
-template <typename PA, typename PB>
-__device__ __forceinline__ void dma_chunk128(PA A, int64_t lda, PB Bm, int64_t ldb, int kc, FW_LDS uint16_t *As,
-                                             FW_LDS uint16_t *Bs) {
+template <typename E, typename PA, typename PB>
+__device__ __forceinline__ void dma_chunk128(PA A, int64_t lda, PB Bm, int64_t ldb, int kc, FW_LDS E *As,
+                                             FW_LDS E *Bs) {
     const int t = lane_tid(), w = t >> 6, l = t & 63;
     // A: instruction i = rows 16 i .. 16 i + 15, four 16-byte pieces each
     for (int i = w; i < 8; i += 4)
@@ -196,14 +271,12 @@ __device__ __forceinline__ void dma_chunk128(PA A, int64_t lda, PB Bm, int64_t l
 template <typename E, int B, typename PA, typename PB>
 __device__ inline void acc_product(Acc<E, B> &a, PA A, int64_t lda, PB Bm, int64_t ldb, E *lds) {
     using C = Cfg<E, B>;
-    using L = Lane<E>;
-    using W = typename L::W;
-    constexpr int TM = C::TM, TN = C::TN, WN = C::WN, KC = C::KC, LA = C::LA, LB = C::LB;
+    constexpr int TM = C::TM, TN = C::TN, KC = C::KC, LA = C::LA, LB = C::LB;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     if constexpr (sizeof(E) == 2 && B == 128) {
         using D = Dma128;
         static_assert(D::LDS_ELEMS <= C::LDS_ELEMS, "LDS of the staged product");
-        FW_LDS uint16_t *buf = (FW_LDS uint16_t *)lds;
+        FW_LDS E *buf = (FW_LDS E *)lds;
         // (scalar operand addresses: the per-lane load addresses are built
         // here, not hoisted out of the caller's loops)
         A = scalar_ptr(A);
@@ -212,19 +285,19 @@ __device__ inline void acc_product(Acc<E, B> &a, PA A, int64_t lda, PB Bm, int64
         dma_chunk128(A, lda, Bm, ldb, 0, buf, buf + D::AS);
 #pragma unroll 1
         for (int c = 0; c < B / D::KC; ++c) {
-            FW_LDS uint16_t *As = buf + (c & 1) * (D::AS + D::BS);
-            FW_LDS uint16_t *Bs = As + D::AS;
+            FW_LDS E *As = buf + (c & 1) * (D::AS + D::BS);
+            FW_LDS E *Bs = As + D::AS;
             __builtin_amdgcn_s_waitcnt(0);  // this wave's pieces of chunk c are in LDS
             __syncthreads();                // everyone's are, and chunk c-1 is consumed
             if (c + 1 < B / D::KC) {
-                FW_LDS uint16_t *An = buf + ((c + 1) & 1) * (D::AS + D::BS);
+                FW_LDS E *An = buf + ((c + 1) & 1) * (D::AS + D::BS);
                 dma_chunk128(A, lda, Bm, ldb, (c + 1) * D::KC, An, An + D::AS);
             }
 #pragma unroll 1
             for (int k = 0; k < D::KC; k += 4) {
                 v2u32 av[TM];
                 for (int ii = 0; ii < TM; ++ii) av[ii] = *(const FW_LDS v2u32 *)(As + (ty * TM + ii) * D::KC + k);
-                step4_16<B>(a, av, &Bs[k * B + tx * TN], B);
+                step4_16<E, B>(a, av, &Bs[k * B + tx * TN], B);
             }
         }
         __syncthreads();
@@ -262,36 +335,13 @@ __device__ inline void acc_product(Acc<E, B> &a, PA A, int64_t lda, PB Bm, int64
                 }
             }
         } else {
-            // four k per step: A values come as one 8-byte read per row; the
-            // B row of step k+1 is read before the products of step k (the
-            // scheduling barrier keeps it there), so that only the first read
-            // of each step waits
+            // four k per step: A values come as one 8-byte read per row
 #pragma unroll 1
             for (int k = 0; k < KC; k += 4) {
-                uint2 av[TM];
-                for (int ii = 0; ii < TM; ++ii) av[ii] = *reinterpret_cast<const uint2 *>(&As[(ty * TM + ii) * LA + k]);
-                W bq[2][WN];
-                for (int jj = 0; jj < WN; ++jj) bq[0][jj] = *reinterpret_cast<const W *>(&Bs[k * LB + tx * TN + 2 * jj]);
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    if (kk + 1 < 4) {
-                        for (int jj = 0; jj < WN; ++jj)
-                            bq[(kk + 1) & 1][jj] = *reinterpret_cast<const W *>(&Bs[(k + kk + 1) * LB + tx * TN + 2 * jj]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    const W *bp = bq[kk & 1];
-                    for (int ii = 0; ii < TM; ++ii) {
-                        const uint32_t word = kk < 2 ? av[ii].x : av[ii].y;
-                        const unsigned short av16 = (kk & 1) ? (unsigned short)(word >> 16) : (unsigned short)word;
-                        const W aa = L::splat(av16);
-                        // all mins of the row before its maxes: a max right after the
-                        // min it reads needs a wait state when that min takes the high
-                        // half of its operand (the compiler inserts an s_nop there)
-                        W t[WN];
-                        for (int jj = 0; jj < WN; ++jj) t[jj] = __builtin_elementwise_min(aa, bp[jj]);
-                        for (int jj = 0; jj < WN; ++jj) a.c[ii][jj] = __builtin_elementwise_max(a.c[ii][jj], t[jj]);
-                    }
-                }
+                v2u32 av[TM];
+                for (int ii = 0; ii < TM; ++ii)
+                    av[ii] = *(const FW_LDS v2u32 *)((const FW_LDS E *)As + (ty * TM + ii) * LA + k);
+                step4_16<E, B>(a, av, (const FW_LDS E *)Bs + k * LB + tx * TN, LB);
             }
         }
     }
@@ -396,7 +446,7 @@ struct Diag {
                 if constexpr (sizeof(E) == 4) {
                     d[i / S][i % S] = (E)wv[i];
                 } else {
-                    d[i / S][i % S] = (E)((i & 1) ? (wv[i >> 1] >> 16) : (wv[i >> 1] & 0xFFFFu));
+                    d[i / S][i % S] = half_of<E>(wv[i >> 1], i & 1);
                 }
             }
         }
@@ -422,7 +472,7 @@ struct Diag {
 #pragma unroll
                 for (int s3 = s + 1; s3 < S; ++s3)
                     if (s2 != s3)
-                        d[s2][s3] = (E)max((int32_t)d[s2][s3], min((int32_t)d[s2][s], (int32_t)d[s][s3]));
+                        d[s2][s3] = L::relax1(d[s2][s3], d[s2][s], d[s][s3]);
             __builtin_amdgcn_sched_barrier(0);  // one step at a time: bounded register demand
         }
     }
@@ -476,7 +526,7 @@ __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, 
                 if constexpr (sizeof(E) == 4) {
                     v[a][c] = row[16 * c];
                 } else {
-                    v[a][c] = us2{row[16 * (2 * c)], row[16 * (2 * c + 1)]};
+                    v[a][c] = W{row[16 * (2 * c)], row[16 * (2 * c + 1)]};
                 }
             }
         }
@@ -488,7 +538,7 @@ __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, 
                 if constexpr (sizeof(E) == 4) {
                     v[a][c] = row[16 * c];
                 } else {
-                    v[a][c] = us2{row[16 * (2 * c)], row[16 * (2 * c + 1)]};
+                    v[a][c] = W{row[16 * (2 * c)], row[16 * (2 * c + 1)]};
                 }
             }
         }
