@@ -14,8 +14,9 @@
 // buffer; a call that needs more than the slot holds reallocates it.
 enum WsSlot {
     WS_BALLOT_META = 0,  // per-ballot listed length and class, counters
-    WS_POSITIONS,        // packed rank pairs of full rankings
-    WS_TRUNC_POS,        // packed rank pairs of truncated ballots (U space)
+    WS_POSITIONS,        // rank planes of full rankings
+    WS_TRUNC_POS,        // rank planes of truncated ballots (U space)
+    WS_PARTIAL,          // partial tiles of the bit-plane count
     WS_ACC32,            // m x m uint32 accumulator of the count
     WS_ROWSUM,           // per-candidate uint32 sums
     WS_CLOSURE,          // padded closure matrix

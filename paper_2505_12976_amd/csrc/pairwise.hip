@@ -4,23 +4,22 @@
 // at all.  Ballots are split by a scan into full rankings (at least m-1
 // listed candidates) and truncated ballots, which take different routes:
 //
-//  * Position counting.  The rank of every candidate is scattered into a
-//    position array, two voters per 32-bit word (low half: one voter, high
-//    half: the next).  For one (x, y) pair and one voter, the 16-bit
-//    difference t = (pos(x) - pos(y)) mod 2^16 equals
-//    pos(x) - pos(y) + 2^16 [pos(x) < pos(y)], so summed over voters
-//        sum t = Sx - Sy + 2^16 * #(x before y),
-//    where Sx is the sum of x's positions.  One v_pk_sub_u16 yields t for two
-//    voters and one v_dot2_u32_u16 adds both halves into a 32-bit
-//    accumulator: one VALU lane-op per comparison.  The count is
-//    (acc - Sx + Sy) >> 16, exact while fewer than 2^16 voters are summed.
+//  * Bit-plane counting.  The ranks of 32 voters are kept as bit planes, one
+//    32-bit word per candidate and bit (a bit per voter).  For one (x, y)
+//    pair the mask of the voters with pos(x) < pos(y) comes from the bits
+//    from the lowest up: lt = (~x & y) | (~(x ^ y) & lt), one v_bitop3_b32
+//    per bit, and one v_bcnt_u32_b32 adds its population count: (bits + 1)
+//    instructions for 32 comparisons, where a packed subtraction and a dot
+//    product took 32.  Voter weights go through the same masks, bit plane by
+//    bit plane of the weights.
 //    - Full rankings have no ties, so only tiles with x-block <= y-block are
 //      counted and d[y][x] = voters - d[x][y].
 //    - Truncated ballots are counted the same way over the candidates U that
 //      any truncated ballot lists (unlisted candidates share one sentinel
-//      position, so ties count for neither side), over all ordered tiles.
-//      One extra always-sentinel column gives R[x], the number of truncated
-//      ballots listing x, and d[x][y] = R[x] for x in U, y outside U.
+//      position, all ones, so ties count for neither side), over all ordered
+//      tiles.  One extra always-sentinel column gives R[x], the number of
+//      truncated ballots listing x, and d[x][y] = R[x] for x in U, y outside
+//      U.
 //  * Pair scattering, for truncated ballots when U is large: d[x][y] =
 //    R[x] - C[y][x], where C[y][x] is the weight of ballots listing y before
 //    x; the listed pairs are scattered with atomics.
@@ -32,25 +31,32 @@
 namespace {
 
 constexpr int CT = 128;           // count tile (candidates per side)
-constexpr int VC = 32;            // voter pairs per staged chunk
-constexpr int CNT_THREADS = 256;
-constexpr int SEG_PAIRS = 32767;  // at most 65534 voters per exact segment
-constexpr int SEGC = SEG_PAIRS / VC;
-constexpr int SCATTER_CH = 8192;  // columns per LDS chunk of the scatters
+constexpr int COUNT_PER_CU = 3;   // workgroups of the count per CU (168 vector registers)
+constexpr int MAX_BITS = 16;      // bit planes of a rank (m <= 65535)
 constexpr int LONG_CHUNK = 32;    // ballots per workgroup of the long-row scan
 constexpr int SHORT_PER_WAVE = 8; // steps (groups of ballots) per wavefront of the short-row scan
 constexpr int NPART = 64;         // partial sums of the pair-scattering cost
-constexpr uint16_t UNSET = 0xFFFF;
 
 enum { MODE_SPARSE = 0, MODE_DENSE_U = 1 };
 
-typedef __attribute__((ext_vector_type(2))) unsigned short us2;
+#define CNT_LDS __attribute__((address_space(3)))
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Bits that hold the ranks 0 .. last and, above every rank that is less
+// than `last`, all ones for "not listed".
+__host__ __device__ inline int32_t rank_bits(int32_t last) {
+    int32_t b = 1;
+    while (((1 << b) - 1) < last) ++b;
+    return b;
+}
 
 // Workspace views (WS_BALLOT_META).
 struct Meta {
     int32_t *ctr;            // [0] full rankings [1] truncated ballots [2] route
-                             // [3] |U| [4] U-space pitch [32..33] total voter
-                             // weight (64 bits) [34] its workgroups done
+                             // [3] |U| [4] U-space pitch [6] longest truncated
+                             // ballot [7] voter weights or-ed together [8] total
+                             // weight of the full rankings (mod 2^32) [32..33] total
+                             // voter weight (64 bits) [34] its workgroups done
     unsigned long long *k2;  // NPART partial sums of k(k-1)/2 over truncated ballots
     int32_t *len;            // listed length per ballot
     int32_t *full_src;       // slot -> ballot of a full ranking
@@ -107,6 +113,7 @@ __global__ __launch_bounds__(256) void k_scan_long(const void *__restrict__ ball
     if (threadIdx.x == 0) nf = nt = 0;
     bool bad = false;
     unsigned long long k2 = 0;
+    int32_t longest = 0;  // listed by a truncated ballot
     for (int q = 0; q < LONG_CHUNK; ++q) {
         const int64_t v = v0 + q;
         if (v >= n) break;
@@ -134,6 +141,7 @@ __global__ __launch_bounds__(256) void k_scan_long(const void *__restrict__ ball
             if (trunc) {
                 lt[nt++] = (int32_t)v;
                 k2 += (unsigned long long)k * (k - 1) / 2;
+                longest = max(longest, k);
             } else {
                 lf[nf++] = (int32_t)v;
             }
@@ -141,6 +149,7 @@ __global__ __launch_bounds__(256) void k_scan_long(const void *__restrict__ ball
     }
     if (bad) set_device_error(err, SCHULZE_EBALLOT);
     if (threadIdx.x == 0 && k2) atomicAdd(&meta.k2[blockIdx.x % NPART], k2);
+    if (threadIdx.x == 0 && longest) atomicMax(&meta.ctr[6], longest);
     __syncthreads();
     record_ballots(meta, nf, lf, nt, lt);
 }
@@ -159,6 +168,7 @@ __global__ __launch_bounds__(256) void k_scan_long_vec(const uint16_t *__restric
     const int32_t L8 = L / 8;
     bool bad = false;
     unsigned long long k2 = 0;
+    int32_t longest = 0;
     for (int q = wave; q < LONG_CHUNK; q += 4) {
         const int64_t v = v0 + q;
         if (v >= n) {
@@ -193,11 +203,15 @@ __global__ __launch_bounds__(256) void k_scan_long_vec(const uint16_t *__restric
         if (lane == 0) {
             meta.len[v] = k;
             kind[q] = trunc ? 2 : 1;
-            if (trunc) k2 += (unsigned long long)k * (k - 1) / 2;
+            if (trunc) {
+                k2 += (unsigned long long)k * (k - 1) / 2;
+                longest = max(longest, k);
+            }
         }
     }
     if (bad) set_device_error(err, SCHULZE_EBALLOT);
     if (lane == 0 && k2) atomicAdd(&meta.k2[blockIdx.x % NPART], k2);
+    if (lane == 0 && longest) atomicMax(&meta.ctr[6], longest);
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t a = 0, b = 0;
@@ -243,6 +257,7 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
     const uint64_t group_bits = (L == 64) ? ~0ull : ((1ull << L) - 1ull);
     bool bad = false;
     unsigned long long k2 = 0;
+    int32_t longest = 0;
     for (int round = 0; round < SHORT_ROUNDS; ++round) {
         const int64_t v0 = (((int64_t)blockIdx.x * SHORT_ROUNDS + round) * 4 + wave) * SHORT_PER_WAVE * bpw;
         int32_t c[SHORT_PER_WAVE];
@@ -279,6 +294,7 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
                 if (trunc) {
                     lt[atomicAdd(&nt, 1)] = (int32_t)v;
                     k2 += (unsigned long long)k * (k - 1) / 2;
+                    longest = max(longest, k);
                 } else {
                     lf[atomicAdd(&nf, 1)] = (int32_t)v;
                 }
@@ -286,8 +302,12 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
         }
     }
     if (__ballot(bad) && lane == 0) set_device_error(err, SCHULZE_EBALLOT);
-    for (int off = 32; off >= 1; off >>= 1) k2 += __shfl_xor(k2, off);
+    for (int off = 32; off >= 1; off >>= 1) {
+        k2 += __shfl_xor(k2, off);
+        longest = max(longest, __shfl_xor(longest, off));
+    }
     if (lane == 0 && k2) atomicAdd(&meta.k2[(blockIdx.x * 4 + wave) % NPART], k2);
+    if (lane == 0 && longest) atomicMax(&meta.ctr[6], longest);
     __syncthreads();
     if (use_seen)
         for (int32_t c = threadIdx.x; c < m; c += 256)
@@ -298,16 +318,19 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
 // ------------------------------------------------------------------ route decision
 // One workgroup: U-space compaction (prefix sum over candidates) and the
 // choice between the dense route over U and pair scattering for truncated
-// ballots.  Costs: dense ~ (n_T / 2) * pitch^2 lane-ops, pair counting
-// ~ sum k(k-1)/2 pairs, a pair charged as pair_cost lane-ops (about the
-// measured ratio of the two rates on MI355X: 1024 for device-wide atomics,
-// 512 for the bucketed count).
-constexpr double ATOMIC_PAIR_COST = 1024.0;
-constexpr double BUCKETED_PAIR_COST = 512.0;
+// ballots, by the time each is expected to take (picoseconds, from measured
+// rates on MI355X): dense, the masks' instructions over the tiles at 45 T
+// lane operations/s and the m x m accumulator written, read and converted;
+// pair scattering, a pair's share of the bucketed accumulation (5-6 ps at
+// n = 10^6 top-20 and n = 15553 top-150) or a device-wide atomic, and d
+// written once; both have their own passes over the ballots (about 60 us).
+constexpr double DENSE_RATE = 45.0;            // lane operations per picosecond
+constexpr double ATOMIC_PAIR_COST = 66.0;
+constexpr double BUCKETED_PAIR_COST = 6.0;
 
 constexpr int ROUTE_THREADS = 1024;
 constexpr int ROUTE_VEC = 4;  // 16-byte groups of flags per thread (m <= 65536)
-__global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, Meta meta, int weighted, int64_t cap_words,
+__global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, Meta meta, int64_t cap_words,
                                                          double pair_cost) {
     __shared__ int32_t part[ROUTE_THREADS];
     // A thread takes consecutive flags (0 or 1 bytes; zero past m up to the
@@ -365,132 +388,240 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, Meta meta, i
         const int64_t n_t = meta.ctr[1];
         unsigned long long k2 = 0;
         for (int i = 0; i < NPART; ++i) k2 += meta.k2[i];
-        const int64_t pairs = (n_t + 1) / 2;
-        const double dense = (double)pairs * (double)pitch * (double)pitch;
-        const bool fits = pairs * (int64_t)pitch <= cap_words;
-        const bool use_dense = !weighted && fits && n_t > 0 && dense <= pair_cost * (double)k2;
+        const int64_t groups = (n_t + 31) / 32;
+        const int32_t bits = rank_bits(meta.ctr[6]);
+        const double mm = (double)m * m;
+        const double dense =
+            (double)groups * (double)pitch * (double)pitch * (bits + 2) / DENSE_RATE + 3.0 * mm;
+        const bool fits = groups * (int64_t)pitch * bits <= cap_words;
+        const bool use_dense = fits && n_t > 0 && dense <= pair_cost * (double)k2 + mm;
         meta.ctr[2] = use_dense ? MODE_DENSE_U : MODE_SPARSE;
         meta.ctr[3] = nu;
         meta.ctr[4] = pitch;
     }
 }
 
-// ------------------------------------------------------------------ scatters
-// A workgroup per voter pair q (grid-stride over the pairs): positions of slots 2q (low half) and
-// 2q+1 (high half; 0 for the missing partner of an odd count), staged in
-// LDS in chunks of SCATTER_CH columns and written as rows of `pitch` words.
-// A ballot lists distinct candidates iff its entries leave exactly
-// (columns - listed) positions unset; anything else is a repeated id.
-template <bool FULL, bool I32>
-__global__ __launch_bounds__(256) void k_scatter(const void *__restrict__ ballots, int32_t L, int32_t m,
-                                                 int32_t full_pitch, Meta meta, uint32_t *__restrict__ pos,
-                                                 int32_t *err) {
-    __shared__ uint16_t buf[2 * SCATTER_CH];
-    __shared__ int32_t unset_cnt[2];
-    const int32_t count = FULL ? meta.ctr[0] : meta.ctr[1];
-    if (!FULL && meta.ctr[2] != MODE_DENSE_U) return;
-    for (int64_t q = blockIdx.x; 2 * q < count; q += gridDim.x) {
-    const int32_t pitch = FULL ? full_pitch : meta.ctr[4];
-    const int32_t ncols = FULL ? m : meta.ctr[3];  // real columns: candidates or U
-    const int32_t *srcs = FULL ? meta.full_src : meta.trunc_src;
-    const bool has_hi = 2 * q + 1 < count;
-    const int32_t src[2] = {srcs[2 * q], has_hi ? srcs[2 * q + 1] : -1};
-    // 16-byte ballot reads (uint16 ids, rows 16-byte aligned) and position
-    // stores (rows and chunks in multiples of four words)
-    const bool vec16 = !I32 && (L % 8) == 0 && (reinterpret_cast<uintptr_t>(ballots) % 16) == 0;
-    const bool vec_out = (pitch % 4) == 0 && (reinterpret_cast<uintptr_t>(pos) % 16) == 0;
-    __syncthreads();  // the previous pair's counts have been read
-    if (threadIdx.x < 2) unset_cnt[threadIdx.x] = 0;
-    for (int32_t c0 = 0; c0 < pitch; c0 += SCATTER_CH) {
-        const int32_t cn = min(SCATTER_CH, pitch - c0);
-        __syncthreads();
-        for (int i = threadIdx.x; i < 2 * cn; i += 256) buf[i] = UNSET;
-        __syncthreads();
-        for (int h = 0; h < 2; ++h) {
-            if (src[h] < 0) continue;
-            const int32_t k = meta.len[src[h]];
-            const int64_t base = (int64_t)src[h] * L;
-            auto place = [&](int32_t t, int32_t id) {
-                if (id < 0 || id >= m) return;  // reported by the scan
-                const int32_t col = FULL ? id : meta.umap[id];
-                if (col >= c0 && col < c0 + cn) buf[2 * (col - c0) + h] = (uint16_t)t;
-            };
-            if (vec16) {
-                // eight uint16 ids per 16-byte load
-                const uint4 *row = reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(ballots) + base);
-                for (int32_t t8 = 8 * threadIdx.x; t8 < k; t8 += 8 * 256) {
-                    const uint4 v = row[t8 >> 3];
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-                    for (int e = 0; e < 8; ++e) {
-                        const uint32_t raw = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu);
-                        if (t8 + e < k) place(t8 + e, raw == 0xFFFFu ? -1 : (int32_t)raw);
-                    }
-                }
-            } else {
-                for (int t = threadIdx.x; t < k; t += 256) place(t, read_id<I32>(ballots, base + t));
-            }
+// ------------------------------------------------------------------ rank planes
+// Group g of 32 voters (slots 32 g ..) as bit planes: word (g, b, c) holds
+// bit b of candidate c's rank for every voter of the group, voter 2p + h at
+// bit 16 h + p.  A workgroup scatters the ranks of one group over CH columns
+// into LDS, two voters per 32-bit word, and each thread then transposes the
+// 16 words of a column as two 16 x 16 bit matrices (four butterfly stages).
+// Unlisted candidates keep all ones; slots past the last voter are zero in
+// every column and count for no pair.  Every ballot lists distinct candidates
+// iff together they set as many columns as they have entries (no ballot can
+// set more).  With voter weights, the group's weights are kept as 32 bit
+// planes too, and those of full rankings are summed.
+struct PlaneArgs {
+    const void *ballots;
+    int32_t L, m;
+    int32_t pitch, bits;  // full rankings; truncated ballots take theirs from meta
+    Meta meta;
+    const uint32_t *weight;  // nullptr: every voter counts once
+    uint32_t *planes;
+    uint32_t *wplanes;  // 32 words per group
+    int32_t *err;
+    int vec;  // rows in 16-byte pieces
+};
+
+// 16 x 16 bit transpose of both halves: bit (16 h + p) of w[b] becomes bit
+// (16 h + b) of the old w[p].
+__device__ inline void transpose16(uint32_t (&w)[16]) {
+    const uint32_t masks[4] = {0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        const int sh = 8 >> st;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            if (p & sh) continue;
+            const uint32_t t = ((w[p] >> sh) ^ w[p + sh]) & masks[st];
+            w[p + sh] ^= t;
+            w[p] ^= t << sh;
         }
-        __syncthreads();
-        int32_t un0 = 0, un1 = 0;
-        auto word = [&](int i) -> uint32_t {
-            const int32_t col = c0 + i;
-            uint16_t lo = buf[2 * i], hi = buf[2 * i + 1];
-            if (col < ncols) {
-                un0 += lo == UNSET;
-                un1 += hi == UNSET;
-            }
-            if (FULL) {
-                // the candidate a ballot of m-1 entries leaves out is last
-                if (col >= m) lo = hi = 0;
-                if (lo == UNSET) lo = (uint16_t)(m - 1);
-                if (hi == UNSET) hi = has_hi ? (uint16_t)(m - 1) : (uint16_t)0;
-            } else {
-                // unlisted (and the sentinel column): one shared position
-                if (!has_hi) hi = 0;
-            }
-            return (uint32_t)lo | ((uint32_t)hi << 16);
-        };
-        if (vec_out) {
-            // four words per 16-byte store
-            for (int i4 = 4 * threadIdx.x; i4 < cn; i4 += 4 * 256) {
-                const uint4 o = make_uint4(word(i4), word(i4 + 1), word(i4 + 2), word(i4 + 3));
-                *reinterpret_cast<uint4 *>(pos + q * (int64_t)pitch + c0 + i4) = o;
-            }
-        } else {
-            for (int i = threadIdx.x; i < cn; i += 256) pos[q * (int64_t)pitch + c0 + i] = word(i);
-        }
-        if (un0) atomicAdd(&unset_cnt[0], un0);
-        if (un1) atomicAdd(&unset_cnt[1], un1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int h = 0; h < 2; ++h) {
-            if (src[h] < 0) continue;
-            if (unset_cnt[h] != ncols - meta.len[src[h]]) set_device_error(err, SCHULZE_EBALLOT);
-        }
-    }
     }
 }
 
-// ------------------------------------------------------------------ position count
-// Persistent kernel.  Work units are (tile, chunk of VC voter pairs); each
-// workgroup takes a contiguous range of units (equal work per workgroup)
-// and flushes its accumulators into acc whenever the tile changes, a
-// segment of SEG_PAIRS pairs ends, or its range ends.
-//   SQUARE = false: full rankings, tiles X <= Y over candidates; the flush
-//                   also writes d[y][x] = voters - d[x][y].
+template <bool FULL, bool I32, int CH, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
+    constexpr int WAVES = THREADS / 64;
+    __shared__ uint32_t buf[16 * CH];
+    __shared__ int32_t repeated;  // entries less columns set
+    const int32_t count = FULL ? a.meta.ctr[0] : a.meta.ctr[1];
+    if (!FULL && a.meta.ctr[2] != MODE_DENSE_U) return;
+    const int64_t g = blockIdx.x;
+    if (32 * g >= count) return;
+    const int32_t pitch = FULL ? a.pitch : a.meta.ctr[4];
+    const int32_t c0 = (int32_t)blockIdx.y * CH;
+    if (c0 >= pitch) return;
+    const int32_t cn = min(CH, pitch - c0);             // a multiple of 64
+    const int32_t ncols = FULL ? a.m : a.meta.ctr[3];   // real columns: candidates or U
+    const int32_t bits = FULL ? a.bits : rank_bits(a.meta.ctr[6]);
+    const int32_t *srcs = FULL ? a.meta.full_src : a.meta.trunc_src;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t live = (int32_t)min((int64_t)32, count - 32 * g);  // voters of this group
+
+    for (int i = threadIdx.x; i < 16 * CH; i += THREADS) {
+        const int p = i / CH;
+        buf[i] = (2 * p < live ? 0xFFFFu : 0u) | (2 * p + 1 < live ? 0xFFFF0000u : 0u);
+    }
+    if (threadIdx.x == 0) repeated = 0;
+    int32_t extra = 0;
+    __syncthreads();
+    uint16_t *half = reinterpret_cast<uint16_t *>(buf);
+    for (int v = wave; v < live; v += WAVES) {  // a wavefront per ballot
+        const int32_t src = srcs[32 * g + v];
+        const int32_t k = a.meta.len[src];
+        const int64_t base = (int64_t)src * a.L;
+        uint16_t *row = half + (v >> 1) * (2 * CH) + (v & 1);
+        auto place = [&](int32_t t, int32_t id) {
+            if (t >= k || (uint32_t)id >= (uint32_t)a.m) return;  // reported by the scan
+            const int32_t col = (FULL ? id : a.meta.umap[id]) - c0;
+            if ((uint32_t)col >= (uint32_t)cn) return;
+            row[2 * col] = (uint16_t)t;
+            ++extra;
+        };
+        // several 16-byte pieces (or entries) per lane in flight
+        constexpr int FLY = 4;
+        constexpr int PER = I32 ? 4 : 8;
+        if (a.vec) {
+            const v4u *r4 = reinterpret_cast<const v4u *>(static_cast<const char *>(a.ballots) +
+                                                          base * (I32 ? 4 : 2));
+            const int32_t pieces = (k + PER - 1) / PER;
+            for (int32_t j0 = 0; j0 < pieces; j0 += 64 * FLY) {
+                v4u x[FLY];
+                for (int u = 0; u < FLY; ++u) x[u] = r4[min(j0 + 64 * u + lane, pieces - 1)];
+                for (int u = 0; u < FLY; ++u) {
+                    const int32_t j = j0 + 64 * u + lane;
+                    if (j >= pieces) break;
+                    for (int e = 0; e < PER; ++e) {
+                        const uint32_t w = x[u][I32 ? e : e >> 1];
+                        place(PER * j + e, (int32_t)(I32 ? w : (e & 1) ? w >> 16 : w & 0xFFFFu));
+                    }
+                }
+            }
+        } else {
+            for (int32_t j0 = 0; j0 < k; j0 += 64 * FLY) {
+                uint32_t x[FLY];
+                for (int u = 0; u < FLY; ++u) x[u] = load_raw<I32>(a.ballots, base + min(j0 + 64 * u + lane, k - 1));
+                for (int u = 0; u < FLY; ++u) place(j0 + 64 * u + lane, (int32_t)x[u]);
+            }
+        }
+    }
+    __syncthreads();
+    // the group's voters in the order of the planes' bits
+    const uint32_t voters = (uint32_t)((1u << ((live + 1) / 2)) - 1u) | (((1u << (live / 2)) - 1u) << 16);
+    for (int32_t cb = wave * 64; cb < cn; cb += THREADS) {
+        const int32_t c = cb + lane;
+        uint32_t w[16];
+        for (int p = 0; p < 16; ++p) w[p] = buf[p * CH + c];
+        transpose16(w);
+        uint32_t unset = w[0];
+        for (int b = 1; b < 16; ++b) unset &= w[b];
+        if (c0 + c < ncols) extra -= __popc(voters & ~unset);
+        uint32_t *out = a.planes + g * bits * (int64_t)pitch + c0 + c;
+#pragma unroll
+        for (int b = 0; b < MAX_BITS; ++b)
+            if (b < bits) out[(int64_t)b * pitch] = w[b];
+    }
+    for (int off = 32; off >= 1; off >>= 1) extra += __shfl_xor(extra, off);
+    if (lane == 0) atomicAdd(&repeated, extra);
+    __syncthreads();
+    if (threadIdx.x == 0 && repeated != 0) set_device_error(a.err, SCHULZE_EBALLOT);
+    if (a.weight && blockIdx.y == 0 && wave == 0) {
+        const int v = 2 * (lane & 15) + ((lane >> 4) & 1);  // the voter of bit `lane`
+        const uint32_t w = lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u;
+        uint32_t mine = 0u, sum = w;
+        for (int j = 0; j < 32; ++j) {
+            const uint32_t mask = (uint32_t)__ballot((w >> j) & 1u);
+            if (lane == j) mine = mask;
+        }
+        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+        if (lane < 32) a.wplanes[32 * g + lane] = mine;
+        if (FULL && lane == 0) atomicAdd(&a.meta.ctr[8], (int32_t)sum);
+    }
+}
+
+// ------------------------------------------------------------------ bit-plane count
+// Persistent kernel.  Work units are (tile of CT x CT candidates, group of
+// 32 voters); each workgroup takes a contiguous range of units (equal work
+// per workgroup).  A tile whose groups are all counted by one workgroup goes
+// straight into acc; the others' counts (at most the first and the last tile
+// of a range) go to that workgroup's two slots of partial tiles, which
+// k_count_reduce adds up: 64 KB written per slot, where device-wide atomics
+// into acc took 0.5 us per flushed tile for the whole chip (m = 1023,
+// n = 12007: 431 us, of which the counting is about 90).
+//   SQUARE = false: full rankings, tiles X <= Y over candidates; acc also
+//                   takes d[y][x] = voters - d[x][y].
 //   SQUARE = true:  truncated ballots over U space, all tiles (X, Y); U
 //                   indices map back through ulist; the sentinel column
 //                   y = |U| gives R[x].
+// Bound by the vector ALU: a thread carries 8 x 8 masks and counts, so a
+// bit takes 64 v_bitop3_b32 and four 16-byte LDS reads (8 row and 8 column
+// words), and the reads' 32 cycles per wavefront and bit hide behind the
+// products of the other wavefronts (three per SIMD).  v_bitop3_b32 issues at
+// twice the rate of v_bcnt_u32_b32 (66 against 37 T lane operations/s
+// measured) unless its three sources sit in registers of the same parity,
+// which the order of `lt` below avoids.  Larger thread tiles (16 x 8, counts
+// packed in 16 bits) had fewer reads per mask but two wavefronts per SIMD:
+// 81 T comparisons/s against 90.
 struct DenseArgs {
-    const uint32_t *pos;
-    int32_t pitch;  // full rankings: words per position row (multiple of CT)
+    const uint32_t *planes;
+    int32_t pitch, bits;  // full rankings (pitch a multiple of CT)
     int32_t m;
     Meta meta;
     uint32_t *acc;  // m x m
     int64_t lda;
     uint32_t *rsum;
+    const uint32_t *wplanes;  // with voter weights
+    uint32_t *partial;        // two CT x CT tiles per workgroup
 };
+
+// The units of a count and their division among the workgroups.
+struct CountPlan {
+    int32_t nvoters, groups, pitch, nb, nu;
+    int64_t ntiles, units, workers;
+    __device__ int64_t first(int64_t w) const { return units * w / workers; }
+};
+template <bool SQUARE>
+__device__ inline CountPlan count_plan(const DenseArgs &a, int32_t grid) {
+    CountPlan c;
+    c.nvoters = SQUARE ? a.meta.ctr[1] : a.meta.ctr[0];
+    c.groups = (c.nvoters + 31) / 32;  // units per tile
+    c.pitch = SQUARE ? a.meta.ctr[4] : a.pitch;
+    c.nu = SQUARE ? a.meta.ctr[3] : a.m;
+    c.nb = c.pitch / CT;
+    c.ntiles = SQUARE ? (int64_t)c.nb * c.nb : (int64_t)c.nb * (c.nb + 1) / 2;
+    // ranges of at least four units (writing and adding up a partial tile
+    // costs about as much as one)
+    c.units = c.ntiles * c.groups;
+    c.workers = min((int64_t)grid, (c.units + 3) / 4);
+    return c;
+}
+
+// Voters (their weight) that a full-ranking tile's mirror takes d[y][x] from.
+template <bool WEIGHTED>
+__device__ inline uint32_t full_total(const DenseArgs &a) {
+    return (uint32_t)(WEIGHTED ? a.meta.ctr[8] : a.meta.ctr[0]);
+}
+
+// cnt voters prefer x to y (indices of the count): into acc, and for full
+// rankings outside diagonal tiles the mirror too.  One thread per element
+// and launch: plain additions.
+template <bool SQUARE>
+__device__ inline void add_count(const DenseArgs &a, int32_t nu, int32_t x, int32_t y, bool mirror, uint32_t total,
+                                 uint32_t cnt) {
+    if (SQUARE) {
+        if (x >= nu || y > nu) return;
+        const int32_t gx = a.meta.ulist[x];
+        if (y == nu)
+            a.rsum[gx] += cnt;
+        else if (x != y)
+            a.acc[(int64_t)gx * a.lda + a.meta.ulist[y]] += cnt;
+    } else if (x < nu && y < nu && x != y) {
+        a.acc[(int64_t)x * a.lda + y] += cnt;
+        if (mirror) a.acc[(int64_t)y * a.lda + x] += total - cnt;
+    }
+}
 
 __device__ inline void tri_coords(int32_t t, int32_t nb, int32_t &X, int32_t &Y) {
     int32_t x = 0, start = 0;
@@ -502,192 +633,217 @@ __device__ inline void tri_coords(int32_t t, int32_t nb, int32_t &X, int32_t &Y)
     Y = x + (t - start);
 }
 
-template <bool SQUARE>
-__global__ __launch_bounds__(CNT_THREADS, 2) void k_count_pos(DenseArgs a) {
-    __shared__ __attribute__((aligned(16))) uint32_t xs[2][VC][CT];  // two buffers: the chunk counted
-    __shared__ __attribute__((aligned(16))) uint32_t ys[2][VC][CT];  // and the next one being staged
-    __shared__ uint32_t sred[4][2 * CT];
-
+template <bool SQUARE, bool WEIGHTED>
+__global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
+    constexpr int ROW = 2 * CT;  // LDS words per bit: the tile's rows, then its columns
+    constexpr int FLIP = WEIGHTED ? 1 : 0;  // (see above: registers are given in this order)
+    __shared__ __attribute__((aligned(16))) uint32_t lds[2 * MAX_BITS * ROW];
     if (SQUARE && a.meta.ctr[2] != MODE_DENSE_U) return;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int32_t nvoters = SQUARE ? a.meta.ctr[1] : a.meta.ctr[0];
-    const int64_t n_pairs = (nvoters + 1) / 2;
-    if (n_pairs == 0) return;
-    const int32_t pitch = SQUARE ? a.meta.ctr[4] : a.pitch;
-    const int32_t nu = SQUARE ? a.meta.ctr[3] : a.m;
-    const int32_t nb = pitch / CT;
-    const int64_t ntiles = SQUARE ? (int64_t)nb * nb : (int64_t)nb * (nb + 1) / 2;
-    const int64_t cpt = (n_pairs + VC - 1) / VC;  // chunks per tile
-    const int64_t U = ntiles * cpt;
-    const int64_t u0 = U * blockIdx.x / gridDim.x;
-    const int64_t u1 = U * (blockIdx.x + 1) / gridDim.x;
-    if (u0 >= u1) return;
+    CNT_LDS uint32_t *st = (CNT_LDS uint32_t *)lds;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the thread index, opaque: what the staging and the flush build from it
+    // is computed there, not kept in registers through the counting
+    auto thread = [] {
+        int i = (int)threadIdx.x;
+        asm volatile("" : "+v"(i));
+        return i;
+    };
+    const CountPlan c = count_plan<SQUARE>(a, gridDim.x);
+    if (blockIdx.x >= c.workers) return;
+    const int32_t groups = c.groups, pitch = c.pitch, nb = c.nb;
+    const int32_t bits = SQUARE ? rank_bits(a.meta.ctr[6]) : a.bits;
+    const int32_t wbits = WEIGHTED && a.meta.ctr[7] ? 32 - __clz(a.meta.ctr[7]) : 0;
+    const int64_t u0 = c.first(blockIdx.x), u1 = c.first(blockIdx.x + 1);
 
-    // staging role: fixed 4 columns, pairs (tid >> 6) + 4 * q
-    const int col4 = tid & 63;
-    const int prow = tid >> 6;
-
+    // a thread counts rows ty * 4 + (0 .. 3) and 64 + ty * 4 + (0 .. 3) of
+    // the tile, and columns likewise by tx: its 16-byte LDS reads are then
+    // contiguous over the lanes
     uint32_t acc[8][8];
-    uint32_t s4[4];
-    uint4 stage[8];
     for (int i = 0; i < 8; ++i)
         for (int j = 0; j < 8; ++j) acc[i][j] = 0u;
-    for (int e = 0; e < 4; ++e) s4[e] = 0u;
-
-    int32_t cur_tile = -1, X = 0, Y = 0;
-    int64_t seg_p0 = 0, seg_p1 = 0;
-
-    auto coords = [&](int32_t t, int32_t &tX, int32_t &tY) {
+    const int32_t t0 = (int32_t)(u0 / groups);
+    int32_t t = t0, X, Y;
+    int32_t g = (int32_t)(u0 % groups), seg0 = g;
+    auto coords = [&](int32_t tile, int32_t &tX, int32_t &tY) {
         if (SQUARE) {
-            tX = t / nb;
-            tY = t % nb;
+            tX = tile / nb;
+            tY = tile % nb;
         } else {
-            tri_coords(t, nb, tX, tY);
+            tri_coords(tile, nb, tX, tY);
         }
     };
-
-    auto load_unit = [&](int64_t u, uint4 (&dst)[8]) {
-        const int32_t t = (int32_t)(u / cpt);
-        const int64_t chunk = u % cpt;
-        int32_t tX, tY;
-        coords(t, tX, tY);
-        const int32_t col = col4 < 32 ? tX * CT + col4 * 4 : tY * CT + (col4 - 32) * 4;
-        const int64_t p0 = chunk * VC;
-        for (int q = 0; q < 8; ++q) {
-            const int64_t pr = p0 + prow + 4 * q;
-            if (pr < n_pairs)
-                dst[q] = *reinterpret_cast<const uint4 *>(a.pos + pr * pitch + col);
-            else
-                dst[q] = make_uint4(0u, 0u, 0u, 0u);
-        }
+    // group sg of tile (tX, tY) to buffer sb: one wavefront instruction per
+    // bit, lanes 0 .. 31 the tile's rows, 32 .. 63 its columns
+    auto stage = [&](int32_t tX, int32_t tY, int32_t sg, int sb) {
+        const uint32_t *src = a.planes + (int64_t)sg * bits * pitch;
+        const int lane = thread() & 63;
+        const uint32_t off = lane < 32 ? tX * CT + 4 * lane : tY * CT + 4 * (lane - 32);
+        for (int b = wave; b < bits; b += 4)
+            __builtin_amdgcn_global_load_lds(src + (int64_t)b * pitch + off, st + (sb * MAX_BITS + b) * ROW, 16, 0, 0);
     };
-
-    auto flush = [&]() {
-        __syncthreads();
-        for (int e = 0; e < 4; ++e) sred[prow][col4 * 4 + e] = s4[e];
-        __syncthreads();
-        uint32_t sx[8], sy[8];
-        for (int i = 0; i < 8; ++i) {
-            const int c = ty * 8 + i;
-            sx[i] = sred[0][c] + sred[1][c] + sred[2][c] + sred[3][c];
-        }
-        for (int j = 0; j < 8; ++j) {
-            const int c = CT + tx * 8 + j;
-            sy[j] = sred[0][c] + sred[1][c] + sred[2][c] + sred[3][c];
-        }
-        const int64_t hi = min((int64_t)nvoters, 2 * seg_p1);
-        const uint32_t nv = (uint32_t)max((int64_t)0, hi - 2 * seg_p0);
+    auto flush = [&](int32_t seg1) {
+        const int ftx = thread() & 15, fty = thread() >> 4;
+        if (seg0 == 0 && seg1 == groups) {
+            const uint32_t total = full_total<WEIGHTED>(a);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int32_t x = X * CT + ty * 8 + i;
+            for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int32_t y = Y * CT + tx * 8 + j;
-                const uint32_t cnt = (acc[i][j] - sx[i] + sy[j]) >> 16;
-                if (SQUARE) {
-                    if (x < nu) {
-                        const int32_t gx = a.meta.ulist[x];
-                        if (y < nu && x != y)
-                            atomicAdd(&a.acc[(int64_t)gx * a.lda + a.meta.ulist[y]], cnt);
-                        else if (y == nu)
-                            atomicAdd(&a.rsum[gx], cnt);
-                    }
-                } else if (x < nu && y < nu && x != y) {
-                    atomicAdd(&a.acc[(int64_t)x * a.lda + y], cnt);
-                    if (X != Y) atomicAdd(&a.acc[(int64_t)y * a.lda + x], nv - cnt);
-                }
-                acc[i][j] = 0u;
-            }
+                for (int j = 0; j < 8; ++j)
+                    add_count<SQUARE>(a, c.nu, X * CT + (i & 4) * 16 + fty * 4 + (i & 3),
+                                      Y * CT + (j & 4) * 16 + ftx * 4 + (j & 3), X != Y, total, acc[i][j]);
+        } else {
+            uint32_t *out = a.partial + ((int64_t)blockIdx.x * 2 + (t != t0)) * (CT * CT);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; j += 4)
+                    *reinterpret_cast<uint4 *>(out + ((i & 4) * 16 + fty * 4 + (i & 3)) * CT + (j & 4) * 16 + ftx * 4) =
+                        make_uint4(acc[i][j], acc[i][j + 1], acc[i][j + 2], acc[i][j + 3]);
         }
-        for (int e = 0; e < 4; ++e) s4[e] = 0u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = 0u;
     };
 
-    const us2 ones = {1, 1};
-    // staged words into LDS buffer sb, their column sums added to sadd
-    auto stage_write = [&](int sb, uint32_t (&sadd)[4]) {
-        for (int q = 0; q < 8; ++q) {
-            const int pr = prow + 4 * q;
-            uint32_t *dst = col4 < 32 ? &xs[sb][pr][col4 * 4] : &ys[sb][pr][(col4 - 32) * 4];
-            *reinterpret_cast<uint4 *>(dst) = stage[q];
-            sadd[0] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, stage[q].x), ones, sadd[0], false);
-            sadd[1] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, stage[q].y), ones, sadd[1], false);
-            sadd[2] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, stage[q].z), ones, sadd[2], false);
-            sadd[3] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, stage[q].w), ones, sadd[3], false);
-        }
-    };
-
-    // Unit u is counted from one LDS buffer while unit u+1 is staged into the
-    // other: one barrier per unit.  The next unit's column sums wait in s4n
-    // until the current segment has been flushed.
-    load_unit(u0, stage);
-    stage_write(0, s4);
-    __syncthreads();
-    int cur = 0;
+    coords(t, X, Y);
+    stage(X, Y, g, 0);
     for (int64_t u = u0; u < u1; ++u) {
-        const int32_t t = (int32_t)(u / cpt);
-        const int64_t chunk = u % cpt;
-        if (t != cur_tile) {
-            cur_tile = t;
-            coords(t, X, Y);
-            seg_p0 = chunk * VC;
-        } else if (chunk % SEGC == 0) {
-            seg_p0 = chunk * VC;
+        const int sb = (int)((u - u0) & 1);
+        __builtin_amdgcn_s_waitcnt(0);  // this wavefront's pieces of unit u are in LDS
+        __syncthreads();                // everyone's are, and unit u-1 is consumed
+        int32_t nX = X, nY = Y;
+        int32_t ng = g + 1;
+        if (ng == groups) {
+            ng = 0;
+            if (u + 1 < u1) coords(t + 1, nX, nY);
         }
-        seg_p1 = min(n_pairs, (chunk + 1) * VC);
-        const bool more = u + 1 < u1;
-        if (more) load_unit(u + 1, stage);  // overlaps the compute below
+        if (u + 1 < u1) stage(nX, nY, ng, sb ^ 1);
 
-        // Two voter pairs per iteration, the LDS reads of each pair issued
-        // before the products of the previous one (scheduling barriers keep
-        // them there), so that their latency hides behind 128 VALU
-        // instructions.
-        const uint32_t(*xb)[CT] = cur ? xs[1] : xs[0];  // (selects: no dynamically indexed arrays)
-        const uint32_t(*yb)[CT] = cur ? ys[1] : ys[0];
-        auto read_pair = [&](int v, uint4 (&q)[4]) {
-            q[0] = *reinterpret_cast<const uint4 *>(&xb[v][ty * 8]);
-            q[1] = *reinterpret_cast<const uint4 *>(&xb[v][ty * 8 + 4]);
-            q[2] = *reinterpret_cast<const uint4 *>(&yb[v][tx * 8]);
-            q[3] = *reinterpret_cast<const uint4 *>(&yb[v][tx * 8 + 4]);
+        const CNT_LDS uint32_t *rows = st + sb * MAX_BITS * ROW;
+        uint32_t lt[8][8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) lt[i][j ^ FLIP] = 0u;
+        struct Bit {
+            v4u x[2], y[2];
         };
-        auto count_pair = [&](const uint4 (&q)[4]) {
-            const uint32_t xv[8] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w};
-            const uint32_t yv[8] = {q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const us2 xi = __builtin_bit_cast(us2, xv[i]);
-                us2 diff[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) diff[j] = xi - __builtin_bit_cast(us2, yv[j]);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_udot2(diff[j], ones, acc[i][j], false);
-            }
+        auto read = [&](int b, Bit &q) {
+            const CNT_LDS uint32_t *r = rows + b * ROW;
+            q.x[0] = *(const CNT_LDS v4u *)(r + ty * 4);
+            q.x[1] = *(const CNT_LDS v4u *)(r + 64 + ty * 4);
+            q.y[0] = *(const CNT_LDS v4u *)(r + CT + tx * 4);
+            q.y[1] = *(const CNT_LDS v4u *)(r + CT + 64 + tx * 4);
         };
-        static_assert(VC % 2 == 0 && (VC & (VC - 1)) == 0, "voter pairs per chunk");
-        uint4 qa[4], qb[4];
-        read_pair(0, qa);
+        auto step = [&](const Bit &q) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)  // (~x & y) | (~(x ^ y) & lt)
+                    lt[i][j] = __builtin_amdgcn_bitop3_b32(q.x[i >> 2][i & 3], q.y[j >> 2][j & 3], lt[i][j], 0x8E);
+        };
+        // the next bit's reads are issued before the products of this one
+        // (the scheduling barriers keep them there)
+        Bit q0, q1;
+        read(0, q0);
 #pragma unroll 1
-        for (int v = 0; v < VC; v += 2) {
-            read_pair(v + 1, qb);
+        for (int b = 0; b + 1 < bits; b += 2) {
+            read(b + 1, q1);
             __builtin_amdgcn_sched_barrier(0);
-            count_pair(qa);
-            read_pair((v + 2) & (VC - 1), qa);  // (after the last pair: pair 0 again, unused)
+            step(q0);
             __builtin_amdgcn_sched_barrier(0);
-            count_pair(qb);
+            read(b + 2 < bits ? b + 2 : 0, q0);
+            __builtin_amdgcn_sched_barrier(0);
+            step(q1);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        uint32_t s4n[4] = {0u, 0u, 0u, 0u};
-        if (more) stage_write(cur ^ 1, s4n);
-        __syncthreads();  // the next unit is staged; everyone is done with this one
+        if (bits & 1) step(q0);
+        if constexpr (WEIGHTED) {
+            for (int32_t b = 0; b < wbits; ++b) {
+                const uint32_t wm = a.wplanes[32 * g + b];
+                if (wm == 0u) continue;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[i][j] += (uint32_t)__popc(lt[i][j] & wm) << b;
+            }
+        } else {
+            // (the popcount instruction adds: written out, as the compiler
+            // splits the addition off)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    asm("v_bcnt_u32_b32 %0, %1, %0" : "+v"(acc[i][j]) : "v"(lt[i][j]));
+        }
+        if (ng == 0 || u + 1 == u1) {
+            flush(g + 1);
+            seg0 = 0;
+            if (ng == 0) ++t;
+        }
+        X = nX;
+        Y = nY;
+        g = ng;
+    }
+}
 
-        bool boundary = !more;
-        if (more) {
-            const int32_t tn = (int32_t)((u + 1) / cpt);
-            const int64_t cn = (u + 1) % cpt;
-            boundary = tn != t || cn % SEGC == 0;
+// The partial tiles added up: a workgroup takes 32 rows of a tile that
+// several workgroups of k_count_bits (launched with `grid`) counted.  The
+// mirror of a full-ranking tile goes through LDS, so that both are written
+// along rows.
+template <bool SQUARE, bool WEIGHTED>
+__global__ __launch_bounds__(256) void k_count_reduce(DenseArgs a, int32_t grid) {
+    __shared__ uint32_t buf[32][CT + 1];
+    if (SQUARE && a.meta.ctr[2] != MODE_DENSE_U) return;
+    const CountPlan c = count_plan<SQUARE>(a, grid);
+    if (c.units == 0) return;
+    const uint32_t total = full_total<WEIGHTED>(a);
+    const int col = (threadIdx.x & 31) * 4, row = threadIdx.x >> 5;
+    for (int64_t q = blockIdx.x; q < 4 * c.ntiles; q += gridDim.x) {
+        const int32_t t = (int32_t)(q >> 2), r0 = (int32_t)(q & 3) * 32;
+        const int64_t ub = (int64_t)t * c.groups, ue = ub + c.groups;
+        // the workgroups whose ranges meet the tile's
+        int64_t w0 = ub * c.workers / c.units, w1 = (ue - 1) * c.workers / c.units;
+        while (c.first(w0 + 1) <= ub) ++w0;
+        while (c.first(w0) > ub) --w0;
+        while (c.first(w1 + 1) < ue) ++w1;
+        while (c.first(w1) >= ue) --w1;
+        if (w0 == w1) continue;  // counted whole, in acc already
+        uint32_t v[4][4] = {};
+        for (int64_t w = w0; w <= w1; ++w) {
+            const uint32_t *p = a.partial + (2 * w + (c.first(w) < ub)) * (CT * CT) + r0 * CT + col;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(p + (row + 8 * k) * CT);
+                v[k][0] += x.x;
+                v[k][1] += x.y;
+                v[k][2] += x.z;
+                v[k][3] += x.w;
+            }
         }
-        if (boundary) flush();
-        for (int e = 0; e < 4; ++e) s4[e] += s4n[e];
-        cur ^= 1;
+        int32_t X, Y;
+        if (SQUARE) {
+            X = t / c.nb;
+            Y = t % c.nb;
+        } else {
+            tri_coords(t, c.nb, X, Y);
+        }
+        __syncthreads();  // the last tile's mirror has been read
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                add_count<SQUARE>(a, c.nu, X * CT + r0 + row + 8 * k, Y * CT + col + e, false, 0u, v[k][e]);
+                if (!SQUARE) buf[row + 8 * k][col + e] = v[k][e];
+            }
+        if (SQUARE || X == Y) continue;
+        __syncthreads();
+        for (int i = threadIdx.x; i < 32 * CT; i += 256) {
+            const int32_t x = X * CT + r0 + (i & 31), y = Y * CT + (i >> 5);
+            if (x < c.nu && y < c.nu) a.acc[(int64_t)y * a.lda + x] += total - buf[i & 31][i >> 5];
+        }
     }
 }
 
@@ -1231,28 +1387,6 @@ __global__ __launch_bounds__(256) void k_occ_finish(OccArgs a, T *__restrict__ d
     if (over) set_device_error(a.err, SCHULZE_ERANGE);
 }
 
-// ------------------------------------------------------------------ weighted full rankings
-// Full rankings with voter weights: plain compare-and-add per voter (the
-// modular trick needs unit weights to bound a segment's total).
-__global__ __launch_bounds__(256) void k_count_full_weighted(const uint32_t *__restrict__ weight, Meta meta,
-                                                             const uint32_t *__restrict__ pos, int32_t pitch, int32_t m,
-                                                             uint32_t *__restrict__ acc, int64_t lda) {
-    // one thread per (x, y) pair of a 16 x 16 block, looping over voters
-    const int32_t x = blockIdx.y * 16 + (threadIdx.x >> 4);
-    const int32_t y = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int32_t n_full = meta.ctr[0];
-    if (x >= m || y >= m || x == y) return;
-    uint32_t s = 0u;
-    for (int32_t q = 0; 2 * q < n_full; ++q) {
-        const uint32_t px = pos[(int64_t)q * pitch + x], py = pos[(int64_t)q * pitch + y];
-        const uint32_t w0 = weight[meta.full_src[2 * q]];
-        const uint32_t w1 = 2 * q + 1 < n_full ? weight[meta.full_src[2 * q + 1]] : 0u;
-        s += ((px & 0xFFFFu) < (py & 0xFFFFu)) ? w0 : 0u;
-        s += ((px >> 16) < (py >> 16)) ? w1 : 0u;
-    }
-    acc[(int64_t)x * lda + y] += s;
-}
-
 // ------------------------------------------------------------------ finish
 // d[x][y] = acc[x][y] plus the truncated ballots' R term, 0 on the
 // diagonal; range-checked store.
@@ -1292,10 +1426,17 @@ __global__ __launch_bounds__(256) void k_count_finish(const uint32_t *__restrict
 // SCHULZE_ERANGE.  total and done start at zero; the last workgroup to add
 // its part decides.
 __global__ __launch_bounds__(256) void k_weight_total(const uint32_t *__restrict__ w, int64_t n,
-                                                      unsigned long long *total, int32_t *done, int32_t *err) {
+                                                      unsigned long long *total, int32_t *done, int32_t *any,
+                                                      int32_t *err) {
     __shared__ unsigned long long part[256];
     unsigned long long acc = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) acc += w[i];
+    uint32_t ored = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        acc += w[i];
+        ored |= w[i];
+    }
+    for (int off = 32; off >= 1; off >>= 1) ored |= __shfl_xor(ored, off);
+    if ((threadIdx.x & 63) == 0 && ored) atomicOr(any, (int32_t)ored);
     part[threadIdx.x] = acc;
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {
@@ -1464,7 +1605,43 @@ int occ_accumulate(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid
     return SCHULZE_OK;
 }
 
-constexpr size_t TRUNC_POS_CAP = (size_t)1 << 30;
+// Rank planes and the bit-plane count of the full rankings (FULL) or, if the
+// device chose the dense route, of the truncated ballots over U (pitch: at
+// most that many columns).  A workgroup of the planes takes 2048 columns
+// with 1024 threads (128 KB of LDS; each further chunk of columns reads the
+// ballots again) or, for at most 1024 columns, 512 with 256 threads.
+template <bool FULL>
+int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32, int32_t L, int32_t m, int32_t pitch,
+                int32_t bits, int64_t max_groups, const Meta &meta, const uint32_t *weight, uint32_t *planes,
+                uint32_t *wplanes, uint32_t *acc, int64_t lda, uint32_t *rsum) {
+    const int vec = L % (dtype32 ? 4 : 8) == 0 && reinterpret_cast<uintptr_t>(ballots) % 16 == 0;
+    const PlaneArgs pa{ballots, L, m, pitch, bits, meta, weight, planes, wplanes, ctx->err, vec};
+    const int wide = pitch > 1024;
+    const dim3 pg((unsigned)max_groups, (unsigned)ceil_div(pitch, wide ? 2048 : 512));
+    if (wide && dtype32)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, true, 2048, 1024><<<pg, dim3(1024), 0, s>>>(pa)));
+    else if (wide)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, false, 2048, 1024><<<pg, dim3(1024), 0, s>>>(pa)));
+    else if (dtype32)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, true, 512, 256><<<pg, dim3(256), 0, s>>>(pa)));
+    else
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, false, 512, 256><<<pg, dim3(256), 0, s>>>(pa)));
+    const int32_t grid = ctx->num_cus * COUNT_PER_CU;
+    const DenseArgs da{planes, pitch, bits, m, meta, acc, lda, rsum, wplanes, static_cast<uint32_t *>(ctx->ws[WS_PARTIAL])};
+    const dim3 cg((unsigned)grid), rg((unsigned)std::min<int64_t>(4 * ceil_div(pitch, CT) * ceil_div(pitch, CT),
+                                                                   (int64_t)ctx->num_cus * 8));
+    const int kid = FULL ? K_COUNT_DENSE : K_COUNT_TRUNC;
+    if (FULL && weight) {
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<!FULL, FULL><<<cg, dim3(256), 0, s>>>(da)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<!FULL, FULL><<<rg, dim3(256), 0, s>>>(da, grid)));
+    } else {
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<!FULL, false><<<cg, dim3(256), 0, s>>>(da)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<!FULL, false><<<rg, dim3(256), 0, s>>>(da, grid)));
+    }
+    return SCHULZE_OK;
+}
+
+constexpr size_t TRUNC_PLANES_CAP = (size_t)1 << 30;
 
 }  // namespace
 
@@ -1482,13 +1659,18 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     hipStream_t s = (hipStream_t)stream;
     const int dtype32 = ballot_dtype == SCHULZE_I32;
     const int32_t pitch = (int32_t)round_up(m, CT);
-    const int64_t max_pairs = (n + 1) / 2;
+    const int64_t max_groups = ceil_div(n, 32);  // of 32 voters
     const bool may_have_full = L >= m - 1 && n > 0;
     const bool may_have_trunc = n > 0;  // a row may always end early
     const int64_t upitch_max = round_up((int64_t)m + 1, CT);
-    const size_t tpos_bytes = may_have_trunc && !voter_weight
-                                  ? std::min(TRUNC_POS_CAP, sizeof(uint32_t) * (size_t)max_pairs * (size_t)upitch_max)
-                                  : 0;
+    const int32_t full_bits = rank_bits(m - 1), trunc_bits = rank_bits(L);
+    const size_t trunc_bytes =
+        may_have_trunc && !voter_weight
+            ? std::min(TRUNC_PLANES_CAP,
+                       sizeof(uint32_t) * (size_t)max_groups * trunc_bits * (size_t)upitch_max)
+            : 0;
+    // weights: 32 planes per group of the full rankings (weighted truncated ballots are counted by pairs)
+    const size_t weight_words = voter_weight ? 32 * (size_t)max_groups : 0;
 
     const MetaLayout lay(n, m);
     int rc;
@@ -1496,9 +1678,15 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     if ((rc = ws_reserve(ctx, WS_ACC32, sizeof(uint32_t) * (size_t)m * m)) != SCHULZE_OK) return rc;
     if ((rc = ws_reserve(ctx, WS_ROWSUM, sizeof(uint32_t) * (size_t)m)) != SCHULZE_OK) return rc;
     if (may_have_full &&
-        (rc = ws_reserve(ctx, WS_POSITIONS, sizeof(uint32_t) * (size_t)max_pairs * pitch)) != SCHULZE_OK)
+        (rc = ws_reserve(ctx, WS_POSITIONS, sizeof(uint32_t) * ((size_t)max_groups * full_bits * pitch + weight_words))) !=
+            SCHULZE_OK)
         return rc;
-    if (tpos_bytes && (rc = ws_reserve(ctx, WS_TRUNC_POS, tpos_bytes)) != SCHULZE_OK) return rc;
+    if (trunc_bytes &&
+        (rc = ws_reserve(ctx, WS_TRUNC_POS, trunc_bytes)) != SCHULZE_OK)
+        return rc;
+    if (n > 0 && (rc = ws_reserve(ctx, WS_PARTIAL, sizeof(uint32_t) * 2 * CT * CT * (size_t)ctx->num_cus * COUNT_PER_CU)) !=
+                     SCHULZE_OK)
+        return rc;
     // bucketed pair counting: an LDS row of counts per candidate and a bounded occurrence buffer
     const int64_t occ_cap = n * (int64_t)L;
     const bool occ_ok = n > 0 && m <= OCC_MAX_M && occ_cap <= OCC_MAX && !ctx->legacy_pairs;
@@ -1553,9 +1741,16 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
                 SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
                                k_scan_long<false><<<lg, dim3(256), 0, s>>>(ballots, n, L, m, meta, ctx->err));
         }
+        if (voter_weight) {
+            // counters 32..33: the 64-bit total; 34: workgroups done; 7: the weights or-ed (zeroed above)
+            const unsigned tg = (unsigned)std::min<int64_t>(ceil_div(n, 256), (int64_t)ctx->num_cus * 4);
+            SCHULZE_LAUNCH(ctx, K_ROUTE, s,
+                           k_weight_total<<<dim3(tg), dim3(256), 0, s>>>(
+                               voter_weight, n, reinterpret_cast<unsigned long long *>(meta.ctr + 32), meta.ctr + 34,
+                               meta.ctr + 7, ctx->err));
+        }
         SCHULZE_LAUNCH(ctx, K_ROUTE, s,
-                       k_route<<<dim3(1), dim3(ROUTE_THREADS), 0, s>>>(m, meta, voter_weight != nullptr,
-                                                             (int64_t)(tpos_bytes / sizeof(uint32_t)),
+                       k_route<<<dim3(1), dim3(ROUTE_THREADS), 0, s>>>(m, meta, (int64_t)(trunc_bytes / sizeof(uint32_t)),
                                                              occ_ok ? BUCKETED_PAIR_COST : ATOMIC_PAIR_COST));
         {
             // the m x m accumulator starts at zero unless the device chose the
@@ -1566,48 +1761,18 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
             SCHULZE_LAUNCH(ctx, K_FILL, s,
                            k_fill_acc<<<dim3(fg), dim3(256), 0, s>>>(acc, words, meta, occ_ok && !may_have_full ? 1 : 0));
         }
-        if (voter_weight) {
-            // counters 32..33: the 64-bit total; 34: workgroups done (zeroed above)
-            const unsigned tg = (unsigned)std::min<int64_t>(ceil_div(n, 256), (int64_t)ctx->num_cus * 4);
-            SCHULZE_LAUNCH(ctx, K_ROUTE, s,
-                           k_weight_total<<<dim3(tg), dim3(256), 0, s>>>(
-                               voter_weight, n, reinterpret_cast<unsigned long long *>(meta.ctr + 32), meta.ctr + 34,
-                               ctx->err));
-        }
-        const unsigned cgrid = (unsigned)ctx->num_cus * 2;
-        const unsigned scatter_grid = (unsigned)std::min<int64_t>(max_pairs, (int64_t)ctx->num_cus * 16);
         if (may_have_full) {
-            uint32_t *pos = static_cast<uint32_t *>(ctx->ws[WS_POSITIONS]);
-            if (dtype32)
-                SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s,
-                               k_scatter<true, true><<<dim3(scatter_grid), dim3(256), 0, s>>>(
-                                   ballots, L, m, pitch, meta, pos, ctx->err));
-            else
-                SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s,
-                               k_scatter<true, false><<<dim3(scatter_grid), dim3(256), 0, s>>>(
-                                   ballots, L, m, pitch, meta, pos, ctx->err));
-            if (!voter_weight) {
-                DenseArgs da{pos, pitch, m, meta, acc, lda, rsum};
-                SCHULZE_LAUNCH(ctx, K_COUNT_DENSE, s, k_count_pos<false><<<dim3(cgrid), dim3(CNT_THREADS), 0, s>>>(da));
-            } else {
-                dim3 grid((unsigned)ceil_div(m, 16), (unsigned)ceil_div(m, 16));
-                SCHULZE_LAUNCH(ctx, K_COUNT_DENSE, s,
-                               k_count_full_weighted<<<grid, dim3(256), 0, s>>>(voter_weight, meta, pos, pitch, m, acc,
-                                                                               lda));
-            }
+            uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_POSITIONS]);
+            uint32_t *wplanes = voter_weight ? planes + (size_t)max_groups * full_bits * pitch : nullptr;
+            if ((rc = count_dense<true>(ctx, s, ballots, dtype32, L, m, pitch, full_bits, max_groups, meta,
+                                        voter_weight, planes, wplanes, acc, lda, rsum)) != SCHULZE_OK)
+                return rc;
         }
-        if (tpos_bytes) {
-            uint32_t *tpos = static_cast<uint32_t *>(ctx->ws[WS_TRUNC_POS]);
-            if (dtype32)
-                SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s,
-                               k_scatter<false, true><<<dim3(scatter_grid), dim3(256), 0, s>>>(
-                                   ballots, L, m, 0, meta, tpos, ctx->err));
-            else
-                SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s,
-                               k_scatter<false, false><<<dim3(scatter_grid), dim3(256), 0, s>>>(
-                                   ballots, L, m, 0, meta, tpos, ctx->err));
-            DenseArgs da{tpos, 0, m, meta, acc, lda, rsum};
-            SCHULZE_LAUNCH(ctx, K_COUNT_TRUNC, s, k_count_pos<true><<<dim3(cgrid), dim3(CNT_THREADS), 0, s>>>(da));
+        if (trunc_bytes) {
+            uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_TRUNC_POS]);
+            if ((rc = count_dense<false>(ctx, s, ballots, dtype32, L, m, (int32_t)upitch_max, 0, max_groups, meta,
+                                         nullptr, planes, nullptr, acc, lda, rsum)) != SCHULZE_OK)
+                return rc;
         }
         if (occ_ok) {
             // bucketed pair counting (runs only if the device chose pair scattering)
