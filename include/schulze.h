@@ -535,7 +535,7 @@ typedef struct {
 
 typedef struct {
     int32_t max_range_pairs; /* 0 = automatic; else at most this many voter pairs per counting range */
-    int32_t closure_only;    /* 1 = the plan only serves runs without ballots (no rank-pair buffer) */
+    int32_t closure_only;    /* 1 = the plan only serves runs without ballots (no buffer of ranks) */
     int32_t topk;            /* 0 = no levels; k > 0: runs given a level array rank at least k candidates
                                 per election by iterated winner removal (as schulze_topk_propagate) */
     int32_t reserved[5];     /* zero */
@@ -547,7 +547,7 @@ typedef struct schulze_batch schulze_batch;
  * Plan a batch: validate the descriptors (host memory, E entries), choose per
  * election the counting layout and the closure schedule (see
  * schulze_batch_set_closure), order the work largest election first, and
- * allocate the plan's device memory: about n*m*2 bytes of rank pairs per
+ * allocate the plan's device memory: n*m*log2(m)/8 bytes of rank planes per
  * election, one closure matrix per resident workgroup, counters.
  *
  * Ballots follow schulze_pairwise (ids best first, padding ends a ballot), with

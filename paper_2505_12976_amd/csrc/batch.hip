@@ -5,18 +5,16 @@
 // plan turns the batch into a queue of work items; the workgroups of one
 // persistent kernel take items in queue order from an atomic ticket:
 //
-//   scan    ballots of one range of voters -> rank pairs (the ranks of two
-//           voters in one 32-bit word, low half the even voter), checked for
-//           ids out of range, repeated ids and ids after padding;
+//   scan    ballots of one range of voters -> bit planes of the ranks (32
+//           voters per 32-bit word), checked for ids out of range, repeated
+//           ids and ids after padding;
 //   count   one run of up to 256 sub-blocks of 8 x 8 candidates of one
-//           election over one range of voters.  For a pair (x, y) and a
-//           voter, t = (rank(x) - rank(y)) mod 2^16 equals
-//           rank(x) - rank(y) + 2^16 [rank(x) < rank(y)], so summed over
-//           voters  sum t = Sx - Sy + 2^16 #(x before y)  with Sx the sum of
-//           x's ranks: one v_pk_sub_u16 and one v_dot2_u32_u16 handle two
-//           voters.  Complete rankings have no ties, so only sub-blocks with
-//           x-block <= y-block are counted and d[y][x] = voters - d[x][y];
-//           elections with truncated ballots count every ordered sub-block;
+//           election over one range of voters: per pair (x, y) the mask of
+//           the voters with rank(x) < rank(y), one v_bitop3_b32 per bit of
+//           the ranks, and its population count.  Complete rankings have no
+//           ties, so only sub-blocks with x-block <= y-block are counted and
+//           d[y][x] = voters - d[x][y]; elections with truncated ballots
+//           count every ordered sub-block;
 //   finish  edge weights, closure, beaten-by counts, winners and ranking of
 //           one election in one workgroup, started by the workgroup that
 //           completes the election's last count item.
@@ -41,22 +39,21 @@
 #include <vector>
 
 #include "fw_tiles.h"
+#include "planes.h"
 
 namespace {
 
 using namespace fw;
 
 constexpr int BT = 256;                          // threads per workgroup
-constexpr int STAGE_WORDS = 16384;               // count staging: VC x cols words
-constexpr int SRED_WORDS = SCHULZE_BATCH_MAX_M;  // column sums of a count item
-constexpr int SMEM_WORDS = STAGE_WORDS + SRED_WORDS + 64;
-constexpr int SEG_PAIRS = 32767;           // at most 65534 voters per exact sum
-constexpr int64_t SCAN_WORDS = 1 << 20;    // rank-pair words written per scan item
+constexpr int STAGE_WORDS = 16384;               // count staging: two buffers of rows x cols words
+constexpr int SMEM_WORDS = STAGE_WORDS + 1024 + 64;
+constexpr int RANGE_PAIRS = 32767;         // voter pairs per count range unless the caller asks for fewer
+constexpr int64_t SCAN_WORDS = 1 << 20;    // rank-pair words staged per scan item
 constexpr int SCAN_GROUP_WORDS = 16384;    // rank-pair words staged at once by a scan
 constexpr int SCAN_VEC = 16;              // 16-byte ballot loads in flight per thread
 constexpr int SCAN_GROUP_PAIRS = 32;      // voter pairs staged at once by a scan, at most
-constexpr int MAX_PF = 8;                  // 16-byte loads per thread per count chunk
-constexpr uint16_t UNSET = 0xFFFF;
+constexpr int CHUNK_QUADS = 32;            // staged rows of 64 16-byte quads per count chunk
 constexpr int64_t SPIN_LIMIT = (int64_t)1 << 24;
 
 enum ItemKind : int32_t { IT_SCAN = 0, IT_COUNT = 1, IT_FINISH = 2 };
@@ -68,22 +65,24 @@ struct BElec {
     int64_t n;           // voters
     int64_t mat_off;     // elements of d and p
     int64_t vec_off;     // elements of is_winner, beaten_by, order
-    int64_t pos_off;     // rank-pair words
+    int64_t pos_off;     // rank-plane words
     int32_t m, L;
-    int32_t pitch;        // rank-pair words per voter pair (= 8 * nb8)
+    int32_t pitch;        // words per plane row (= 8 * nb8)
     int32_t flags;        // ElecFlags
     int32_t n_scan;       // scan items
     int32_t n_count;      // count items
     int32_t variant;      // closure schedule
     int32_t mp;           // padded closure size
     int32_t nb8;          // blocks of 8 candidates
-    int32_t vc;           // voter pairs per staged chunk (64 / ng)
+    int32_t rows;         // plane rows per staged chunk
     int32_t ng;           // column groups of 64 quads in a staged row (1, 2 or 4)
     int32_t vs;           // voter split of small elections (1, 2 or 4)
-    int32_t range_pairs;  // voter pairs per count range
-    int32_t scan_pairs;   // voter pairs per scan item
+    int32_t bits;         // planes per group of voters
+    int32_t group_pairs;  // voter pairs per group (16, or fewer if the caller asks for smaller ranges)
+    int32_t range_groups; // groups per count range
+    int32_t scan_pairs;   // voter pairs per scan item (a multiple of group_pairs)
 };
-static_assert(sizeof(BElec) == 96, "BElec layout");
+static_assert(sizeof(BElec) == 104, "BElec layout");
 
 struct BItem {
     int32_t kind, e, a, b;  // scan: a = first voter pair, b = pairs; count: a = run, b = range
@@ -99,7 +98,7 @@ struct BatchArgs {
     int32_t mode;
     int32_t closure_only;
     int32_t pad0;
-    uint32_t *pos;
+    uint32_t *planes;
     int32_t *d;
     int32_t *p;
     uint8_t *is_winner;
@@ -136,8 +135,10 @@ __device__ inline int32_t ballot_id(uint16_t v) { return v == 0xFFFF ? -1 : (int
 // the error x * (inv - 2^32/d) / 2^32 < 2^-16 <= 1/d never crosses an integer.
 __device__ inline uint32_t div_small(uint32_t x, uint32_t inv) { return __umulhi(x, inv); }
 
-__host__ __device__ inline int32_t scan_group_pairs(int32_t pitch) {
-    return SCAN_GROUP_WORDS / pitch < SCAN_GROUP_PAIRS ? SCAN_GROUP_WORDS / pitch : SCAN_GROUP_PAIRS;
+// Voter pairs staged at once: whole groups (pitch <= 1024: at least 16 pairs fit)
+__host__ __device__ inline int32_t scan_group_pairs(int32_t pitch, int32_t group_pairs) {
+    const int32_t fit = SCAN_GROUP_WORDS / pitch < SCAN_GROUP_PAIRS ? SCAN_GROUP_WORDS / pitch : SCAN_GROUP_PAIRS;
+    return fit / group_pairs * group_pairs;
 }
 
 __device__ inline void abort_all(const BatchArgs &a) {
@@ -146,11 +147,14 @@ __device__ inline void abort_all(const BatchArgs &a) {
 }
 
 // ------------------------------------------------------------------ scan
-// Voter pairs [q0, q0 + nq) of one election, SCAN_GROUP_WORDS words at a time.
+// Voter pairs [q0, q0 + nq) of one election, SCAN_GROUP_WORDS words at a time:
+// ranks are scattered into LDS (two voters per word, a row per pair) and each
+// column of a group of voters is transposed into its bit planes (planes.h).
 // A ballot lists k = (index of its first padding entry) candidates; it is
-// valid iff no id follows a padding entry, every listed id is < m, and the
-// listed ids leave exactly m - k candidates unset (no repeats).  Complete
-// elections (L >= m - 1) also need k >= m - 1: their unset candidate is last.
+// valid iff no id follows a padding entry, every listed id is < m, and no id
+// is listed twice (the ballots of the item then set as many columns as they
+// have entries, which no ballot can exceed).  Complete elections (L >= m - 1)
+// also need k >= m - 1: their unset candidate (all ones) is last.
 template <typename Id>
 __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BElec &el_in, int64_t q0, int64_t nq) {
     // Local copies: a re-read through the references would be a flat load,
@@ -161,14 +165,17 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
     const int tid = threadIdx.x;
     const int32_t m = el.m, L = el.L, pitch = el.pitch;
     const bool complete = (el.flags & EF_SQUARE) == 0;
-    const int32_t vpb = scan_group_pairs(pitch);  // voter pairs per group, 8 .. SCAN_GROUP_PAIRS
+    const int32_t gp = el.group_pairs, bits = el.bits;
+    const int32_t vpb = scan_group_pairs(pitch, gp);  // voter pairs staged at once, at most SCAN_GROUP_PAIRS
     uint16_t *buf = reinterpret_cast<uint16_t *>(smem);
     int32_t *first_pad = reinterpret_cast<int32_t *>(smem + SCAN_GROUP_WORDS);  // [2 vpb]
     int32_t *npads = first_pad + 64;
-    int32_t *unset = npads + 64;
+    int32_t *repeated = npads + 64;  // entries less columns set
     const uint32_t inv_l = L > 1 ? (uint32_t)((0x100000000ull + (uint64_t)L - 1) / (uint64_t)L) : 0u;
     const uint32_t inv_p = (uint32_t)((0x100000000ull + (uint64_t)pitch - 1) / (uint64_t)pitch);
-    FW_GLOBAL uint32_t *pos = gmem(a.pos + el.pos_off);
+    FW_GLOBAL uint32_t *planes = gmem(a.planes + el.pos_off);
+    int32_t extra = 0;
+    if (tid == 0) *repeated = 0;
 
     if ((el.flags & EF_MULTI) && q0 == 0) {  // counts accumulate with atomics: start at zero
         FW_GLOBAL int32_t *D = gmem(a.d + el.mat_off);
@@ -179,6 +186,7 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
         const int32_t npg = (int32_t)min((int64_t)vpb, q0 + nq - g);
         const int64_t v0 = 2 * g;  // first voter of the group
         const int32_t nballots = (int32_t)min((int64_t)2 * npg, el.n - v0);
+        const int32_t ngroups = (npg + gp - 1) / gp;
         const int32_t nquads = npg * pitch / 4;  // pitch is a multiple of 8
         __syncthreads();
         for (int32_t w4 = tid; w4 < nquads; w4 += BT)
@@ -186,7 +194,6 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
         if (tid < 2 * vpb) {
             first_pad[tid] = L;
             npads[tid] = 0;
-            unset[tid] = 0;
         }
         __syncthreads();
         const int64_t base = el.ballot_off + v0 * (int64_t)L;  // ballots of the group are contiguous
@@ -196,7 +203,10 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
             const int32_t b = (int32_t)div_small((uint32_t)f, inv_l) + (L == 1 ? f : 0);  // inv_l = 0 if L = 1
             const int32_t t = f - b * L;
             bad |= id >= m;
-            if ((uint32_t)id < (uint32_t)m) buf[(b >> 1) * 2 * pitch + 2 * id + (b & 1)] = (uint16_t)t;
+            if ((uint32_t)id < (uint32_t)m) {
+                buf[(b >> 1) * 2 * pitch + 2 * id + (b & 1)] = (uint16_t)t;
+                ++extra;
+            }
             if (id < 0) {  // padding: rare, and never in complete elections' valid ballots
                 atomicAdd(&npads[b], 1);
                 atomicMin(&first_pad[b], t);
@@ -239,10 +249,12 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
 #pragma unroll
                     for (int u = 0; u < V; ++u) {
                         const int32_t id = id_of(u);
-                        if ((uint32_t)id < (uint32_t)m)
+                        if ((uint32_t)id < (uint32_t)m) {
                             buf[row + 2 * id] = (uint16_t)t;
-                        else
+                            ++extra;
+                        } else {
                             take(f0 + u, id);  // padding or out of range
+                        }
                         if (++t == L) {
                             t = 0;
                             ++b;
@@ -265,61 +277,36 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
             if (tid < nt) take((int32_t)(t0 + tid - base), ballot_id(ballots[t0 + tid]));
         }
         __syncthreads();
-        // four words per thread: one voter pair's columns c .. c+3 (pitch is a multiple of 8)
-        for (int32_t w4 = tid; w4 < nquads; w4 += BT) {
-            const int32_t w = 4 * w4;
-            const int32_t q = (int32_t)div_small((uint32_t)w, inv_p);
-            const int32_t c0 = w - q * pitch;
-            const bool has_hi = 2 * q + 1 < nballots;
-            const v4u32 in4 = reinterpret_cast<const v4u32 *>(smem)[w4];
-            const uint32_t words[4] = {in4.x, in4.y, in4.z, in4.w};
-            uint32_t out[4];
-            int32_t un_lo = 0, un_hi = 0;
-            if (c0 + 4 <= m) {  // all four columns are candidates
-                const uint32_t fill = complete ? (uint32_t)(m - 1) : UNSET;
+        // a column of a group per thread and step: its pairs' words transposed
+        for (int32_t f = tid; f < ngroups * pitch; f += BT) {
+            const int32_t j = (int32_t)div_small((uint32_t)f, inv_p), c = f - j * pitch;
+            const int32_t live = min(2 * gp, nballots - 2 * gp * j);  // voters of the group
+            uint32_t w[16];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t lo = words[e] & 0xFFFFu, hi = words[e] >> 16;
-                    const bool ul = lo == UNSET, uh = hi == UNSET;
-                    un_lo += ul ? 1 : 0;
-                    un_hi += uh ? 1 : 0;
-                    lo = ul ? fill : lo;
-                    hi = uh ? fill : hi;
-                    out[e] = lo | (hi << 16);
-                }
-                if (!has_hi) {  // missing partner of an odd count: equal ranks, counts nothing
-                    un_hi = 0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) out[e] &= 0xFFFFu;
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t lo = words[e] & 0xFFFFu, hi = words[e] >> 16;
-                    if (c0 + e < m) {
-                        un_lo += lo == UNSET ? 1 : 0;
-                        un_hi += (has_hi && hi == UNSET) ? 1 : 0;
-                        if (complete) {
-                            if (lo == UNSET) lo = (uint32_t)(m - 1);
-                            if (hi == UNSET) hi = (uint32_t)(m - 1);
-                        }
-                    } else {
-                        lo = hi = 0u;
-                    }
-                    if (!has_hi) hi = 0u;
-                    out[e] = lo | (hi << 16);
-                }
+            for (int p = 0; p < 16; ++p) {
+                // (every row read, the missing ones cleared: no load waits under a branch)
+                const uint32_t x = smem[min(j * gp + p, npg - 1) * pitch + c];
+                w[p] = 2 * p + 1 < live ? x : (2 * p < live ? x & 0xFFFFu : 0u);
             }
-            if (un_lo) atomicAdd(&unset[2 * q], un_lo);
-            if (un_hi) atomicAdd(&unset[2 * q + 1], un_hi);
-            *(FW_GLOBAL v4u32 *)(pos + (g + q) * (int64_t)pitch + c0) = v4u32{out[0], out[1], out[2], out[3]};
+            transpose16(w);
+            uint32_t unset = w[0];
+#pragma unroll
+            for (int b = 1; b < 16; ++b) unset &= w[b];
+            if (c < m) extra -= live - __popc(unset);
+            FW_GLOBAL uint32_t *out = planes + ((g / gp + j) * bits) * (int64_t)pitch + c;
+#pragma unroll
+            for (int b = 0; b < 10; ++b)
+                if (b < bits) out[(int64_t)b * pitch] = w[b];
         }
-        __syncthreads();
-        if (tid < nballots) {
+        if (tid < nballots) {  // (written before the last barrier, reset after the next)
             const int32_t k = first_pad[tid];
-            if (L - npads[tid] != k || unset[tid] != m - k || (complete && k < m - 1)) bad = true;
+            if (L - npads[tid] != k || (complete && k < m - 1)) bad = true;
         }
     }
+    for (int off = 32; off >= 1; off >>= 1) extra += __shfl_xor(extra, off);
+    if ((tid & 63) == 0 && extra) atomicAdd(repeated, extra);
+    __syncthreads();
+    if (tid == 0 && *repeated != 0) bad = true;
     if (bad) set_device_error(a.err, SCHULZE_EBALLOT);
 }
 
@@ -339,14 +326,16 @@ __device__ inline void sub_coords(int32_t s, int32_t nb8, bool square, int32_t &
     by = x + (s - start);
 }
 
-typedef __attribute__((ext_vector_type(2))) unsigned short cus2;
-
 __device__ void finish(const BatchArgs &a, const BElec &el, int32_t e);
 
-// Sub-blocks [run * per_phase, ...) of election e over voter pairs of range
-// `range`.  Staged rows hold columns c0 .. 8 nb8 - 1 of VC voter pairs, each
-// 8-column block split into two 16-byte halves stored in separate row
-// halves so that neighbouring sub-blocks read neighbouring 16 bytes.
+// Sub-blocks [run * per_phase, ...) of election e over the groups of voters of
+// range `range`, on bit planes: a thread's 8 x 8 sub-block takes 64
+// v_bitop3_b32 per plane row for the masks of the voters that prefer x to y
+// and 64 population counts per group (the single-election count has the
+// rates).  Staged rows hold columns c0 .. 8 nb8 - 1 of consecutive plane rows,
+// streamed into LDS without passing through registers, each 8-column block
+// split into two 16-byte halves stored in separate row halves so that
+// neighbouring sub-blocks read neighbouring 16 bytes.
 __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const BElec &el_in, int32_t e, int32_t run,
                                                     int32_t range) {
     const BElec el = el_in;  // local copy (see scan_item)
@@ -358,10 +347,10 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
     const bool multi = (el.flags & EF_MULTI) != 0;
     const int32_t m = el.m, nb8 = el.nb8;
     const int32_t vs = el.vs, per_phase = BT / vs;
-    const int32_t phase = tid / per_phase, lt = tid - phase * per_phase;
+    const int32_t phase = tid / per_phase, sub = tid - phase * per_phase;
     const int32_t S = square ? nb8 * nb8 : nb8 * (nb8 + 1) / 2;
     const int32_t s_first = run * per_phase;
-    const int32_t s_mine = s_first + lt;
+    const int32_t s_mine = s_first + sub;
     const bool active = s_mine < S;
     int32_t bx0, by0;
     sub_coords(s_first, nb8, square, bx0, by0);
@@ -372,16 +361,14 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
     const int32_t cols = 8 * (nb8 - cb0);
     const int32_t half = cols / 2;
     const int32_t nq = cols / 4;  // 16-byte quads per staged row
-    const int32_t ng = el.ng, lg = ng == 1 ? 0 : (ng == 2 ? 1 : 2);
-    const int32_t VC = el.vc;  // 4 MAX_PF / ng: VC * cols <= STAGE_WORDS, ng * VC / 4 == MAX_PF
-    const int64_t pairs = (el.n + 1) / 2;
-    const int64_t p0 = (int64_t)range * el.range_pairs;
-    const int64_t p1 = min(pairs, p0 + el.range_pairs);
-    const uint32_t nv = (uint32_t)(min(el.n, 2 * p1) - 2 * p0);
-    const FW_GLOBAL uint32_t *pos = gmem(a.pos + el.pos_off);
+    const int32_t bits = el.bits, ROWS = el.rows;  // ROWS * cols <= STAGE_WORDS / 2
+    const int64_t gv = 2 * el.group_pairs;         // voters per group
+    const int64_t g0 = (int64_t)range * el.range_groups;
+    const int64_t g1 = min((el.n + gv - 1) / gv, g0 + el.range_groups);
+    const uint32_t nv = (uint32_t)(min(el.n, gv * g1) - gv * g0);
+    const int32_t nrows = (int32_t)(g1 - g0) * bits;  // (at most 2^27 groups of at most 10 planes)
+    const FW_GLOBAL uint32_t *src = gmem(a.planes + el.pos_off) + g0 * bits * pitch + c0;
     uint32_t *stage = smem;
-    uint32_t *sred = smem + STAGE_WORDS;
-    const int32_t qlane = tid & 63, prow = tid >> 6;
 
     // the scans of this election must be complete
     if (tid == 0) {
@@ -403,110 +390,94 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 
     uint32_t acc[8][8];
-    uint32_t scol[4][4];
-    v4u32 pf[MAX_PF];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[i][j] = 0u;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) scol[i][j] = 0u;
+    Masks lt;
+    lt.clear();
 
-    // slot k holds quad qlane + 64 (k & (ng-1)) of voter pair prow + 4 (k >> lg)
-    // Unconditional loads, so that all MAX_PF are in flight at once: a slot
-    // outside the chunk reads the election's first word, and stage_store
-    // writes zeros for it instead.
-    auto slot_ok = [&](int k, int64_t q0) {
-        return qlane + 64 * (k & (ng - 1)) < nq && q0 + prow + 4 * (k >> lg) < p1;
-    };
-    auto prefetch = [&](int64_t q0) {
-#pragma unroll
-        for (int k = 0; k < MAX_PF; ++k) {
-            const int32_t qd = qlane + 64 * (k & (ng - 1));
-            const int64_t pr = q0 + prow + 4 * (k >> lg);
-            pf[k] = *(const FW_GLOBAL v4u32 *)(pos + (slot_ok(k, q0) ? pr * pitch + c0 + 4 * qd : 0));
-        }
-    };
-    const cus2 ones = {1, 1};
-    auto stage_store = [&](int64_t q0, uint32_t *stb) {
-#pragma unroll
-        for (int k = 0; k < MAX_PF; ++k) {
-            const int32_t qd = qlane + 64 * (k & (ng - 1));
-            const int32_t vp = prow + 4 * (k >> lg);
-            if (qd < nq) {
-                const v4u32 v = slot_ok(k, q0) ? pf[k] : v4u32{0u, 0u, 0u, 0u};
-                *reinterpret_cast<v4u32 *>(stb + vp * cols + (qd & 1) * half + (qd >> 1) * 4) = v;
-                // words through scalars: a bit_cast of an element of a vector value
-                // has compiled to the first element here
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    scol[k & 3][q] = __builtin_amdgcn_udot2(__builtin_bit_cast(cus2, w[q]), ones, scol[k & 3][q], false);
+    // rows r0 .. of the range to LDS buffer st: a wavefront takes every
+    // fourth row, 64 quads per instruction; LDS quad i of a row is its
+    // global quad 2 i (first halves) or 2 (i - nq / 2) + 1
+    FW_LDS uint32_t *const lds = (FW_LDS uint32_t *)stage;
+    const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto fill = [&](int32_t r0, FW_LDS uint32_t *st) {
+        int ti = tid;
+        asm volatile("" : "+v"(ti));  // (addresses built here, not kept in registers)
+        const int32_t lane = ti & 63, rend = min(ROWS, nrows - r0);
+        for (int32_t r = wave; r < rend; r += 4) {
+            const FW_GLOBAL uint32_t *row = src + (int64_t)(r0 + r) * pitch;
+            for (int32_t q = 0; q < nq; q += 64) {
+                const int32_t i = q + lane;
+                if (i < nq)
+                    __builtin_amdgcn_global_load_lds(row + 4 * (i < nq / 2 ? 2 * i : 2 * (i - nq / 2) + 1),
+                                                     st + r * cols + 4 * q, 16, 0, 0);
             }
         }
     };
+    struct Row {
+        v4u32 x[2], y[2];
+    };
+    auto read = [&](const FW_LDS uint32_t *xp, const FW_LDS uint32_t *yp, Row &q) {
+        q.x[0] = *(const FW_LDS v4u32 *)xp;
+        q.x[1] = *(const FW_LDS v4u32 *)(xp + half);
+        q.y[0] = *(const FW_LDS v4u32 *)yp;
+        q.y[1] = *(const FW_LDS v4u32 *)(yp + half);
+    };
 
-    // Two stage buffers (VC * cols <= 8192 words each): chunk c is counted
-    // from one while chunk c+1 is written to the other, one barrier per chunk.
+    // Two stage buffers: one chunk is counted while the next streams in, one
+    // barrier per chunk.  With the voters split (vs > 1) a chunk holds whole
+    // groups and each phase takes every vs-th of them; otherwise a group may
+    // go on in the next chunk.
     const int32_t xo = (bx - cb0) * 4, yo = (by - cb0) * 4;
-    uint32_t *const stage_b[2] = {stage, stage + VC * cols};
-    prefetch(p0);
     __syncthreads();  // the stage is free (a previous item of this workgroup may have used it)
-    stage_store(p0, stage_b[0]);
-    __syncthreads();
-    int cur = 0;
-    for (int64_t q0 = p0; q0 < p1; q0 += VC) {
-        const bool more = q0 + VC < p1;
-        if (more) prefetch(q0 + VC);  // overlaps the compute below
-        const uint32_t *st = cur ? stage_b[1] : stage_b[0];  // (select: a dynamically indexed array would live in scratch)
-        const int32_t vend = (int32_t)min((int64_t)VC, p1 - q0);
-        if (active) {
+    fill(0, lds);
+    int32_t cur = 0, b = 0;  // b: planes of the current group done
+    for (int32_t r0 = 0; r0 < nrows; r0 += ROWS) {
+        __builtin_amdgcn_s_waitcnt(0);  // this wavefront's pieces of the chunk are in LDS
+        __syncthreads();                // everyone's are, and the chunk before is consumed
+        FW_LDS uint32_t *st = lds + cur * (STAGE_WORDS / 2);
+        cur ^= 1;
+        if (r0 + ROWS < nrows) fill(r0 + ROWS, lds + cur * (STAGE_WORDS / 2));
+        const int32_t rend = min(ROWS, nrows - r0);
+        if (!active) continue;
+        for (int32_t r = phase * bits; r < rend;) {
+            const int32_t take = min(bits - b, rend - r);
+            const FW_LDS uint32_t *xp = st + r * cols + xo, *yp = st + r * cols + yo;
+            Row q0, q1;
+            read(xp, yp, q0);
 #pragma unroll 1
-            for (int32_t v = phase; v < vend; v += vs) {
-                const uint32_t *row = st + v * cols;
-                const uint4 xa = *reinterpret_cast<const uint4 *>(row + xo);
-                const uint4 xb = *reinterpret_cast<const uint4 *>(row + half + xo);
-                const uint4 ya = *reinterpret_cast<const uint4 *>(row + yo);
-                const uint4 yb = *reinterpret_cast<const uint4 *>(row + half + yo);
-                const uint32_t xv[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
-                const uint32_t yv[8] = {ya.x, ya.y, ya.z, ya.w, yb.x, yb.y, yb.z, yb.w};
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const cus2 xi = __builtin_bit_cast(cus2, xv[i]);
-                    cus2 diff[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) diff[j] = xi - __builtin_bit_cast(cus2, yv[j]);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_udot2(diff[j], ones, acc[i][j], false);
-                }
+            for (int32_t k = 0; k + 1 < take; k += 2) {
+                read(xp + cols, yp + cols, q1);
+                __builtin_amdgcn_sched_barrier(0);
+                lt.step(q0.x, q0.y);
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t on = k + 2 < take ? 2 * cols : 0;  // (after the last row: a row again, unused)
+                xp += on;
+                yp += on;
+                read(xp, yp, q0);
+                __builtin_amdgcn_sched_barrier(0);
+                lt.step(q1.x, q1.y);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (take & 1) lt.step(q0.x, q0.y);
+            r += take;
+            b += take;
+            if (b == bits) {
+                lt.count(acc);
+                lt.clear();
+                b = 0;
+                r += (vs - 1) * bits;
             }
         }
-        if (more) stage_store(q0 + VC, cur ? stage_b[0] : stage_b[1]);
-        __syncthreads();  // the next chunk is staged; everyone is done with this one
-        cur ^= 1;
     }
-
-    // column sums of the range, then the counts
-    __syncthreads();
-    for (int32_t c = tid; c < cols; c += BT) sred[c] = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int32_t qd = qlane + 64 * (j & (ng - 1));
-        if (qd < nq) {
-            // slots j, j+4, ... of this thread all hold quad qd
-            const int32_t col = 4 * qd;  // first staged column of the quad
-#pragma unroll
-            for (int q = 0; q < 4; ++q) atomicAdd(&sred[col + q], scol[j][q]);
-        }
-    }
+    __syncthreads();  // the stage is consumed: the phases' counts go there
     if (vs > 1 && phase > 0) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) stage[((phase - 1) * 64 + i * 8 + j) * per_phase + lt] = acc[i][j];
+            for (int j = 0; j < 8; ++j) stage[((phase - 1) * 64 + i * 8 + j) * per_phase + sub] = acc[i][j];
     }
     __syncthreads();
     if (phase == 0 && active) {
@@ -515,13 +486,8 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[i][j] += stage[((ph - 1) * 64 + i * 8 + j) * per_phase + lt];
+                    for (int j = 0; j < 8; ++j) acc[i][j] += stage[((ph - 1) * 64 + i * 8 + j) * per_phase + sub];
         }
-        uint32_t sx[8], sy[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) sx[i] = sred[8 * (bx - cb0) + i];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sy[j] = sred[8 * (by - cb0) + j];
         FW_GLOBAL int32_t *D = gmem(a.d + el.mat_off);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -531,7 +497,7 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
             for (int j = 0; j < 8; ++j) {
                 const int32_t y = 8 * by + j;
                 if (y >= m) continue;
-                const uint32_t cnt = (acc[i][j] - sx[i] + sy[j]) >> 16;
+                const uint32_t cnt = acc[i][j];
                 if (square) {
                     if (x == y) {
                         if (!multi) D[(int64_t)x * m + y] = 0;
@@ -611,7 +577,7 @@ __device__ __attribute__((noinline)) void closure_tiled(E *P_, int32_t mp) {
     }
 }
 
-static_assert(2 * 4 * MAX_PF * 64 * 4 <= STAGE_WORDS, "two count stage buffers: VC * cols <= 32 / ng * 256 ng words each");
+static_assert(2 * CHUNK_QUADS * 64 * 4 <= STAGE_WORDS, "two count stage buffers: rows * cols <= 32 / ng * 256 ng words each");
 static_assert(diag_lds_elems<uint16_t, 192>() * 2 <= SMEM_WORDS * 4 && diag_lds_elems<int32_t, 128>() * 4 <= SMEM_WORDS * 4,
               "diagonal closure LDS");
 
@@ -914,7 +880,7 @@ struct schulze_batch {
     BElec *elec_dev = nullptr;
     BItem *items_full = nullptr, *items_closure = nullptr;
     int32_t n_full = 0, n_closure = 0;
-    uint32_t *pos = nullptr;
+    uint32_t *planes = nullptr;
     char *scratch = nullptr;
     int64_t scratch_bytes = 0;
     int32_t grid = 0;
@@ -975,7 +941,7 @@ void free_plan(schulze_batch *pl) {
     if (pl->exec) (void)hipGraphExecDestroy(pl->exec);
     if (pl->graph) (void)hipGraphDestroy(pl->graph);
     if (pl->cap) (void)hipStreamDestroy(pl->cap);
-    for (void *ptr : {(void *)pl->elec_dev, (void *)pl->items_full, (void *)pl->items_closure, (void *)pl->pos,
+    for (void *ptr : {(void *)pl->elec_dev, (void *)pl->items_full, (void *)pl->items_closure, (void *)pl->planes,
                       (void *)pl->scratch, (void *)pl->ctr})
         if (ptr) (void)hipFree(ptr);
     delete pl;
@@ -993,7 +959,7 @@ int upload(T **dst, const std::vector<T> &src) {
 int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ballot_dtype, int mode,
                const schulze_batch_options *opt, int forced_variant, schulze_batch **out) {
     *out = nullptr;
-    int32_t max_range = SEG_PAIRS;
+    int32_t max_range = RANGE_PAIRS;
     bool closure_only = false;
     if (opt) {
         if (opt->max_range_pairs < 0) return SCHULZE_EINVAL;
@@ -1043,23 +1009,27 @@ int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ba
         const int32_t nq = el.pitch / 4;
         const int32_t groups = (int32_t)ceil_div(nq, 64);
         el.ng = groups <= 1 ? 1 : (groups <= 2 ? 2 : 4);
-        el.vc = 4 * MAX_PF / el.ng;
-        el.range_pairs = max_range;
-        const int64_t ranges = pairs > 0 ? ceil_div(pairs, max_range) : 0;
+        el.bits = rank_bits(std::min(s.L, s.m - 1));
+        el.rows = CHUNK_QUADS / el.ng;
+        if (el.vs > 1) el.rows = el.rows / el.bits * el.bits;  // whole groups (m <= 120: at most 7 planes of 32 rows)
+        el.group_pairs = std::min(16, max_range);
+        el.range_groups = max_range / el.group_pairs;
+        const int64_t vgroups = ceil_div(s.n, 2 * el.group_pairs);
+        const int64_t ranges = ceil_div(vgroups, el.range_groups);
         el.flags = (square ? EF_SQUARE : 0) | (ranges > 1 ? EF_MULTI : 0) | (val16 ? EF_VAL16 : 0) |
                    (s.n == 0 ? EF_ZERO_D : 0);
         el.n_count = (int32_t)(runs * ranges);
         runs_of[e] = runs;
         ranges_of[e] = (int32_t)ranges;
-        const int32_t vpb = scan_group_pairs(el.pitch);
-        el.scan_pairs = (int32_t)std::max<int64_t>(vpb, std::min<int64_t>(pairs, SCAN_WORDS / el.pitch));
+        const int32_t vpb = scan_group_pairs(el.pitch, el.group_pairs);
+        el.scan_pairs = (int32_t)std::max<int64_t>(vpb, std::min<int64_t>(pairs, SCAN_WORDS / el.pitch) / vpb * vpb);
         el.n_scan = pairs > 0 ? (int32_t)ceil_div(pairs, el.scan_pairs) : 0;
         el.pos_off = pos_words;
-        if (!closure_only) pos_words += pairs * el.pitch;
+        if (!closure_only) pos_words += vgroups * el.bits * el.pitch;
         const int64_t es = val16 ? 2 : 4;
         scratch = std::max<int64_t>(scratch, round_up(es * el.mp * el.mp, 256));
         cost[e] = closure_only ? (double)el.mp * el.mp * el.mp
-                               : (double)pairs * S * 128.0 + 4.0 * (double)el.mp * el.mp * el.mp;
+                               : (double)vgroups * S * (el.bits + 2) * 64.0 + 4.0 * (double)el.mp * el.mp * el.mp;
     }
     // queue: largest elections first
     std::vector<int32_t> order(E);
@@ -1097,7 +1067,7 @@ int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ba
     if (rc == SCHULZE_OK) rc = upload(&pl->items_full, full);
     if (rc == SCHULZE_OK) rc = upload(&pl->items_closure, fin);
     if (rc == SCHULZE_OK && pos_words > 0 &&
-        hipMalloc((void **)&pl->pos, sizeof(uint32_t) * (size_t)pos_words) != hipSuccess)
+        hipMalloc((void **)&pl->planes, sizeof(uint32_t) * (size_t)pos_words) != hipSuccess)
         rc = SCHULZE_ENOMEM;
     pl->scratch_bytes = scratch;
     if (rc == SCHULZE_OK && hipMalloc((void **)&pl->scratch, (size_t)scratch * pl->grid) != hipSuccess)
@@ -1170,7 +1140,7 @@ extern "C" int schulze_batch_run(schulze_ctx *ctx, void *stream, schulze_batch *
     args.dtype32 = plan->ballot_dtype == SCHULZE_I32;
     args.mode = plan->mode;
     args.closure_only = closure_only ? 1 : 0;
-    args.pos = plan->pos;
+    args.planes = plan->planes;
     args.d = d;
     args.p = p;
     args.is_winner = is_winner;
