@@ -49,7 +49,7 @@ constexpr int BT = 256;                          // threads per workgroup
 constexpr int STAGE_WORDS = 16384;               // count staging: two buffers of rows x cols words
 constexpr int SMEM_WORDS = STAGE_WORDS + 1024 + 64;
 constexpr int RANGE_PAIRS = 32767;         // voter pairs per count range unless the caller asks for fewer
-constexpr int64_t SCAN_WORDS = 1 << 20;    // rank-pair words staged per scan item
+constexpr int64_t SCAN_WORDS = 1 << 18;    // rank-pair words staged per scan item
 constexpr int SCAN_GROUP_WORDS = 16384;    // rank-pair words staged at once by a scan
 constexpr int SCAN_VEC = 16;              // 16-byte ballot loads in flight per thread
 constexpr int SCAN_GROUP_PAIRS = 32;      // voter pairs staged at once by a scan, at most
@@ -88,16 +88,26 @@ struct BItem {
     int32_t kind, e, a, b;  // scan: a = first voter pair, b = pairs; count: a = run, b = range
 };
 
+// The items are dealt to QUEUES queues by election.  Workgroups are
+// dispatched to the dies in turn, so a workgroup starts with the queue of its
+// number mod QUEUES: the count items of an election, which read the same
+// planes at about the same time, then run on one die and find each other's
+// rows in its L2.  A workgroup that finds its queue empty goes on with the next.
+constexpr int QUEUES = 8;
+constexpr int CTR_STRIDE = 32;                     // one ticket per 128-byte line
+constexpr int CTR_ABORT = QUEUES * CTR_STRIDE;     // then the abort word,
+constexpr int CTR_ELEC = CTR_ABORT + CTR_STRIDE;   // E scans done and E counts done
+
 struct BatchArgs {
     const BElec *elec;
     const BItem *items;
     int32_t n_items;
     int32_t n_elec;
+    int32_t queue[QUEUES + 1];  // first item of each queue
     const void *ballots;
     int32_t dtype32;
     int32_t mode;
     int32_t closure_only;
-    int32_t pad0;
     uint32_t *planes;
     int32_t *d;
     int32_t *p;
@@ -108,7 +118,7 @@ struct BatchArgs {
     int32_t *level;  // NULL or top-k levels (-1 = not reached)
     int32_t topk;    // rank at least this many candidates per election (0: no levels)
     int32_t pad1;
-    int32_t *ctr;  // [0] ticket, [1] abort, [2, 2+E) scans done, [2+E, 2+2E) counts done
+    int32_t *ctr;  // tickets, abort word, scans and counts done (CTR_*)
     char *scratch;
     int64_t scratch_bytes;  // per workgroup
     int32_t *err;
@@ -142,7 +152,7 @@ __host__ __device__ inline int32_t scan_group_pairs(int32_t pitch, int32_t group
 }
 
 __device__ inline void abort_all(const BatchArgs &a) {
-    __hip_atomic_store(gmem(a.ctr) + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(gmem(a.ctr) + CTR_ABORT, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     set_device_error(a.err, SCHULZE_EDEVICE);
 }
 
@@ -174,7 +184,7 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
     const uint32_t inv_l = L > 1 ? (uint32_t)((0x100000000ull + (uint64_t)L - 1) / (uint64_t)L) : 0u;
     const uint32_t inv_p = (uint32_t)((0x100000000ull + (uint64_t)pitch - 1) / (uint64_t)pitch);
     FW_GLOBAL uint32_t *planes = gmem(a.planes + el.pos_off);
-    int32_t extra = 0;
+    int32_t extra = 0;  // entries less columns set, of this thread
     if (tid == 0) *repeated = 0;
 
     if ((el.flags & EF_MULTI) && q0 == 0) {  // counts accumulate with atomics: start at zero
@@ -182,126 +192,171 @@ __device__ __attribute__((noinline)) void scan_item(const BatchArgs &a, const BE
         for (int64_t i = tid; i < (int64_t)m * m; i += BT) D[i] = 0;
     }
     bool bad = false;
+    // One stage: pairs g .. of the item, its entries and the aligned 16-byte
+    // span that covers them (the span's head lies inside the ballot array
+    // before them and is skipped).
+    constexpr int V = 16 / (int)sizeof(Id);
+    struct Stage {
+        int32_t npg, nballots, entries, nvec;
+        int64_t base, a0;
+    };
+    auto stage_at = [&](int64_t g) {
+        Stage t;
+        t.npg = (int32_t)min((int64_t)vpb, q0 + nq - g);
+        t.nballots = (int32_t)min((int64_t)2 * t.npg, el.n - 2 * g);
+        t.base = el.ballot_off + 2 * g * (int64_t)L;  // ballots of the stage are contiguous
+        t.entries = t.nballots * L;                   // < 2^16
+        t.a0 = t.base & ~(int64_t)(V - 1);
+        const int64_t vend = (t.base + t.entries) & ~(int64_t)(V - 1);
+        t.nvec = vend > t.a0 ? (int32_t)((vend - t.a0) / V) : 0;
+        return t;
+    };
+    // SCAN_VEC vectors per thread from vector k0 on, unconditional (clamped),
+    // so that all are in flight together
+    v4u32 raw[SCAN_VEC];
+    auto load = [&](const Stage &t, int32_t k0) {
+        const FW_GLOBAL v4u32 *bv = (const FW_GLOBAL v4u32 *)(ballots + t.a0);
+        if (t.nvec == 0) return;
+#pragma unroll
+        for (int j = 0; j < SCAN_VEC; ++j) raw[j] = bv[min(k0 + tid + BT * j, t.nvec - 1)];
+    };
+    // every rank unset; the transposition leaves it so for the next stage
+    for (int32_t w4 = tid; w4 < vpb * pitch / 4; w4 += BT)
+        reinterpret_cast<v4u32 *>(smem)[w4] = v4u32{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+    if (tid < 64) {
+        first_pad[tid] = L;
+        npads[tid] = 0;
+    }
+    Stage t = stage_at(q0);
+    load(t, 0);
+    __syncthreads();
     for (int64_t g = q0; g < q0 + nq; g += vpb) {
-        const int32_t npg = (int32_t)min((int64_t)vpb, q0 + nq - g);
-        const int64_t v0 = 2 * g;  // first voter of the group
-        const int32_t nballots = (int32_t)min((int64_t)2 * npg, el.n - v0);
+        const int32_t nballots = t.nballots, entries = t.entries, npg = t.npg;
         const int32_t ngroups = (npg + gp - 1) / gp;
-        const int32_t nquads = npg * pitch / 4;  // pitch is a multiple of 8
-        __syncthreads();
-        for (int32_t w4 = tid; w4 < nquads; w4 += BT)
-            reinterpret_cast<v4u32 *>(smem)[w4] = v4u32{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-        if (tid < 2 * vpb) {
-            first_pad[tid] = L;
-            npads[tid] = 0;
-        }
-        __syncthreads();
-        const int64_t base = el.ballot_off + v0 * (int64_t)L;  // ballots of the group are contiguous
-        const int32_t entries = nballots * L;                // < 2^16
-        // entry f of the group: id -> LDS (ballot b = f / L at position t)
+        const int64_t base = t.base, a0 = t.a0;
+        extra += tid == 0 ? entries : 0;
+        // entry f of the stage: id -> LDS (ballot b = f / L at position t)
         auto take = [&](int32_t f, int32_t id) {
             const int32_t b = (int32_t)div_small((uint32_t)f, inv_l) + (L == 1 ? f : 0);  // inv_l = 0 if L = 1
             const int32_t t = f - b * L;
-            bad |= id >= m;
             if ((uint32_t)id < (uint32_t)m) {
                 buf[(b >> 1) * 2 * pitch + 2 * id + (b & 1)] = (uint16_t)t;
-                ++extra;
+                return;
             }
+            --extra;
+            bad |= id >= m;
             if (id < 0) {  // padding: rare, and never in complete elections' valid ballots
                 atomicAdd(&npads[b], 1);
                 atomicMin(&first_pad[b], t);
             }
         };
-        // 16-byte loads over the aligned span that covers the entries (its
-        // head lies inside the ballot array before them and is skipped), the
-        // last partial vector entry by entry; SCAN_VEC loads in flight per
-        // thread, issued unconditionally (clamped) before any is used
-        constexpr int V = 16 / (int)sizeof(Id);
-        const int64_t a0 = base & ~(int64_t)(V - 1);
-        const int64_t end = base + entries;
-        const int64_t vend = end & ~(int64_t)(V - 1);
-        const int32_t nvec = vend > a0 ? (int32_t)((vend - a0) / V) : 0;
-        const FW_GLOBAL v4u32 *bv = (const FW_GLOBAL v4u32 *)(ballots + a0);
-        for (int32_t k0 = tid; k0 < nvec; k0 += BT * SCAN_VEC) {
-            v4u32 raw[SCAN_VEC];
+        // Whole vectors of valid ids go straight to LDS; the few others (the
+        // span's ends, padding, ids out of range) are read again one by one
+        // afterwards, by one copy of the code that handles them: with a copy
+        // at every entry the unrolled loop was larger than the instruction
+        // cache and took twice as long.
+        for (int32_t k0 = 0; k0 < t.nvec; k0 += BT * SCAN_VEC) {
+            if (k0) load(t, k0);
+            uint32_t rest = 0u;  // vectors left over
 #pragma unroll
             for (int j = 0; j < SCAN_VEC; ++j) {
-                const int32_t k = k0 + BT * j;
-                raw[j] = bv[k < nvec ? k : nvec - 1];
-            }
-#pragma unroll
-            for (int j = 0; j < SCAN_VEC; ++j) {
-                const int32_t k = k0 + BT * j;
-                if (k >= nvec) break;
+                const int32_t k = k0 + tid + BT * j;
+                if (k0 + BT * j >= t.nvec) break;  // (uniform)
                 const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+                uint32_t top;  // largest id, padding above all
+                if constexpr (sizeof(Id) == 2) {
+                    const us2 h = __builtin_elementwise_max(
+                        __builtin_elementwise_max(__builtin_bit_cast(us2, w[0]), __builtin_bit_cast(us2, w[1])),
+                        __builtin_elementwise_max(__builtin_bit_cast(us2, w[2]), __builtin_bit_cast(us2, w[3])));
+                    top = max((uint32_t)h.x, (uint32_t)h.y);
+                } else {
+                    top = max(max(w[0], w[1]), max(w[2], w[3]));
+                }
                 const int32_t f0 = (int32_t)(a0 + (int64_t)k * V - base);  // entry of the first id (may be < 0)
-                auto id_of = [&](int u) -> int32_t {
+                if (k >= t.nvec) continue;
+                if (f0 < 0 || f0 + V > entries || top >= (uint32_t)m) {
+                    rest |= 1u << j;
+                    continue;
+                }
+                // ballot and position of the first id, then stepped
+                int32_t b = (int32_t)div_small((uint32_t)f0, inv_l) + (L == 1 ? f0 : 0);
+                int32_t pos = f0 - b * L;
+                int32_t row = (b >> 1) * 2 * pitch + (b & 1);
+                auto id_of = [&](int u) -> uint32_t {
                     if constexpr (sizeof(Id) == 2)
-                        return ballot_id((uint16_t)((w[u >> 1] >> ((u & 1) * 16)) & 0xFFFFu));
+                        return (u & 1) ? w[u >> 1] >> 16 : w[u >> 1] & 0xFFFFu;
                     else
-                        return ballot_id((int32_t)w[u]);
+                        return w[u];
                 };
-                if (f0 >= 0 && f0 + V <= entries) {
-                    // whole vector inside the group: ballot and position once, then stepped
-                    int32_t b = (int32_t)div_small((uint32_t)f0, inv_l) + (L == 1 ? f0 : 0);
-                    int32_t t = f0 - b * L;
-                    int32_t row = (b >> 1) * 2 * pitch + (b & 1);
+                if (pos + V <= L) {
+#pragma unroll
+                    for (int u = 0; u < V; ++u) buf[row + 2 * id_of(u)] = (uint16_t)(pos + u);
+                } else {
 #pragma unroll
                     for (int u = 0; u < V; ++u) {
-                        const int32_t id = id_of(u);
-                        if ((uint32_t)id < (uint32_t)m) {
-                            buf[row + 2 * id] = (uint16_t)t;
-                            ++extra;
-                        } else {
-                            take(f0 + u, id);  // padding or out of range
-                        }
-                        if (++t == L) {
-                            t = 0;
+                        buf[row + 2 * id_of(u)] = (uint16_t)pos;
+                        if (++pos == L) {
+                            pos = 0;
                             ++b;
                             row = (b >> 1) * 2 * pitch + (b & 1);
                         }
                     }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < V; ++u) {
-                        const int32_t f = f0 + u;
-                        if (f >= 0 && f < entries) take(f, id_of(u));
-                    }
+                }
+            }
+            while (rest) {
+                const int j = __builtin_ctz(rest);
+                rest &= rest - 1;
+                const int64_t at = a0 + (int64_t)(k0 + tid + BT * j) * V;
+#pragma unroll 1
+                for (int u = 0; u < V; ++u) {
+                    const int32_t f = (int32_t)(at + u - base);
+                    if (f >= 0 && f < entries) take(f, ballot_id(ballots[at + u]));
                 }
             }
         }
         // entries after the last whole vector
         {
+            const int64_t vend = a0 + (int64_t)t.nvec * V;
             const int64_t t0 = vend > base ? vend : base;
-            const int32_t nt = (int32_t)(end - t0);
+            const int32_t nt = (int32_t)(base + entries - t0);
             if (tid < nt) take((int32_t)(t0 + tid - base), ballot_id(ballots[t0 + tid]));
+        }
+        // the next stage's vectors stream in during the transposition
+        if (g + vpb < q0 + nq) {
+            t = stage_at(g + vpb);
+            load(t, 0);
         }
         __syncthreads();
         // a column of a group per thread and step: its pairs' words transposed
         for (int32_t f = tid; f < ngroups * pitch; f += BT) {
             const int32_t j = (int32_t)div_small((uint32_t)f, inv_p), c = f - j * pitch;
-            const int32_t live = min(2 * gp, nballots - 2 * gp * j);  // voters of the group
+            const uint32_t voters = voter_bits(min(2 * gp, nballots - 2 * gp * j));
             uint32_t w[16];
+            uint32_t *col = smem + j * gp * pitch + c;
+            if (gp == 16) {  // (rows past the last pair are inside the stage; their voters are cleared)
 #pragma unroll
-            for (int p = 0; p < 16; ++p) {
-                // (every row read, the missing ones cleared: no load waits under a branch)
-                const uint32_t x = smem[min(j * gp + p, npg - 1) * pitch + c];
-                w[p] = 2 * p + 1 < live ? x : (2 * p < live ? x & 0xFFFFu : 0u);
+                for (int p = 0; p < 16; ++p) w[p] = col[p * pitch];
+#pragma unroll
+                for (int p = 0; p < 16; ++p) col[p * pitch] = 0xFFFFFFFFu;
+            } else {
+                for (int p = 0; p < 16; ++p) w[p] = col[min(p, npg - 1 - j * gp) * pitch];
+                for (int p = 0; p < gp && j * gp + p < npg; ++p) col[p * pitch] = 0xFFFFFFFFu;
             }
             transpose16(w);
-            uint32_t unset = w[0];
-#pragma unroll
-            for (int b = 1; b < 16; ++b) unset &= w[b];
-            if (c < m) extra -= live - __popc(unset);
+            // ranks are below 1024: the highest bit is that of the columns not set
+            if (c < m) extra -= __popc(voters & ~w[15]);
             FW_GLOBAL uint32_t *out = planes + ((g / gp + j) * bits) * (int64_t)pitch + c;
 #pragma unroll
             for (int b = 0; b < 10; ++b)
-                if (b < bits) out[(int64_t)b * pitch] = w[b];
+                if (b < bits) out[b * pitch] = w[b] & voters;
         }
-        if (tid < nballots) {  // (written before the last barrier, reset after the next)
+        if (tid < nballots) {
             const int32_t k = first_pad[tid];
             if (L - npads[tid] != k || (complete && k < m - 1)) bad = true;
+            first_pad[tid] = L;
+            npads[tid] = 0;
         }
+        __syncthreads();
     }
     for (int off = 32; off >= 1; off >>= 1) extra += __shfl_xor(extra, off);
     if ((tid & 63) == 0 && extra) atomicAdd(repeated, extra);
@@ -375,8 +430,8 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
         int32_t ok = 1;
         int64_t spins = 0;
         FW_GLOBAL int32_t *ctr = gmem(a.ctr);
-        while (__hip_atomic_load(ctr + 2 + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < el.n_scan) {
-            if (__hip_atomic_load(ctr + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || ++spins > SPIN_LIMIT) {
+        while (__hip_atomic_load(ctr + CTR_ELEC + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < el.n_scan) {
+            if (__hip_atomic_load(ctr + CTR_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || ++spins > SPIN_LIMIT) {
                 abort_all(a);
                 ok = 0;
                 break;
@@ -528,7 +583,7 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (tid == 0)
-        sh_flag = __hip_atomic_fetch_add(gmem(a.ctr) + 2 + a.n_elec + e, 1, __ATOMIC_RELAXED,
+        sh_flag = __hip_atomic_fetch_add(gmem(a.ctr) + CTR_ELEC + a.n_elec + e, 1, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT) == el.n_count - 1;
     __syncthreads();
     if (sh_flag) {
@@ -816,12 +871,22 @@ __device__ __attribute__((noinline)) void finish(const BatchArgs &a, const BElec
 
 __global__ __launch_bounds__(BT, 2) void k_batch(BatchArgs a) {
     __shared__ int32_t sh_item;
+    int32_t home = blockIdx.x % QUEUES, tried = 0;  // (thread 0's are used)
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
             FW_GLOBAL int32_t *ctr = gmem(a.ctr);
-            int32_t t = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__hip_atomic_load(ctr + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) t = a.n_items;
+            int32_t t = a.n_items;
+            if (__hip_atomic_load(ctr + CTR_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+                for (; tried < QUEUES; ++tried, home = (home + 1) % QUEUES) {
+                    const int32_t k = __hip_atomic_fetch_add(ctr + home * CTR_STRIDE, 1, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT);
+                    if (k < a.queue[home + 1] - a.queue[home]) {
+                        t = a.queue[home] + k;
+                        break;
+                    }
+                }
+            }
             sh_item = t;
         }
         __syncthreads();
@@ -837,7 +902,7 @@ __global__ __launch_bounds__(BT, 2) void k_batch(BatchArgs a) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
             if (threadIdx.x == 0)
-                __hip_atomic_fetch_add(gmem(a.ctr) + 2 + it.e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(gmem(a.ctr) + CTR_ELEC + it.e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (it.kind == IT_COUNT) {
             count_item(a, el, it.e, it.a, it.b);
         } else {
@@ -879,7 +944,7 @@ struct schulze_batch {
     std::vector<BElec> elec;
     BElec *elec_dev = nullptr;
     BItem *items_full = nullptr, *items_closure = nullptr;
-    int32_t n_full = 0, n_closure = 0;
+    int32_t queue_full[QUEUES + 1] = {}, queue_closure[QUEUES + 1] = {};
     uint32_t *planes = nullptr;
     char *scratch = nullptr;
     int64_t scratch_bytes = 0;
@@ -1036,32 +1101,45 @@ int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ba
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[x] > cost[y]; });
     int rc = batch_grid(ctx, &pl->grid);
-    std::vector<BItem> full, fin;
-    if (!closure_only && rc == SCHULZE_OK) {
-        // Scans (memory-bound) run ahead of the counts (VALU-bound) by `ahead`
-        // elections, so that the two overlap; every scan of an election still
-        // precedes its counts in the queue.
-        auto push_scans = [&](int32_t e) {
-            const BElec &el = pl->elec[e];
-            const int64_t pairs = (el.n + 1) / 2;
-            for (int64_t q = 0; q < pairs; q += el.scan_pairs)
-                full.push_back(BItem{IT_SCAN, e, (int32_t)q, (int32_t)std::min<int64_t>(el.scan_pairs, pairs - q)});
-        };
-        int32_t ahead = 0;
-        for (int64_t items = 0; ahead < E && items < 2 * (int64_t)pl->grid; ++ahead) items += pl->elec[order[ahead]].n_count;
-        for (int32_t i = 0; i < ahead; ++i) push_scans(order[i]);
-        for (int32_t i = 0; i < E; ++i) {
-            const int32_t e = order[i];
-            for (int32_t r = 0; r < ranges_of[e]; ++r)
-                for (int32_t u = 0; u < runs_of[e]; ++u) full.push_back(BItem{IT_COUNT, e, u, r});
-            if (i + ahead < E) push_scans(order[i + ahead]);
-        }
-        for (int32_t e : order)
-            if (pl->elec[e].n_count == 0) full.push_back(BItem{IT_FINISH, e, 0, 0});
+    // each election to the queue with the least work so far
+    std::vector<std::vector<int32_t>> queues(QUEUES);
+    double load[QUEUES] = {};
+    for (int32_t e : order) {
+        const int q = (int)(std::min_element(load, load + QUEUES) - load);
+        queues[q].push_back(e);
+        load[q] += cost[e];
     }
-    for (int32_t e : order) fin.push_back(BItem{IT_FINISH, e, 0, 0});
-    pl->n_full = (int32_t)full.size();
-    pl->n_closure = (int32_t)fin.size();
+    std::vector<BItem> full, fin;
+    for (int q = 0; q < QUEUES; ++q) {
+        const std::vector<int32_t> &of = queues[q];
+        const int32_t Eq = (int32_t)of.size();
+        if (!closure_only && rc == SCHULZE_OK) {
+            // Scans (memory-bound) run ahead of the counts (VALU-bound) by `ahead`
+            // elections, so that the two overlap; every scan of an election still
+            // precedes its counts in the queue.
+            auto push_scans = [&](int32_t e) {
+                const BElec &el = pl->elec[e];
+                const int64_t pairs = (el.n + 1) / 2;
+                for (int64_t k = 0; k < pairs; k += el.scan_pairs)
+                    full.push_back(BItem{IT_SCAN, e, (int32_t)k, (int32_t)std::min<int64_t>(el.scan_pairs, pairs - k)});
+            };
+            int32_t ahead = 0;
+            for (int64_t items = 0; ahead < Eq && items < 2 * (int64_t)pl->grid / QUEUES; ++ahead)
+                items += pl->elec[of[ahead]].n_count;
+            for (int32_t i = 0; i < ahead; ++i) push_scans(of[i]);
+            for (int32_t i = 0; i < Eq; ++i) {
+                const int32_t e = of[i];
+                for (int32_t r = 0; r < ranges_of[e]; ++r)
+                    for (int32_t u = 0; u < runs_of[e]; ++u) full.push_back(BItem{IT_COUNT, e, u, r});
+                if (i + ahead < Eq) push_scans(of[i + ahead]);
+            }
+            for (int32_t e : of)
+                if (pl->elec[e].n_count == 0) full.push_back(BItem{IT_FINISH, e, 0, 0});
+        }
+        for (int32_t e : of) fin.push_back(BItem{IT_FINISH, e, 0, 0});
+        pl->queue_full[q + 1] = (int32_t)full.size();
+        pl->queue_closure[q + 1] = (int32_t)fin.size();
+    }
 
     if (rc == SCHULZE_OK) rc = upload(&pl->elec_dev, pl->elec);
     if (rc == SCHULZE_OK) rc = upload(&pl->items_full, full);
@@ -1072,7 +1150,7 @@ int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ba
     pl->scratch_bytes = scratch;
     if (rc == SCHULZE_OK && hipMalloc((void **)&pl->scratch, (size_t)scratch * pl->grid) != hipSuccess)
         rc = SCHULZE_ENOMEM;
-    if (rc == SCHULZE_OK && hipMalloc((void **)&pl->ctr, sizeof(int32_t) * (size_t)(2 + 2 * (int64_t)E)) != hipSuccess)
+    if (rc == SCHULZE_OK && hipMalloc((void **)&pl->ctr, sizeof(int32_t) * (size_t)(CTR_ELEC + 2 * (int64_t)E)) != hipSuccess)
         rc = SCHULZE_ENOMEM;
     if (rc != SCHULZE_OK) {
         (void)hipGetLastError();
@@ -1086,7 +1164,7 @@ int build_plan(schulze_ctx *ctx, const schulze_election *desc, int32_t E, int ba
 // The reset of the counters and the persistent launch (graph-capturable).
 int enqueue(schulze_batch *pl, hipStream_t s, const BatchArgs &args) {
     schulze_ctx *ctx = pl->ctx;
-    int rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(pl->ctr), (size_t)(2 + 2 * (int64_t)pl->E), 0u);
+    int rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(pl->ctr), (size_t)(CTR_ELEC + 2 * (int64_t)pl->E), 0u);
     if (rc != SCHULZE_OK) return rc;
     if (args.n_items == 0) return SCHULZE_OK;
     SCHULZE_LAUNCH(ctx, K_BATCH, s, k_batch<<<dim3((unsigned)pl->grid), dim3(BT), 0, s>>>(args));
@@ -1134,7 +1212,8 @@ extern "C" int schulze_batch_run(schulze_ctx *ctx, void *stream, schulze_batch *
     BatchArgs args{};
     args.elec = plan->elec_dev;
     args.items = closure_only ? plan->items_closure : plan->items_full;
-    args.n_items = closure_only ? plan->n_closure : plan->n_full;
+    std::copy_n(closure_only ? plan->queue_closure : plan->queue_full, QUEUES + 1, args.queue);
+    args.n_items = args.queue[QUEUES];
     args.n_elec = plan->E;
     args.ballots = ballots;
     args.dtype32 = plan->ballot_dtype == SCHULZE_I32;

@@ -15,20 +15,33 @@ __host__ __device__ inline int32_t rank_bits(int32_t last) {
 }
 
 // 16 x 16 bit transpose of both halves: bit (16 h + p) of w[b] becomes bit
-// (16 h + b) of the old w[p].
-__device__ inline void transpose16(uint32_t (&w)[16]) {
-    const uint32_t masks[4] = {0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+// (16 h + b) of the old w[p].  The bytes of a pair of words are exchanged by
+// two v_perm_b32, the smaller parts by two shifts and two v_bitop3_b32.
+__device__ __forceinline__ void transpose16(uint32_t (&w)[16]) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const int sh = 8 >> st;
+    for (int p = 0; p < 8; ++p) {
+        const uint32_t a = w[p], b = w[p + 8];
+        w[p] = __builtin_amdgcn_perm(b, a, 0x06020400u);      // low bytes of each half: a0 b0 a2 b2
+        w[p + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u);  // high bytes: a1 b1 a3 b3
+    }
+    const uint32_t masks[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+    for (int st = 0; st < 3; ++st) {
+        const int sh = 4 >> st;
+        const uint32_t k = masks[st];
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             if (p & sh) continue;
-            const uint32_t t = ((w[p] >> sh) ^ w[p + sh]) & masks[st];
-            w[p + sh] ^= t;
-            w[p] ^= t << sh;
+            const uint32_t a = w[p], b = w[p + sh];
+            w[p] = (a & k) | ((b << sh) & ~k);
+            w[p + sh] = ((a >> sh) & k) | (b & ~k);
         }
     }
+}
+
+// Bits of the `live` first voters of a group (voter 2p + h at bit 16 h + p).
+__device__ __forceinline__ uint32_t voter_bits(int32_t live) {
+    return ((1u << ((live + 1) / 2)) - 1u) | (((1u << (live / 2)) - 1u) << 16);
 }
 
 // The masks of an 8 x 8 block of candidate pairs, four to a register tuple.
