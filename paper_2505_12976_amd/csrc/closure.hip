@@ -431,6 +431,54 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : (B < 128 ? 2 : 1)) void k
     persist_run<E, B>(a, lds, owned, no, probe_seen);
 }
 
+// ------------------------------------------------------------------ one workgroup
+// m <= B: weights, closure and output of a whole small matrix in one
+// workgroup's registers and one launch, by the diagonal tile's recurrence.
+// Each launch of the other paths takes about 4.5 us on its own (m = 64:
+// three of them around a 10 us recurrence), and at B = 128 the two rounds
+// of 64-wide tiles take longer than 128 steps in registers.
+template <typename E, int B>
+__global__ __launch_bounds__(256) void k_closure_small(const E *__restrict__ d, int64_t ldd, int32_t m, int mode,
+                                                       E *__restrict__ p, int64_t ldp) {
+    using D = Diag<E, B>;
+    using W = typename D::W;
+    __shared__ __attribute__((aligned(16))) E buf[D::LDS_ELEMS];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    W v[D::RA][D::WC];
+#pragma unroll
+    for (int a = 0; a < D::RA; ++a) {
+        E x[D::CW], y[D::CW];
+#pragma unroll
+        for (int b = 0; b < D::CW; ++b) {  // (clamped, so that the loads are in flight together)
+            const int32_t i = min(ty + 16 * a, m - 1), j = min(tx + 16 * b, m - 1);
+            x[b] = d[(int64_t)i * ldd + j];
+            y[b] = d[(int64_t)j * ldd + i];
+        }
+#pragma unroll
+        for (int b = 0; b < D::CW; ++b) {
+            const int32_t i = ty + 16 * a, j = tx + 16 * b;
+            x[b] = i >= m || j >= m || i == j || x[b] <= y[b] ? (E)0 : mode == SCHULZE_MARGIN ? (E)(x[b] - y[b]) : x[b];
+        }
+#pragma unroll
+        for (int c = 0; c < D::WC; ++c) {
+            if constexpr (sizeof(E) == 4)
+                v[a][c] = x[c];
+            else
+                v[a][c] = W{x[2 * c], x[2 * c + 1]};
+        }
+    }
+    FW_LDS E *lb = (FW_LDS E *)buf;
+    D::template publish<0>(v, 0, lb, tx, ty);
+    D::template steps<0>(v, tx, ty, lb);
+#pragma unroll
+    for (int a = 0; a < D::RA; ++a)
+#pragma unroll
+        for (int b = 0; b < D::CW; ++b) {
+            const int32_t i = ty + 16 * a, j = tx + 16 * b;
+            if (i < m && j < m) p[(int64_t)i * ldp + j] = i == j ? (E)0 : lane_get<E>(v[a], b);
+        }
+}
+
 // ------------------------------------------------------------------ per-phase launches
 // Used when a cooperative launch is not available: three launches per round.
 template <typename E, int B>
@@ -578,6 +626,18 @@ int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, 
             }
         }
     }
+    return SCHULZE_OK;
+}
+
+template <typename E>
+int run_closure_small(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, E *p, int64_t ldp) {
+    if (m <= 64)
+        SCHULZE_LAUNCH(ctx, K_FW_DIAG, s,
+                       (k_closure_small<E, 64><<<dim3(1), dim3(256), 0, s>>>(d, ldd, m, mode, p, ldp)));
+    else
+        SCHULZE_LAUNCH(ctx, K_FW_DIAG, s,
+                       (k_closure_small<E, 128><<<dim3(1), dim3(256), 0, s>>>(d, ldd, m, mode, p, ldp)));
+    ctx->closure_bits = sizeof(E) * 8;
     return SCHULZE_OK;
 }
 
@@ -986,6 +1046,10 @@ extern "C" int schulze_closure(schulze_ctx *ctx, void *stream, const void *d, in
     const int bi = tile ? tile : (m >= 2048 ? 128 : 64);  // int32 tile
     const int32_t *di = static_cast<const int32_t *>(d);
     int32_t *pi = static_cast<int32_t *>(p);
+    if (m <= 128 && !tile && !ctx->force_phased)
+        return dtype == SCHULZE_U16 ? run_closure_small(ctx, s, static_cast<const uint16_t *>(d), ldd, m, mode,
+                                                        static_cast<uint16_t *>(p), ldp)
+                                    : run_closure_small(ctx, s, di, ldd, m, mode, pi, ldp);
     if (dtype == SCHULZE_U16)
         return bu == 128 ? run_closure<uint16_t, 128>(ctx, s, static_cast<const uint16_t *>(d), ldd, m, mode,
                                                       static_cast<uint16_t *>(p), ldp)
