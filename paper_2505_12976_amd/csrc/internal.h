@@ -18,7 +18,6 @@ enum WsSlot {
     WS_TRUNC_POS,        // rank planes of truncated ballots (U space)
     WS_PARTIAL,          // partial tiles of the bit-plane count
     WS_ACC32,            // m x m uint32 accumulator of the count
-    WS_ROWSUM,           // per-candidate uint32 sums
     WS_CLOSURE,          // padded closure matrix
     WS_RANK,             // ranking keys
     WS_RING,             // closure tiles published once per round

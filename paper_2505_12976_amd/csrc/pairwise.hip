@@ -34,7 +34,7 @@ namespace {
 constexpr int CT = 128;           // count tile (candidates per side)
 constexpr int COUNT_PER_CU = 3;   // workgroups of the count per CU (168 vector registers)
 constexpr int MAX_BITS = 16;      // bit planes of a rank (m <= 65535)
-constexpr int LONG_CHUNK = 32;    // ballots per workgroup of the long-row scan
+constexpr int LONG_CHUNK = 256;   // ballots per list of the long-row scan
 constexpr int SHORT_PER_WAVE = 8; // steps (groups of ballots) per wavefront of the short-row scan
 constexpr int NPART = 64;         // partial sums of the pair-scattering cost
 
@@ -82,8 +82,10 @@ __device__ inline int32_t read_id(const void *ballots, int64_t idx) {
 
 // ------------------------------------------------------------------ scan
 // Listed length, id range check, full/truncated split (slots reserved once
-// per workgroup), candidates listed by truncated ballots, and the pair count
-// of the truncated ballots.
+// per workgroup: every reservation is an atomic on the same two counters,
+// about 30 ns each one after the other, which with a reservation per 32
+// ballots was most of the scan's time), candidates listed by truncated
+// ballots, and the pair count of the truncated ballots.
 __device__ inline void record_ballots(Meta meta, int nf, const int32_t *lf, int nt, const int32_t *lt) {
     __shared__ int32_t base_f, base_t;
     if (threadIdx.x == 0) {
@@ -95,104 +97,131 @@ __device__ inline void record_ballots(Meta meta, int nf, const int32_t *lf, int 
     for (int i = threadIdx.x; i < nt; i += blockDim.x) meta.trunc_src[base_t + i] = lt[i];
 }
 
-// Long rows: one workgroup walks LONG_CHUNK ballots.
+// Ballot rows in 16-byte pieces whatever their length and alignment: piece j
+// of a row is the j-th aligned 16 bytes that hold one of its entries, and
+// entry e of it has position j PER + e - head (outside 0 .. L-1: another
+// row's).  The few pieces that reach outside the ballot array (its first and
+// last, if the array is not aligned) are put together entry by entry.
 template <bool I32>
-__global__ __launch_bounds__(256) void k_scan_long(const void *__restrict__ ballots, int64_t n, int32_t L,
-                                                   int32_t m, Meta meta, int32_t *err) {
-    __shared__ int32_t first_pad;
-    __shared__ int32_t lf[LONG_CHUNK], lt[LONG_CHUNK];
-    __shared__ int32_t nf, nt;
-    const int64_t v0 = (int64_t)blockIdx.x * LONG_CHUNK;
-    if (threadIdx.x == 0) nf = nt = 0;
-    bool bad = false;
-    unsigned long long k2 = 0;
-    int32_t longest = 0;  // listed by a truncated ballot
-    for (int q = 0; q < LONG_CHUNK; ++q) {
-        const int64_t v = v0 + q;
-        if (v >= n) break;
-        __syncthreads();
-        if (threadIdx.x == 0) first_pad = L;
-        __syncthreads();
-        const int64_t base = v * (int64_t)L;
-        for (int t = threadIdx.x; t < L; t += 256)
-            if (read_id<I32>(ballots, base + t) < 0) {
-                atomicMin(&first_pad, t);
-                break;
-            }
-        __syncthreads();
-        const int k = first_pad;
-        const bool trunc = k < m - 1;
-        for (int t = threadIdx.x; t < k; t += 256) {
-            const int32_t c = read_id<I32>(ballots, base + t);
-            if (c >= m)
-                bad = true;
-            else if (trunc)
-                meta.in_u[c] = 1;
+struct RowPieces {
+    static constexpr int SIZE = I32 ? 4 : 2, PER = 16 / SIZE;
+    const char *lo, *hi, *at;  // the ballot array, and the row's first piece
+    int32_t head, count;
+    __device__ RowPieces(const void *ballots, int64_t n, int32_t L, int64_t row) {
+        lo = static_cast<const char *>(ballots);
+        hi = lo + n * L * SIZE;
+        const char *p = lo + row * L * SIZE;
+        at = reinterpret_cast<const char *>(reinterpret_cast<uintptr_t>(p) & ~(uintptr_t)15);
+        head = (int32_t)(p - at) / SIZE;
+        count = (head + L + PER - 1) / PER;
+    }
+    __device__ const char *piece(int32_t j) const { return at + 16 * (int64_t)min(j, count - 1); }
+    __device__ bool inside(const char *p) const { return p >= lo && p + 16 <= hi; }
+    // pieces j, j + 64, .. of a lane, in flight together
+    template <int FLY>
+    __device__ void load(v4u (&x)[FLY], int32_t j) const {
+        for (int u = 0; u < FLY; ++u) {
+            const char *p = piece(j + 64 * u);
+            x[u] = *reinterpret_cast<const v4u *>(inside(p) ? p : at + 16 * (count > 2 ? 1 : 0));
         }
-        if (threadIdx.x == 0) {
-            meta.len[v] = k;
-            if (trunc) {
-                lt[nt++] = (int32_t)v;
-                k2 += (unsigned long long)k * (k - 1) / 2;
-                longest = max(longest, k);
-            } else {
-                lf[nf++] = (int32_t)v;
+        if (count <= 2 || !inside(at) || !inside(piece(count - 1)))
+            for (int u = 0; u < FLY; ++u) {
+                const char *p = piece(j + 64 * u);
+                if (inside(p)) continue;
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t w = 0xFFFFFFFFu;
+                    for (int h = 0; h < PER / 4; ++h) {
+                        const char *q = p + 4 * e + SIZE * h;
+                        if (q < lo || q + SIZE > hi) continue;
+                        if (I32)
+                            w = *reinterpret_cast<const uint32_t *>(q);
+                        else
+                            w = h ? (w & 0xFFFFu) | ((uint32_t)*reinterpret_cast<const uint16_t *>(q) << 16)
+                                  : (w & 0xFFFF0000u) | *reinterpret_cast<const uint16_t *>(q);
+                    }
+                    x[u][e] = w;
+                }
             }
+    }
+    // f(position, raw id) for the row's entries of piece j
+    template <typename F>
+    __device__ void each(const v4u &x, int32_t j, int32_t L, F f) const {
+        for (int e = 0; e < PER; ++e) {
+            const int32_t t = j * PER + e - head;
+            if ((uint32_t)t < (uint32_t)L) f(t, I32 ? x[e] : (e & 1) ? x[e >> 1] >> 16 : x[e >> 1] & 0xFFFFu);
         }
     }
-    if (bad) set_device_error(err, SCHULZE_EBALLOT);
-    if (threadIdx.x == 0 && k2) atomicAdd(&meta.k2[blockIdx.x % NPART], k2);
-    if (threadIdx.x == 0 && longest) atomicMax(&meta.ctr[6], longest);
-    __syncthreads();
-    record_ballots(meta, nf, lf, nt, lt);
-}
+    // the largest id of the piece, padding above all
+    __device__ static uint32_t top(const v4u &x) {
+        if constexpr (I32) return max(max(x[0], x[1]), max(x[2], x[3]));
+        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+        const uint32_t w[4] = {x[0], x[1], x[2], x[3]};
+        const us2 h = __builtin_elementwise_max(
+            __builtin_elementwise_max(__builtin_bit_cast(us2, w[0]), __builtin_bit_cast(us2, w[1])),
+            __builtin_elementwise_max(__builtin_bit_cast(us2, w[2]), __builtin_bit_cast(us2, w[3])));
+        return max((uint32_t)h.x, (uint32_t)h.y);
+    }
+};
 
-// Long rows of uint16 ids (L a multiple of 8, 16-byte aligned rows): one
-// wavefront per ballot, eight ids per 16-byte load; the first padding entry
-// is a wavefront minimum, so no workgroup barrier is needed per ballot.  The
-// full and truncated lists keep ballot order, as in k_scan_long.
-__global__ __launch_bounds__(256) void k_scan_long_vec(const uint16_t *__restrict__ ballots, int64_t n, int32_t L,
-                                                       int32_t m, Meta meta, int32_t *err) {
+// Long rows: one wavefront per ballot, a workgroup of 16 takes `chunk`
+// ballots (at most one workgroup per CU, so that there are few
+// reservations), LONG_CHUNK to a list.  Bound by reading the ballots once:
+// eight 16-byte pieces per lane in flight, and a piece whose ids are all
+// below m takes one comparison; only ballots that end early are read again,
+// as far as they go, to mark what they list.
+template <bool I32>
+__global__ __launch_bounds__(1024) void k_scan_long(const void *__restrict__ ballots, int64_t n, int32_t L, int32_t m,
+                                                   int32_t chunk, Meta meta, int32_t *err) {
+    using P = RowPieces<I32>;
+    constexpr int FLY = 8;
     __shared__ int32_t lf[LONG_CHUNK], lt[LONG_CHUNK];
     __shared__ uint8_t kind[LONG_CHUNK];  // 0 none, 1 full, 2 truncated
     __shared__ int32_t nf, nt;
+    // candidates listed by this workgroup's truncated ballots (m <= 65535):
+    // byte stores of every workgroup to the same few lines were slower
+    __shared__ uint32_t seen[65536 / 32];
+    for (int32_t w = threadIdx.x; w < (m + 31) / 32; w += 1024) seen[w] = 0u;
+    __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t v0 = (int64_t)blockIdx.x * LONG_CHUNK;
-    const int32_t L8 = L / 8;
+    const int64_t c0 = (int64_t)blockIdx.x * chunk, c1 = min(n, c0 + chunk);
     bool bad = false;
     unsigned long long k2 = 0;
-    int32_t longest = 0;
-    for (int q = wave; q < LONG_CHUNK; q += 4) {
+    int32_t longest = 0;  // listed by a truncated ballot
+    for (int64_t v0 = c0; v0 < c1; v0 += LONG_CHUNK) {
+    const int32_t here = (int32_t)min((int64_t)LONG_CHUNK, c1 - v0);
+    for (int q = wave; q < here; q += 16) {
         const int64_t v = v0 + q;
-        if (v >= n) {
-            if (lane == 0) kind[q] = 0;
-            continue;
-        }
-        const uint4 *row = reinterpret_cast<const uint4 *>(ballots + v * (int64_t)L);
-        int32_t first = L;
-        for (int32_t j = lane; j < L8; j += 64) {
-            const uint4 x = row[j];
-            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-            for (int e = 7; e >= 0; --e) {  // the lowest padding index of the eight wins
-                const uint32_t raw = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu);
-                if (raw == 0xFFFFu) first = min(first, 8 * j + e);
+        const P row(ballots, n, L, v);
+        int32_t first = L, wrong = L;  // first padding entry, first id out of range
+        for (int32_t j0 = 0; j0 < row.count; j0 += 64 * FLY) {
+            v4u x[FLY];
+            row.template load<FLY>(x, j0 + lane);
+            for (int u = 0; u < FLY; ++u) {
+                const int32_t j = j0 + 64 * u + lane;
+                if (j >= row.count || P::top(x[u]) < (uint32_t)m) continue;
+                row.each(x[u], j, L, [&](int32_t t, uint32_t raw) {
+                    const int32_t id = raw_id<I32>(raw);
+                    if (id < 0)
+                        first = min(first, t);
+                    else if (id >= m)
+                        wrong = min(wrong, t);
+                });
             }
+            if (__ballot(first < L)) break;
         }
         for (int off = 32; off >= 1; off >>= 1) first = min(first, __shfl_xor(first, off));
         const int32_t k = first;
+        bad |= wrong < k;
         const bool trunc = k < m - 1;
-        for (int32_t j = lane; 8 * j < k; j += 64) {
-            const uint4 x = row[j];
-            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-            for (int e = 0; e < 8; ++e) {
-                if (8 * j + e >= k) break;
-                const int32_t c = (int32_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
-                if (c >= m)
-                    bad = true;
-                else if (trunc)
-                    meta.in_u[c] = 1;
+        if (trunc)
+            for (int32_t j = lane; j < row.count && j * P::PER - row.head < k; j += 64) {
+                v4u x[1];
+                row.template load<1>(x, j);
+                row.each(x[0], j, k, [&](int32_t, uint32_t raw) {
+                    const uint32_t bit = 1u << (raw & 31);
+                    if (raw < (uint32_t)m && !(seen[raw >> 5] & bit)) atomicOr(&seen[raw >> 5], bit);
+                });
             }
-        }
         if (lane == 0) {
             meta.len[v] = k;
             kind[q] = trunc ? 2 : 1;
@@ -202,35 +231,46 @@ __global__ __launch_bounds__(256) void k_scan_long_vec(const uint16_t *__restric
             }
         }
     }
-    if (bad) set_device_error(err, SCHULZE_EBALLOT);
-    if (lane == 0 && k2) atomicAdd(&meta.k2[blockIdx.x % NPART], k2);
-    if (lane == 0 && longest) atomicMax(&meta.ctr[6], longest);
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0) {  // the lists, in ballot order
         int32_t a = 0, b = 0;
-        for (int q = 0; q < LONG_CHUNK; ++q) {
-            if (kind[q] == 1) lf[a++] = (int32_t)(v0 + q);
-            if (kind[q] == 2) lt[b++] = (int32_t)(v0 + q);
+        for (int q0 = 0; q0 < here; q0 += 64) {
+            const int q = q0 + lane, kq = q < here ? kind[q] : 0;
+            const uint64_t f = __ballot(kq == 1), t = __ballot(kq == 2), below = (1ull << lane) - 1ull;
+            if (kq == 1) lf[a + __popcll(f & below)] = (int32_t)(v0 + q);
+            if (kq == 2) lt[b + __popcll(t & below)] = (int32_t)(v0 + q);
+            a += __popcll(f);
+            b += __popcll(t);
         }
-        nf = a;
-        nt = b;
+        if (lane == 0) {
+            nf = a;
+            nt = b;
+        }
     }
     __syncthreads();
     record_ballots(meta, nf, lf, nt, lt);
+    __syncthreads();  // the lists are copied
+    }
+    for (int32_t c = threadIdx.x; c < m; c += 1024)
+        if ((seen[c >> 5] >> (c & 31)) & 1u) meta.in_u[c] = 1;
+    if (bad) set_device_error(err, SCHULZE_EBALLOT);
+    if (lane == 0 && k2) atomicAdd(&meta.k2[(blockIdx.x * 16 + wave) % NPART], k2);
+    if (lane == 0 && longest > __hip_atomic_load(&meta.ctr[6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(&meta.ctr[6], longest);
 }
 
 // Short rows (L <= 64): a wavefront takes 64 / L ballots at once (at most
 // SHORT_BPW), one lane per entry, SHORT_PER_WAVE such steps with all their
-// loads issued first, SHORT_ROUNDS times; a ballot's listed length is the
+// loads issued first, `rounds` times; a ballot's listed length is the
 // first padding lane of its group (a wavefront ballot).  (More ballots per
 // workgroup mean fewer list reservations on the two shared counters.)
 constexpr int SHORT_BPW = 4;
-constexpr int SHORT_ROUNDS = 4;
+constexpr int SHORT_ROUNDS = 4, SHORT_MAX_ROUNDS = 16;
 constexpr int32_t SEEN_BITS = 65536;
 template <bool I32>
 __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ ballots, int64_t n, int32_t L,
-                                                    int32_t m, Meta meta, int32_t *err) {
-    constexpr int PER_WG = 4 * SHORT_PER_WAVE * SHORT_BPW * SHORT_ROUNDS;
+                                                    int32_t m, int32_t rounds, Meta meta, int32_t *err) {
+    constexpr int PER_WG = 4 * SHORT_PER_WAVE * SHORT_BPW * SHORT_MAX_ROUNDS;
     __shared__ int32_t lf[PER_WG], lt[PER_WG];
     __shared__ int32_t nf, nt;
     // candidates listed by this workgroup's truncated ballots, as bits (for
@@ -250,9 +290,8 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
     const uint64_t group_bits = (L == 64) ? ~0ull : ((1ull << L) - 1ull);
     bool bad = false;
     unsigned long long k2 = 0;
-    int32_t longest = 0;
-    for (int round = 0; round < SHORT_ROUNDS; ++round) {
-        const int64_t v0 = (((int64_t)blockIdx.x * SHORT_ROUNDS + round) * 4 + wave) * SHORT_PER_WAVE * bpw;
+    for (int round = 0; round < rounds; ++round) {
+        const int64_t v0 = (((int64_t)blockIdx.x * rounds + round) * 4 + wave) * SHORT_PER_WAVE * bpw;
         int32_t c[SHORT_PER_WAVE];
         for (int q = 0; q < SHORT_PER_WAVE; ++q) {  // every load first
             const int64_t v = v0 + (int64_t)q * bpw + sub;
@@ -287,7 +326,6 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
                 if (trunc) {
                     lt[atomicAdd(&nt, 1)] = (int32_t)v;
                     k2 += (unsigned long long)k * (k - 1) / 2;
-                    longest = max(longest, k);
                 } else {
                     lf[atomicAdd(&nf, 1)] = (int32_t)v;
                 }
@@ -295,12 +333,8 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
         }
     }
     if (__ballot(bad) && lane == 0) set_device_error(err, SCHULZE_EBALLOT);
-    for (int off = 32; off >= 1; off >>= 1) {
-        k2 += __shfl_xor(k2, off);
-        longest = max(longest, __shfl_xor(longest, off));
-    }
+    for (int off = 32; off >= 1; off >>= 1) k2 += __shfl_xor(k2, off);
     if (lane == 0 && k2) atomicAdd(&meta.k2[(blockIdx.x * 4 + wave) % NPART], k2);
-    if (lane == 0 && longest) atomicMax(&meta.ctr[6], longest);
     __syncthreads();
     if (use_seen)
         for (int32_t c = threadIdx.x; c < m; c += 256)
@@ -323,8 +357,8 @@ constexpr double BUCKETED_PAIR_COST = 6.0;
 
 constexpr int ROUTE_THREADS = 1024;
 constexpr int ROUTE_VEC = 4;  // 16-byte groups of flags per thread (m <= 65536)
-__global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, Meta meta, int64_t cap_words,
-                                                         double pair_cost) {
+__global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, int32_t short_L, Meta meta,
+                                                         int64_t cap_words, double pair_cost) {
     __shared__ int32_t part[ROUTE_THREADS];
     // A thread takes consecutive flags (0 or 1 bytes; zero past m up to the
     // next 16 bytes), as ROUTE_VEC 16-byte loads issued together (a byte at
@@ -382,6 +416,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, Meta meta, i
         unsigned long long k2 = 0;
         for (int i = 0; i < NPART; ++i) k2 += meta.k2[i];
         const int64_t groups = (n_t + 31) / 32;
+        if (short_L) meta.ctr[6] = short_L;  // (the short-row scan does not look for the longest ballot)
         const int32_t bits = rank_bits(meta.ctr[6]);
         const double mm = (double)m * m;
         const double dense =
@@ -414,8 +449,51 @@ struct PlaneArgs {
     uint32_t *planes;
     uint32_t *wplanes;  // 32 words per group
     int32_t *err;
-    int vec;  // rows in 16-byte pieces
+    int64_t n;           // ballots of the profile
 };
+
+// The columns of a group in LDS (16 words each, CH apart) as planes at `out`;
+// returns minus the ranks set in the thread's columns below `real`.
+template <int CH, int THREADS>
+__device__ inline int32_t planes_out(const uint32_t *buf, int32_t cn, int32_t real, uint32_t voters, int32_t bits,
+                                     int64_t pitch, uint32_t *out) {
+    int32_t extra = 0;
+    for (int32_t c = threadIdx.x; c < cn; c += THREADS) {
+        uint32_t w[16];
+        for (int p = 0; p < 16; ++p) w[p] = buf[p * CH + c];
+        transpose16(w);
+        uint32_t unset = w[0];
+        for (int b = 1; b < 16; ++b) unset &= w[b];
+        if (c < real) extra -= __popc(voters & ~unset);
+#pragma unroll
+        for (int b = 0; b < MAX_BITS; ++b)
+            if (b < bits) out[b * pitch + c] = w[b];
+    }
+    return extra;
+}
+
+// extra: entries placed less columns set, by thread; not zero in total if a
+// ballot lists a candidate twice.  *total is zero on entry.
+__device__ inline void check_repeats(int32_t extra, int32_t *total, int32_t *err) {
+    for (int off = 32; off >= 1; off >>= 1) extra += __shfl_xor(extra, off);
+    if ((threadIdx.x & 63) == 0 && extra) atomicAdd(total, extra);
+    __syncthreads();
+    if (threadIdx.x == 0 && *total != 0) set_device_error(err, SCHULZE_EBALLOT);
+}
+
+// One wavefront: the 32 bit planes of its lanes' weights (lanes 0 .. 31 hold
+// the voter of their bit, the others 0); returns the weights' sum.
+__device__ inline uint32_t weight_planes(uint32_t w, uint32_t *out) {
+    const int lane = threadIdx.x & 63;
+    uint32_t mine = 0u, sum = w;
+    for (int j = 0; j < 32; ++j) {
+        const uint32_t mask = (uint32_t)__ballot((w >> j) & 1u);
+        if (lane == j) mine = mask;
+    }
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane < 32) out[lane] = mine;
+    return sum;
+}
 
 template <bool FULL, bool I32, int CH, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
@@ -424,11 +502,11 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
     __shared__ int32_t repeated;  // entries less columns set
     const int32_t count = FULL ? a.meta.ctr[0] : a.meta.ctr[1];
     if (!FULL && a.meta.ctr[2] != MODE_DENSE_U) return;
-    const int64_t g = blockIdx.x;
-    if (32 * g >= count) return;
     const int32_t pitch = FULL ? a.pitch : a.meta.ctr[4];
-    const int32_t c0 = (int32_t)blockIdx.y * CH;
-    if (c0 >= pitch) return;
+    const int32_t chunks = (pitch + CH - 1) / CH;
+    for (int64_t item = blockIdx.x; item < (int64_t)(count + 31) / 32 * chunks; item += gridDim.x) {
+    const int64_t g = item / chunks;
+    const int32_t c0 = (int32_t)(item % chunks) * CH;
     const int32_t cn = min(CH, pitch - c0);             // a multiple of 64
     const int32_t ncols = FULL ? a.m : a.meta.ctr[3];   // real columns: candidates or U
     const int32_t bits = FULL ? a.bits : rank_bits(a.meta.ctr[6]);
@@ -447,74 +525,193 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
     for (int v = wave; v < live; v += WAVES) {  // a wavefront per ballot
         const int32_t src = srcs[32 * g + v];
         const int32_t k = a.meta.len[src];
-        const int64_t base = (int64_t)src * a.L;
         uint16_t *row = half + (v >> 1) * (2 * CH) + (v & 1);
         auto place = [&](int32_t t, int32_t id) {
-            if (t >= k || (uint32_t)id >= (uint32_t)a.m) return;  // reported by the scan
+            if ((uint32_t)id >= (uint32_t)a.m) return;  // reported by the scan
             const int32_t col = (FULL ? id : a.meta.umap[id]) - c0;
             if ((uint32_t)col >= (uint32_t)cn) return;
             row[2 * col] = (uint16_t)t;
             ++extra;
         };
-        // several 16-byte pieces (or entries) per lane in flight
-        constexpr int FLY = 4;
-        constexpr int PER = I32 ? 4 : 8;
-        if (a.vec) {
-            const v4u *r4 = reinterpret_cast<const v4u *>(static_cast<const char *>(a.ballots) +
-                                                          base * (I32 ? 4 : 2));
-            const int32_t pieces = (k + PER - 1) / PER;
-            for (int32_t j0 = 0; j0 < pieces; j0 += 64 * FLY) {
-                v4u x[FLY];
-                for (int u = 0; u < FLY; ++u) x[u] = r4[min(j0 + 64 * u + lane, pieces - 1)];
-                for (int u = 0; u < FLY; ++u) {
-                    const int32_t j = j0 + 64 * u + lane;
-                    if (j >= pieces) break;
-                    for (int e = 0; e < PER; ++e) {
-                        const uint32_t w = x[u][I32 ? e : e >> 1];
-                        place(PER * j + e, (int32_t)(I32 ? w : (e & 1) ? w >> 16 : w & 0xFFFFu));
-                    }
-                }
-            }
-        } else {
-            for (int32_t j0 = 0; j0 < k; j0 += 64 * FLY) {
-                uint32_t x[FLY];
-                for (int u = 0; u < FLY; ++u) x[u] = load_raw<I32>(a.ballots, base + min(j0 + 64 * u + lane, k - 1));
-                for (int u = 0; u < FLY; ++u) place(j0 + 64 * u + lane, (int32_t)x[u]);
-            }
+        constexpr int FLY = 4;  // pieces per lane in flight
+        const RowPieces<I32> pieces(a.ballots, a.n, a.L, src);
+        const int32_t need = (pieces.head + k + pieces.PER - 1) / pieces.PER;
+        for (int32_t j0 = 0; j0 < need; j0 += 64 * FLY) {
+            v4u x[FLY];
+            pieces.template load<FLY>(x, j0 + lane);
+            for (int u = 0; u < FLY; ++u)
+                pieces.each(x[u], j0 + 64 * u + lane, k, [&](int32_t t, uint32_t raw) { place(t, (int32_t)raw); });
         }
     }
     __syncthreads();
     // the group's voters in the order of the planes' bits
-    const uint32_t voters = (uint32_t)((1u << ((live + 1) / 2)) - 1u) | (((1u << (live / 2)) - 1u) << 16);
-    for (int32_t cb = wave * 64; cb < cn; cb += THREADS) {
-        const int32_t c = cb + lane;
-        uint32_t w[16];
-        for (int p = 0; p < 16; ++p) w[p] = buf[p * CH + c];
-        transpose16(w);
-        uint32_t unset = w[0];
-        for (int b = 1; b < 16; ++b) unset &= w[b];
-        if (c0 + c < ncols) extra -= __popc(voters & ~unset);
-        uint32_t *out = a.planes + g * bits * (int64_t)pitch + c0 + c;
-#pragma unroll
-        for (int b = 0; b < MAX_BITS; ++b)
-            if (b < bits) out[(int64_t)b * pitch] = w[b];
-    }
-    for (int off = 32; off >= 1; off >>= 1) extra += __shfl_xor(extra, off);
-    if (lane == 0) atomicAdd(&repeated, extra);
-    __syncthreads();
-    if (threadIdx.x == 0 && repeated != 0) set_device_error(a.err, SCHULZE_EBALLOT);
-    if (a.weight && blockIdx.y == 0 && wave == 0) {
+    const uint32_t voters = voter_bits(live);
+    extra += planes_out<CH, THREADS>(buf, cn, ncols - c0, voters, bits, pitch,
+                                     a.planes + g * bits * (int64_t)pitch + c0);
+    check_repeats(extra, &repeated, a.err);
+    if (a.weight && c0 == 0 && wave == 0) {
         const int v = 2 * (lane & 15) + ((lane >> 4) & 1);  // the voter of bit `lane`
-        const uint32_t w = lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u;
-        uint32_t mine = 0u, sum = w;
-        for (int j = 0; j < 32; ++j) {
-            const uint32_t mask = (uint32_t)__ballot((w >> j) & 1u);
-            if (lane == j) mine = mask;
-        }
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-        if (lane < 32) a.wplanes[32 * g + lane] = mine;
+        const uint32_t sum = weight_planes(lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u, a.wplanes + 32 * g);
         if (FULL && lane == 0) atomicAdd(&a.meta.ctr[8], (int32_t)sum);
     }
+    __syncthreads();  // the LDS is read
+    }
+}
+
+// The planes of every ballot over all candidates, straight from the ballots
+// (the one-pass count of small elections): the listed length is found on the
+// way.  1024 threads and a group of 32 ballots, two ballots per wavefront
+// with their first pieces loaded together.
+struct AllArgs {
+    const void *ballots;
+    int32_t n, L, m, pitch, bits;
+    const uint32_t *weight;
+    uint32_t *planes, *wplanes;
+    int32_t *err;
+};
+
+template <bool I32, int CH>
+__global__ __launch_bounds__(1024) void k_planes_all(AllArgs a) {
+    using P = RowPieces<I32>;
+    constexpr int FLY = 2;  // pieces per lane and ballot in flight
+    __shared__ uint32_t buf[16 * CH];
+    __shared__ int32_t repeated;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t g = blockIdx.x, c0 = (int32_t)blockIdx.y * CH, cn = min(CH, a.pitch - c0);
+    const int32_t live = min(32, a.n - 32 * g);
+    v4u x[2][FLY];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        P(a.ballots, a.n, a.L, 32 * g + min(wave + 16 * h, live - 1)).template load<FLY>(x[h], lane);
+    for (int p = 0; p < 16; ++p) {
+        const uint32_t fill = (2 * p < live ? 0xFFFFu : 0u) | (2 * p + 1 < live ? 0xFFFF0000u : 0u);
+        for (int c = threadIdx.x; c < cn; c += 1024) buf[p * CH + c] = fill;
+    }
+    if (threadIdx.x == 0) repeated = 0;
+    __syncthreads();
+    int32_t extra = 0;
+    bool bad = false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int v = wave + 16 * h;
+        if (v >= live) continue;
+        const P row(a.ballots, a.n, a.L, 32 * g + v);
+        int32_t k = a.L;  // first padding entry
+        auto pads = [&](const v4u &p, int32_t j) {
+            if (j < row.count && P::top(p) >= (uint32_t)a.m)
+                row.each(p, j, a.L, [&](int32_t t, uint32_t raw) {
+                    if (raw_id<I32>(raw) < 0) k = min(k, t);
+                });
+        };
+        for (int u = 0; u < FLY; ++u) pads(x[h][u], 64 * u + lane);
+        for (int32_t j = 64 * FLY + lane; j < row.count; j += 64) {
+            v4u p[1];
+            row.template load<1>(p, j);
+            pads(p[0], j);
+        }
+        for (int off = 32; off >= 1; off >>= 1) k = min(k, __shfl_xor(k, off));
+        uint16_t *out = reinterpret_cast<uint16_t *>(buf) + (v >> 1) * (2 * CH) + (v & 1);
+        auto place = [&](int32_t t, uint32_t raw) {
+            if (raw >= (uint32_t)a.m) {
+                bad = true;
+                return;
+            }
+            const int32_t c = (int32_t)raw - c0;
+            if ((uint32_t)c >= (uint32_t)cn) return;
+            out[2 * c] = (uint16_t)t;
+            ++extra;
+        };
+        for (int u = 0; u < FLY; ++u) row.each(x[h][u], 64 * u + lane, k, place);
+        for (int32_t j = 64 * FLY + lane; j < row.count; j += 64) {
+            v4u p[1];
+            row.template load<1>(p, j);
+            row.each(p[0], j, k, place);
+        }
+    }
+    if (bad) set_device_error(a.err, SCHULZE_EBALLOT);
+    __syncthreads();
+    extra += planes_out<CH, 1024>(buf, cn, a.m - c0, voter_bits(live), a.bits, a.pitch,
+                                  a.planes + (int64_t)g * a.bits * a.pitch + c0);
+    check_repeats(extra, &repeated, a.err);
+    if (a.weight && blockIdx.y == 0 && wave == 0) {
+        const int v = 2 * (lane & 15) + ((lane >> 4) & 1);
+        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
+    }
+}
+
+// The same for short rows (L <= 64): 256 threads take a group's entries as
+// one run, so that no lane idles on a ballot shorter than a wavefront (n =
+// 180227 top-10 of m = 159: a wavefront per ballot took 100 us, this 16).
+template <bool I32, int CH>
+__global__ __launch_bounds__(256) void k_planes_short(AllArgs a) {
+    constexpr int FLY = 8;  // entries per thread: 32 ballots of at most 64
+    __shared__ uint32_t buf[16 * CH];
+    __shared__ int32_t first[32];
+    __shared__ int32_t repeated;
+    const int32_t g = blockIdx.x, c0 = (int32_t)blockIdx.y * CH, cn = min(CH, a.pitch - c0);
+    const int32_t live = min(32, a.n - 32 * g), entries = live * a.L;
+    const int64_t base = (int64_t)32 * g * a.L;
+    uint32_t x[FLY];
+    for (int u = 0; u < FLY; ++u)  // (clamped: all in flight together)
+        x[u] = load_raw<I32>(a.ballots, base + min((int32_t)threadIdx.x + 256 * u, entries - 1));
+    for (int p = 0; p < 16; ++p) {
+        const uint32_t fill = (2 * p < live ? 0xFFFFu : 0u) | (2 * p + 1 < live ? 0xFFFF0000u : 0u);
+        for (int c = threadIdx.x; c < cn; c += 256) buf[p * CH + c] = fill;
+    }
+    if (threadIdx.x < 32) first[threadIdx.x] = a.L;
+    if (threadIdx.x == 0) repeated = 0;
+    __syncthreads();
+    const uint32_t inv = (uint32_t)((0x100000000ull + (uint64_t)a.L - 1) / (uint64_t)a.L);  // entry / L for L > 1
+    auto place_of = [&](int u, int32_t &v, int32_t &t) {
+        const int32_t f = (int32_t)threadIdx.x + 256 * u;
+        v = a.L > 1 ? (int32_t)__umulhi((uint32_t)f, inv) : f;
+        t = f - v * a.L;
+        return f < entries;
+    };
+    for (int u = 0; u < FLY; ++u) {
+        int32_t v, t;
+        if (place_of(u, v, t) && raw_id<I32>(x[u]) < 0) atomicMin(&first[v], t);
+    }
+    __syncthreads();
+    int32_t extra = 0;
+    bool bad = false;
+    uint16_t *half = reinterpret_cast<uint16_t *>(buf);
+    for (int u = 0; u < FLY; ++u) {
+        int32_t v, t;
+        if (!place_of(u, v, t) || t >= first[v]) continue;
+        if (x[u] >= (uint32_t)a.m) {
+            bad = true;
+            continue;
+        }
+        const int32_t c = (int32_t)x[u] - c0;
+        if ((uint32_t)c >= (uint32_t)cn) continue;
+        half[(v >> 1) * (2 * CH) + 2 * c + (v & 1)] = (uint16_t)t;
+        ++extra;
+    }
+    if (bad) set_device_error(a.err, SCHULZE_EBALLOT);
+    __syncthreads();
+    extra += planes_out<CH, 256>(buf, cn, a.m - c0, voter_bits(live), a.bits, a.pitch,
+                                 a.planes + (int64_t)g * a.bits * a.pitch + c0);
+    check_repeats(extra, &repeated, a.err);
+    if (a.weight && blockIdx.y == 0 && threadIdx.x < 64) {
+        const int lane = threadIdx.x, v = 2 * (lane & 15) + ((lane >> 4) & 1);
+        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
+    }
+}
+
+template <bool I32>
+int planes_all(schulze_ctx *ctx, hipStream_t s, const AllArgs &pa, int64_t groups) {
+    const int ch = pa.L <= 64 ? (pa.pitch <= 128 ? 128 : 512) : (pa.pitch <= 512 ? 512 : 2048);
+    const dim3 pg((unsigned)groups, (unsigned)ceil_div(pa.pitch, ch));
+    if (ch == 128)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes_short<I32, 128><<<pg, dim3(256), 0, s>>>(pa)));
+    else if (pa.L <= 64)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes_short<I32, 512><<<pg, dim3(256), 0, s>>>(pa)));
+    else if (ch == 512)
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes_all<I32, 512><<<pg, dim3(1024), 0, s>>>(pa)));
+    else
+        SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes_all<I32, 2048><<<pg, dim3(1024), 0, s>>>(pa)));
+    return SCHULZE_OK;
 }
 
 // ------------------------------------------------------------------ bit-plane count
@@ -526,11 +723,13 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
 // k_count_reduce adds up: 64 KB written per slot, where device-wide atomics
 // into acc took 0.5 us per flushed tile for the whole chip (m = 1023,
 // n = 12007: 431 us, of which the counting is about 90).
-//   SQUARE = false: full rankings, tiles X <= Y over candidates; acc also
-//                   takes d[y][x] = voters - d[x][y].
-//   SQUARE = true:  truncated ballots over U space, all tiles (X, Y); U
-//                   indices map back through ulist; the sentinel column
-//                   y = |U| gives R[x].
+//   COUNT_FULL  full rankings, tiles X <= Y over candidates; acc also takes
+//               d[y][x] = voters - d[x][y].
+//   COUNT_U     truncated ballots over U space, all tiles (X, Y); U indices
+//               map back through ulist; the sentinel column y = |U| gives
+//               R[x].
+//   COUNT_ALL   every ballot over all candidates, all tiles; the counts are
+//               final and go to d (small elections: see count_all).
 // Bound by the vector ALU: a thread carries 8 x 8 masks and counts, so a
 // bit takes 64 v_bitop3_b32 and four 16-byte LDS reads (8 row and 8 column
 // words), and the reads' 32 cycles per wavefront and bit hide behind the
@@ -538,6 +737,8 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
 // 90 T comparisons/s (the packed subtractions: 31 T); larger thread tiles
 // (16 x 8, counts packed in 16 bits) had fewer reads per mask but two
 // wavefronts per SIMD: 10% slower.
+enum CountMode { COUNT_FULL, COUNT_U, COUNT_ALL };
+
 struct DenseArgs {
     const uint32_t *planes;
     int32_t pitch, bits;  // full rankings (pitch a multiple of CT)
@@ -547,28 +748,40 @@ struct DenseArgs {
     int64_t lda;
     uint32_t *rsum;
     const uint32_t *wplanes;  // with voter weights
-    uint32_t *partial;        // two CT x CT tiles per workgroup
+    uint32_t *partial;        // two CT x CT tiles per workgroup (COUNT_ALL: one per workgroup and tile)
+    // COUNT_ALL
+    int32_t n;
+    int32_t whole;  // every workgroup counts whole tiles
+    void *d;
+    int64_t ldd;
+    int32_t d32;
+    uint32_t limit;
+    int32_t *err;
 };
 
 // The units of a count and their division among the workgroups.
 struct CountPlan {
     int32_t nvoters, groups, pitch, nb, nu;
+    int32_t whole;
     int64_t ntiles, units, workers;
-    __device__ int64_t first(int64_t w) const { return units * w / workers; }
+    __device__ int64_t first(int64_t w) const {
+        return whole ? ntiles * w / workers * groups : units * w / workers;
+    }
 };
-template <bool SQUARE>
+template <int MODE>
 __device__ inline CountPlan count_plan(const DenseArgs &a, int32_t grid) {
     CountPlan c;
-    c.nvoters = SQUARE ? a.meta.ctr[1] : a.meta.ctr[0];
+    c.nvoters = MODE == COUNT_ALL ? a.n : MODE == COUNT_U ? a.meta.ctr[1] : a.meta.ctr[0];
     c.groups = (c.nvoters + 31) / 32;  // units per tile
-    c.pitch = SQUARE ? a.meta.ctr[4] : a.pitch;
-    c.nu = SQUARE ? a.meta.ctr[3] : a.m;
+    c.pitch = MODE == COUNT_U ? a.meta.ctr[4] : a.pitch;
+    c.nu = MODE == COUNT_U ? a.meta.ctr[3] : a.m;
     c.nb = c.pitch / CT;
-    c.ntiles = SQUARE ? (int64_t)c.nb * c.nb : (int64_t)c.nb * (c.nb + 1) / 2;
+    c.ntiles = MODE == COUNT_FULL ? (int64_t)c.nb * (c.nb + 1) / 2 : (int64_t)c.nb * c.nb;
     // ranges of at least four units (writing and adding up a partial tile
-    // costs about as much as one)
+    // costs about as much as one); COUNT_ALL is launched with its workers
     c.units = c.ntiles * c.groups;
-    c.workers = min((int64_t)grid, (c.units + 3) / 4);
+    c.whole = MODE == COUNT_ALL && a.whole;
+    c.workers = MODE == COUNT_ALL ? grid : min((int64_t)grid, (c.units + 3) / 4);
     return c;
 }
 
@@ -581,17 +794,26 @@ __device__ inline uint32_t full_total(const DenseArgs &a) {
 // cnt voters prefer x to y (indices of the count): into acc, and for full
 // rankings outside diagonal tiles the mirror too.  One thread per element
 // and launch: plain additions.
-template <bool SQUARE>
+template <int MODE>
 __device__ inline void add_count(const DenseArgs &a, int32_t nu, int32_t x, int32_t y, bool mirror, uint32_t total,
-                                 uint32_t cnt) {
-    if (SQUARE) {
+                                 uint32_t cnt, bool &over) {
+    if (MODE == COUNT_U) {
         if (x >= nu || y > nu) return;
         const int32_t gx = a.meta.ulist[x];
         if (y == nu)
             a.rsum[gx] += cnt;
         else if (x != y)
             a.acc[(int64_t)gx * a.lda + a.meta.ulist[y]] += cnt;
-    } else if (x < nu && y < nu && x != y) {
+    } else if (x >= nu || y >= nu) {
+        return;
+    } else if (MODE == COUNT_ALL) {  // (ranks equal to themselves: the diagonal is 0)
+        over |= cnt > a.limit;
+        const uint32_t v = min(cnt, a.limit);
+        if (a.d32)
+            static_cast<uint32_t *>(a.d)[(int64_t)x * a.ldd + y] = v;
+        else
+            static_cast<uint16_t *>(a.d)[(int64_t)x * a.ldd + y] = (uint16_t)v;
+    } else if (x != y) {
         a.acc[(int64_t)x * a.lda + y] += cnt;
         if (mirror) a.acc[(int64_t)y * a.lda + x] += total - cnt;
     }
@@ -607,11 +829,11 @@ __device__ inline void tri_coords(int32_t t, int32_t nb, int32_t &X, int32_t &Y)
     Y = x + (t - start);
 }
 
-template <bool SQUARE, bool WEIGHTED>
+template <int MODE, bool WEIGHTED>
 __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
     constexpr int ROW = 2 * CT;  // LDS words per bit: the tile's rows, then its columns
     __shared__ __attribute__((aligned(16))) uint32_t lds[2 * MAX_BITS * ROW];
-    if (SQUARE && a.meta.ctr[2] != MODE_DENSE_U) return;
+    if (MODE == COUNT_U && a.meta.ctr[2] != MODE_DENSE_U) return;
     CNT_LDS uint32_t *st = (CNT_LDS uint32_t *)lds;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -622,10 +844,10 @@ __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
         asm volatile("" : "+v"(i));
         return i;
     };
-    const CountPlan c = count_plan<SQUARE>(a, gridDim.x);
+    const CountPlan c = count_plan<MODE>(a, gridDim.x);
     if (blockIdx.x >= c.workers) return;
     const int32_t groups = c.groups, pitch = c.pitch, nb = c.nb;
-    const int32_t bits = SQUARE ? rank_bits(a.meta.ctr[6]) : a.bits;
+    const int32_t bits = MODE == COUNT_U ? rank_bits(a.meta.ctr[6]) : a.bits;
     const int32_t wbits = WEIGHTED && a.meta.ctr[7] ? 32 - __clz(a.meta.ctr[7]) : 0;
     const int64_t u0 = c.first(blockIdx.x), u1 = c.first(blockIdx.x + 1);
 
@@ -639,7 +861,7 @@ __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
     int32_t t = t0, X, Y;
     int32_t g = (int32_t)(u0 % groups), seg0 = g;
     auto coords = [&](int32_t tile, int32_t &tX, int32_t &tY) {
-        if (SQUARE) {
+        if (MODE != COUNT_FULL) {
             tX = tile / nb;
             tY = tile % nb;
         } else {
@@ -657,16 +879,19 @@ __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
     };
     auto flush = [&](int32_t seg1) {
         const int ftx = thread() & 15, fty = thread() >> 4;
-        if (seg0 == 0 && seg1 == groups) {
-            const uint32_t total = full_total<WEIGHTED>(a);
+        if (MODE == COUNT_ALL ? c.whole : seg0 == 0 && seg1 == groups) {
+            const uint32_t total = MODE == COUNT_FULL ? full_total<WEIGHTED>(a) : 0u;
+            bool over = false;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    add_count<SQUARE>(a, c.nu, X * CT + (i & 4) * 16 + fty * 4 + (i & 3),
-                                      Y * CT + (j & 4) * 16 + ftx * 4 + (j & 3), X != Y, total, acc[i][j]);
+                    add_count<MODE>(a, c.nu, X * CT + (i & 4) * 16 + fty * 4 + (i & 3),
+                                    Y * CT + (j & 4) * 16 + ftx * 4 + (j & 3), X != Y, total, acc[i][j], over);
+            if (MODE == COUNT_ALL && over) set_device_error(a.err, SCHULZE_ERANGE);
         } else {
-            uint32_t *out = a.partial + ((int64_t)blockIdx.x * 2 + (t != t0)) * (CT * CT);
+            const int64_t slot = MODE == COUNT_ALL ? (int64_t)blockIdx.x + t : (int64_t)blockIdx.x * 2 + (t != t0);
+            uint32_t *out = a.partial + slot * (CT * CT);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -746,62 +971,104 @@ __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
     }
 }
 
-// The partial tiles added up: a workgroup takes 32 rows of a tile that
-// several workgroups of k_count_bits (launched with `grid`) counted.  The
-// mirror of a full-ranking tile goes through LDS, so that both are written
-// along rows.
-template <bool SQUARE, bool WEIGHTED>
+// The partial tiles of tile t, those of the workgroups w0 .. w1 whose ranges
+// meet it, the first in slot s0 (a workgroup's slot: twice its number for its
+// first tile, the next one for its last; in COUNT_ALL its number plus t).
+struct TileParts {
+    int64_t w0, w1, s0;
+};
+template <int MODE>
+__device__ inline TileParts tile_parts(const CountPlan &c, int32_t t) {
+    const int64_t ub = (int64_t)t * c.groups, ue = ub + c.groups;
+    TileParts q{ub * c.workers / c.units, (ue - 1) * c.workers / c.units, 0};
+    while (c.first(q.w0 + 1) <= ub) ++q.w0;
+    while (c.first(q.w0) > ub) --q.w0;
+    while (c.first(q.w1 + 1) < ue) ++q.w1;
+    while (c.first(q.w1) >= ue) --q.w1;
+    q.s0 = MODE == COUNT_ALL ? q.w0 + t : 2 * q.w0 + (c.first(q.w0) < ub);
+    return q;
+}
+
+// The partial tiles added up.  With few per tile, a workgroup takes 32 rows
+// of a tile and the mirror of a full-ranking tile goes through LDS, so that
+// both are written along rows; with many (few tiles, many voters), two rows,
+// and the four wavefronts share the partial tiles out (one thread adding 391
+// of them took 400 us).
+template <int MODE, bool WEIGHTED>
 __global__ __launch_bounds__(256) void k_count_reduce(DenseArgs a, int32_t grid) {
     __shared__ uint32_t buf[32][CT + 1];
-    if (SQUARE && a.meta.ctr[2] != MODE_DENSE_U) return;
-    const CountPlan c = count_plan<SQUARE>(a, grid);
+    if (MODE == COUNT_U && a.meta.ctr[2] != MODE_DENSE_U) return;
+    const CountPlan c = count_plan<MODE>(a, grid);
     if (c.units == 0) return;
-    const uint32_t total = full_total<WEIGHTED>(a);
-    const int col = (threadIdx.x & 31) * 4, row = threadIdx.x >> 5;
-    for (int64_t q = blockIdx.x; q < 4 * c.ntiles; q += gridDim.x) {
-        const int32_t t = (int32_t)(q >> 2), r0 = (int32_t)(q & 3) * 32;
-        const int64_t ub = (int64_t)t * c.groups, ue = ub + c.groups;
-        // the workgroups whose ranges meet the tile's
-        int64_t w0 = ub * c.workers / c.units, w1 = (ue - 1) * c.workers / c.units;
-        while (c.first(w0 + 1) <= ub) ++w0;
-        while (c.first(w0) > ub) --w0;
-        while (c.first(w1 + 1) < ue) ++w1;
-        while (c.first(w1) >= ue) --w1;
-        if (w0 == w1) continue;  // counted whole, in acc already
-        uint32_t v[4][4] = {};
-        for (int64_t w = w0; w <= w1; ++w) {
-            const uint32_t *p = a.partial + (2 * w + (c.first(w) < ub)) * (CT * CT) + r0 * CT + col;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint4 x = *reinterpret_cast<const uint4 *>(p + (row + 8 * k) * CT);
-                v[k][0] += x.x;
-                v[k][1] += x.y;
-                v[k][2] += x.z;
-                v[k][3] += x.w;
-            }
-        }
+    const uint32_t total = MODE == COUNT_FULL ? full_total<WEIGHTED>(a) : 0u;
+    constexpr int64_t STEP = MODE == COUNT_ALL ? 1 : 2;  // slots per workgroup
+    bool over = false;
+    const bool many = c.workers > 4 * c.ntiles;
+    const int32_t rows = many ? 2 : 32, per = CT / rows;  // rows of a piece, pieces of a tile
+    for (int64_t q = blockIdx.x; q < per * c.ntiles; q += gridDim.x) {
+        const int32_t t = (int32_t)(q / per), r0 = (int32_t)(q % per) * rows;
+        const TileParts parts = tile_parts<MODE>(c, t);
+        if (MODE != COUNT_ALL && parts.w0 == parts.w1) continue;  // counted whole, in acc already
         int32_t X, Y;
-        if (SQUARE) {
+        if (MODE != COUNT_FULL) {
             X = t / c.nb;
             Y = t % c.nb;
         } else {
             tri_coords(t, c.nb, X, Y);
         }
-        __syncthreads();  // the last tile's mirror has been read
+        const int64_t s1 = STEP * parts.w1 + (MODE == COUNT_ALL ? t : 0);
+        // slots of the parts after the first: STEP apart up to s1
+        const int64_t s2 = MODE == COUNT_ALL ? parts.s0 + 1 : 2 * parts.w0 + 2;
+        __syncthreads();  // the last piece's LDS has been read
+        if (many) {
+            const int col = (threadIdx.x & 31) * 4, row = (threadIdx.x >> 5) & 1, wave = threadIdx.x >> 6;
+            const uint32_t *p = a.partial + (r0 + row) * CT + col;
+            uint32_t v[4] = {};
+            auto add = [&](int64_t slot) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(p + slot * (CT * CT));
+                v[0] += x.x, v[1] += x.y, v[2] += x.z, v[3] += x.w;
+            };
+            if (wave == 0) add(parts.s0);
+#pragma unroll 8
+            for (int64_t sl = s2 + STEP * wave; sl <= s1; sl += 4 * STEP) add(sl);
+            for (int e = 0; e < 4; ++e) buf[wave * 2 + row][col + e] = v[e];
+            __syncthreads();
+            if (wave == 0)
+                for (int e = 0; e < 4; ++e)
+                    add_count<MODE>(a, c.nu, X * CT + r0 + row, Y * CT + col + e, X != Y, total,
+                                    buf[row][col + e] + buf[2 + row][col + e] + buf[4 + row][col + e] +
+                                        buf[6 + row][col + e],
+                                    over);
+            continue;
+        }
+        const int col = (threadIdx.x & 31) * 4, row = threadIdx.x >> 5;
+        uint32_t v[4][4] = {};
+        auto add = [&](int64_t slot) {
+            const uint32_t *p = a.partial + slot * (CT * CT) + r0 * CT + col;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint4 x = *reinterpret_cast<const uint4 *>(p + (row + 8 * k) * CT);
+                v[k][0] += x.x, v[k][1] += x.y, v[k][2] += x.z, v[k][3] += x.w;
+            }
+        };
+        add(parts.s0);
+#pragma unroll 2
+        for (int64_t sl = s2; sl <= s1; sl += STEP) add(sl);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                add_count<SQUARE>(a, c.nu, X * CT + r0 + row + 8 * k, Y * CT + col + e, false, 0u, v[k][e]);
-                if (!SQUARE) buf[row + 8 * k][col + e] = v[k][e];
+                add_count<MODE>(a, c.nu, X * CT + r0 + row + 8 * k, Y * CT + col + e, false, 0u, v[k][e], over);
+                if (MODE == COUNT_FULL) buf[row + 8 * k][col + e] = v[k][e];
             }
-        if (SQUARE || X == Y) continue;
+        if (MODE != COUNT_FULL || X == Y) continue;
         __syncthreads();
         for (int i = threadIdx.x; i < 32 * CT; i += 256) {
             const int32_t x = X * CT + r0 + (i & 31), y = Y * CT + (i >> 5);
             if (x < c.nu && y < c.nu) a.acc[(int64_t)y * a.lda + x] += total - buf[i & 31][i >> 5];
         }
     }
+    if (MODE == COUNT_ALL && over) set_device_error(a.err, SCHULZE_ERANGE);
 }
 
 // ------------------------------------------------------------------ pair scattering
@@ -1423,7 +1690,8 @@ __global__ __launch_bounds__(256) void k_fill_acc(uint32_t *__restrict__ p, int6
 }
 
 struct MetaLayout {
-    size_t ctr, k2, len, full_src, trunc_src, in_u, ulist, umap, total;
+    // cleared by each call: ctr .. rsum (one fill); then the rest
+    size_t ctr, k2, over, in_u, rsum, len, full_src, trunc_src, ulist, umap, total;
     MetaLayout(int64_t n, int32_t m) {
         size_t o = 0;
         auto take = [&](size_t bytes) {
@@ -1433,10 +1701,12 @@ struct MetaLayout {
         };
         ctr = take(64 * sizeof(int32_t));
         k2 = take(NPART * sizeof(unsigned long long));
+        over = take(sizeof(uint32_t));  // a count above the limit was clamped (bucketed route)
+        in_u = take((size_t)m);
+        rsum = take(sizeof(uint32_t) * (size_t)m);
         len = take(sizeof(int32_t) * (size_t)n);
         full_src = take(sizeof(int32_t) * (size_t)n);
         trunc_src = take(sizeof(int32_t) * (size_t)n);
-        in_u = take((size_t)m);
         ulist = take(sizeof(int32_t) * (size_t)m);
         umap = take(sizeof(int32_t) * (size_t)m);
         total = o;
@@ -1449,7 +1719,7 @@ struct MetaLayout {
 // and such a candidate has more than OCC_CHUNK occurrences, so there are at
 // most 2 cap / OCC_CHUNK of them.
 struct OccLayout {
-    size_t hist, row_start, item_start, part_start, fin, occ, partial, over_flag, total;
+    size_t hist, row_start, item_start, part_start, fin, occ, partial, total;
     int64_t ppitch, max_parts;
     OccLayout(int64_t G, int32_t m, int64_t cap, size_t partial_elem) {
         size_t o = 0;
@@ -1467,7 +1737,6 @@ struct OccLayout {
         occ = take(sizeof(uint32_t) * (size_t)cap);
         partial = take(partial_elem * (size_t)max_parts * (size_t)ppitch);
         fin = take(sizeof(int32_t) * (size_t)m);
-        over_flag = take(sizeof(uint32_t));  // a count above the limit was clamped
         total = o;
     }
 };
@@ -1562,19 +1831,30 @@ int occ_accumulate(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid
     return SCHULZE_OK;
 }
 
+// The total voter weight (counters 32 and 33, and the workgroups done in 34)
+// and the weights or-ed (7); all start at zero.
+int weight_total(schulze_ctx *ctx, hipStream_t s, const uint32_t *weight, int64_t n, int32_t *ctr) {
+    const unsigned tg = (unsigned)std::min<int64_t>(ceil_div(n, 256), (int64_t)ctx->num_cus * 4);
+    SCHULZE_LAUNCH(ctx, K_ROUTE, s,
+                   k_weight_total<<<dim3(tg), dim3(256), 0, s>>>(weight, n, reinterpret_cast<unsigned long long *>(ctr + 32),
+                                                                 ctr + 34, ctr + 7, ctx->err));
+    return SCHULZE_OK;
+}
+
 // Rank planes and the bit-plane count of the full rankings (FULL) or, if the
 // device chose the dense route, of the truncated ballots over U (pitch: at
 // most that many columns).  A workgroup of the planes takes 2048 columns
 // with 1024 threads (128 KB of LDS; each further chunk of columns reads the
 // ballots again) or, for at most 1024 columns, 512 with 256 threads.
 template <bool FULL>
-int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32, int32_t L, int32_t m, int32_t pitch,
+int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32, int64_t n, int32_t L, int32_t m, int32_t pitch,
                 int32_t bits, int64_t max_groups, const Meta &meta, const uint32_t *weight, uint32_t *planes,
                 uint32_t *wplanes, uint32_t *acc, int64_t lda, uint32_t *rsum) {
-    const int vec = L % (dtype32 ? 4 : 8) == 0 && reinterpret_cast<uintptr_t>(ballots) % 16 == 0;
-    const PlaneArgs pa{ballots, L, m, pitch, bits, meta, weight, planes, wplanes, ctx->err, vec};
+    const PlaneArgs pa{ballots, L, m, pitch, bits, meta, weight, planes, wplanes, ctx->err, n};
     const int wide = pitch > 1024;
-    const dim3 pg((unsigned)max_groups, (unsigned)ceil_div(pitch, wide ? 2048 : 512));
+    // (the route may leave nothing to do: no more workgroups than stay resident)
+    const dim3 pg((unsigned)std::min<int64_t>(max_groups * ceil_div(pitch, wide ? 2048 : 512),
+                                              (int64_t)ctx->num_cus * (wide ? 1 : 4)));
     if (wide && dtype32)
         SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, true, 2048, 1024><<<pg, dim3(1024), 0, s>>>(pa)));
     else if (wide)
@@ -1584,17 +1864,78 @@ int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype3
     else
         SCHULZE_LAUNCH(ctx, K_BALLOT_SCATTER, s, (k_planes<FULL, false, 512, 256><<<pg, dim3(256), 0, s>>>(pa)));
     const int32_t grid = ctx->num_cus * COUNT_PER_CU;
-    const DenseArgs da{planes, pitch, bits, m, meta, acc, lda, rsum, wplanes, static_cast<uint32_t *>(ctx->ws[WS_PARTIAL])};
-    const dim3 cg((unsigned)grid), rg((unsigned)std::min<int64_t>(4 * ceil_div(pitch, CT) * ceil_div(pitch, CT),
+    DenseArgs da{};
+    da.planes = planes, da.pitch = pitch, da.bits = bits, da.m = m, da.meta = meta;
+    da.acc = acc, da.lda = lda, da.rsum = rsum, da.wplanes = wplanes;
+    da.partial = static_cast<uint32_t *>(ctx->ws[WS_PARTIAL]);
+    const dim3 cg((unsigned)grid), rg((unsigned)std::min<int64_t>(64 * ceil_div(pitch, CT) * ceil_div(pitch, CT),
                                                                    (int64_t)ctx->num_cus * 8));
     const int kid = FULL ? K_COUNT_DENSE : K_COUNT_TRUNC;
+    constexpr int MODE = FULL ? COUNT_FULL : COUNT_U;
     if (FULL && weight) {
-        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<!FULL, FULL><<<cg, dim3(256), 0, s>>>(da)));
-        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<!FULL, FULL><<<rg, dim3(256), 0, s>>>(da, grid)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<MODE, FULL><<<cg, dim3(256), 0, s>>>(da)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<MODE, FULL><<<rg, dim3(256), 0, s>>>(da, grid)));
     } else {
-        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<!FULL, false><<<cg, dim3(256), 0, s>>>(da)));
-        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<!FULL, false><<<rg, dim3(256), 0, s>>>(da, grid)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_bits<MODE, false><<<cg, dim3(256), 0, s>>>(da)));
+        SCHULZE_LAUNCH(ctx, kid, s, (k_count_reduce<MODE, false><<<rg, dim3(256), 0, s>>>(da, grid)));
     }
+    return SCHULZE_OK;
+}
+
+// Small elections: every ballot over all candidates in one dense pass, three
+// launches (planes, count, adding up; five with voter weights) instead of the
+// scan, the route decision and both routes' kernels (19, at about 4.5 us
+// each even where they find nothing to do).  Taken while the count costs at
+// most ALL_COST lane operations (65 us at 45 T/s), about what the other
+// launches would (n = 7001 weighted top-25 of m = 389: 434 us by pairs, 366 us
+// so); weights are charged as 12 bits.
+constexpr double ALL_COST = 3.0e9;
+constexpr int32_t ALL_MAX_M = 4096;
+inline bool count_all_fits(int64_t n, int32_t L, int32_t m, bool weighted) {
+    if (n < 1 || m > ALL_MAX_M) return false;
+    const double pitch = (double)round_up(m, CT);
+    return (double)ceil_div(n, 32) * pitch * pitch * (rank_bits(std::min(L, m - 1)) + 2 + (weighted ? 36 : 0)) <= ALL_COST;
+}
+
+int count_all(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32, int64_t n, int32_t L, int32_t m,
+              const uint32_t *weight, int d_dtype, void *d, int64_t ldd) {
+    const int32_t pitch = (int32_t)round_up(m, CT), bits = rank_bits(std::min(L, m - 1));
+    const int64_t groups = ceil_div(n, 32), nb = pitch / CT, ntiles = nb * nb, units = ntiles * groups;
+    const size_t plane_words = (size_t)groups * bits * pitch;
+    int rc = ws_reserve(ctx, WS_POSITIONS, sizeof(uint32_t) * (plane_words + (weight ? 32 * (size_t)groups : 0)));
+    if (rc != SCHULZE_OK) return rc;
+    // whole tiles per workgroup when there are enough of them; else ranges of
+    // two units or more, whose partial tiles are added up
+    const int64_t grid_max = (int64_t)ctx->num_cus * COUNT_PER_CU;
+    const bool whole = 2 * ntiles >= grid_max || groups == 1;
+    const int64_t workers = whole ? std::min(grid_max, ntiles) : std::min(grid_max, ceil_div(units, 2));
+    if (!whole && (rc = ws_reserve(ctx, WS_PARTIAL, sizeof(uint32_t) * CT * CT * (size_t)(workers + ntiles))) != SCHULZE_OK)
+        return rc;
+    uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_POSITIONS]);
+    DenseArgs da{};
+    da.planes = planes, da.pitch = pitch, da.bits = bits, da.m = m;
+    da.wplanes = weight ? planes + plane_words : nullptr;
+    da.partial = static_cast<uint32_t *>(ctx->ws[WS_PARTIAL]);
+    da.n = (int32_t)n, da.whole = whole;
+    da.d = d, da.ldd = ldd, da.d32 = d_dtype == SCHULZE_I32, da.err = ctx->err;
+    da.limit = d_dtype == SCHULZE_U16 ? 65535u : (uint32_t)INT32_MAX;
+    if (weight) {
+        if ((rc = ws_reserve(ctx, WS_BALLOT_META, 64 * sizeof(int32_t))) != SCHULZE_OK) return rc;
+        da.meta.ctr = static_cast<int32_t *>(ctx->ws[WS_BALLOT_META]);
+        if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(da.meta.ctr), 64, 0u)) != SCHULZE_OK) return rc;
+        if ((rc = weight_total(ctx, s, weight, n, da.meta.ctr)) != SCHULZE_OK) return rc;
+    }
+    const AllArgs pa{ballots, (int32_t)n, L, m, pitch, bits, weight, planes, const_cast<uint32_t *>(da.wplanes), ctx->err};
+    if ((rc = dtype32 ? planes_all<true>(ctx, s, pa, groups) : planes_all<false>(ctx, s, pa, groups)) != SCHULZE_OK)
+        return rc;
+    const dim3 cg((unsigned)workers), rg((unsigned)std::min<int64_t>(64 * ntiles, (int64_t)ctx->num_cus * 8));
+    if (weight)
+        SCHULZE_LAUNCH(ctx, K_COUNT_DENSE, s, (k_count_bits<COUNT_ALL, true><<<cg, dim3(256), 0, s>>>(da)));
+    else
+        SCHULZE_LAUNCH(ctx, K_COUNT_DENSE, s, (k_count_bits<COUNT_ALL, false><<<cg, dim3(256), 0, s>>>(da)));
+    if (!whole)
+        SCHULZE_LAUNCH(ctx, K_COUNT_FINISH, s,
+                       (k_count_reduce<COUNT_ALL, false><<<rg, dim3(256), 0, s>>>(da, (int32_t)workers)));
     return SCHULZE_OK;
 }
 
@@ -1615,6 +1956,8 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     const int dtype32 = ballot_dtype == SCHULZE_I32;
+    if (!ctx->legacy_pairs && count_all_fits(n, L, m, voter_weight != nullptr))
+        return count_all(ctx, s, ballots, dtype32, n, L, m, voter_weight, d_dtype, d, ldd);
     const int32_t pitch = (int32_t)round_up(m, CT);
     const int64_t max_groups = ceil_div(n, 32);  // of 32 voters
     const bool may_have_full = L >= m - 1 && n > 0;
@@ -1633,7 +1976,6 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     int rc;
     if ((rc = ws_reserve(ctx, WS_BALLOT_META, lay.total)) != SCHULZE_OK) return rc;
     if ((rc = ws_reserve(ctx, WS_ACC32, sizeof(uint32_t) * (size_t)m * m)) != SCHULZE_OK) return rc;
-    if ((rc = ws_reserve(ctx, WS_ROWSUM, sizeof(uint32_t) * (size_t)m)) != SCHULZE_OK) return rc;
     if (may_have_full &&
         (rc = ws_reserve(ctx, WS_POSITIONS, sizeof(uint32_t) * ((size_t)max_groups * full_bits * pitch + weight_words))) !=
             SCHULZE_OK)
@@ -1661,53 +2003,40 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
               reinterpret_cast<int32_t *>(mb + lay.ulist),
               reinterpret_cast<int32_t *>(mb + lay.umap)};
     uint32_t *acc = static_cast<uint32_t *>(ctx->ws[WS_ACC32]);
-    uint32_t *rsum = static_cast<uint32_t *>(ctx->ws[WS_ROWSUM]);
+    uint32_t *rsum = reinterpret_cast<uint32_t *>(mb + lay.rsum);
     const int64_t lda = m;
 
-    // counters, partial sums and the U bitmap start at zero
-    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(mb + lay.ctr), (lay.len - lay.ctr) / 4, 0u)) !=
-        SCHULZE_OK)
-        return rc;
-    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(mb + lay.in_u), (lay.ulist - lay.in_u) / 4, 0u)) !=
-        SCHULZE_OK)
-        return rc;
+    // counters, partial sums, the U bitmap and the row sums start at zero
+    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(mb), lay.len / 4, 0u)) != SCHULZE_OK) return rc;
     if (n == 0 && (rc = fill_u32(ctx, s, acc, (size_t)m * m, 0u)) != SCHULZE_OK) return rc;
-    if ((rc = fill_u32(ctx, s, rsum, (size_t)m, 0u)) != SCHULZE_OK) return rc;
 
     uint8_t *over_flag = nullptr;  // the bucketed count's overflow flag (set: it ran and wrote its rows)
     if (n > 0) {
         if (L <= 64) {
-            const int64_t per_wg = 4 * SHORT_PER_WAVE * SHORT_ROUNDS * std::min<int64_t>(SHORT_BPW, 64 / L);
-            const dim3 sg((unsigned)ceil_div(n, per_wg));
+            // more ballots per workgroup where there are many (fewer reservations)
+            const int64_t per_round = 4 * SHORT_PER_WAVE * std::min<int64_t>(SHORT_BPW, 64 / L);
+            const int32_t rounds = (int32_t)std::max<int64_t>(
+                SHORT_ROUNDS, std::min<int64_t>(SHORT_MAX_ROUNDS, ceil_div(n, per_round * 2 * ctx->num_cus)));
+            const dim3 sg((unsigned)ceil_div(n, per_round * rounds));
             if (dtype32)
                 SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
-                               k_scan_short<true><<<sg, dim3(256), 0, s>>>(ballots, n, L, m, meta, ctx->err));
+                               k_scan_short<true><<<sg, dim3(256), 0, s>>>(ballots, n, L, m, rounds, meta, ctx->err));
             else
                 SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
-                               k_scan_short<false><<<sg, dim3(256), 0, s>>>(ballots, n, L, m, meta, ctx->err));
-        } else if (!dtype32 && L % 8 == 0 && reinterpret_cast<uintptr_t>(ballots) % 16 == 0) {
-            SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
-                           k_scan_long_vec<<<dim3((unsigned)ceil_div(n, LONG_CHUNK)), dim3(256), 0, s>>>(
-                               static_cast<const uint16_t *>(ballots), n, L, m, meta, ctx->err));
+                               k_scan_short<false><<<sg, dim3(256), 0, s>>>(ballots, n, L, m, rounds, meta, ctx->err));
         } else {
-            const dim3 lg((unsigned)ceil_div(n, LONG_CHUNK));
+            const int32_t chunk = (int32_t)round_up(ceil_div(n, ctx->num_cus), 16);
+            const dim3 lg((unsigned)ceil_div(n, chunk));
             if (dtype32)
                 SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
-                               k_scan_long<true><<<lg, dim3(256), 0, s>>>(ballots, n, L, m, meta, ctx->err));
+                               k_scan_long<true><<<lg, dim3(1024), 0, s>>>(ballots, n, L, m, chunk, meta, ctx->err));
             else
                 SCHULZE_LAUNCH(ctx, K_BALLOT_SCAN, s,
-                               k_scan_long<false><<<lg, dim3(256), 0, s>>>(ballots, n, L, m, meta, ctx->err));
+                               k_scan_long<false><<<lg, dim3(1024), 0, s>>>(ballots, n, L, m, chunk, meta, ctx->err));
         }
-        if (voter_weight) {
-            // counters 32..33: the 64-bit total; 34: workgroups done; 7: the weights or-ed (zeroed above)
-            const unsigned tg = (unsigned)std::min<int64_t>(ceil_div(n, 256), (int64_t)ctx->num_cus * 4);
-            SCHULZE_LAUNCH(ctx, K_ROUTE, s,
-                           k_weight_total<<<dim3(tg), dim3(256), 0, s>>>(
-                               voter_weight, n, reinterpret_cast<unsigned long long *>(meta.ctr + 32), meta.ctr + 34,
-                               meta.ctr + 7, ctx->err));
-        }
+        if (voter_weight && (rc = weight_total(ctx, s, voter_weight, n, meta.ctr)) != SCHULZE_OK) return rc;
         SCHULZE_LAUNCH(ctx, K_ROUTE, s,
-                       k_route<<<dim3(1), dim3(ROUTE_THREADS), 0, s>>>(m, meta, (int64_t)(trunc_bytes / sizeof(uint32_t)),
+                       k_route<<<dim3(1), dim3(ROUTE_THREADS), 0, s>>>(m, L <= 64 ? L : 0, meta, (int64_t)(trunc_bytes / sizeof(uint32_t)),
                                                              occ_ok ? BUCKETED_PAIR_COST : ATOMIC_PAIR_COST));
         {
             // the m x m accumulator starts at zero unless the device chose the
@@ -1721,13 +2050,13 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
         if (may_have_full) {
             uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_POSITIONS]);
             uint32_t *wplanes = voter_weight ? planes + (size_t)max_groups * full_bits * pitch : nullptr;
-            if ((rc = count_dense<true>(ctx, s, ballots, dtype32, L, m, pitch, full_bits, max_groups, meta,
+            if ((rc = count_dense<true>(ctx, s, ballots, dtype32, n, L, m, pitch, full_bits, max_groups, meta,
                                         voter_weight, planes, wplanes, acc, lda, rsum)) != SCHULZE_OK)
                 return rc;
         }
         if (trunc_bytes) {
             uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_TRUNC_POS]);
-            if ((rc = count_dense<false>(ctx, s, ballots, dtype32, L, m, (int32_t)upitch_max, 0, max_groups, meta,
+            if ((rc = count_dense<false>(ctx, s, ballots, dtype32, n, L, m, (int32_t)upitch_max, 0, max_groups, meta,
                                          nullptr, planes, nullptr, acc, lda, rsum)) != SCHULZE_OK)
                 return rc;
         }
@@ -1749,10 +2078,7 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
                        static_cast<void *>(ob + ol.partial), ol.ppitch,
                        acc, lda, rsum, ctx->err};
             const dim3 g(occ_grid);
-            over_flag = reinterpret_cast<uint8_t *>(ob + ol.over_flag);
-            if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(over_flag), 1, 0u)) !=
-                SCHULZE_OK)
-                return rc;
+            over_flag = reinterpret_cast<uint8_t *>(mb + lay.over);
             if ((rc = occ_bucket<false>(ctx, s, oa, g)) != SCHULZE_OK) return rc;
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                            k_occ_columns<<<dim3((unsigned)ceil_div(m, 64)), dim3(64 * COL_GROUPS), 0, s>>>(
