@@ -22,6 +22,7 @@ namespace {
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -44,7 +45,10 @@ struct NetBf16 {
     bf16 *w1t, *w2t, *w2, *w3;
 };
 
-__global__ __launch_bounds__(256) void k_mlp_prepare(const float *__restrict__ p, NetBf16 q) {
+// With `step`, the train step's Adam counter is advanced here (one launch less).
+__global__ __launch_bounds__(256) void k_mlp_prepare(const float *__restrict__ p, NetBf16 q,
+                                                     int32_t *__restrict__ step) {
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) step[0] += 1;
     for (int t = blockIdx.x * 256 + threadIdx.x; t < NH * NH; t += gridDim.x * 256) {
         const int i = t / NH, j = t % NH;
         const bf16 v = to_bf16(p[OFF_W2 + i * NH + j]);
@@ -66,22 +70,41 @@ struct Lds {
     float part[ROWS][4];
 };
 
+// (16-byte pieces: eight loads per thread in flight instead of 64 two-byte ones)
 __device__ inline void load_weights(Lds &L, const NetBf16 &q) {
-    for (int t = threadIdx.x; t < NH * NH; t += 256) L.w2t[(t / NH) * PH + t % NH] = q.w2t[t];
-    for (int t = threadIdx.x; t < NH * NF; t += 256) L.w1t[(t / NF) * PF + t % NF] = q.w1t[t];
-}
-
-__device__ inline void load_tile(Lds &L, const float *__restrict__ X, int64_t row0, int64_t M) {
-    for (int t = threadIdx.x; t < ROWS * NF; t += 256) {
-        const int r = t / NF, f = t % NF;
-        const int64_t row = row0 + r;
-        L.xs[r * PF + f] = to_bf16(row < M ? X[row * NF + f] : 0.0f);
+    constexpr int N2 = NH * NH / 8 / 256;
+    bf16x8 w[N2];
+    for (int k = 0; k < N2; ++k) w[k] = ld8(q.w2t + 8 * (threadIdx.x + 256 * k));
+    const bf16x8 w1 = ld8(q.w1t + 8 * threadIdx.x);  // NH * NF = 8 * 256
+    for (int k = 0; k < N2; ++k) {
+        const int t = 8 * (threadIdx.x + 256 * k);
+        *reinterpret_cast<bf16x8 *>(&L.w2t[(t / NH) * PH + t % NH]) = w[k];
     }
+    *reinterpret_cast<bf16x8 *>(&L.w1t[(threadIdx.x / 2) * PF + 8 * (threadIdx.x % 2)]) = w1;
+}
+static_assert(NH * NF == 8 * 256 && NH * NH % (8 * 256) == 0, "pieces of the weights");
+
+// One tile's inputs: four features per thread, loaded ahead of the tile
+// before (fetch) and rounded into LDS (put).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // feat may be any float pointer
+__device__ inline f32x4 fetch_tile(const float *__restrict__ X, int64_t row0, int64_t M) {
+    if (M < 1) return f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t row = row0 + threadIdx.x / 4;
+    const f32x4 v = *reinterpret_cast<const f32x4u *>(X + min(row, M - 1) * NF + 4 * (threadIdx.x % 4));
+    return row < M ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+}
+__device__ inline bf16x4 round4(const f32x4 &v) {
+    return bf16x4{to_bf16(v[0]), to_bf16(v[1]), to_bf16(v[2]), to_bf16(v[3])};
+}
+__device__ inline void put_tile(Lds &L, const f32x4 &v) {
+    *reinterpret_cast<bf16x4 *>(&L.xs[(threadIdx.x / 4) * PF + 4 * (threadIdx.x % 4)]) = round4(v);
 }
 
 // Wave w: row block rb = w >> 1, column blocks 2 (w & 1) + {0, 1}.
+// With h1t, the hidden layer is also written transposed (pitch PR): the four
+// consecutive rows a lane holds are one 8-byte store.
 __device__ inline void forward_tile(Lds &L, const float *__restrict__ b1, const float *__restrict__ b2,
-                                    f32x16 (&h2)[2], uint32_t (&mask2)[2]) {
+                                    f32x16 (&h2)[2], uint32_t (&mask2)[2], bf16 *h1t = nullptr) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rb = wave >> 1, hi = lane >> 5, lo = lane & 31;
     // layer 1: h1 = relu(x W1 + b1)
@@ -92,9 +115,14 @@ __device__ inline void forward_tile(Lds &L, const float *__restrict__ b1, const 
                                                      ld8(&L.w1t[(cb * 32 + lo) * PF + 8 * hi]), acc, 0, 0, 0);
         const int col = cb * 32 + lo;
         const float bias = b1[col];
-        for (int i = 0; i < 16; ++i) {
-            const int row = rb * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-            L.h1[row * PH + col] = to_bf16(fmaxf(acc[i] + bias, 0.0f));
+        for (int i = 0; i < 16; i += 4) {
+            const int row = rb * 32 + 8 * (i >> 2) + 4 * hi;
+            bf16x4 h;
+            for (int e = 0; e < 4; ++e) {
+                h[e] = to_bf16(fmaxf(acc[i + e] + bias, 0.0f));
+                L.h1[(row + e) * PH + col] = h[e];
+            }
+            if (h1t) *reinterpret_cast<bf16x4 *>(&h1t[col * PR + row]) = h;
         }
     }
     __syncthreads();
@@ -117,10 +145,29 @@ __device__ inline void forward_tile(Lds &L, const float *__restrict__ b1, const 
     }
 }
 
-// Sum over the 32 lanes of a half-wave (fixed butterfly order).
-__device__ inline float half_sum(float v) {
-    for (int off = 1; off < 32; off <<= 1) v += __shfl_xor(v, off);
-    return v;
+// Sums of sixteen values over the 32 lanes of a half-wave, each the same
+// tree of additions as a butterfly over lane distances 1, 2, 4, 8, 16: each
+// step adds the lane's half of the values to the partner's other half, so
+// that 16 exchanges do what 80 would.  Returns, in lane l, the sum of value
+// 8 b0 + 4 b1 + 2 b2 + b3 for the bits b of l (bit 4 of l: the same).
+__device__ inline float half_sums(const float (&v)[16]) {
+    const int lane = threadIdx.x;
+    float a[8], b[4], c[2];
+    for (int i = 0; i < 8; ++i) {
+        const bool up = lane & 1;
+        a[i] = (up ? v[8 + i] : v[i]) + __shfl_xor(up ? v[i] : v[8 + i], 1);
+    }
+    for (int i = 0; i < 4; ++i) {
+        const bool up = lane & 2;
+        b[i] = (up ? a[4 + i] : a[i]) + __shfl_xor(up ? a[i] : a[4 + i], 2);
+    }
+    for (int i = 0; i < 2; ++i) {
+        const bool up = lane & 4;
+        c[i] = (up ? b[2 + i] : b[i]) + __shfl_xor(up ? b[i] : b[2 + i], 4);
+    }
+    const bool up = lane & 8;
+    const float d = (up ? c[1] : c[0]) + __shfl_xor(up ? c[0] : c[1], 8);
+    return d + __shfl_xor(d, 16);
 }
 
 // ------------------------------------------------------------------ forward
@@ -131,20 +178,25 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float *__restrict__ p, Ne
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rb = wave >> 1, hi = lane >> 5, lo = lane & 31;
     const int64_t ntiles = (M + ROWS - 1) / ROWS;
+    float w3[2];
+    for (int c = 0; c < 2; ++c) w3[c] = from_bf16(q.w3[(2 * (wave & 1) + c) * 32 + lo]);
+    f32x4 x = fetch_tile(X, (int64_t)blockIdx.x * ROWS, M);
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         __syncthreads();
-        load_tile(L, X, t * ROWS, M);
+        put_tile(L, x);
+        if (t + gridDim.x < ntiles) x = fetch_tile(X, (t + gridDim.x) * ROWS, M);
         __syncthreads();
         f32x16 h2[2];
         uint32_t mk[2];
         forward_tile(L, p + OFF_B1, p + OFF_B2, h2, mk);
         // layer 3: s = h2 W3 + b3 (deterministic: lanes, then blocks in order)
         for (int c = 0; c < 2; ++c) {
-            const int cb = 2 * (wave & 1) + c;
-            const float w3 = from_bf16(q.w3[cb * 32 + lo]);
-            for (int i = 0; i < 16; ++i) {
-                const float sum = half_sum(h2[c][i] * w3);
-                if (lo == 0) L.part[rb * 32 + 8 * (i >> 2) + 4 * hi + (i & 3)][cb] = sum;
+            float v[16];
+            for (int i = 0; i < 16; ++i) v[i] = h2[c][i] * w3[c];
+            const float sum = half_sums(v);
+            if (lo < 16) {
+                const int i = ((lo & 1) << 3) | ((lo & 2) << 1) | ((lo & 4) >> 1) | (lo >> 3);
+                L.part[rb * 32 + 8 * (i >> 2) + 4 * hi + (i & 3)][2 * (wave & 1) + c] = sum;
             }
         }
         __syncthreads();
@@ -157,45 +209,76 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float *__restrict__ p, Ne
 }
 
 // ------------------------------------------------------------------ loss
-// One wavefront per election e over rows [off[e], off[e+1]): softmax
+// One workgroup per election e over rows [off[e], off[e+1]): softmax
 // cross-entropy with the probability mass of the winner set,
 //   loss_e = log sum_all exp(s) - log sum_winners exp(s),
 // ds = (softmax over all - softmax over winners, on winners) / E.
+// The exponentials of elections of up to SEG_KEEP rows are computed once, by
+// all threads, into LDS; the first wavefront adds them up (row a + lane, a +
+// lane + 64, .. per lane, then the lanes: the sums do not depend on how many
+// threads took part).  With a wavefront doing all of it, 128 elections of
+// 1150 rows left half the chip idle and took 25 us, of which this 7.
+constexpr int SEG_KEEP = 8192;
 __global__ __launch_bounds__(256) void k_seg_loss(const float *__restrict__ score, const int64_t *__restrict__ off,
                                                   const uint8_t *__restrict__ winner, int32_t E,
                                                   float *__restrict__ ds, float *__restrict__ loss) {
-    const int lane = threadIdx.x & 63;
-    const int32_t e = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (e >= E) return;
+    __shared__ float ex[SEG_KEEP];
+    __shared__ float red[4], sums[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t e = blockIdx.x;
     const int64_t a = off[e], b = off[e + 1];
+    const bool keep = b - a <= SEG_KEEP;
     float mx = -INFINITY;
-    for (int64_t r = a + lane; r < b; r += 64) mx = fmaxf(mx, score[r]);
+    for (int64_t r = a + threadIdx.x; r < b; r += 256) {
+        const float s = score[r];
+        if (keep) ex[r - a] = s;
+        mx = fmaxf(mx, s);
+    }
     for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    float sa = 0.f, sw = 0.f;
-    for (int64_t r = a + lane; r < b; r += 64) {
-        const float ex = expf(score[r] - mx);
-        sa += ex;
-        if (winner[r]) sw += ex;
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    if (keep)
+        for (int64_t r = threadIdx.x; r < b - a; r += 256) ex[r] = expf(ex[r] - mx);
+    __syncthreads();
+    if (wave == 0) {
+        float sa = 0.f, sw = 0.f;
+        for (int64_t r = a + lane; r < b; r += 64) {
+            const float x = keep ? ex[r - a] : expf(score[r] - mx);
+            sa += x;
+            if (winner[r]) sw += x;
+        }
+        for (int o = 1; o < 64; o <<= 1) {
+            sa += __shfl_xor(sa, o);
+            sw += __shfl_xor(sw, o);
+        }
+        if (lane == 0) {
+            sums[0] = sa;
+            sums[1] = sw;
+        }
     }
-    for (int o = 1; o < 64; o <<= 1) {
-        sa += __shfl_xor(sa, o);
-        sw += __shfl_xor(sw, o);
-    }
+    __syncthreads();
+    const float sa = sums[0], sw = sums[1];
     const float inv_e = 1.0f / (float)E;
     const bool ok = sw > 0.f;
-    for (int64_t r = a + lane; r < b; r += 64) {
-        const float ex = expf(score[r] - mx);
-        float g = ex / sa;
-        if (winner[r] && ok) g -= ex / sw;
+    for (int64_t r = a + threadIdx.x; r < b; r += 256) {
+        const float x = keep ? ex[r - a] : expf(score[r] - mx);
+        float g = x / sa;
+        if (winner[r] && ok) g -= x / sw;
         ds[r] = ok ? g * inv_e : 0.f;
     }
-    if (lane == 0) loss[e] = ok ? logf(sa) - logf(sw) : 0.f;
+    if (threadIdx.x == 0) loss[e] = ok ? logf(sa) - logf(sw) : 0.f;
 }
 
 // ------------------------------------------------------------------ backward
-// Persistent workgroups; each walks a fixed set of tiles (deterministic),
-// recomputes the forward part, and accumulates its parameter-gradient
-// partials in registers, written once at the end to partial[block][NPARAM].
+// A share of the tiles (share s of n: tiles s, s + n, ..) has its
+// parameter-gradient partials accumulated in registers, after the forward
+// part is recomputed, and written once to partial[s][NPARAM].  The number of
+// shares is fixed by the rows, not by the launch, so that the gradient is the
+// same however many workgroups run (one per CU: the LDS holds no second).
+// Bound by latency: four wavefronts per CU between barriers, so the next
+// tile's inputs are loaded a tile ahead and the transposed operands are
+// written as 8-byte stores of the four consecutive rows a lane holds.
 struct BwdLds {
     Lds f;
     bf16 dz2[ROWS * PH];   // row-major
@@ -208,7 +291,7 @@ struct BwdLds {
 };
 
 __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, NetBf16 q, const float *__restrict__ X,
-                                                 const float *__restrict__ dsg, int64_t M,
+                                                 const float *__restrict__ dsg, int64_t M, int32_t shares,
                                                  float *__restrict__ partial) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     BwdLds &L = *reinterpret_cast<BwdLds *>(smem);
@@ -221,51 +304,60 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, Ne
         for (int kk = 0; kk < NH / 16; ++kk)
             w2f[c][kk] = ld8(&q.w2[(int64_t)((2 * (wave & 1) + c) * 32 + lo) * NH + 16 * kk + 8 * hi]);
 
+    float w3c[2];
+    for (int c = 0; c < 2; ++c) w3c[c] = from_bf16(q.w3[(2 * (wave & 1) + c) * 32 + lo]);
+
+    const int64_t ntiles = (M + ROWS - 1) / ROWS;
+    auto fetch_ds = [&](int64_t t) {
+        const int64_t row = t * ROWS + threadIdx.x;
+        return threadIdx.x < ROWS && row < M ? dsg[row] : 0.f;
+    };
+    for (int32_t share = blockIdx.x; share < shares; share += gridDim.x) {
     f32x16 gw2[4] = {};     // dW2 blocks (ib = wave, jb = 0..3)
     f32x4 gw1[2] = {};      // dW1 blocks (16 x 16): ib = 2 wave + {0,1}
     float gw3[2] = {0.f, 0.f}, gb2[2] = {0.f, 0.f}, gb1[2] = {0.f, 0.f}, gb3 = 0.f;
-
-    const int64_t ntiles = (M + ROWS - 1) / ROWS;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    f32x4 x = fetch_tile(X, (int64_t)share * ROWS, M);
+    float dsv = fetch_ds(share);
+    for (int64_t t = share; t < ntiles; t += shares) {
         __syncthreads();
-        load_tile(L.f, X, t * ROWS, M);
-        if (threadIdx.x < ROWS) {
-            const int64_t row = t * ROWS + threadIdx.x;
-            L.ds[threadIdx.x] = row < M ? dsg[row] : 0.f;
+        put_tile(L.f, x);
+        {  // transposed inputs for dW1
+            const bf16x4 r = round4(x);
+            for (int e = 0; e < 4; ++e) L.xt[(4 * (threadIdx.x % 4) + e) * PR + threadIdx.x / 4] = r[e];
+        }
+        if (threadIdx.x < ROWS) L.ds[threadIdx.x] = dsv;
+        if (t + shares < ntiles) {  // the next tile's rows, in flight during this one
+            x = fetch_tile(X, (t + shares) * ROWS, M);
+            dsv = fetch_ds(t + shares);
         }
         __syncthreads();
         f32x16 h2[2];
         uint32_t mk2[2];
-        forward_tile(L.f, p + OFF_B1, p + OFF_B2, h2, mk2);
+        forward_tile(L.f, p + OFF_B1, p + OFF_B2, h2, mk2, L.h1t);
         // dz2 = mask2 * ds * w3; dW3 += h2 ds; db2 += dz2 (from the rounded dz2)
         for (int c = 0; c < 2; ++c) {
             const int cb = 2 * (wave & 1) + c;
             const int col = cb * 32 + lo;
-            const float w3 = from_bf16(q.w3[col]);
+            const float w3 = w3c[c];
             float s3 = 0.f, s2 = 0.f;
-            for (int i = 0; i < 16; ++i) {
-                const int row = rb * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-                const float dsr = L.ds[row];
-                s3 += h2[c][i] * dsr;
-                const bf16 dz = to_bf16(((mk2[c] >> i) & 1u) ? dsr * w3 : 0.0f);
-                s2 += from_bf16(dz);
-                L.dz2[row * PH + col] = dz;
-                L.dz2t[col * PR + row] = dz;
+            for (int i = 0; i < 16; i += 4) {
+                const int row = rb * 32 + 8 * (i >> 2) + 4 * hi;
+                bf16x4 dz;
+                for (int e = 0; e < 4; ++e) {
+                    const float dsr = L.ds[row + e];
+                    s3 += h2[c][i + e] * dsr;
+                    dz[e] = to_bf16(((mk2[c] >> (i + e)) & 1u) ? dsr * w3 : 0.0f);
+                    s2 += from_bf16(dz[e]);
+                    L.dz2[(row + e) * PH + col] = dz[e];
+                }
+                *reinterpret_cast<bf16x4 *>(&L.dz2t[col * PR + row]) = dz;  // four consecutive rows
             }
             gw3[c] += s3;
             gb2[c] += s2;
         }
-        // transposed h1 and x for the weight-gradient products
-        for (int e = threadIdx.x; e < ROWS * NH; e += 256) {
-            const int r = e / NH, i = e % NH;
-            L.h1t[i * PR + r] = L.f.h1[r * PH + i];
-        }
-        for (int e = threadIdx.x; e < ROWS * NF; e += 256) {
-            const int r = e / NF, f = e % NF;
-            L.xt[f * PR + r] = L.f.xs[r * PF + f];
-        }
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 192) {  // (row order)
             float s = 0.f;
+#pragma unroll 16
             for (int r = 0; r < ROWS; ++r) s += L.ds[r];
             gb3 += s;
         }
@@ -285,12 +377,15 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, Ne
                                                              w2f[c][kk], acc, 0, 0, 0);
             const int col = ib * 32 + lo;
             float s1 = 0.f;
-            for (int i = 0; i < 16; ++i) {
-                const int row = rb * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-                const bool on = from_bf16(L.f.h1[row * PH + col]) > 0.0f;
-                const bf16 dz = to_bf16(on ? acc[i] : 0.0f);
-                s1 += from_bf16(dz);
-                L.dz1t[col * PR + row] = dz;
+            for (int i = 0; i < 16; i += 4) {
+                const int row = rb * 32 + 8 * (i >> 2) + 4 * hi;
+                const bf16x4 h = *reinterpret_cast<const bf16x4 *>(&L.h1t[col * PR + row]);
+                bf16x4 dz;
+                for (int e = 0; e < 4; ++e) {
+                    dz[e] = to_bf16(from_bf16(h[e]) > 0.0f ? acc[i + e] : 0.0f);
+                    s1 += from_bf16(dz[e]);
+                }
+                *reinterpret_cast<bf16x4 *>(&L.dz1t[col * PR + row]) = dz;
             }
             gb1[c] += s1;
         }
@@ -305,7 +400,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, Ne
         }
     }
     // write this workgroup's partials (fixed order reductions only)
-    float *out = partial + (int64_t)blockIdx.x * NPARAM;
+    float *out = partial + (int64_t)share * NPARAM;
     for (int jb = 0; jb < 4; ++jb)
         for (int i = 0; i < 16; ++i) {
             const int r = wave * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
@@ -342,45 +437,61 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, Ne
         const int col = threadIdx.x;
         out[OFF_B1 + col] = (L.red[0][col] + L.red[1][col]) + (L.red[2][col] + L.red[3][col]);
     }
-    if (threadIdx.x == 0) out[OFF_B3] = gb3;
+    if (threadIdx.x == 192) out[OFF_B3] = gb3;
+    }
 }
 
-// grad[k] = sum over blocks of partial[block][k], in block order.
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partial, int32_t nblocks,
-                                                    float *__restrict__ grad) {
+// Adam (FP32 master weights), bias-corrected, step t >= 1.
+struct AdamArgs {
+    float *p, *m1, *m2;
+    float lr, b1, b2, eps;
+    int32_t t_host;
+    const int32_t *t_dev;  // when given, the device counter (the train step advances it first)
+};
+__device__ inline void adam_step(const AdamArgs &a, int k, float gk) {
+    const int32_t t = a.t_dev ? *a.t_dev : a.t_host;
+    const float m = a.b1 * a.m1[k] + (1.f - a.b1) * gk;
+    const float v = a.b2 * a.m2[k] + (1.f - a.b2) * gk * gk;
+    a.m1[k] = m;
+    a.m2[k] = v;
+    const float ah = m / (1.f - powf(a.b1, (float)t));
+    const float vh = v / (1.f - powf(a.b2, (float)t));
+    a.p[k] -= a.lr * ah / (sqrtf(vh) + a.eps);
+}
+__global__ __launch_bounds__(256) void k_adam(AdamArgs a, const float *__restrict__ g) {
     const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < NPARAM) adam_step(a, k, g[k]);
+}
+
+// grad[k] = sum over shares of partial[share][k], in share order; with a.p,
+// the parameter's Adam step follows.  One wavefront per 64 parameters, so
+// that the additions, one after the other, spread over the whole chip with
+// 64 loads in flight per thread (256 parameters per workgroup and few loads
+// in flight took 122 us of a 292 us train step).
+__global__ __launch_bounds__(64) void k_mlp_reduce(const float *__restrict__ partial, int32_t shares,
+                                                   float *__restrict__ grad, AdamArgs a) {
+    constexpr int FLY = 64;
+    const int k = blockIdx.x * 64 + threadIdx.x;
     if (k >= NPARAM) return;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * NPARAM + k];
+    int b = 0;
+    for (; b + FLY <= shares; b += FLY) {
+        float v[FLY];
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) v[u] = partial[(int64_t)(b + u) * NPARAM + k];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) s += v[u];
+    }
+#pragma unroll 8
+    for (; b < shares; ++b) s += partial[(int64_t)b * NPARAM + k];
     grad[k] = s;
-}
-
-// Adam (FP32 master weights), bias-corrected, step t >= 1: t_host, or the
-// device counter *t_dev when given (the train step advances it first).
-__global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float *__restrict__ g,
-                                              float *__restrict__ m1, float *__restrict__ m2, float lr, float b1,
-                                              float b2, float eps, int32_t t_host, const int32_t *__restrict__ t_dev) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= NPARAM) return;
-    const int32_t t = t_dev ? *t_dev : t_host;
-    const float gk = g[k];
-    const float a = b1 * m1[k] + (1.f - b1) * gk;
-    const float v = b2 * m2[k] + (1.f - b2) * gk * gk;
-    m1[k] = a;
-    m2[k] = v;
-    const float ah = a / (1.f - powf(b1, (float)t));
-    const float vh = v / (1.f - powf(b2, (float)t));
-    p[k] -= lr * ah / (sqrtf(vh) + eps);
-}
-
-// The train step's Adam counter: one more step.
-__global__ void k_step_next(int32_t *__restrict__ step) {
-    if (threadIdx.x == 0) step[0] += 1;
+    if (a.p) adam_step(a, k, s);
 }
 
 size_t bwd_lds_bytes() { return sizeof(BwdLds); }
 
-int prepare(schulze_ctx *ctx, hipStream_t s, const float *params, NetBf16 &q) {
+int prepare(schulze_ctx *ctx, hipStream_t s, const float *params, NetBf16 &q, int32_t *step = nullptr) {
     const size_t w2b = sizeof(bf16) * NH * NH, w1b = sizeof(bf16) * NH * NF;
     int rc = ws_reserve(ctx, WS_MLP, 2 * w2b + w1b + 256 + 256);
     if (rc != SCHULZE_OK) return rc;
@@ -389,7 +500,7 @@ int prepare(schulze_ctx *ctx, hipStream_t s, const float *params, NetBf16 &q) {
     q.w2 = reinterpret_cast<bf16 *>(b + w2b);
     q.w1t = reinterpret_cast<bf16 *>(b + 2 * w2b);
     q.w3 = reinterpret_cast<bf16 *>(b + 2 * w2b + w1b + 256);
-    SCHULZE_LAUNCH(ctx, K_MLP_PREP, s, k_mlp_prepare<<<dim3(16), dim3(256), 0, s>>>(params, q));
+    SCHULZE_LAUNCH(ctx, K_MLP_PREP, s, k_mlp_prepare<<<dim3(16), dim3(256), 0, s>>>(params, q, step));
     return SCHULZE_OK;
 }
 
@@ -416,21 +527,23 @@ extern "C" int schulze_mlp_forward(schulze_ctx *ctx, void *stream, const float *
 
 namespace {
 
-// Backward of the prepared network (q) into grad; arguments checked.
+// Backward of the prepared network (q) into grad, and its Adam step if
+// adam.p is given; arguments checked.
 int backward(schulze_ctx *ctx, hipStream_t s, const float *params, const NetBf16 &q, const float *feat, int64_t M,
-             const float *dscore, float *grad) {
+             const float *dscore, float *grad, const AdamArgs &adam) {
     int rc;
-    const int G = grid_for(ctx, M);
-    if ((rc = ws_reserve(ctx, WS_MLP_PARTIAL, sizeof(float) * (size_t)G * NPARAM)) != SCHULZE_OK) return rc;
+    const int shares = grid_for(ctx, M);
+    const int G = std::min(shares, ctx->num_cus);
+    if ((rc = ws_reserve(ctx, WS_MLP_PARTIAL, sizeof(float) * (size_t)shares * NPARAM)) != SCHULZE_OK) return rc;
     float *partial = static_cast<float *>(ctx->ws[WS_MLP_PARTIAL]);
     const size_t lds = bwd_lds_bytes();
     if (hipFuncSetAttribute((const void *)k_mlp_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess)
         return SCHULZE_EDEVICE;
     SCHULZE_LAUNCH(ctx, K_MLP_BWD, s,
-                   k_mlp_bwd<<<dim3((unsigned)G), dim3(256), lds, s>>>(params, q, feat, dscore, M, partial));
+                   k_mlp_bwd<<<dim3((unsigned)G), dim3(256), lds, s>>>(params, q, feat, dscore, M, shares, partial));
     SCHULZE_LAUNCH(ctx, K_MLP_BWD, s,
-                   k_mlp_reduce<<<dim3((unsigned)ceil_div(NPARAM, 256)), dim3(256), 0, s>>>(partial, G, grad));
+                   k_mlp_reduce<<<dim3((unsigned)ceil_div(NPARAM, 64)), dim3(64), 0, s>>>(partial, shares, grad, adam));
     return SCHULZE_OK;
 }
 
@@ -444,7 +557,7 @@ extern "C" int schulze_mlp_backward(schulze_ctx *ctx, void *stream, const float 
     NetBf16 q;
     int rc = prepare(ctx, s, params, q);
     if (rc != SCHULZE_OK) return rc;
-    return backward(ctx, s, params, q, feat, M, dscore, grad);
+    return backward(ctx, s, params, q, feat, M, dscore, grad, AdamArgs{});
 }
 
 extern "C" int schulze_mlp_loss(schulze_ctx *ctx, void *stream, const float *score, const int64_t *offsets,
@@ -453,7 +566,7 @@ extern "C" int schulze_mlp_loss(schulze_ctx *ctx, void *stream, const float *sco
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
-                   k_seg_loss<<<dim3((unsigned)ceil_div(E, 4)), dim3(256), 0, s>>>(score, offsets, winner, E, dscore,
+                   k_seg_loss<<<dim3((unsigned)E), dim3(256), 0, s>>>(score, offsets, winner, E, dscore,
                                                                                     loss));
     return SCHULZE_OK;
 }
@@ -464,9 +577,8 @@ extern "C" int schulze_mlp_adam(schulze_ctx *ctx, void *stream, float *params, c
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     SCHULZE_LAUNCH(ctx, K_MLP_ADAM, s,
-                   k_adam<<<dim3((unsigned)ceil_div(NPARAM, 256)), dim3(256), 0, s>>>(params, grad, adam_m, adam_v, lr,
-                                                                                     beta1, beta2, eps, step,
-                                                                                     nullptr));
+                   k_adam<<<dim3((unsigned)ceil_div(NPARAM, 256)), dim3(256), 0, s>>>(
+                       AdamArgs{params, adam_m, adam_v, lr, beta1, beta2, eps, step, nullptr}, grad));
     return SCHULZE_OK;
 }
 
@@ -487,20 +599,16 @@ extern "C" int schulze_mlp_train_step(schulze_ctx *ctx, void *stream, const schu
     float *score = static_cast<float *>(ctx->ws[WS_MLP_TRAIN]);
     float *dscore = reinterpret_cast<float *>(static_cast<char *>(ctx->ws[WS_MLP_TRAIN]) + vec);
     NetBf16 q;
-    if ((rc = prepare(ctx, s, net->params, q)) != SCHULZE_OK) return rc;
+    if ((rc = prepare(ctx, s, net->params, q, net->step)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_MLP_FWD, s,
                    k_mlp_fwd<<<dim3((unsigned)grid_for(ctx, b->M)), dim3(256), 0, s>>>(net->params, q, b->feat, b->M,
                                                                                        score));
     SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
-                   k_seg_loss<<<dim3((unsigned)ceil_div(b->E, 4)), dim3(256), 0, s>>>(score, b->offsets, b->winner,
+                   k_seg_loss<<<dim3((unsigned)b->E), dim3(256), 0, s>>>(score, b->offsets, b->winner,
                                                                                        b->E, dscore, loss));
-    if ((rc = backward(ctx, s, net->params, q, b->feat, b->M, dscore, net->grad)) != SCHULZE_OK) return rc;
-    SCHULZE_LAUNCH(ctx, K_MLP_ADAM, s, k_step_next<<<dim3(1), dim3(64), 0, s>>>(net->step));
-    SCHULZE_LAUNCH(ctx, K_MLP_ADAM, s,
-                   k_adam<<<dim3((unsigned)ceil_div(NPARAM, 256)), dim3(256), 0, s>>>(
-                       net->params, net->grad, net->adam_m, net->adam_v, net->lr, net->beta1, net->beta2, net->eps, 0,
-                       net->step));
-    return SCHULZE_OK;
+    return backward(ctx, s, net->params, q, b->feat, b->M, dscore, net->grad,
+                    AdamArgs{net->params, net->adam_m, net->adam_v, net->lr, net->beta1, net->beta2, net->eps, 0,
+                             net->step});
 }
 
 extern "C" int schulze_mlp_param_count(void) { return NPARAM; }
