@@ -26,8 +26,9 @@
 // wait, so every wait ends however many workgroups are resident.  A bounded
 // spin turns anything else into a device error.
 //
-// The closure of the finish runs on a per-workgroup scratch matrix of uint16
-// (counts of elections with at most 65535 voters) or int32, padded with zero
+// The closure of the finish runs on a per-workgroup scratch matrix of 16-bit
+// elements (counts of elections with at most 65535 voters: half-precision
+// keys, or uint16 where a weight is above KEY_MAX) or int32, padded with zero
 // rows and columns, by one of two schedules chosen per election size:
 // REGISTERS, the plain recurrence with the whole padded matrix (up to
 // 192 x 192 uint16 or 128 x 128 int32) held in registers, or TILED(B), the
@@ -632,6 +633,177 @@ __device__ __attribute__((noinline)) void closure_tiled(E *P_, int32_t mp) {
     }
 }
 
+// The same recurrence for 16-bit elements and B = 64 with the operand tiles
+// streamed into LDS while the product before them runs (two slots each of A
+// and B, refilled only when the next product needs another tile; the next
+// output tile's elements come into registers).  One workgroup closes the
+// whole matrix and only one other shares its CU, so nothing else hides the
+// waits.  One election of m = 448 in every workgroup, uint16 and each
+// product's tiles copied through registers first: 2500 us; half-precision
+// keys and streamed: 1730 (the 205 MB of the matrices, re-read and rewritten
+// each round, at 2.9 TB/s); top-3 of 167 elections of m <= 410: 6550 and
+// 4810 us.
+// A's rows are 128 bytes; the 16-byte pieces of row R sit at piece ^ 2 ((R / 4)
+// % 4), so that the four rows that a wavefront reads together fall on
+// different banks.
+template <typename E>
+struct Stream64 {
+    using L = Lane<E>;
+    using W = typename L::W;
+    static constexpr int TILE = 64 * 64;
+    static constexpr int LDS_ELEMS = 4 * TILE;
+
+    // this thread's element offsets in a tile of pitch mp <= SCHULZE_BATCH_MAX_M
+    // (so that no product of the pitch is left in the loops)
+    struct Offsets {
+        uint32_t a, b;  // first operand piece (A swizzled), + 32 mp: the second
+        uint32_t c;     // first of four output rows
+    };
+    __device__ static Offsets offsets(int32_t mp) {
+        const uint32_t t = threadIdx.x, l = t & 63, row = 8 * (t >> 6) + (l >> 3);
+        const uint32_t tx = t & 15, ty = t >> 4;
+        // (row and row + 32 have the same swizzle)
+        return Offsets{row * mp + 8 * ((l & 7) ^ (((row >> 2) & 3) << 1)), row * mp + 8 * (l & 7),
+                       4 * ty * mp + 4 * tx};
+    }
+    // 64 x 64 elements at src into lds; a wavefront instruction moves 8 rows
+    __device__ static void tile_in(FW_GLOBAL const E *src, uint32_t off, int32_t mp, FW_LDS E *lds) {
+        const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        __builtin_amdgcn_global_load_lds(src + off, lds + w * 512, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(src + 32 * mp + off, lds + (w + 4) * 512, 16, 0, 0);
+    }
+    // the thread's 4 x 4 output elements: one 8-byte access a row
+    __device__ static void out_load(Acc<E, 64> &c, FW_GLOBAL const E *tile, uint32_t off, int32_t mp) {
+        for (int i = 0; i < 4; ++i) {
+            const v2u32 x = *retype<const v2u32>(tile + i * mp + off);
+            const uint32_t x0 = x.x, x1 = x.y;
+            c.c[i][0] = __builtin_bit_cast(W, x0);
+            c.c[i][1] = __builtin_bit_cast(W, x1);
+        }
+    }
+    __device__ static void out_store(const Acc<E, 64> &c, FW_GLOBAL E *tile, uint32_t off, int32_t mp) {
+        for (int i = 0; i < 4; ++i)
+            *retype<v2u32>(tile + i * mp + off) =
+                v2u32{__builtin_bit_cast(uint32_t, c.c[i][0]), __builtin_bit_cast(uint32_t, c.c[i][1])};
+    }
+
+    __device__ static W lo(W x, W y) {
+        if constexpr (__is_same(E, _Float16)) return __builtin_elementwise_minimum(x, y);
+        else return __builtin_elementwise_min(x, y);
+    }
+    __device__ static W hi(W x, W y) {
+        if constexpr (__is_same(E, _Float16)) return __builtin_elementwise_maximum(x, y);
+        else return __builtin_elementwise_max(x, y);
+    }
+
+    struct Step {  // four k: this thread's A rows and B columns
+        v2u32 a[4];
+        W b[4][2];
+    };
+    __device__ static void step_in(Step &s, const FW_LDS E *As, const FW_LDS E *Bs, int k, int tx, int ty) {
+        const int piece = (k >> 3) ^ ((ty & 3) << 1);
+        for (int i = 0; i < 4; ++i) s.a[i] = *(const FW_LDS v2u32 *)(As + (4 * ty + i) * 64 + piece * 8 + (k & 7));
+        for (int q = 0; q < 4; ++q) {
+            const FW_LDS W *b = (const FW_LDS W *)(Bs + (k + q) * 64 + 4 * tx);
+            s.b[q][0] = b[0];
+            s.b[q][1] = b[1];
+        }
+    }
+    __device__ static void step(Acc<E, 64> &c, const Step &s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t word = h ? s.a[i].y : s.a[i].x;
+                const W a0 = L::splat(half_of<E>(word, 0)), a1 = L::splat(half_of<E>(word, 1));
+                W t0[2], t1[2];
+                for (int j = 0; j < 2; ++j) {
+                    t0[j] = lo(a0, s.b[2 * h][j]);
+                    t1[j] = lo(a1, s.b[2 * h + 1][j]);
+                }
+                for (int j = 0; j < 2; ++j) c.c[i][j] = hi(hi(c.c[i][j], t0[j]), t1[j]);
+            }
+    }
+    // c = max(c, A (x) B); the next step's operands are read before this one's products
+    __device__ static void product(Acc<E, 64> &c, const FW_LDS E *As, const FW_LDS E *Bs) {
+        const int t = lane_tid(), tx = t & 15, ty = t >> 4;
+        Step s0, s1;
+        step_in(s0, As, Bs, 0, tx, ty);
+#pragma unroll 1
+        for (int k = 0; k < 64; k += 8) {
+            step_in(s1, As, Bs, k + 4, tx, ty);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC47F);  // lgkmcnt(4): s0 is in (a step is four LDS reads)
+            __builtin_amdgcn_sched_barrier(0);
+            step(c, s0);
+            __builtin_amdgcn_sched_barrier(0);
+            step_in(s0, As, Bs, (k + 8) & 63, tx, ty);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC47F);
+            __builtin_amdgcn_sched_barrier(0);
+            step(c, s1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+};
+
+template <typename E>
+__device__ __attribute__((noinline)) void closure_stream64(E *P_, int32_t mp) {
+    using S = Stream64<E>;
+    FW_GLOBAL E *P = scalar_ptr(gmem(P_));
+    mp = __builtin_amdgcn_readfirstlane(mp);  // (uniform: scalar addresses and loops)
+    FW_LDS E *As = (FW_LDS E *)reinterpret_cast<E *>(batch_smem), *Bs = As + 2 * S::TILE;
+    const int32_t nb = mp / 64;
+    auto tile = [&](int32_t I, int32_t J) { return P + (uint32_t)(64 * (I * mp + J)); };
+    const typename S::Offsets off = S::offsets(mp);
+    // count output tiles at(t) = (I, J), each with A = (I, r) and B = (r, J);
+    // no tile is both an output and the operand of another one
+    auto run = [&](int32_t count, int32_t r, auto at) {
+        if (count == 0) return;
+        int32_t I, J, sa = 0, sb = 0;
+        at(0, I, J);
+        Acc<E, 64> c, next;
+        __syncthreads();  // the tiles are stored and the LDS is free
+        S::tile_in(tile(I, r), off.a, mp, As);
+        S::tile_in(tile(r, J), off.b, mp, Bs);
+        S::out_load(next, tile(I, J), off.c, mp);
+        int32_t I0 = I, J0 = J;
+#pragma unroll 1
+        for (int32_t t = 0; t < count; ++t) {
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's pieces of the operands are in LDS
+            __syncthreads();                // everyone's are, and the other slots are consumed
+            // (the last product is stored here, not before the wait above)
+            if (t > 0) S::out_store(c, tile(I0, J0), off.c, mp);
+            c = next;
+            I0 = I;
+            J0 = J;
+            const FW_LDS E *A = As + sa * S::TILE, *B = Bs + sb * S::TILE;
+            at(min(t + 1, count - 1), I, J);  // (the last one again: nothing to fetch, a load that is not used)
+            if (I != I0) S::tile_in(tile(I, r), off.a, mp, As + (sa ^= 1) * S::TILE);
+            if (J != J0) S::tile_in(tile(r, J), off.b, mp, Bs + (sb ^= 1) * S::TILE);
+            S::out_load(next, tile(I, J), off.c, mp);
+            S::product(c, A, B);
+        }
+        S::out_store(c, tile(I0, J0), off.c, mp);
+    };
+    for (int32_t r = 0; r < nb; ++r) {
+        diag_close<E, 64>(tile(r, r), mp, tile(r, r), mp, nullptr, 0, reinterpret_cast<E *>(batch_smem));
+        const int32_t o = nb - 1;
+        run(2 * o, r, [&](int32_t t, int32_t &I, int32_t &J) {
+            const int32_t u = t < o ? t : t - o, x = u < r ? u : u + 1;
+            I = t < o ? r : x;
+            J = t < o ? x : r;
+        });
+        run(o * o, r, [&](int32_t t, int32_t &I, int32_t &J) {
+            const int32_t i = t / o, j = t - i * o;
+            I = i < r ? i : i + 1;
+            J = j < r ? j : j + 1;
+        });
+        __syncthreads();
+    }
+}
+
+static_assert(Stream64<_Float16>::LDS_ELEMS * 2 <= SMEM_WORDS * 4, "streamed closure LDS");
 static_assert(2 * CHUNK_QUADS * 64 * 4 <= STAGE_WORDS, "two count stage buffers: rows * cols <= 32 / ng * 256 ng words each");
 static_assert(diag_lds_elems<uint16_t, 192>() * 2 <= SMEM_WORDS * 4 && diag_lds_elems<int32_t, 128>() * 4 <= SMEM_WORDS * 4,
               "diagonal closure LDS");
@@ -665,14 +837,32 @@ __device__ void closure_dispatch(E *P, int32_t mp, int32_t variant) {
     } else if (variant == SCHULZE_BATCH_CLOSURE_TILED32) {
         if constexpr (sizeof(E) == 2) closure_tiled<E, 32>(P, mp);
     } else if (variant == SCHULZE_BATCH_CLOSURE_TILED64) {
-        closure_tiled<E, 64>(P, mp);
+        if constexpr (sizeof(E) == 2)
+            closure_stream64<E>(P, mp);
+        else
+            closure_tiled<E, 64>(P, mp);
     } else {
         if constexpr (sizeof(E) == 2) closure_tiled<E, 128>(P, mp);
     }
 }
 
+// An entry of the scratch matrix as the integer it stands for (half-precision
+// keys: of the values up to KEY_MAX; no branch, so that loads before it stay
+// in flight together).
 template <typename E>
-__device__ void finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_t *smem) {
+__device__ __forceinline__ int32_t value_of(E x) {
+    if constexpr (__is_same(E, _Float16)) {
+        const int32_t k = __builtin_bit_cast(int16_t, x), sign = k >> 15;
+        return 31744 + (((k & 0x7FFF) ^ sign) - sign);
+    } else {
+        return (int32_t)x;
+    }
+}
+
+// false (half-precision keys only): a weight is above KEY_MAX and nothing
+// has been written.
+template <typename E>
+__device__ bool finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_t *smem) {
     const int tid = threadIdx.x;
     const int32_t m = el.m, mp = el.mp;
     const int32_t mode = a.mode;
@@ -695,92 +885,96 @@ __device__ void finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_
     int32_t *bb = tb + 64 * 65;                       // [SCHULZE_BATCH_MAX_M]
     int32_t *lvl = bb + SCHULZE_BATCH_MAX_M;          // [SCHULZE_BATCH_MAX_M]
     const int32_t nt = (mp + 63) / 64;
-    auto weights = [&](const int32_t *gone) {
-        bool too_big = false;
-        for (int32_t I = 0; I < nt; ++I) {
-            for (int32_t J = 0; J < nt; ++J) {
-                __syncthreads();
-                // all 32 loads in flight at once: addresses clamped into the matrix
-                // (a conditional load would wait for the ones before it)
-                constexpr int PER = 64 * 64 / BT;
-                int32_t va[PER], vb[PER];
+    // both tiles of a pair (I, J), (J, I) at once: each is read once.  All 32
+    // loads are in flight together, with addresses clamped into the matrix (a
+    // conditional load would wait for the ones before it); entries outside
+    // the m x m matrix are 0
+    auto pair_in = [&](int32_t I, int32_t J, auto at) {
+        __syncthreads();
+        constexpr int PER = 64 * 64 / BT;
+        int32_t va[PER], vb[PER];
 #pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    const int q = tid + k * BT;
-                    const int r = q >> 6, c = q & 63;
-                    const int32_t i = min(I * 64 + r, m - 1), j = min(J * 64 + c, m - 1);
-                    const int32_t i2 = min(J * 64 + r, m - 1), j2 = min(I * 64 + c, m - 1);
-                    va[k] = D[(int64_t)i * m + j];
-                    vb[k] = D[(int64_t)i2 * m + j2];
-                }
+        for (int k = 0; k < PER; ++k) {
+            const int q = tid + k * BT, r = q >> 6, c = q & 63;
+            va[k] = at(min(I * 64 + r, m - 1), min(J * 64 + c, m - 1));
+            vb[k] = at(min(J * 64 + r, m - 1), min(I * 64 + c, m - 1));
+        }
 #pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    const int q = tid + k * BT;
-                    const int r = q >> 6, c = q & 63;
-                    const bool in_a = I * 64 + r < m && J * 64 + c < m;
-                    const bool in_b = J * 64 + r < m && I * 64 + c < m;
-                    ta[r * 65 + c] = in_a ? va[k] : 0;
-                    tb[r * 65 + c] = in_b ? vb[k] : 0;
-                }
-                __syncthreads();
-                for (int q = tid; q < 64 * 64; q += BT) {
-                    const int r = q >> 6, c = q & 63;
-                    const int32_t i = I * 64 + r, j = J * 64 + c;
-                    if (i >= mp || j >= mp) continue;
-                    const int32_t x = ta[r * 65 + c], y = tb[c * 65 + r];  // d[i][j], d[j][i]
-                    int32_t w = 0;
-                    if (i != j && i < m && j < m && x > y) w = mode == SCHULZE_MARGIN ? x - y : x;
-                    if (gone && w && (gone[i] >= 0 || gone[j] >= 0)) w = 0;
-                    if constexpr (sizeof(E) == 2) {
-                        if ((uint32_t)w > 65535u) {  // counts above the bound the plan assumed
-                            too_big = true;
-                            w = 65535;
-                        }
+        for (int k = 0; k < PER; ++k) {
+            const int q = tid + k * BT, r = q >> 6, c = q & 63;
+            ta[r * 65 + c] = I * 64 + r < m && J * 64 + c < m ? va[k] : 0;
+            tb[r * 65 + c] = J * 64 + r < m && I * 64 + c < m ? vb[k] : 0;
+        }
+        __syncthreads();
+    };
+    // false: a weight is above KEY_MAX (half-precision keys)
+    auto weights = [&](const int32_t *gone) -> bool {
+        bool too_big = false, wide = false;
+        auto out = [&](int32_t I, int32_t J, const int32_t *fw, const int32_t *bw) {
+            for (int q = tid; q < 64 * 64; q += BT) {
+                const int r = q >> 6, c = q & 63;
+                const int32_t i = I * 64 + r, j = J * 64 + c;
+                if (i >= mp || j >= mp) continue;
+                const int32_t x = fw[r * 65 + c], y = bw[c * 65 + r];  // d[i][j], d[j][i]
+                int32_t w = 0;
+                if (i != j && x > y) w = mode == SCHULZE_MARGIN ? x - y : x;
+                if (gone && w && (gone[i] >= 0 || gone[j] >= 0)) w = 0;
+                if constexpr (sizeof(E) == 2) {
+                    if ((uint32_t)w > 65535u) {  // counts above the bound the plan assumed
+                        too_big = true;
+                        w = 65535;
                     }
+                }
+                if constexpr (__is_same(E, _Float16)) {
+                    wide = wide || w > (int32_t)KEY_MAX;
+                    P[(int64_t)i * mp + j] = __builtin_bit_cast(E, key_of((uint32_t)w));
+                } else {
                     P[(int64_t)i * mp + j] = (E)w;
                 }
             }
+        };
+        for (int32_t I = 0; I < nt; ++I) {
+            for (int32_t J = I; J < nt; ++J) {
+                pair_in(I, J, [&](int32_t i, int32_t j) { return D[(int64_t)i * m + j]; });
+                out(I, J, ta, tb);
+                if (I != J) out(J, I, tb, ta);
+            }
+        }
+        if constexpr (__is_same(E, _Float16)) {
+            if (__syncthreads_or(wide)) return false;
         }
         if (too_big) set_device_error(a.err, SCHULZE_ERANGE);
         __syncthreads();
+        return true;
     };
     // bb[x] = #{y : P[y][x] > P[x][y]}
     auto beaten = [&]() {
         for (int32_t x = tid; x < m; x += BT) bb[x] = 0;
         const int32_t mt = (m + 63) / 64;
-        for (int32_t I = 0; I < mt; ++I) {      // block of x
-            for (int32_t J = 0; J < mt; ++J) {  // block of y
-                __syncthreads();
-                constexpr int PER = 64 * 64 / BT;
-                int32_t va[PER], vb[PER];
+        for (int32_t I = 0; I < mt; ++I) {
+            for (int32_t J = I; J < mt; ++J) {
+                pair_in(I, J, [&](int32_t i, int32_t j) { return value_of<E>(P[(int64_t)i * mp + j]); });
+                // lane c of wavefront g: candidate y = (J, c) against x = (I, r) for r = g, g + 4, ..
+                const int32_t c = tid & 63, g = tid >> 6;
+                const int32_t y = J * 64 + c;
+                int32_t cnt = 0, other = 0;  // (other: lane q holds the count of x = (I, g + 4 q))
 #pragma unroll
-                for (int k = 0; k < PER; ++k) {  // clamped, unconditional loads
-                    const int q = tid + k * BT;
-                    const int r = q >> 6, c = q & 63;
-                    const int32_t y = min(J * 64 + r, m - 1), x = min(I * 64 + c, m - 1);    // ta[y][x] = P[y][x]
-                    const int32_t x2 = min(I * 64 + r, m - 1), y2 = min(J * 64 + c, m - 1);  // tb[x][y] = P[x][y]
-                    va[k] = (int32_t)P[(int64_t)y * mp + x];
-                    vb[k] = (int32_t)P[(int64_t)x2 * mp + y2];
+                for (int q = 0; q < 16; ++q) {
+                    const int32_t r = g + 4 * q;
+                    const int32_t pxy = ta[r * 65 + c], pyx = tb[c * 65 + r];
+                    cnt += pxy > pyx ? 1 : 0;
+                    const int32_t beats = (int32_t)__popcll(__ballot(pyx > pxy));
+                    other = c == q ? beats : other;
                 }
-#pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    const int q = tid + k * BT;
-                    const int r = q >> 6, c = q & 63;
-                    ta[r * 65 + c] = (J * 64 + r < m && I * 64 + c < m) ? va[k] : 0;
-                    tb[r * 65 + c] = (I * 64 + r < m && J * 64 + c < m) ? vb[k] : 0;
-                }
-                __syncthreads();
-                const int32_t xl = tid & 63, g = tid >> 6;
-                const int32_t x = I * 64 + xl;
-                int32_t cnt = 0;
-                for (int32_t yl = g; yl < 64; yl += 4) cnt += ta[yl * 65 + xl] > tb[xl * 65 + yl] ? 1 : 0;
-                if (x < m && cnt) atomicAdd(&bb[x], cnt);
+                // (on a diagonal block the lanes' counts see every pair from both sides)
+                if (I != J && c < 16 && other) atomicAdd(&bb[I * 64 + g + 4 * c], other);
+                if (y < m && cnt) atomicAdd(&bb[y], cnt);
             }
         }
         __syncthreads();
     };
 
-    weights(nullptr);
+    if (!weights(nullptr)) return false;
     closure_dispatch<E>(Pv, mp, el.variant);
     __syncthreads();
     beaten();
@@ -815,7 +1009,7 @@ __device__ void finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int h = 0; h < H; ++h)
-                    v[r][h] = (int32_t)P[(int64_t)min(x0 + r, m - 1) * mp + min(tid + h * BT, m - 1)];
+                    v[r][h] = value_of<E>(P[(int64_t)min(x0 + r, m - 1) * mp + min(tid + h * BT, m - 1)]);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -838,7 +1032,7 @@ __device__ void finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_
         __syncthreads();
         // every nonempty set of candidates has a winner, so each level ranks at least one
         for (int32_t level = 1; level < m && sh_ranked < a.topk && sh_ranked < m; ++level) {
-            weights(lvl);
+            weights(lvl);  // (some of the first level's weights)
             closure_dispatch<E>(Pv, mp, el.variant);
             __syncthreads();
             beaten();
@@ -859,14 +1053,16 @@ __device__ void finish_t(const BatchArgs &a, const BElec &el, int32_t e, uint32_
         for (int32_t x = tid; x < m; x += BT) lv[el.vec_off + x] = lvl[x];
     }
     __syncthreads();
+    return true;
 }
 
 __device__ __attribute__((noinline)) void finish(const BatchArgs &a, const BElec &el_in, int32_t e) {
     const BElec el = el_in;  // local copy (see scan_item)
-    if (el.flags & EF_VAL16)
-        finish_t<uint16_t>(a, el, e, batch_smem);
-    else
+    // 16-bit values: half-precision keys, unless a weight is above KEY_MAX
+    if (!(el.flags & EF_VAL16))
         finish_t<int32_t>(a, el, e, batch_smem);
+    else if (!finish_t<_Float16>(a, el, e, batch_smem))
+        finish_t<uint16_t>(a, el, e, batch_smem);
 }
 
 __global__ __launch_bounds__(BT, 2) void k_batch(BatchArgs a) {
@@ -890,7 +1086,7 @@ __global__ __launch_bounds__(BT, 2) void k_batch(BatchArgs a) {
             sh_item = t;
         }
         __syncthreads();
-        const int32_t t = sh_item;
+        const int32_t t = __builtin_amdgcn_readfirstlane(sh_item);  // uniform: the item and its election load as scalars
         if (t >= a.n_items) return;
         const BItem it = a.items[t];
         const BElec el = a.elec[it.e];
@@ -959,9 +1155,12 @@ struct schulze_batch {
 
 namespace {
 
+// REGISTERS while its one barrier per step costs less than the tiles' rounds.
+// One election per workgroup, us, REGISTERS / TILED64: 16 bits m = 96:
+// 84 / 100, m = 128: 212 / 99; int32 m = 96: 84 / 126, m = 128: 121 / 126
+// (larger matrices do not fit its registers).
 int default_variant(int bits, int32_t m) {
-    (void)bits;
-    return m <= 128 ? SCHULZE_BATCH_CLOSURE_REGISTERS : SCHULZE_BATCH_CLOSURE_TILED64;
+    return m <= (bits == 16 ? 96 : 128) ? SCHULZE_BATCH_CLOSURE_REGISTERS : SCHULZE_BATCH_CLOSURE_TILED64;
 }
 
 bool variant_ok(int bits, int32_t m, int variant) {
