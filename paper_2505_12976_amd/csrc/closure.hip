@@ -60,15 +60,15 @@ __device__ inline bool gated_off(const int32_t *gate, int32_t want) { return gat
 // set when one of them is above KEY_MAX.
 template <typename E>
 __global__ __launch_bounds__(256) void k_weights(const E *__restrict__ d, int64_t ldd, int32_t m, int mode,
-                                                 E *__restrict__ P, int64_t ld, int32_t mp, int dvec,
+                                                 E *__restrict__ P, int64_t ld, int32_t mp,
                                                  int32_t *wide = nullptr, const int32_t *gate = nullptr,
                                                  int32_t want = 0) {
     __shared__ E a[64][65];  // a[r][c] = d[I0 + r][J0 + c]
     __shared__ E b[64][65];  // b[r][c] = d[J0 + r][I0 + c]
     if (blockIdx.y > blockIdx.x || gated_off(gate, want)) return;
     const int32_t I0 = blockIdx.y * 64, J0 = blockIdx.x * 64;
-    tio::load<E>(a, d, ldd, I0, J0, m, m, dvec != 0);
-    tio::load<E>(b, d, ldd, J0, I0, m, m, dvec != 0);
+    tio::load<E>(a, d, ldd, I0, J0, m, m);
+    tio::load<E>(b, d, ldd, J0, I0, m, m);
     __syncthreads();
     bool above = false;
     auto weight = [&](E x, E y, bool diag) -> E {  // edge weight given d[i][j] = x, d[j][i] = y
@@ -82,13 +82,15 @@ __global__ __launch_bounds__(256) void k_weights(const E *__restrict__ d, int64_
         return w;
     };
     // the workspace matrix is 16-byte aligned with a pitch that is a multiple of 64
-    tio::store<E>(P, ld, I0, J0, mp, mp, true, [&](int r, int c) { return weight(a[r][c], b[c][r], I0 + r == J0 + c); });
+    tio::store<E>(P, ld, I0, J0, mp, mp, [&](int r, int c) { return weight(a[r][c], b[c][r], I0 + r == J0 + c); });
     if (I0 != J0)  // the mirrored tile (J, I)
-        tio::store<E>(P, ld, J0, I0, mp, mp, true, [&](int r, int c) { return weight(b[r][c], a[c][r], false); });
+        tio::store<E>(P, ld, J0, I0, mp, mp, [&](int r, int c) { return weight(b[r][c], a[c][r], false); });
     if (above) *wide = 1;
 }
 
-// p[i][j] = P[i][j] for i != j, 0 on the diagonal; one workgroup per row.
+// p[i][j] = P[i][j] for i != j, 0 on the diagonal; one workgroup per row, 16
+// bytes per access whatever p's alignment (m = 14187, uint16: 132 us; an
+// access per element, 276 to 302).
 // With `wide` (uint16 only) P holds half-precision keys unless *wide is set.
 template <typename E>
 __global__ __launch_bounds__(256) void k_fw_store(const E *__restrict__ P, int64_t ld, int32_t m, E *__restrict__ p,
@@ -98,13 +100,26 @@ __global__ __launch_bounds__(256) void k_fw_store(const E *__restrict__ P, int64
     const int32_t i = blockIdx.x;
     const E *src = P + (int64_t)i * ld;
     E *dst = p + (int64_t)i * ldp;
-    if constexpr (sizeof(E) == 2) {
-        if (wide && !*wide) {
-            for (int32_t j = threadIdx.x; j < m; j += 256) dst[j] = i == j ? (E)0 : key_value(src[j]);
-            return;
+    const bool keys = sizeof(E) == 2 && wide && !*wide;
+    constexpr int V = 16 / (int)sizeof(E), FLY = 2;
+    for (int32_t jb = threadIdx.x * V; jb < m; jb += 256 * V * FLY) {
+        uint4 x[FLY];  // (rows of P hold ld >= m elements, a multiple of 64)
+        for (int u = 0; u < FLY; ++u) x[u] = tio::load16<E>(src + min(jb + 256 * V * u, (int32_t)ld - V));
+        for (int u = 0; u < FLY; ++u) {
+            const int32_t j0 = jb + 256 * V * u;
+            if (j0 >= m) break;
+            E e[V];
+            tio::unpack<E>(x[u], e);
+            for (int c = 0; c < V; ++c) {
+                if (keys) e[c] = (E)key_value((uint32_t)e[c]);
+                if (j0 + c == i) e[c] = (E)0;
+            }
+            if (j0 + V <= m)
+                tio::store16<E>(dst + j0, tio::pack<E>(e));
+            else
+                for (int c = 0; c < V && j0 + c < m; ++c) dst[j0 + c] = e[c];
         }
     }
-    for (int32_t j = threadIdx.x; j < m; j += 256) dst[j] = i == j ? (E)0 : src[j];
 }
 
 // A matrix of keys back to values, and *wide set (only when the persistent
@@ -655,8 +670,7 @@ int run_closure(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_
         if (sizeof(E) == 2) wide = static_cast<int32_t *>(ctx->ws[WS_FLAGS]) + (flag_words(nb) - 1);
     }
     dim3 wgrid((unsigned)ceil_div(mp, 64), (unsigned)ceil_div(mp, 64));
-    SCHULZE_LAUNCH(ctx, K_WEIGHTS, s, k_weights<E><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp,
-                                                                          tio::vec_ok<E>(d, ldd) ? 1 : 0, wide));
+    SCHULZE_LAUNCH(ctx, K_WEIGHTS, s, k_weights<E><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp, wide));
     if ((rc = close_padded<E, B>(ctx, s, P, ld, nb, wide)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FW_STORE, s,
                    k_fw_store<E><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, wide, nullptr, 0));
@@ -797,7 +811,6 @@ __device__ inline void pair_of(int64_t q, int32_t &I, int32_t &J) {
 // tiles are loaded into registers while the current pair is marked (VEC:
 // 16-byte loads, d 16-byte aligned with m a multiple of 4; what they read
 // past m is ignored).
-template <bool VEC>
 __global__ __launch_bounds__(256) void k_weights_mark(const int32_t *__restrict__ d, int64_t ldd, int32_t m,
                                                       int mode, uint32_t *__restrict__ bitmap,
                                                       int32_t *__restrict__ flags) {
@@ -826,8 +839,8 @@ __global__ __launch_bounds__(256) void k_weights_mark(const int32_t *__restrict_
     auto fetch_pair = [&](int64_t q) {
         int32_t I, J;
         pair_of(q, I, J);
-        tio::fetch<int32_t, VEC>(ga, d, ldd, I * 64, J * 64, m, m);
-        tio::fetch<int32_t, VEC>(gb, d, ldd, J * 64, I * 64, m, m);
+        tio::fetch<int32_t>(ga, d, ldd, I * 64, J * 64, m, m);
+        tio::fetch<int32_t>(gb, d, ldd, J * 64, I * 64, m, m);
     };
     if (blockIdx.x < npairs) fetch_pair(blockIdx.x);
     for (int64_t q = blockIdx.x; q < npairs; q += gridDim.x) {
@@ -858,7 +871,7 @@ __global__ __launch_bounds__(256) void k_weights_mark(const int32_t *__restrict_
 // (zero past m); the table lookups of a thread's 32 elements are issued
 // together before the ranks are formed.
 __global__ __launch_bounds__(256) void k_rank_apply_d(const int32_t *__restrict__ d, int64_t ldd, int32_t m,
-                                                      int mode, int dvec, const uint32_t *__restrict__ bitmap,
+                                                      int mode, const uint32_t *__restrict__ bitmap,
                                                       const uint32_t *__restrict__ word_rank,
                                                       uint16_t *__restrict__ P16, int64_t ld, int32_t mp, int keys,
                                                       const int32_t *gate) {
@@ -866,8 +879,8 @@ __global__ __launch_bounds__(256) void k_rank_apply_d(const int32_t *__restrict_
     __shared__ int32_t b[64][65];
     if (blockIdx.y > blockIdx.x || gated_off(gate, 1)) return;
     const int32_t I0 = blockIdx.y * 64, J0 = blockIdx.x * 64;
-    tio::load<int32_t>(a, d, ldd, I0, J0, m, m, dvec != 0);
-    tio::load<int32_t>(b, d, ldd, J0, I0, m, m, dvec != 0);
+    tio::load<int32_t>(a, d, ldd, I0, J0, m, m);
+    tio::load<int32_t>(b, d, ldd, J0, I0, m, m);
     __syncthreads();
     // thread: rows r = t / 8 and r + 32, eight columns from c8 = 8 (t % 8); both tiles
     const int r0 = threadIdx.x >> 3, c8 = (threadIdx.x & 7) * 8;
@@ -919,7 +932,6 @@ __global__ __launch_bounds__(256) void k_rank_store(const uint16_t *__restrict__
     // table lookup unconditional (P16 rows hold ld >= m columns, a multiple
     // of 64; rank 0 looks up value_of[0] = 0), the stores under the bounds
     constexpr int STORE_STEP = 4;
-    const bool vec = (ldp % 4) == 0 && (reinterpret_cast<uintptr_t>(p) % 16) == 0;
     for (int32_t jb = threadIdx.x * 4; jb < m; jb += 1024 * STORE_STEP) {
         ushort4 r[STORE_STEP];
         for (int u = 0; u < STORE_STEP; ++u)
@@ -939,8 +951,8 @@ __global__ __launch_bounds__(256) void k_rank_store(const uint16_t *__restrict__
             if (j0 >= m) break;
             for (int e = 0; e < 4; ++e)
                 if (j0 + e == i) v[u][e] = 0;
-            if (vec && j0 + 4 <= m)
-                *reinterpret_cast<int4 *>(row + j0) = make_int4(v[u][0], v[u][1], v[u][2], v[u][3]);
+            if (j0 + 4 <= m)
+                tio::store16<int32_t>(row + j0, tio::pack<int32_t>(v[u]));
             else
                 for (int e = 0; e < 4 && j0 + e < m; ++e) row[j0 + e] = v[u][e];
         }
@@ -973,7 +985,6 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
                                          std::max(flag_words(mp / BI), flag_words(mp / BU)))) != SCHULZE_OK)
         return rc;
     int32_t *P = static_cast<int32_t *>(ctx->ws[WS_CLOSURE]);
-    const int dvec = tio::vec_ok<int32_t>(d, ldd) ? 1 : 0;
 
     char *q = static_cast<char *>(ctx->ws[WS_RANKED]);
     uint32_t *bitmap = reinterpret_cast<uint32_t *>(q);
@@ -989,12 +1000,8 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
     // written here): four marking workgroups per CU, each merging its LDS
     // bitmap once.
     const unsigned mgrid = (unsigned)std::min<int64_t>(ceil_div((int64_t)m * m, 8192), (int64_t)ctx->num_cus * 4);
-    if (dvec && m % 4 == 0)
-        SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
-                       k_weights_mark<true><<<dim3(mgrid), dim3(256), 0, s>>>(d, ldd, m, mode, bitmap, flags));
-    else
-        SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
-                       k_weights_mark<false><<<dim3(mgrid), dim3(256), 0, s>>>(d, ldd, m, mode, bitmap, flags));
+    SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
+                   k_weights_mark<<<dim3(mgrid), dim3(256), 0, s>>>(d, ldd, m, mode, bitmap, flags));
     SCHULZE_LAUNCH(ctx, K_RANK, s, k_rank_blocks<<<dim3(RANK_BLOCKS), dim3(256), 0, s>>>(bitmap, block_off));
     SCHULZE_LAUNCH(ctx, K_RANK, s, k_rank_top<<<dim3(1), dim3(256), 0, s>>>(block_off, flags));
     // flags[2] decides on the device; both variants are queued, each gated
@@ -1003,7 +1010,7 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
     const dim3 wgrid((unsigned)ceil_div(mp, 64), (unsigned)ceil_div(mp, 64));
     // values too wide or too many: the weights, then the int32 closure on them
     SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
-                   k_weights<int32_t><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp, dvec, nullptr, ranked, 0));
+                   k_weights<int32_t><<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, P, ld, mp, nullptr, ranked, 0));
     if ((rc = close_padded<int32_t, BI>(ctx, s, P, ld, mp / BI, nullptr, ranked, 0)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FW_STORE, s,
                    k_fw_store<int32_t><<<dim3((unsigned)m), dim3(256), 0, s>>>(P, ld, m, p, ldp, nullptr, ranked,
@@ -1013,7 +1020,7 @@ int run_closure_ranked(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_
                    k_rank_words<<<dim3(RANK_BLOCKS), dim3(256), 0, s>>>(bitmap, block_off, word_rank, value_of,
                                                                         ranked));
     SCHULZE_LAUNCH(ctx, K_RANK, s,
-                   k_rank_apply_d<<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, dvec, bitmap, word_rank, P16, ld, mp,
+                   k_rank_apply_d<<<wgrid, dim3(256), 0, s>>>(d, ldd, m, mode, bitmap, word_rank, P16, ld, mp,
                                                               persist ? 1 : 0, ranked));
     if ((rc = close_padded<uint16_t, BU>(ctx, s, P16, ld, mp / BU, wide, ranked, 1)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_RANK, s,

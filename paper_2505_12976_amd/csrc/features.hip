@@ -182,8 +182,8 @@ __device__ __forceinline__ void tile_rows_edge(const E (*A)[tio::PITCH], const E
 // columns of super-block s: rows of I over J and rows of J over I, each
 // (row, slot) written by exactly one workgroup (on the diagonal
 // super-block, row tile i adds what the tiles before it gave it as
-// mirrored rows).  VD: d is read in 16-byte vectors (see tio::fetch).
-template <typename E, bool MARGIN, int SBV, bool VD>
+// mirrored rows).
+template <typename E, bool MARGIN, int SBV>
 __global__ __launch_bounds__(256) void k_feature_rows(const E *__restrict__ d, int64_t ldd, int32_t m, RawStats part) {
     __shared__ E a[tio::T][tio::PITCH];  // a[r][c] = d[X0 + r][Y0 + c]
     __shared__ E b[tio::T][tio::PITCH];  // b[r][c] = d[Y0 + r][X0 + c]
@@ -214,8 +214,8 @@ __global__ __launch_bounds__(256) void k_feature_rows(const E *__restrict__ d, i
     tio::Regs<E> ga, gb;
     auto fetch_pair = [&](int32_t i, int32_t j) {
         const int32_t X0 = (I * SBV + i) * 64, Y0 = (J * SBV + j) * 64;
-        tio::fetch<E, VD>(ga, d, ldd, X0, Y0, m, m);
-        if (X0 != Y0) tio::fetch<E, VD>(gb, d, ldd, Y0, X0, m, m);
+        tio::fetch<E>(ga, d, ldd, X0, Y0, m, m);
+        if (X0 != Y0) tio::fetch<E>(gb, d, ldd, Y0, X0, m, m);
     };
     int32_t i = 0, j = 0;
     if (!valid(i, j)) i = SBV;
@@ -397,32 +397,37 @@ RawStats carve(char *p, size_t n, size_t *bytes) {
     return st;
 }
 
-template <typename E, int SBV, bool VD>
+template <typename E, int SBV>
 int launch_rows(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, RawStats part,
                 int32_t S) {
     const dim3 grid((unsigned)S, (unsigned)S);
     if (mode == SCHULZE_MARGIN)
         SCHULZE_LAUNCH(ctx, K_FEATURE_ROWS, s,
-                       k_feature_rows<E, true, SBV, VD><<<grid, dim3(256), 0, s>>>(d, ldd, m, part));
+                       k_feature_rows<E, true, SBV><<<grid, dim3(256), 0, s>>>(d, ldd, m, part));
     else
         SCHULZE_LAUNCH(ctx, K_FEATURE_ROWS, s,
-                       k_feature_rows<E, false, SBV, VD><<<grid, dim3(256), 0, s>>>(d, ldd, m, part));
+                       k_feature_rows<E, false, SBV><<<grid, dim3(256), 0, s>>>(d, ldd, m, part));
     return SCHULZE_OK;
 }
 
 // Tiles per super-block side: more tiles mean fewer partial slots to write
-// and reduce, fewer mean less LDS per workgroup (more workgroups per CU).
-template <typename E>
-constexpr int feature_sb() {
-    return 4;
+// and reduce, fewer mean more workgroups.  The largest of 4, 2 and 1 that
+// leaves two workgroups per CU, else 1: at m = 1501 (uint16) 21 workgroups of
+// up to 16 tile pairs took 113 us, 300 of one 9.5.
+int feature_sb(const schulze_ctx *ctx, int32_t m) {
+    for (int sb = 4; sb > 1; sb /= 2) {
+        const int64_t S = ceil_div(ceil_div(m, 64), sb);
+        if (S * (S + 1) / 2 >= 2 * (int64_t)ctx->num_cus) return sb;
+    }
+    return 1;
 }
 
 template <typename E>
 int run_features(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, float n_voters,
                  float *feat) {
-    constexpr int SBV = feature_sb<E>();
+    const int sb = feature_sb(ctx, m);
     // S super-blocks per side: a partial slot per super-block column
-    const int32_t S = (int32_t)ceil_div(ceil_div(m, 64), SBV);
+    const int32_t S = (int32_t)ceil_div(ceil_div(m, 64), sb);
     size_t fin_bytes = 0, part_bytes = 0;
     (void)carve(nullptr, (size_t)m, &fin_bytes);
     (void)carve(nullptr, (size_t)m * S, &part_bytes);
@@ -433,9 +438,9 @@ int run_features(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32
     RawStats part = carve(p + fin_bytes, (size_t)m * S, &part_bytes);
     uint32_t *mx = reinterpret_cast<uint32_t *>(p + fin_bytes + part_bytes);
     if ((rc = fill_u32(ctx, s, mx, 4, 0u)) != SCHULZE_OK) return rc;
-    const bool vd = tio::vec_ok<E>(d, ldd) && m % (16 / (int)sizeof(E)) == 0;
-    rc = vd ? launch_rows<E, SBV, true>(ctx, s, d, ldd, m, mode, part, S)
-            : launch_rows<E, SBV, false>(ctx, s, d, ldd, m, mode, part, S);
+    rc = sb == 4   ? launch_rows<E, 4>(ctx, s, d, ldd, m, mode, part, S)
+         : sb == 2 ? launch_rows<E, 2>(ctx, s, d, ldd, m, mode, part, S)
+                   : launch_rows<E, 1>(ctx, s, d, ldd, m, mode, part, S);
     if (rc != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FEATURES, s,
                    k_feature_reduce<<<dim3((unsigned)ceil_div(m, 64)), dim3(256), 0, s>>>(m, S, part, st));

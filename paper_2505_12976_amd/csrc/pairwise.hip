@@ -28,6 +28,7 @@
 // completes and converts to the output dtype.
 #include "internal.h"
 #include "planes.h"
+#include "tile_io.h"
 
 namespace {
 
@@ -1147,17 +1148,17 @@ struct OccArgs {
     int32_t *err;
 };
 
-// Eight consecutive values of a row of d: 16-byte stores when the row is
-// aligned for them and all eight columns exist, else one at a time.
+// Eight consecutive values of a row of d: 16-byte stores (at any alignment)
+// when all eight columns exist, else one at a time.
 template <typename T>
-__device__ inline void store8(T *__restrict__ drow, int32_t y, int32_t m, bool vec, const uint32_t (&v)[8]) {
-    if (vec && y + 8 <= m) {
+__device__ inline void store8(T *__restrict__ drow, int32_t y, int32_t m, const uint32_t (&v)[8]) {
+    if (y + 8 <= m) {
         if constexpr (sizeof(T) == 4) {
-            reinterpret_cast<uint4 *>(drow + y)[0] = make_uint4(v[0], v[1], v[2], v[3]);
-            reinterpret_cast<uint4 *>(drow + y)[1] = make_uint4(v[4], v[5], v[6], v[7]);
+            tio::store16<T>(drow + y, make_uint4(v[0], v[1], v[2], v[3]));
+            tio::store16<T>(drow + y + 4, make_uint4(v[4], v[5], v[6], v[7]));
         } else {
-            reinterpret_cast<uint4 *>(drow + y)[0] =
-                make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+            tio::store16<T>(drow + y, make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16),
+                                                 v[6] | (v[7] << 16)));
         }
         return;
     }
@@ -1352,7 +1353,7 @@ __global__ __launch_bounds__(1024) void k_occ_scan(OccArgs a) {
 // counts to its partial row and adds its part of R to rsum[r].
 template <int MAXM, bool PACKED, typename T, int WMAX, bool PIECES, bool I32>
 __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict__ d, int64_t ldd, uint32_t limit,
-                                                        uint8_t *__restrict__ over_flag, int acc_zero, int dvec) {
+                                                        uint8_t *__restrict__ over_flag, int acc_zero) {
     constexpr int WORDS = PACKED ? MAXM / 2 : MAXM;
     constexpr int B = WMAX <= 16 ? 2 : 1;  // occurrences per batch
     __shared__ __attribute__((aligned(16))) uint32_t row[WORDS];
@@ -1523,7 +1524,7 @@ __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict
                     v[e] = limit;
                 }
             }
-            store8<T>(drow, y, m, dvec != 0, v);
+            store8<T>(drow, y, m, v);
         }
         // reported by the finish, after every ballot error of this launch
         if (over) over_flag[0] = 1;
@@ -1546,7 +1547,7 @@ __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict
 // flight.  Also reports an overflow found by the accumulation.
 template <typename T, bool PACKED>
 __global__ __launch_bounds__(256) void k_occ_finish(OccArgs a, T *__restrict__ d, int64_t ldd, uint32_t limit,
-                                                    const uint8_t *__restrict__ over_flag, int acc_zero, int dvec) {
+                                                    const uint8_t *__restrict__ over_flag, int acc_zero) {
     static_assert(OCC_FIN_COLS == 8 * 256, "a thread takes eight columns");
     if (a.meta.ctr[2] != MODE_SPARSE) return;
     const int32_t m = a.m;
@@ -1606,7 +1607,7 @@ __global__ __launch_bounds__(256) void k_occ_finish(OccArgs a, T *__restrict__ d
                 v[e] = limit;
             }
         }
-        store8<T>(d + (int64_t)r * ldd, y, m, dvec != 0, v);
+        store8<T>(d + (int64_t)r * ldd, y, m, v);
     }
     if (over) set_device_error(a.err, SCHULZE_ERANGE);
 }
@@ -1765,42 +1766,42 @@ int occ_bucket(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 g) {
 // m; rows read as 32-bit words when the layout allows (WMAX words at most).
 template <typename T, int MAXM, bool PACKED>
 int occ_accumulate_m(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid, T *d, int64_t ldd,
-                     uint32_t limit, uint8_t *over_flag, int az, int dvec) {
+                     uint32_t limit, uint8_t *over_flag, int az) {
     const dim3 b(256);
     if constexpr (PACKED) {
         if (oa.row_vec == 2 && oa.L <= 32) {
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                            (k_occ_accumulate<MAXM, PACKED, T, 16, true, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                          az, dvec)));
+                                                                                          az)));
             return SCHULZE_OK;
         }
         if (oa.row_vec == 2 && oa.L <= 64) {
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                            (k_occ_accumulate<MAXM, PACKED, T, 32, true, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                          az, dvec)));
+                                                                                          az)));
             return SCHULZE_OK;
         }
         if (oa.row_vec && oa.L <= 32) {
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                            (k_occ_accumulate<MAXM, PACKED, T, 16, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                           az, dvec)));
+                                                                                           az)));
             return SCHULZE_OK;
         }
         if (oa.row_vec && oa.L <= 64) {
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                            (k_occ_accumulate<MAXM, PACKED, T, 32, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                           az, dvec)));
+                                                                                           az)));
             return SCHULZE_OK;
         }
     }
     if (oa.dtype32)
         SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                        (k_occ_accumulate<MAXM, PACKED, T, 0, false, true><<<grid, b, 0, s>>>(oa, d, ldd, limit,
-                                                                                             over_flag, az, dvec)));
+                                                                                             over_flag, az)));
     else
         SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
                        (k_occ_accumulate<MAXM, PACKED, T, 0, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit,
-                                                                                              over_flag, az, dvec)));
+                                                                                              over_flag, az)));
     return SCHULZE_OK;
 }
 
@@ -1809,24 +1810,23 @@ int occ_accumulate(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid
                    int64_t ldd, uint32_t limit, uint8_t *over_flag, bool acc_zero) {
     const int az = acc_zero ? 1 : 0;
     // rows of d 16-byte aligned: eight columns per 16-byte store (uint16) or two (int32)
-    const int dvec = reinterpret_cast<uintptr_t>(d) % 16 == 0 && (ldd * (int64_t)sizeof(T)) % 16 == 0;
     int rc;
     if (!weighted && m <= OCC_MAX_M / 2)
-        rc = occ_accumulate_m<T, OCC_MAX_M / 2, true>(ctx, s, oa, grid, d, ldd, limit, over_flag, az, dvec);
+        rc = occ_accumulate_m<T, OCC_MAX_M / 2, true>(ctx, s, oa, grid, d, ldd, limit, over_flag, az);
     else if (!weighted)
-        rc = occ_accumulate_m<T, OCC_MAX_M, true>(ctx, s, oa, grid, d, ldd, limit, over_flag, az, dvec);
+        rc = occ_accumulate_m<T, OCC_MAX_M, true>(ctx, s, oa, grid, d, ldd, limit, over_flag, az);
     else if (m <= OCC_MAX_M / 2)
-        rc = occ_accumulate_m<T, OCC_MAX_M / 2, false>(ctx, s, oa, grid, d, ldd, limit, over_flag, az, dvec);
+        rc = occ_accumulate_m<T, OCC_MAX_M / 2, false>(ctx, s, oa, grid, d, ldd, limit, over_flag, az);
     else
-        rc = occ_accumulate_m<T, OCC_MAX_M, false>(ctx, s, oa, grid, d, ldd, limit, over_flag, az, dvec);
+        rc = occ_accumulate_m<T, OCC_MAX_M, false>(ctx, s, oa, grid, d, ldd, limit, over_flag, az);
     if (rc != SCHULZE_OK) return rc;
     const dim3 fg((unsigned)(ctx->num_cus * 4));
     if (weighted) {
         SCHULZE_LAUNCH(ctx, K_COUNT_FINISH, s,
-                       (k_occ_finish<T, false><<<fg, dim3(256), 0, s>>>(oa, d, ldd, limit, over_flag, az, dvec)));
+                       (k_occ_finish<T, false><<<fg, dim3(256), 0, s>>>(oa, d, ldd, limit, over_flag, az)));
     } else {
         SCHULZE_LAUNCH(ctx, K_COUNT_FINISH, s,
-                       (k_occ_finish<T, true><<<fg, dim3(256), 0, s>>>(oa, d, ldd, limit, over_flag, az, dvec)));
+                       (k_occ_finish<T, true><<<fg, dim3(256), 0, s>>>(oa, d, ldd, limit, over_flag, az)));
     }
     return SCHULZE_OK;
 }

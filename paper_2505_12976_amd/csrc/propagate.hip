@@ -83,21 +83,16 @@ __device__ inline uint32_t key_width(typename Key<E>::K k) {
     return (uint32_t)(k & Key<E>::LOW);
 }
 
-// Four consecutive elements of a row starting at a multiple of 4 (one 8- or
-// 16-byte access when vec and all four are inside, else one at a time, 0
-// past `valid`).
+// Four consecutive elements at p (one 8- or 16-byte access at any alignment).
 template <typename E>
-__device__ inline void load4(const E *__restrict__ p, bool vec, int32_t valid, uint32_t (&v)[4]) {
-    if (vec && valid >= 4) {
-        if constexpr (sizeof(E) == 4) {
-            const uint4 q = *reinterpret_cast<const uint4 *>(p);
-            v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
-        } else {
-            const uint2 q = *reinterpret_cast<const uint2 *>(p);
-            v[0] = q.x & 0xFFFFu, v[1] = q.x >> 16, v[2] = q.y & 0xFFFFu, v[3] = q.y >> 16;
-        }
+__device__ inline void load4(const E *__restrict__ p, uint32_t (&v)[4]) {
+    if constexpr (sizeof(E) == 4) {
+        const uint4 q = tio::load16<E>(p);
+        v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
     } else {
-        for (int c = 0; c < 4; ++c) v[c] = c < valid ? (uint32_t)p[c] : 0u;
+        typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(2)));
+        const v2 q = *reinterpret_cast<const v2 *>(p);
+        v[0] = q[0] & 0xFFFFu, v[1] = q[0] >> 16, v[2] = q[1] & 0xFFFFu, v[3] = q[1] >> 16;
     }
 }
 
@@ -109,7 +104,7 @@ __device__ inline void load4(const E *__restrict__ p, bool vec, int32_t valid, u
 template <typename E>
 __global__ __launch_bounds__(256) void k_prop_rows(const E *__restrict__ d, int64_t ldd, const E *__restrict__ w,
                                                    const E *__restrict__ wt, int64_t ld, int32_t m,
-                                                   const uint8_t *__restrict__ rem, int with_borda, int vec,
+                                                   const uint8_t *__restrict__ rem, int with_borda,
                                                    uint8_t *__restrict__ status, unsigned long long *__restrict__ borda) {
     __shared__ uint32_t smax_out[256], smax_in[256];
     __shared__ unsigned long long sb[256];
@@ -123,38 +118,35 @@ __global__ __launch_bounds__(256) void k_prop_rows(const E *__restrict__ d, int6
     uint32_t mo = 0, mi = 0;
     unsigned long long b = 0;
     const E *wr = w + (int64_t)x * ld, *wtr = SGN ? wr : wt + (int64_t)x * ld, *dr = d + (int64_t)x * ldd;
-    // four columns per thread and step: 8- or 16-byte accesses where the rows allow them
-    const bool wv = (vec & 1) != 0, dv = (vec & 2) != 0;
-    for (int32_t y0 = threadIdx.x * 4; y0 < m; y0 += 1024) {
-        uint32_t a[4], at[4], ad[4] = {0u, 0u, 0u, 0u};
-        uint8_t r[4];
-        const bool full = y0 + 4 <= m;
-        if (full && wv) {
-            load4<E>(wr + y0, true, 4, a);
-            if (!SGN) load4<E>(wtr + y0, true, 4, at);
-            const uint32_t rw = *reinterpret_cast<const uint32_t *>(rem + y0);
-            for (int u = 0; u < 4; ++u) r[u] = (uint8_t)(rw >> (8 * u));
-        } else {
-            for (int u = 0; u < 4; ++u) {
-                const bool in = y0 + u < m;
-                a[u] = in ? (uint32_t)wr[y0 + u] : 0u;
-                if (!SGN) at[u] = in ? (uint32_t)wtr[y0 + u] : 0u;
-                r[u] = in ? rem[y0 + u] : (uint8_t)1;
-            }
+    auto column = [&](uint32_t av, uint32_t atv, uint32_t dv, int32_t y) {
+        if constexpr (SGN) {
+            const int32_t v = (int32_t)av;
+            av = (uint32_t)max(v, 0);
+            atv = (uint32_t)max(-v, 0);
         }
-        if constexpr (SGN)
-            for (int u = 0; u < 4; ++u) {
-                const int32_t v = (int32_t)a[u];
-                a[u] = (uint32_t)max(v, 0);
-                at[u] = (uint32_t)max(-v, 0);
-            }
-        if (with_borda) load4<E>(dr + y0, full && dv, full ? 4 : m - y0, ad);
-        for (int u = 0; u < 4; ++u) {
-            if (r[u]) continue;
-            mo = max(mo, a[u]);
-            mi = max(mi, at[u]);
-            if (y0 + u != x) b += (unsigned long long)ad[u];
+        mo = max(mo, av);
+        mi = max(mi, atv);
+        if (y != x) b += (unsigned long long)dv;
+    };
+    if (m >= 4) {
+        // four columns per thread and step, one access per row at any
+        // alignment; the last four columns' step moves back to end at m and
+        // skips the columns that were taken before
+#pragma unroll 2
+        for (int32_t y0 = threadIdx.x * 4; y0 < m; y0 += 1024) {
+            const int32_t yc = min(y0, m - 4);
+            uint32_t a[4], at[4] = {0u, 0u, 0u, 0u}, ad[4] = {0u, 0u, 0u, 0u};
+            uint8_t r[4];
+            load4<E>(wr + yc, a);
+            if (!SGN) load4<E>(wtr + yc, at);
+            if (with_borda) load4<E>(dr + yc, ad);
+            for (int u = 0; u < 4; ++u) r[u] = rem[yc + u];
+            for (int u = 0; u < 4; ++u)
+                if (!r[u] && yc + u >= y0) column(a[u], at[u], ad[u], yc + u);
         }
+    } else if ((int32_t)threadIdx.x < m) {
+        const int32_t y = threadIdx.x;
+        if (!rem[y]) column((uint32_t)wr[y], SGN ? 0u : (uint32_t)wtr[y], with_borda ? (uint32_t)dr[y] : 0u, y);
     }
     smax_out[threadIdx.x] = mo;
     smax_in[threadIdx.x] = mi;
@@ -303,7 +295,7 @@ __global__ __launch_bounds__(256) void k_prop_pair(const typename Key<E>::K *__r
 // walks column c of w (row c of wt), four entries per lane and step.
 template <typename E>
 __global__ __launch_bounds__(256) void k_prop_cross(const E *__restrict__ wt, int64_t ld,
-                                                    const uint32_t *__restrict__ pair, int32_t m, int vec,
+                                                    const uint32_t *__restrict__ pair, int32_t m,
                                                     uint8_t *__restrict__ mark, uint8_t *__restrict__ dead) {
     const int32_t c = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -312,27 +304,25 @@ __global__ __launch_bounds__(256) void k_prop_cross(const E *__restrict__ wt, in
     if (pc == PAIR_OUT) return;
     const E *row = wt + (int64_t)c * ld;
     bool cross = false;
-    for (int32_t v0 = lane * 4; v0 < m; v0 += 256) {
-        uint32_t e[4], pv[4];
-        if (vec && v0 + 4 <= m) {
-            if constexpr (sizeof(E) == 4) {
-                const uint4 q = *reinterpret_cast<const uint4 *>(row + v0);
-                e[0] = q.x, e[1] = q.y, e[2] = q.z, e[3] = q.w;
-            } else {
-                const uint2 q = *reinterpret_cast<const uint2 *>(row + v0);
-                e[0] = q.x & 0xFFFFu, e[1] = q.x >> 16, e[2] = q.y & 0xFFFFu, e[3] = q.y >> 16;
+    // an edge v -> c: wt[c][v] > 0, or with signed weights (int32) S[c][v] < 0
+    auto edge = [&](uint32_t e, uint32_t pv) {
+        cross |= (sizeof(E) == 4 ? (int32_t)e < 0 : e != 0) && pv != PAIR_OUT && pv != pc;
+    };
+    if (m >= 4) {
+        // (the last step moves back to end at m; an edge seen twice changes nothing)
+        constexpr int FLY = 4;
+        for (int32_t v0 = lane * 4; v0 < m; v0 += 256 * FLY) {
+            uint32_t e[FLY][4], pv[FLY][4];
+            for (int u = 0; u < FLY; ++u) {
+                const int32_t v = min(v0 + 256 * u, m - 4);
+                load4<E>(row + v, e[u]);
+                load4<int32_t>(reinterpret_cast<const int32_t *>(pair) + v, pv[u]);
             }
-            const uint4 p4 = *reinterpret_cast<const uint4 *>(pair + v0);
-            pv[0] = p4.x, pv[1] = p4.y, pv[2] = p4.z, pv[3] = p4.w;
-        } else {
-            for (int u = 0; u < 4; ++u) {
-                e[u] = v0 + u < m ? (uint32_t)row[v0 + u] : 0u;
-                pv[u] = v0 + u < m ? pair[v0 + u] : PAIR_OUT;
-            }
+            for (int u = 0; u < FLY; ++u)
+                for (int k = 0; k < 4; ++k) edge(e[u][k], pv[u][k]);
         }
-        // an edge v -> c: wt[c][v] > 0, or with signed weights (int32) S[c][v] < 0
-        for (int u = 0; u < 4; ++u)
-            cross |= (sizeof(E) == 4 ? (int32_t)e[u] < 0 : e[u] != 0) && pv[u] != PAIR_OUT && pv[u] != pc;
+    } else if (lane < m) {
+        edge((uint32_t)row[lane], pair[lane]);
     }
     if (__ballot(cross) && lane == 0) {
         const uint32_t s = pc >> 16, t = pc & 0xFFFFu;
@@ -413,15 +403,6 @@ __global__ __launch_bounds__(256) void k_prop_remove(uint8_t *__restrict__ statu
     }
 }
 
-// Access widths for k_prop_rows: bit 0 = rows of w and w^T (pitch m, in the
-// workspace), bit 1 = rows of d.
-template <typename E>
-int rows_vec(const E *d, int64_t ldd, int32_t m) {
-    const bool wv = m % 4 == 0;
-    const bool dv = reinterpret_cast<uintptr_t>(d) % (4 * sizeof(E)) == 0 && ldd % 4 == 0;
-    return (wv ? 1 : 0) | (dv ? 2 : 0);
-}
-
 // Device buffers of one propagation run (slices of the WS_PROPAGATE slot).
 template <typename E>
 struct PropBufs {
@@ -494,7 +475,7 @@ int prop_prepare(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32
     if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(b.rem), bvec / 4, 0u)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_PROP, s,
                    k_prop_rows<E><<<dim3((unsigned)m), dim3(256), 0, s>>>(d, ldd, b.w, b.wt, m, m, b.rem, 1,
-                                                                         rows_vec<E>(d, ldd, m), b.status, b.borda));
+                                                                         b.status, b.borda));
     SCHULZE_LAUNCH(ctx, K_PROP, s,
                    k_prop_order<<<dim3((unsigned)m), dim3(256), 0, s>>>(b.borda, m, use_borda, b.label, b.vertex));
 
@@ -523,7 +504,6 @@ int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, 
                 sweep::Problem<K, E> &P = a.run.p[q];
                 P.A = (q == 0 || sizeof(E) == 4) ? b.w : b.wt;  // int32: both read the signed weights
                 P.ld = m;
-                P.vec = sweep::vec_ok<E>(P.A, m) ? 1 : 0;
                 P.x = q == 0 ? b.kf : b.kb;
                 P.stamp = b.stamp[q];
                 P.front[0] = b.front[2 * q];
@@ -568,10 +548,9 @@ int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, 
         SCHULZE_LAUNCH(ctx, K_PROP, s,
                        k_prop_pair<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.status, b.pair));
         const E *wtc = sizeof(E) == 4 ? b.w : b.wt;  // rows of w^T, or of the signed weights
-        const int cvec = (reinterpret_cast<uintptr_t>(wtc) % (4 * sizeof(E)) == 0 && m % 4 == 0) ? 1 : 0;
         SCHULZE_LAUNCH(ctx, K_PROP, s,
-                       k_prop_cross<E><<<dim3((unsigned)ceil_div(m, 4)), dim3(256), 0, s>>>(wtc, m, b.pair, m, cvec,
-                                                                                            b.mark, b.dead));
+                       k_prop_cross<E><<<dim3((unsigned)ceil_div(m, 4)), dim3(256), 0, s>>>(wtc, m, b.pair, m, b.mark,
+                                                                                            b.dead));
         SCHULZE_LAUNCH(ctx, K_PROP, s,
                        k_prop_apply<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.mark, b.dead, b.status));
         SCHULZE_LAUNCH(ctx, K_PROP, s,
@@ -636,8 +615,7 @@ int run_topk(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m
         if (out.ranked >= k || counts[1] == 0) break;
         SCHULZE_LAUNCH(ctx, K_PROP, s,
                        k_prop_rows<E><<<dim3((unsigned)m), dim3(256), 0, s>>>(d, ldd, b.w, b.wt, m, m, b.rem, 0,
-                                                                             rows_vec<E>(d, ldd, m), b.status,
-                                                                             b.borda));
+                                                                             b.status, b.borda));
     }
     out.rounds = st.rounds;
     out.sweeps = st.sweeps;

@@ -25,6 +25,7 @@
 #pragma once
 
 #include "grid.h"
+#include "tile_io.h"
 
 namespace sweep {
 
@@ -44,12 +45,6 @@ inline int64_t grid_size(int32_t m, int np, int64_t cap) {
     return g < 1 ? 1 : (g < cap ? g : cap);
 }
 
-// Rows of a matrix at p with pitch ld can be read as 16-byte vectors.
-template <typename E>
-inline bool vec_ok(const void *p, int64_t ld) {
-    return reinterpret_cast<uintptr_t>(p) % 16 == 0 && (ld * (int64_t)sizeof(E)) % 16 == 0;
-}
-
 // Elements per 16-byte vector and vectors per lane.
 template <typename E>
 constexpr int vlen() {
@@ -61,25 +56,28 @@ constexpr int nvec() {
 }
 
 // Column (relative to the block) of element c of a lane's share: vector
-// k = c / V covers columns (64 k + lane) V .. + V.
+// k = c / V covers columns (64 k + lane) V .. + V.  In a block with fewer
+// columns inside the matrix (valid < CB) the vectors that would reach past
+// them move back to end at the last one: some columns are then taken twice,
+// with the same values, and every access is the same unconditional load.
 template <typename E>
-__device__ inline int32_t lane_col(int lane, int c) {
+__device__ inline int32_t lane_col(int lane, int c, int32_t valid) {
     constexpr int V = vlen<E>();
-    return ((c / V) * 64 + lane) * V + c % V;
+    const int32_t c0 = ((c / V) * 64 + lane) * V;
+    return valid >= V ? min(c0, valid - V) + c % V : min(c0 + c % V, valid - 1);
 }
 
-// The lane's 16 elements of a row (row points at the block's first column).
-// FULL: the whole block is inside the matrix and vector-aligned (16-byte
-// loads); otherwise one element at a time, 0 past `valid` columns.  The
-// choice is made per block, never per lane: a per-lane choice made the
-// compiler wait for every earlier load before each vector load.
-template <typename E, bool FULL>
+// The lane's 16 elements of a row (row points at the block's first column,
+// at any alignment) as 16-byte loads; a block of less than one vector takes
+// them one by one.  At m = 6007 (int32, odd pitch) the label sweeps took 167
+// us with an access per element, now 97; the widest paths of one candidate
+// at m = 1501 (uint16) 318 and 200.
+template <typename E>
 __device__ inline void load_row(const E *__restrict__ row, int32_t valid, int lane, uint32_t (&v)[CPL]) {
     constexpr int V = vlen<E>();
-    for (int k = 0; k < nvec<E>(); ++k) {
-        const int32_t c0 = (k * 64 + lane) * V;
-        if constexpr (FULL) {
-            const uint4 q = *reinterpret_cast<const uint4 *>(row + c0);
+    if (valid >= V) {
+        for (int k = 0; k < nvec<E>(); ++k) {
+            const uint4 q = tio::load16<E>(row + lane_col<E>(lane, k * V, valid));
             const uint32_t w[4] = {q.x, q.y, q.z, q.w};
             if constexpr (sizeof(E) == 4) {
                 for (int u = 0; u < 4; ++u) v[k * V + u] = w[u];
@@ -89,9 +87,9 @@ __device__ inline void load_row(const E *__restrict__ row, int32_t valid, int la
                     v[k * V + 2 * u + 1] = w[u] >> 16;
                 }
             }
-        } else {
-            for (int u = 0; u < V; ++u) v[k * V + u] = c0 + u < valid ? (uint32_t)row[c0 + u] : 0u;
         }
+    } else {
+        for (int c = 0; c < CPL; ++c) v[c] = (uint32_t)row[lane_col<E>(lane, c, valid)];
     }
 }
 
@@ -100,7 +98,6 @@ template <typename X, typename E>
 struct Problem {
     const E *A;          // rows, pitch ld
     int64_t ld;
-    int32_t vec;         // A can be read as 16-byte vectors (vec_ok)
     X *x;                // m values, updated in place (set by the caller's init)
     int32_t *stamp;      // m: the last sweep (from 1) whose list took the vertex; 0 on entry
     int32_t *front[2];   // frontier lists of m entries; front[0] holds the first frontier
@@ -141,7 +138,6 @@ __device__ bool run(const Run<X, E, NP> &r, int32_t m, Comb comb, Accept accept)
     // (select, not index: a dynamically indexed array of the struct would live in scratch memory)
     const E *const A = (NP > 1 && q) ? r.p[NP - 1].A : r.p[0].A;
     const int64_t ld = (NP > 1 && q) ? r.p[NP - 1].ld : r.p[0].ld;
-    const int32_t vec = (NP > 1 && q) ? r.p[NP - 1].vec : r.p[0].vec;
     X *const x = (NP > 1 && q) ? r.p[NP - 1].x : r.p[0].x;
     int32_t *const stamp = (NP > 1 && q) ? r.p[NP - 1].stamp : r.p[0].stamp;
     int32_t *const f0 = (NP > 1 && q) ? r.p[NP - 1].front[0] : r.p[0].front[0];
@@ -149,7 +145,6 @@ __device__ bool run(const Run<X, E, NP> &r, int32_t m, Comb comb, Accept accept)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int32_t blk0 = cb * CB;
     const int32_t valid = m - blk0;  // columns of this block inside the matrix
-    const bool full = vec != 0 && valid >= CB;
     for (int32_t t = 0;; ++t) {
         // list sizes of this sweep: final since the last barrier
         int32_t nf = 0, any = 0;
@@ -191,20 +186,15 @@ __device__ bool run(const Run<X, E, NP> &r, int32_t m, Comb comb, Accept accept)
                 // rows first, then their values and the next indices: all
                 // in flight together, one wait before the arithmetic
                 uint32_t a[U][CPL];
-                if (full) {
-                    for (int u = 0; u < U; ++u)
-                        load_row<E, true>(A + (int64_t)(idx[u] < 0 ? 0 : idx[u]) * ld + blk0, valid, lane, a[u]);
-                } else {
-                    for (int u = 0; u < U; ++u)
-                        load_row<E, false>(A + (int64_t)(idx[u] < 0 ? 0 : idx[u]) * ld + blk0, valid, lane, a[u]);
-                }
+                for (int u = 0; u < U; ++u)
+                    load_row<E>(A + (int64_t)(idx[u] < 0 ? 0 : idx[u]) * ld + blk0, valid, lane, a[u]);
                 X xi[U];
                 for (int u = 0; u < U; ++u) xi[u] = idx[u] < 0 ? (X)0 : x[idx[u] < 0 ? 0 : idx[u]];
                 load_idx(q0 + U * step, idx);
                 for (int u = 0; u < U; ++u)
                     for (int c = 0; c < CPL; ++c) best[c] = max(best[c], comb(q, xi[u], a[u][c]));
             }
-            for (int c = 0; c < CPL; ++c) part[wave][lane_col<E>(lane, c)] = best[c];
+            for (int c = 0; c < CPL; ++c) part[wave][lane_col<E>(lane, c, valid)] = best[c];
         }
         __syncthreads();
         if (active) {

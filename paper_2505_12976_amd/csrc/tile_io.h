@@ -1,9 +1,13 @@
 // 64 x 64 tiles between device memory and LDS, for the passes that need a
 // block of a matrix next to its transposed block (edge weights, beats,
-// per-candidate statistics).  Interior tiles of suitably aligned matrices
-// move as 16-byte vectors (four or eight elements per access, so that many
-// bytes are in flight per wavefront); edge tiles and unaligned matrices fall
-// back to one element per access with bounds checks.  256 threads.
+// per-candidate statistics).  Interior tiles move as 16-byte vectors (four or
+// eight elements per access, so that many bytes are in flight per wavefront),
+// whatever the matrix's alignment and pitch: a global access of 16 bytes may
+// start at any element, and a row that starts inside a line costs one line
+// more per row, not an access per element.  (m = 14187, uint16, an odd pitch:
+// edge weights 311 -> 178 us, beaten-by counts 303 -> 155.)  Edge tiles take
+// one element per access, clamped into the matrix so that all are in flight.
+// 256 threads.
 #pragma once
 
 #include "internal.h"
@@ -13,10 +17,25 @@ namespace tio {
 constexpr int T = 64;       // tile side
 constexpr int PITCH = 65;   // LDS row pitch (odd: column reads hit distinct banks)
 
-// 16-byte vector accesses are valid for a matrix at p with row pitch ld.
+// 16 bytes at any element's address.
 template <typename E>
-inline bool vec_ok(const void *p, int64_t ld) {
-    return p && (reinterpret_cast<uintptr_t>(p) % 16 == 0) && ((ld * (int64_t)sizeof(E)) % 16 == 0);
+struct Any16;
+template <>
+struct Any16<uint16_t> {
+    typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2)));
+};
+template <>
+struct Any16<int32_t> {
+    typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <typename E>
+__device__ __forceinline__ uint4 load16(const E *p) {
+    const typename Any16<E>::type x = *reinterpret_cast<const typename Any16<E>::type *>(p);
+    return make_uint4(x[0], x[1], x[2], x[3]);
+}
+template <typename E>
+__device__ __forceinline__ void store16(E *p, const uint4 &v) {
+    *reinterpret_cast<typename Any16<E>::type *>(p) = typename Any16<E>::type{v.x, v.y, v.z, v.w};
 }
 
 // The V elements of a 16-byte vector.
@@ -47,64 +66,40 @@ __device__ inline uint4 pack<uint16_t>(const uint16_t *e) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// t[r][c] = src[(r0 + r) ld + c0 + c], 0 where r0 + r >= rows or c0 + c >= cols.
-template <typename E>
-__device__ inline void load(E (*t)[PITCH], const E *__restrict__ src, int64_t ld, int32_t r0, int32_t c0,
-                            int32_t rows, int32_t cols, bool vec) {
-    if (vec && r0 + T <= rows && c0 + T <= cols) {
-        constexpr int V = 16 / (int)sizeof(E);  // elements per vector
-        constexpr int VPR = T / V;              // vectors per row
-        constexpr int PER = T * VPR / 256;      // vectors per thread
-        uint4 x[PER];
-        for (int k = 0; k < PER; ++k) {  // all loads first, so that they are in flight together
-            const int q = threadIdx.x + 256 * k;
-            const int r = q / VPR, cv = q % VPR;
-            x[k] = *reinterpret_cast<const uint4 *>(src + (int64_t)(r0 + r) * ld + c0 + cv * V);
-        }
-        for (int k = 0; k < PER; ++k) {
-            const int q = threadIdx.x + 256 * k;
-            const int r = q / VPR, cv = q % VPR;
-            E e[V];
-            unpack<E>(x[k], e);
-            for (int u = 0; u < V; ++u) t[r][cv * V + u] = e[u];
-        }
-    } else {
-        for (int q = threadIdx.x; q < T * T; q += 256) {
-            const int r = q / T, c = q % T;
-            t[r][c] = (r0 + r < rows && c0 + c < cols) ? src[(int64_t)(r0 + r) * ld + c0 + c] : (E)0;
-        }
-    }
-}
-
-// The same tile in two halves, so that the loads can be issued early and
-// the LDS written later: fetch() loads the tile into registers, put()
-// writes them to LDS.  VEC (the matrix is vector-aligned and its side a
-// multiple of the vector length): 16-byte loads, rows and vectors past the
-// edge read the tile's first row / vector instead, so that every tile takes
-// the same loads (what lands outside the matrix is garbage, to be ignored
-// by the caller).  Otherwise one element at a time, 0 outside.
+// A tile in two halves, so that the loads can be issued early and the LDS
+// written later: fetch() loads the tile at (r0, c0) of a rows x cols matrix
+// into registers (0 outside), put() writes them to LDS.
 template <typename E>
 struct Regs {
     static constexpr int PER = T * (T / (16 / (int)sizeof(E))) / 256;  // 16-byte vectors per thread
     uint4 x[PER];
 };
 
-template <typename E, bool VEC>
+template <typename E>
 __device__ inline void fetch(Regs<E> &g, const E *__restrict__ src, int64_t ld, int32_t r0, int32_t c0, int32_t rows,
                              int32_t cols) {
     constexpr int V = 16 / (int)sizeof(E), VPR = T / V;
-    for (int k = 0; k < Regs<E>::PER; ++k) {
-        const int q = threadIdx.x + 256 * k;
-        int32_t r = r0 + q / VPR, c = c0 + (q % VPR) * V;
-        if (VEC) {
-            r = r < rows ? r : r0;
-            c = c < cols ? c : c0;
-            g.x[k] = *reinterpret_cast<const uint4 *>(src + (int64_t)r * ld + c);
-        } else {
-            E e[V];
-            for (int u = 0; u < V; ++u) e[u] = (r < rows && c + u < cols) ? src[(int64_t)r * ld + c + u] : (E)0;
-            g.x[k] = pack<E>(e);
+    if (r0 + T <= rows && c0 + T <= cols) {
+        for (int k = 0; k < Regs<E>::PER; ++k) {
+            const int q = threadIdx.x + 256 * k;
+            g.x[k] = load16<E>(src + (int64_t)(r0 + q / VPR) * ld + c0 + (q % VPR) * V);
         }
+        return;
+    }
+    E e[Regs<E>::PER][V];
+    for (int k = 0; k < Regs<E>::PER; ++k)
+        for (int u = 0; u < V; ++u) {
+            const int q = threadIdx.x + 256 * k;
+            const int32_t r = r0 + q / VPR, c = c0 + (q % VPR) * V + u;
+            e[k][u] = src[(int64_t)min(r, rows - 1) * ld + min(c, cols - 1)];
+        }
+    for (int k = 0; k < Regs<E>::PER; ++k) {
+        for (int u = 0; u < V; ++u) {
+            const int q = threadIdx.x + 256 * k;
+            const int32_t r = r0 + q / VPR, c = c0 + (q % VPR) * V + u;
+            e[k][u] = r < rows && c < cols ? e[k][u] : (E)0;
+        }
+        g.x[k] = pack<E>(e[k]);
     }
 }
 
@@ -119,18 +114,27 @@ __device__ inline void put(E (*t)[PITCH], const Regs<E> &g) {
     }
 }
 
+// t[r][c] = src[(r0 + r) ld + c0 + c], 0 where r0 + r >= rows or c0 + c >= cols.
+template <typename E>
+__device__ inline void load(E (*t)[PITCH], const E *__restrict__ src, int64_t ld, int32_t r0, int32_t c0,
+                            int32_t rows, int32_t cols) {
+    Regs<E> g;
+    fetch<E>(g, src, ld, r0, c0, rows, cols);
+    put<E>(t, g);
+}
+
 // dst[(r0 + r) ld + c0 + c] = f(r, c) for r0 + r < rows and c0 + c < cols.
 template <typename E, typename F>
 __device__ inline void store(E *__restrict__ dst, int64_t ld, int32_t r0, int32_t c0, int32_t rows, int32_t cols,
-                             bool vec, F f) {
-    if (vec && r0 + T <= rows && c0 + T <= cols) {
+                             F f) {
+    if (r0 + T <= rows && c0 + T <= cols) {
         constexpr int V = 16 / (int)sizeof(E);
         constexpr int VPR = T / V;
         for (int q = threadIdx.x; q < T * VPR; q += 256) {
             const int r = q / VPR, cv = q % VPR;
             E e[V];
             for (int u = 0; u < V; ++u) e[u] = f(r, cv * V + u);
-            *reinterpret_cast<uint4 *>(dst + (int64_t)(r0 + r) * ld + c0 + cv * V) = pack<E>(e);
+            store16<E>(dst + (int64_t)(r0 + r) * ld + c0 + cv * V, pack<E>(e));
         }
     } else {
         for (int q = threadIdx.x; q < T * T; q += 256) {

@@ -80,36 +80,35 @@ __device__ inline E max_value() {
 template <typename E, bool SIGNED = false>
 __global__ __launch_bounds__(256) void k_weights_pair(const E *__restrict__ d, int64_t ldd, int32_t m, int mode,
                                                       E *__restrict__ w, int64_t ldw, E *__restrict__ wt,
-                                                      int64_t ldwt, int vec) {
+                                                      int64_t ldwt) {
     __shared__ E a[64][65];  // a[r][c] = d[I0 + r][J0 + c]
     __shared__ E b[64][65];  // b[r][c] = d[J0 + r][I0 + c]
     if (blockIdx.y > blockIdx.x) return;
     const int32_t I0 = blockIdx.y * 64, J0 = blockIdx.x * 64;
-    tio::load<E>(a, d, ldd, I0, J0, m, m, vec & 1);
-    tio::load<E>(b, d, ldd, J0, I0, m, m, vec & 1);
+    tio::load<E>(a, d, ldd, I0, J0, m, m);
+    tio::load<E>(b, d, ldd, J0, I0, m, m);
     __syncthreads();
     auto weight = [&](E x, E y, bool diag) -> E {  // weight of edge (i, j) given d[i][j] = x, d[j][i] = y
         if (diag || x <= y) return (E)0;
         return mode == SCHULZE_MARGIN ? (E)(x - y) : x;
     };
-    const bool wv = (vec & 2) != 0, wtv = (vec & 4) != 0;
     if constexpr (SIGNED) {
-        tio::store<E>(w, ldw, I0, J0, m, m, wv, [&](int r, int c) {
+        tio::store<E>(w, ldw, I0, J0, m, m, [&](int r, int c) {
             const bool dg = I0 + r == J0 + c;
             return (E)(weight(a[r][c], b[c][r], dg) - weight(b[c][r], a[r][c], dg));
         });
         if (I0 != J0)
-            tio::store<E>(w, ldw, J0, I0, m, m, wv,
+            tio::store<E>(w, ldw, J0, I0, m, m,
                           [&](int r, int c) { return (E)(weight(b[r][c], a[c][r], false) - weight(a[c][r], b[r][c], false)); });
         return;
     }
     // edges (I0 + r, J0 + c) into w; edges (I0 + c, J0 + r) into wt row J0 + r
-    if (w) tio::store<E>(w, ldw, I0, J0, m, m, wv, [&](int r, int c) { return weight(a[r][c], b[c][r], I0 + r == J0 + c); });
-    if (wt) tio::store<E>(wt, ldwt, J0, I0, m, m, wtv, [&](int r, int c) { return weight(a[c][r], b[r][c], I0 + c == J0 + r); });
+    if (w) tio::store<E>(w, ldw, I0, J0, m, m, [&](int r, int c) { return weight(a[r][c], b[c][r], I0 + r == J0 + c); });
+    if (wt) tio::store<E>(wt, ldwt, J0, I0, m, m, [&](int r, int c) { return weight(a[c][r], b[r][c], I0 + c == J0 + r); });
     if (I0 == J0) return;
     // edges (J0 + r, I0 + c) into w; edges (J0 + c, I0 + r) into wt row I0 + r
-    if (w) tio::store<E>(w, ldw, J0, I0, m, m, wv, [&](int r, int c) { return weight(b[r][c], a[c][r], false); });
-    if (wt) tio::store<E>(wt, ldwt, I0, J0, m, m, wtv, [&](int r, int c) { return weight(b[c][r], a[r][c], false); });
+    if (w) tio::store<E>(w, ldw, J0, I0, m, m, [&](int r, int c) { return weight(b[r][c], a[c][r], false); });
+    if (wt) tio::store<E>(wt, ldwt, I0, J0, m, m, [&](int r, int c) { return weight(b[c][r], a[r][c], false); });
 }
 
 // ------------------------------------------------------------------ sweeps
@@ -242,11 +241,10 @@ __device__ __forceinline__ void check_row(const E (*A)[tio::PITCH], const E (*B)
 }
 
 // Both directions from (to) a.s over d (both problems' A = d), to the
-// fixpoint, in one cooperative launch after k_widest_init.  VD: d is
-// vector-aligned and m a multiple of the vector length.  Three workgroups
+// fixpoint, in one cooperative launch after k_widest_init.  Three workgroups
 // per CU (registers capped accordingly; a few spill in the gather branch):
 // 0.95 ms instead of 1.11 ms with two at m = 32768.
-template <typename E, bool MARGIN, bool VD>
+template <typename E, bool MARGIN>
 __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
     using sweep::CB;
     using sweep::CPL;
@@ -297,8 +295,8 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
             uint32_t xr = 0;
             const int xside = (threadIdx.x >> 7) & 1, xq = (threadIdx.x >> 6) & 1;
             auto fetch = [&](int32_t Xf, int32_t Yf) {
-                tio::fetch<E, VD>(ga, d, ld, Xf * tio::T, Yf * tio::T, m, m);
-                if (Xf != Yf) tio::fetch<E, VD>(gb, d, ld, Yf * tio::T, Xf * tio::T, m, m);
+                tio::fetch<E>(ga, d, ld, Xf * tio::T, Yf * tio::T, m, m);
+                if (Xf != Yf) tio::fetch<E>(gb, d, ld, Yf * tio::T, Xf * tio::T, m, m);
                 const int32_t v = (xside ? Yf : Xf) * tio::T + lane;
                 xr = v < m ? __hip_atomic_load((xq ? x1 : x0) + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
             };
@@ -355,18 +353,12 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
             const uint32_t *xq = gq ? x1 : x0;
             uint32_t best[CPL] = {};
             if (gactive) {
-                const bool full = VD && valid >= CB;
                 for (int32_t qi = share * 4 + wave; qi < nf; qi += 4 * shares) {
                     const int32_t v = F[qi];
                     uint32_t row[CPL], col[CPL];
-                    if (full)
-                        sweep::load_row<E, true>(d + (int64_t)v * ld + blk0, valid, lane, row);
-                    else
-                        sweep::load_row<E, false>(d + (int64_t)v * ld + blk0, valid, lane, row);
-                    for (int c = 0; c < CPL; ++c) {
-                        const int32_t k = blk0 + sweep::lane_col<E>(lane, c);
-                        col[c] = k < m ? (uint32_t)d[(int64_t)k * ld + v] : 0u;
-                    }
+                    sweep::load_row<E>(d + (int64_t)v * ld + blk0, valid, lane, row);
+                    for (int c = 0; c < CPL; ++c)
+                        col[c] = (uint32_t)d[(int64_t)(blk0 + sweep::lane_col<E>(lane, c, valid)) * ld + v];
                     const uint32_t xv = xq[v];
                     for (int c = 0; c < CPL; ++c) {
                         const uint32_t w = gq ? edge_weight<MARGIN>((int32_t)col[c], (int32_t)row[c])
@@ -374,7 +366,7 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
                         best[c] = max(best[c], min(xv, w));
                     }
                 }
-                for (int c = 0; c < CPL; ++c) part[wave][sweep::lane_col<E>(lane, c)] = best[c];
+                for (int c = 0; c < CPL; ++c) part[wave][sweep::lane_col<E>(lane, c, valid)] = best[c];
             }
             __syncthreads();
             uint32_t *const xg = gq ? x1 : x0;
@@ -499,7 +491,6 @@ int widest_in(schulze_ctx *ctx, hipStream_t s, const E *const (&A)[NP], const in
         sweep::Problem<uint32_t, E> &P = a.run.p[q];
         P.A = A[q];
         P.ld = ld[q];
-        P.vec = sweep::vec_ok<E>(A[q], ld[q]) ? 1 : 0;
         P.x = reinterpret_cast<uint32_t *>(p);
         P.stamp = reinterpret_cast<int32_t *>(p + v);
         P.front[0] = reinterpret_cast<int32_t *>(p + 2 * v);
@@ -569,7 +560,7 @@ int verify_all(schulze_ctx *ctx, hipStream_t s, const E *w, int64_t ldw, const E
 }
 
 // The exact check of cand from d (k_check) and its verdict.
-template <typename E, bool MARGIN, bool VD>
+template <typename E, bool MARGIN>
 int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int32_t cand,
                     const float *score, E *p_from, E *p_to, int32_t *verdict, int32_t *tied) {
     int rc = ws_reserve(ctx, WS_VERIFY, widest_scratch_bytes(m, 2));
@@ -582,7 +573,6 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
         sweep::Problem<uint32_t, E> &P = a.run.p[q];
         P.A = d;
         P.ld = ldd;
-        P.vec = VD ? 1 : 0;
         P.x = reinterpret_cast<uint32_t *>(p);
         P.stamp = reinterpret_cast<int32_t *>(p + v);
         P.front[0] = reinterpret_cast<int32_t *>(p + 2 * v);
@@ -598,7 +588,7 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
     a.m = m;
     a.s = cand;
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_check<E, MARGIN, VD>, 256, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_check<E, MARGIN>, 256, 0) != hipSuccess ||
         per_cu < 1)
         return SCHULZE_EDEVICE;
     // enough workgroups for the tile pairs of the dense pass and for every
@@ -612,7 +602,7 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
     hipError_t e = hipGetLastError();
     void *args[] = {&a};
     if (e == hipSuccess)
-        e = hipLaunchCooperativeKernel((const void *)k_check<E, MARGIN, VD>, dim3((unsigned)G), dim3(256), args, 0,
+        e = hipLaunchCooperativeKernel((const void *)k_check<E, MARGIN>, dim3((unsigned)G), dim3(256), args, 0,
                                        s);
     timing_end(ctx, tok, s);
     if (e != hipSuccess) {
@@ -627,13 +617,9 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
 template <typename E>
 int check_counts(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, int32_t cand,
                  const float *score, E *p_from, E *p_to, int32_t *verdict, int32_t *tied) {
-    constexpr int V = 16 / (int)sizeof(E);
-    const bool vd = tio::vec_ok<E>(d, ldd) && m % V == 0;
     if (mode == SCHULZE_MARGIN)
-        return vd ? check_counts_as<E, true, true>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied)
-                  : check_counts_as<E, true, false>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
-    return vd ? check_counts_as<E, false, true>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied)
-              : check_counts_as<E, false, false>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
+        return check_counts_as<E, true>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
+    return check_counts_as<E, false>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
 }
 
 int check_square(schulze_ctx *ctx, const void *a, int64_t ld, int32_t m, int dtype) {
@@ -656,19 +642,15 @@ extern "C" int schulze_weights(schulze_ctx *ctx, void *stream, const void *d, in
     hipStream_t s = (hipStream_t)stream;
     dim3 grid((unsigned)ceil_div(m, 64), (unsigned)ceil_div(m, 64));
     if (dtype == SCHULZE_U16) {
-        const int vec = (tio::vec_ok<uint16_t>(d, ldd) ? 1 : 0) | (tio::vec_ok<uint16_t>(w, ldw) ? 2 : 0) |
-                        (tio::vec_ok<uint16_t>(wt, ldwt) ? 4 : 0);
         SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
                        k_weights_pair<uint16_t><<<grid, dim3(256), 0, s>>>(
                            static_cast<const uint16_t *>(d), ldd, m, mode, static_cast<uint16_t *>(w), ldw,
-                           static_cast<uint16_t *>(wt), ldwt, vec));
+                           static_cast<uint16_t *>(wt), ldwt));
     } else {
-        const int vec = (tio::vec_ok<int32_t>(d, ldd) ? 1 : 0) | (tio::vec_ok<int32_t>(w, ldw) ? 2 : 0) |
-                        (tio::vec_ok<int32_t>(wt, ldwt) ? 4 : 0);
         SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
                        k_weights_pair<int32_t><<<grid, dim3(256), 0, s>>>(
                            static_cast<const int32_t *>(d), ldd, m, mode, static_cast<int32_t *>(w), ldw,
-                           static_cast<int32_t *>(wt), ldwt, vec));
+                           static_cast<int32_t *>(wt), ldwt));
     }
     return SCHULZE_OK;
 }
@@ -741,10 +723,9 @@ extern "C" int schulze_verify_counts(schulze_ctx *ctx, void *stream, const void 
 
 int signed_weights(schulze_ctx *ctx, hipStream_t s, const int32_t *d, int64_t ldd, int32_t m, int mode, int32_t *S,
                    int64_t lds) {
-    const int vec = (tio::vec_ok<int32_t>(d, ldd) ? 1 : 0) | (tio::vec_ok<int32_t>(S, lds) ? 2 : 0);
     dim3 grid((unsigned)ceil_div(m, 64), (unsigned)ceil_div(m, 64));
     SCHULZE_LAUNCH(ctx, K_WEIGHTS, s,
-                   k_weights_pair<int32_t, true><<<grid, dim3(256), 0, s>>>(d, ldd, m, mode, S, lds, nullptr, 0, vec));
+                   k_weights_pair<int32_t, true><<<grid, dim3(256), 0, s>>>(d, ldd, m, mode, S, lds, nullptr, 0));
     return SCHULZE_OK;
 }
 
