@@ -59,9 +59,18 @@ extern "C" int schulze_create(schulze_ctx **out, int device) {
         delete ctx;
         return SCHULZE_EDEVICE;
     }
+    if (hipHostMalloc((void **)&ctx->host, HOST_WORDS * sizeof(int32_t), hipHostMallocCoherent) != hipSuccess ||
+        hipHostGetDevicePointer((void **)&ctx->host_dev, ctx->host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        if (ctx->host) (void)hipHostFree(ctx->host);
+        (void)hipFree(ctx->err);
+        delete ctx;
+        return SCHULZE_ENOMEM;
+    }
     ctx->launches.assign(K_NUM_KERNELS, 0);
     ctx->total_ms.assign(K_NUM_KERNELS, 0.0);
     if (verify_scratch_init(device, &ctx->verify_scratch) != SCHULZE_OK) {
+        (void)hipHostFree(ctx->host);
         (void)hipFree(ctx->err);
         delete ctx;
         return SCHULZE_EDEVICE;
@@ -81,6 +90,7 @@ extern "C" void schulze_destroy(schulze_ctx *ctx) {
         (void)hipEventDestroy(p.stop);
     }
     for (auto e : ctx->event_pool) (void)hipEventDestroy(e);
+    (void)hipHostFree(ctx->host);
     (void)hipFree(ctx->err);
     delete ctx;
 }
@@ -109,11 +119,10 @@ extern "C" int schulze_get_device_error(schulze_ctx *ctx, void *stream, int32_t 
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     int32_t v = 0;
-    if (hipMemcpyAsync(&v, ctx->err, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-        return SCHULZE_EDEVICE;
-    if (hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
+    int rc = read_words(ctx, s, {{ctx->err, 1}}, &v);
+    if (rc != SCHULZE_OK) return rc;
     if (v != 0) {
-        int rc = fill_u32(ctx, s, (uint32_t *)ctx->err, 1, 0u);
+        rc = fill_u32(ctx, s, (uint32_t *)ctx->err, 1, 0u);
         if (rc != SCHULZE_OK) return rc;
         if (hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
     }
@@ -143,6 +152,45 @@ int fill_u32(schulze_ctx *ctx, hipStream_t s, uint32_t *ptr, size_t words, uint3
     if (blocks > (int64_t)ctx->num_cus * 8) blocks = (int64_t)ctx->num_cus * 8;
     if (blocks < 1) blocks = 1;
     SCHULZE_LAUNCH(ctx, K_FILL, s, k_fill_u32<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(ptr, words, value));
+    return SCHULZE_OK;
+}
+
+// ---------------------------------------------------------------- words to the host
+
+namespace {
+
+constexpr int MAX_SPANS = 4;
+struct Spans {
+    const int32_t *p[MAX_SPANS];
+    int32_t end[MAX_SPANS];  // first word after the span
+};
+
+}  // namespace
+
+static __global__ __launch_bounds__(HOST_WORDS) void k_read_words(Spans a, int32_t *__restrict__ host) {
+    const int t = threadIdx.x;
+    const int32_t *src = nullptr;
+    int begin = 0;
+#pragma unroll
+    for (int k = 0; k < MAX_SPANS; ++k) {
+        if (t >= begin && t < a.end[k]) src = a.p[k] + (t - begin);
+        begin = a.end[k];
+    }
+    if (src) __hip_atomic_store(host + t, *src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+int read_words(schulze_ctx *ctx, hipStream_t s, std::initializer_list<WordSpan> spans, int32_t *out) {
+    Spans a{};
+    int k = 0, n = 0;
+    for (const WordSpan &sp : spans) {
+        if (k == MAX_SPANS || sp.count < 1 || n + sp.count > HOST_WORDS) return SCHULZE_EINVAL;
+        a.p[k] = sp.p;
+        a.end[k++] = n += sp.count;
+    }
+    for (; k < MAX_SPANS; ++k) a.end[k] = n;
+    k_read_words<<<dim3(1), dim3(HOST_WORDS), 0, s>>>(a, ctx->host_dev);
+    if (launch_status() != SCHULZE_OK || hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
+    for (int i = 0; i < n; ++i) out[i] = ctx->host[i];
     return SCHULZE_OK;
 }
 

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <string>
+#include <initializer_list>
 #include <vector>
 
 #include "../../include/schulze.h"
@@ -44,10 +45,15 @@ struct PendingTiming {
 // Polls of a frontier sweep's grid barrier before it is declared stuck.
 constexpr int64_t SWEEP_SPIN_LIMIT = (int64_t)1 << 24;
 
+// Words of a context's pinned result buffer.
+constexpr int HOST_WORDS = 64;
+
 struct schulze_ctx {
     int device = 0;
     int num_cus = 0;
     int32_t *err = nullptr;  // device error word
+    // HOST_WORDS pinned words that kernels write results to (host and device address)
+    int32_t *host = nullptr, *host_dev = nullptr;
     void *ws[WS_NUM_SLOTS] = {};
     size_t ws_bytes[WS_NUM_SLOTS] = {};
     // per-kernel timing
@@ -139,6 +145,17 @@ int launch_status();
 
 // Zero `words` 32-bit words with a fill kernel (graph-capture friendly).
 int fill_u32(schulze_ctx *ctx, hipStream_t s, uint32_t *ptr, size_t words, uint32_t value);
+
+// A few device words on the host: `count` words at each p, one after the
+// other (at most HOST_WORDS together), after everything queued on s.  One
+// small kernel writes them to the context's pinned buffer and one
+// synchronisation waits for it; a copy to pageable memory stalls the stream
+// for 30 to 50 us, and more than one copy for as many times that.
+struct WordSpan {
+    const int32_t *p;
+    int count;
+};
+int read_words(schulze_ctx *ctx, hipStream_t s, std::initializer_list<WordSpan> spans, int32_t *out);
 
 // Signed weights S = w - w^T of d (int32; pitch lds): both weight rules
 // give a pair an edge in at most one direction, so w[i][j] = max(S[i][j], 0)

@@ -10,6 +10,7 @@
 // the tied candidates that pass the same check.  If no winner is found
 // within max_climb steps, or too many candidates are tied, the full closure
 // decides.  The output is always exactly the Schulze winner set.
+#include <algorithm>
 #include <vector>
 
 #include "internal.h"
@@ -132,14 +133,10 @@ extern "C" int schulze_winners_learned(schulze_ctx *ctx, void *stream, const voi
     SCHULZE_LAUNCH(ctx, K_PROPOSE, s,
                    k_propose<<<dim3(1), dim3(PROPOSE_THREADS), 0, s>>>(score, feat, m, use_filter, small + 4));
     int32_t cand = -1;
-    if (hipMemcpyAsync(&cand, small + 4, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return SCHULZE_EDEVICE;
+    if ((rc = read_words(ctx, s, {{small + 4, 1}}, &cand)) != SCHULZE_OK) return rc;
     if (cand < 0) {  // every candidate filtered: cannot happen for consistent data; score all
         SCHULZE_LAUNCH(ctx, K_PROPOSE, s, k_propose<<<dim3(1), dim3(PROPOSE_THREADS), 0, s>>>(score, feat, m, 0, small + 4));
-        if (hipMemcpyAsync(&cand, small + 4, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return SCHULZE_EDEVICE;
+        if ((rc = read_words(ctx, s, {{small + 4, 1}}, &cand)) != SCHULZE_OK) return rc;
     }
     st.proposal = cand;
 
@@ -154,6 +151,11 @@ extern "C" int schulze_winners_learned(schulze_ctx *ctx, void *stream, const voi
     // rows unwritten and sets the word, so the search stops with
     // SCHULZE_EDEVICE (the word stays set for schulze_get_device_error)
     // instead of deciding on stale rows.
+    // The verdict, the error word and the first tied candidates come to the
+    // host together.
+    constexpr int FIRST_TIES = 16;
+    int32_t got[5 + FIRST_TIES];  // verdict, error word, tied candidates
+    const int first_ties = m < FIRST_TIES ? m : FIRST_TIES;
     void *w = nullptr, *wt = nullptr;
     const bool sgn = dtype == SCHULZE_I32;
     auto verify = [&](int32_t c, int32_t (&v)[4]) -> int {
@@ -180,12 +182,9 @@ extern "C" int schulze_winners_learned(schulze_ctx *ctx, void *stream, const voi
         }
         if (r != SCHULZE_OK) return r;
         ++st.verify_calls;
-        int32_t err = 0;
-        if (hipMemcpyAsync(v, small, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(&err, ctx->err, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return SCHULZE_EDEVICE;
-        return err == SCHULZE_OK ? SCHULZE_OK : SCHULZE_EDEVICE;
+        if ((r = read_words(ctx, s, {{small, 4}, {ctx->err, 1}, {tied, first_ties}}, got)) != SCHULZE_OK) return r;
+        std::copy_n(got, 4, v);
+        return got[4] == SCHULZE_OK ? SCHULZE_OK : SCHULZE_EDEVICE;
     };
 
     int32_t v[4];
@@ -204,9 +203,10 @@ extern "C" int schulze_winners_learned(schulze_ctx *ctx, void *stream, const voi
     std::vector<uint8_t> host_win;
     if (winner >= 0 && v[3] <= max_tied) {
         std::vector<int32_t> ties(v[3]);
-        if (v[3] > 0 &&
-            (hipMemcpyAsync(ties.data(), tied, sizeof(int32_t) * v[3], hipMemcpyDeviceToHost, s) != hipSuccess ||
-             hipStreamSynchronize(s) != hipSuccess))
+        if (v[3] <= first_ties)
+            std::copy_n(got + 5, v[3], ties.begin());
+        else if ((hipMemcpyAsync(ties.data(), tied, sizeof(int32_t) * v[3], hipMemcpyDeviceToHost, s) != hipSuccess ||
+                  hipStreamSynchronize(s) != hipSuccess))
             return SCHULZE_EDEVICE;
         host_win.assign(m, 0);
         host_win[winner] = 1;
@@ -244,10 +244,7 @@ extern "C" int schulze_winners_learned(schulze_ctx *ctx, void *stream, const voi
             SCHULZE_OK)
             return rc;
         int32_t nw = 0;
-        if (hipMemcpyAsync(&nw, n_winners ? n_winners : small + 8, sizeof(int32_t), hipMemcpyDeviceToHost, s) !=
-                hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return SCHULZE_EDEVICE;
+        if ((rc = read_words(ctx, s, {{n_winners ? n_winners : small + 8, 1}}, &nw)) != SCHULZE_OK) return rc;
         st.n_winners = nw;
     }
     if (stats) *stats = st;

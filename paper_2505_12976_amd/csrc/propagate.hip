@@ -204,6 +204,8 @@ struct SweepArgs {
     int32_t m;
     const uint8_t *status;
     const int32_t *label;
+    uint8_t *mark, *dead;  // the round's marks, cleared by the init
+    int32_t *counts;       // two words, cleared by the init
 };
 
 // Undecided vertices start with their own label and the empty path; they
@@ -214,9 +216,11 @@ __global__ __launch_bounds__(256) void k_prop_init(SweepArgs<E> a) {
     using K = typename Key<E>::K;
     const int32_t m = a.m;
     const int lane = threadIdx.x & 63;
+    if (blockIdx.x == 0 && threadIdx.x < 2) a.counts[threadIdx.x] = 0;
     for (int32_t j0 = blockIdx.x * 256; j0 < m; j0 += gridDim.x * 256) {
         const int32_t j = j0 + threadIdx.x;
         const bool u = j < m && a.status[j] == ST_UNKNOWN;
+        if (j < m) a.mark[j] = a.dead[j] = 0;
         const uint64_t bal = __ballot(u);
         for (int q = 0; q < 2; ++q) {
             const sweep::Problem<K, E> &P = a.run.p[q];
@@ -253,14 +257,23 @@ __global__ __launch_bounds__(256) void k_prop_sweep(SweepArgs<E> a) {
 
 // ------------------------------------------------------------------ postprocessing
 // Marks from each vertex's own (s, ws, t, wt).  mark[v] = 1: v is beaten;
-// dead[x] = 1: the component labelled x is beaten.
+// dead[x] = 1: the component labelled x is beaten.  And each vertex's (s, t)
+// in one word: labels are below 65534, "no label" is PAIR_NONE, and a removed
+// vertex (no edges) gets PAIR_OUT in both halves.
+constexpr uint32_t PAIR_NONE = 0xFFFEu;
+constexpr uint32_t PAIR_OUT = 0xFFFFFFFFu;
+
 template <typename E>
 __global__ __launch_bounds__(256) void k_prop_post(const typename Key<E>::K *__restrict__ kf,
                                                    const typename Key<E>::K *__restrict__ kb, int32_t m,
-                                                   const int32_t *__restrict__ vertex, uint8_t *__restrict__ mark) {
+                                                   const int32_t *__restrict__ vertex,
+                                                   const uint8_t *__restrict__ status, uint32_t *__restrict__ pair,
+                                                   uint8_t *__restrict__ mark) {
     const int32_t c = blockIdx.x * 256 + threadIdx.x;
     if (c >= m) return;
     const uint32_t s = key_label<E>(kf[c]), t = key_label<E>(kb[c]);
+    pair[c] = status[c] == ST_REMOVED ? PAIR_OUT
+                                       : ((s == 0xFFFFFFFFu ? PAIR_NONE : s) << 16) | (t == 0xFFFFFFFFu ? PAIR_NONE : t);
     if (s == 0xFFFFFFFFu && t == 0xFFFFFFFFu) return;  // joined to no undecided vertex
     if (s < t) {
         mark[c] = 1;
@@ -273,22 +286,6 @@ __global__ __launch_bounds__(256) void k_prop_post(const typename Key<E>::K *__r
         else if (ws < wt)
             mark[vertex[s]] = 1;
     }
-}
-
-// Each vertex's (s, t) in one word: labels are below 65534, "no label" is
-// PAIR_NONE, and a removed vertex (no edges) gets PAIR_OUT in both halves.
-constexpr uint32_t PAIR_NONE = 0xFFFEu;
-constexpr uint32_t PAIR_OUT = 0xFFFFFFFFu;
-
-template <typename E>
-__global__ __launch_bounds__(256) void k_prop_pair(const typename Key<E>::K *__restrict__ kf,
-                                                   const typename Key<E>::K *__restrict__ kb, int32_t m,
-                                                   const uint8_t *__restrict__ status, uint32_t *__restrict__ pair) {
-    const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= m) return;
-    const uint32_t s = key_label<E>(kf[v]), t = key_label<E>(kb[v]);
-    pair[v] = status[v] == ST_REMOVED ? PAIR_OUT
-                                       : ((s == 0xFFFFFFFFu ? PAIR_NONE : s) << 16) | (t == 0xFFFFFFFFu ? PAIR_NONE : t);
 }
 
 // Edges v -> c between vertices with different (s, t): one wavefront per c
@@ -334,30 +331,23 @@ __global__ __launch_bounds__(256) void k_prop_cross(const E *__restrict__ wt, in
     }
 }
 
-// Apply the marks to undecided vertices; then count the undecided ones.
-template <typename E>
-__global__ __launch_bounds__(256) void k_prop_apply(const typename Key<E>::K *__restrict__ kf,
-                                                    const typename Key<E>::K *__restrict__ kb, int32_t m,
-                                                    const uint8_t *__restrict__ mark, const uint8_t *__restrict__ dead,
-                                                    uint8_t *__restrict__ status) {
-    const int32_t c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= m || status[c] != ST_UNKNOWN) return;
-    const uint32_t s = key_label<E>(kf[c]), t = key_label<E>(kb[c]);
-    if (mark[c] || (s == t && s != 0xFFFFFFFFu && dead[s])) status[c] = ST_LOSER;
-}
-
-// Winners: undecided vertices whose own label is their (s, t).  counts[0]
-// receives the number still undecided after this round.
+// The marks applied to undecided vertices, and winners: vertices still
+// undecided whose own label is their (s, t).  counts[0] receives the number
+// undecided after this round.
 template <typename E>
 __global__ __launch_bounds__(256) void k_prop_decide(const typename Key<E>::K *__restrict__ kf,
                                                      const typename Key<E>::K *__restrict__ kb, int32_t m,
-                                                     const int32_t *__restrict__ label, uint8_t *__restrict__ status,
+                                                     const int32_t *__restrict__ label,
+                                                     const uint8_t *__restrict__ mark,
+                                                     const uint8_t *__restrict__ dead, uint8_t *__restrict__ status,
                                                      int32_t *__restrict__ counts) {
     const int32_t c = blockIdx.x * 256 + threadIdx.x;
     int32_t undecided = 0;
     if (c < m && status[c] == ST_UNKNOWN) {
         const uint32_t s = key_label<E>(kf[c]), t = key_label<E>(kb[c]);
-        if (s == (uint32_t)label[c] && t == s)
+        if (mark[c] || (s == t && s != 0xFFFFFFFFu && dead[s]))
+            status[c] = ST_LOSER;
+        else if (s == (uint32_t)label[c] && t == s)
             status[c] = ST_WINNER;
         else
             undecided = 1;
@@ -366,16 +356,36 @@ __global__ __launch_bounds__(256) void k_prop_decide(const typename Key<E>::K *_
     if ((threadIdx.x & 63) == 0 && bal) atomicAdd(&counts[0], (int32_t)__popcll(bal));
 }
 
-__global__ __launch_bounds__(256) void k_prop_out(const uint8_t *__restrict__ status, int32_t m,
-                                                  uint8_t *__restrict__ is_winner, int32_t *__restrict__ counts) {
-    const int32_t c = blockIdx.x * 256 + threadIdx.x;
+// The round's report to the host (host[0 .. 4]: error word, sweeps forward,
+// sweeps backward, vertices undecided, winners), and once nothing is
+// undecided and no sweep gave up, the winners themselves (is_winner may be
+// null; n_winners too).  One workgroup: the host reads the report after one
+// synchronisation and queues another round, or is done.
+__global__ __launch_bounds__(1024) void k_prop_report(const uint8_t *__restrict__ status, int32_t m,
+                                                      const int32_t *__restrict__ err,
+                                                      const int32_t *__restrict__ cnt,
+                                                      const int32_t *__restrict__ counts,
+                                                      uint8_t *__restrict__ is_winner, int32_t *n_winners,
+                                                      int32_t *host) {
+    __shared__ int32_t part[16];
+    const int32_t e = *err, left = counts[0];
     int32_t win = 0;
-    if (c < m) {
-        win = status[c] == ST_WINNER ? 1 : 0;
-        is_winner[c] = (uint8_t)win;
+    if (e == SCHULZE_OK && left == 0)
+        for (int32_t c = threadIdx.x; c < m; c += 1024) {
+            const int32_t w = status[c] == ST_WINNER ? 1 : 0;
+            if (is_winner) is_winner[c] = (uint8_t)w;
+            win += w;
+        }
+    for (int off = 32; off > 0; off >>= 1) win += __shfl_xor(win, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = win;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t n = 0;
+        for (int w = 0; w < 16; ++w) n += part[w];
+        if (n_winners && e == SCHULZE_OK && left == 0) *n_winners = n;
+        const int32_t v[5] = {e, cnt[3], cnt[64 + 3], left, n};
+        for (int i = 0; i < 5; ++i) __hip_atomic_store(host + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    const uint64_t bal = __ballot(win);
-    if ((threadIdx.x & 63) == 0 && bal) atomicAdd(&counts[1], (int32_t)__popcll(bal));
 }
 
 // Top-k: the winners of this round leave the election (level = round);
@@ -487,13 +497,17 @@ int prop_prepare(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32
 }
 
 // Rounds of forward/backward propagation, postprocessing and decisions
-// until no vertex still in is undecided.
+// until no vertex still in is undecided; then the winners (is_winner and
+// n_winners on the device, either may be null).  Each round is queued whole
+// and reports once: a sweep that gave up (labels are then incomplete, but
+// still labels) is found in the report, and nothing decided on it leaves the
+// workspace.
 template <typename E>
-int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, schulze_propagate_stats &st) {
+int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, schulze_propagate_stats &st,
+                    uint8_t *is_winner, int32_t *n_winners) {
     using K = typename Key<E>::K;
     int rc;
     const unsigned vb = (unsigned)ceil_div(m, 256);
-    int32_t counts[2] = {0, 0};
     for (int32_t round = 0; round < m; ++round) {
         {
             // counters and barrier cleared (adjacent), then the init and both directions' sweeps
@@ -517,6 +531,9 @@ int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, 
             a.m = m;
             a.status = b.status;
             a.label = b.label;
+            a.mark = b.mark;
+            a.dead = b.dead;
+            a.counts = b.tail + 16;
             int tok;
             timing_begin(ctx, K_PROP_SWEEP, s, &tok);
             k_prop_init<E><<<dim3((unsigned)std::min<int64_t>(vb, 1024)), dim3(256), 0, s>>>(a);
@@ -530,36 +547,27 @@ int prop_decide_all(schulze_ctx *ctx, hipStream_t s, int32_t m, PropBufs<E> &b, 
                 (void)hipGetLastError();
                 return SCHULZE_EDEVICE;
             }
-            int32_t sweeps[2] = {0, 0}, err = 0;
-            if (hipMemcpyAsync(&sweeps[0], b.cnt + 3, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipMemcpyAsync(&sweeps[1], b.cnt + 64 + 3, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipMemcpyAsync(&err, ctx->err, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess)
-                return SCHULZE_EDEVICE;
-            // a sweep that gave up (the word stays set for schulze_get_device_error)
-            // leaves no labels to decide on
-            if (err != SCHULZE_OK) return SCHULZE_EDEVICE;
-            st.sweeps += sweeps[0] + sweeps[1];
         }
-        // mark and dead are adjacent: clear both
-        if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(b.mark), 2 * b.bvec / 4, 0u)) != SCHULZE_OK) return rc;
-        if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(b.tail + 16), 2, 0u)) != SCHULZE_OK) return rc;
-        SCHULZE_LAUNCH(ctx, K_PROP, s, k_prop_post<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.vertex, b.mark));
         SCHULZE_LAUNCH(ctx, K_PROP, s,
-                       k_prop_pair<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.status, b.pair));
+                       k_prop_post<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.vertex, b.status, b.pair, b.mark));
         const E *wtc = sizeof(E) == 4 ? b.w : b.wt;  // rows of w^T, or of the signed weights
         SCHULZE_LAUNCH(ctx, K_PROP, s,
                        k_prop_cross<E><<<dim3((unsigned)ceil_div(m, 4)), dim3(256), 0, s>>>(wtc, m, b.pair, m, b.mark,
                                                                                             b.dead));
         SCHULZE_LAUNCH(ctx, K_PROP, s,
-                       k_prop_apply<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.mark, b.dead, b.status));
+                       k_prop_decide<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.label, b.mark, b.dead, b.status,
+                                                                       b.tail + 16));
         SCHULZE_LAUNCH(ctx, K_PROP, s,
-                       k_prop_decide<E><<<dim3(vb), dim3(256), 0, s>>>(b.kf, b.kb, m, b.label, b.status, b.tail + 16));
-        if (hipMemcpyAsync(counts, b.tail + 16, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return SCHULZE_EDEVICE;
+                       k_prop_report<<<dim3(1), dim3(1024), 0, s>>>(b.status, m, ctx->err, b.cnt, b.tail + 16, is_winner,
+                                                                    n_winners, ctx->host_dev));
+        if (hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
+        const int32_t *host = ctx->host;
+        // a sweep that gave up (the word stays set for schulze_get_device_error)
+        if (host[0] != SCHULZE_OK) return SCHULZE_EDEVICE;
+        st.sweeps += host[1] + host[2];
         ++st.rounds;
-        if (counts[0] == 0) return SCHULZE_OK;
+        st.n_winners = host[4];
+        if (host[3] == 0) return SCHULZE_OK;
     }
     return SCHULZE_EDEVICE;  // more rounds than candidates: cannot happen
 }
@@ -571,19 +579,7 @@ int run_propagate(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int3
     int rc = prop_prepare<E>(ctx, s, d, ldd, m, mode, use_borda, b);
     if (rc != SCHULZE_OK) return rc;
     schulze_propagate_stats st{};
-    if ((rc = prop_decide_all<E>(ctx, s, m, b, st)) != SCHULZE_OK) return rc;
-    const unsigned vb = (unsigned)ceil_div(m, 256);
-    int32_t counts[2] = {0, 0};
-    if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(b.tail + 16), 2, 0u)) != SCHULZE_OK) return rc;
-    SCHULZE_LAUNCH(ctx, K_PROP, s, k_prop_out<<<dim3(vb), dim3(256), 0, s>>>(b.status, m, is_winner, b.tail + 16));
-    if (hipMemcpyAsync(counts, b.tail + 16, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return SCHULZE_EDEVICE;
-    st.n_winners = counts[1];
-    if (n_winners &&
-        (hipMemcpyAsync(n_winners, &st.n_winners, sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
-         hipStreamSynchronize(s) != hipSuccess))
-        return SCHULZE_EDEVICE;
+    if ((rc = prop_decide_all<E>(ctx, s, m, b, st, is_winner, n_winners)) != SCHULZE_OK) return rc;
     if (stats) *stats = st;
     return SCHULZE_OK;
 }
@@ -601,14 +597,12 @@ int run_topk(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m
     schulze_topk_stats out{};
     schulze_propagate_stats st{};
     for (int32_t lv = 0;; ++lv) {
-        if ((rc = prop_decide_all<E>(ctx, s, m, b, st)) != SCHULZE_OK) return rc;
+        if ((rc = prop_decide_all<E>(ctx, s, m, b, st, nullptr, nullptr)) != SCHULZE_OK) return rc;
         if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(b.tail + 16), 2, 0u)) != SCHULZE_OK) return rc;
         SCHULZE_LAUNCH(ctx, K_PROP, s,
                        k_prop_remove<<<dim3(vb), dim3(256), 0, s>>>(b.status, m, lv, level, b.rem, b.tail + 16));
         int32_t counts[2] = {0, 0};
-        if (hipMemcpyAsync(counts, b.tail + 16, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return SCHULZE_EDEVICE;
+        if ((rc = read_words(ctx, s, {{b.tail + 16, 2}}, counts)) != SCHULZE_OK) return rc;
         if (counts[0] < 1) return SCHULZE_EDEVICE;  // every nonempty election has a winner
         out.levels = lv + 1;
         out.ranked += counts[0];
