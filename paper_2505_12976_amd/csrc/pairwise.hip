@@ -1113,14 +1113,19 @@ __global__ __launch_bounds__(256) void k_count_pairs(const void *__restrict__ ba
 // and then each candidate r's row of C^T (C[y][r] = weight of ballots
 // listing y before r) is accumulated in LDS from the ballot prefixes ahead
 // of its occurrences; d[r][y] = R_r - C[y][r] (plus any full-ranking
-// counts).  A candidate with at most OCC_CHUNK occurrences is one work item
+// counts).  A candidate with at most its chunk of occurrences is one work item
 // that writes its row of d at once; a heavier one is split into items that
 // write their partial rows to a buffer, summed by the finish.  Nothing here
 // needs the m x m accumulator unless full rankings are counted as well.
-constexpr int OCC_CHUNK = 8192;            // occurrences per accumulation item (<= 65535: packed counts)
+// Occurrences per accumulation item (at most 65535: packed counts): a quarter
+// of a workgroup's share of all, so that one item does not outlast the rest,
+// within these bounds (a heavier candidate's items each write a partial row).
+constexpr int OCC_CHUNK_MIN = 1024, OCC_CHUNK_MAX = 8192;
 constexpr int32_t OCC_MAX_M = 32768;       // an LDS row of counts
 constexpr int64_t OCC_MAX = (int64_t)1 << 27;  // occurrence buffer limit (entries)
 constexpr int OCC_FIN_COLS = 2048;         // columns per unit of the finish
+constexpr int OCC_QUEUES = 8, TICKET_STRIDE = 64;
+constexpr uint32_t NO_PARTIAL = 0xFFFFFFFFu;  // the only item of its row
 constexpr int FIN_COUNT = 5;               // meta.ctr slot: rows listed for the finish
 
 struct OccArgs {
@@ -1129,13 +1134,14 @@ struct OccArgs {
     int32_t L, m;
     int64_t n;
     int32_t tbits;        // occurrence word: ballot << tbits | position
-    int32_t row_vec;      // uint16 ids, even L, 4-byte aligned rows: rows read as 32-bit words (1), or as
-                          // 16-byte pieces (2: the ballots 16-byte aligned and n L ids whole pieces)
     const uint32_t *weight;
     Meta meta;
     uint32_t *hist;       // G x m: per-workgroup counts, then their exclusive prefix over workgroups
     uint32_t *row_start;  // m + 1: occurrences per candidate, then the exclusive scan
-    uint32_t *item_start; // m + 1: accumulation items per candidate, then the exclusive scan
+    uint4 *items;         // accumulation items: candidate, its occurrences [begin, end), partial row or NO_PARTIAL
+    uint32_t *item_start; // m + 1: accumulation items, exclusive scan
+    uint32_t *tickets;    // OCC_QUEUES counters of items handed out, TICKET_STRIDE words apart
+    uint32_t chunk;       // occurrences per accumulation item
     uint32_t *part_start; // m + 1: partial rows per candidate (its items if more than one), then the scan
     int32_t *fin;         // candidates whose rows the finish writes (no occurrences, or two or more items);
                           // their number in meta.ctr[FIN_COUNT]
@@ -1245,15 +1251,24 @@ __global__ __launch_bounds__(256) void k_occ_bucket(OccArgs a) {
     if (!PLACE) {
         __syncthreads();
         for (int32_t c = threadIdx.x; c < m; c += 256) a.hist[hrow + c] = cnt[c];
+    } else {
+        // the accumulation items, a candidate per thread
+        for (int32_t c = blockIdx.x * 256 + threadIdx.x; c < m; c += gridDim.x * 256) {
+            const uint32_t begin = a.row_start[c], end = a.row_start[c + 1], i0 = a.item_start[c];
+            const uint32_t n = a.item_start[c + 1] - i0, p0 = a.part_start[c];
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t b = begin + i * a.chunk;
+                a.items[i0 + i] = make_uint4((uint32_t)c, b, min(end, b + a.chunk), n > 1 ? p0 + i : NO_PARTIAL);
+            }
+        }
     }
 }
 
 // 64 candidates per workgroup, the G histogram rows split over COL_GROUPS
 // thread groups (enough loads in flight to stream the histograms):
 // hist[g][c] becomes its exclusive prefix over g; per candidate c,
-// row_start[c] = occurrences, item_start[c] = accumulation items,
-// part_start[c] = partial rows (its items when there are two or more), and
-// the candidates whose rows the finish writes are listed.
+// row_start[c] = occurrences, and the candidates whose rows the finish writes
+// are listed.
 constexpr int COL_GROUPS = 16;
 __global__ __launch_bounds__(64 * COL_GROUPS) void k_occ_columns(OccArgs a, int32_t G) {
     __shared__ uint32_t part[COL_GROUPS][64];
@@ -1275,266 +1290,292 @@ __global__ __launch_bounds__(64 * COL_GROUPS) void k_occ_columns(OccArgs a, int3
         run += h;
     }
     if (grp == COL_GROUPS - 1) {
-        const uint32_t items = (run + OCC_CHUNK - 1) / OCC_CHUNK;
+        const uint32_t items = (run + a.chunk - 1) / a.chunk;
         a.row_start[c] = run;
-        a.item_start[c] = items;
-        a.part_start[c] = items > 1 ? items : 0u;
         if (items != 1) a.fin[atomicAdd(&a.meta.ctr[FIN_COUNT], 1)] = c;
     }
 }
 
-// One workgroup of 1024 threads: exclusive scans of the three per-candidate
-// counts, totals at [m].  A thread takes `per` consecutive candidates, read
-// and written as 16-byte vectors when per is a multiple of 4 (at most
-// SCAN_VEC of them per array in registers), else one at a time.
+// One workgroup of 1024 threads: from the occurrences per candidate in
+// row_start, the exclusive prefixes of occurrences, accumulation items and
+// partial rows, totals at [m].  A thread takes `per` consecutive candidates
+// (a multiple of 4, at most 4 SCAN_VEC) as 16-byte loads that are all in
+// flight together; the three sums go through wavefront shuffles and one LDS
+// step (m = 32768: 30 us; three arrays read, three LDS scans of ten
+// barriers each: 78 us).
 constexpr int SCAN_VEC = 8;
+static_assert(4 * SCAN_VEC * 1024 >= OCC_MAX_M, "candidates per thread of the scan");
 __global__ __launch_bounds__(1024) void k_occ_scan(OccArgs a) {
-    __shared__ uint32_t part[3][1024];
+    __shared__ uint32_t part[3][16];
     if (a.meta.ctr[2] != MODE_SPARSE) return;
     const int32_t m = a.m;
-    const int32_t per = (m + 1023) / 1024;
-    const int32_t c0 = min(m, (int32_t)threadIdx.x * per), c1 = min(m, c0 + per);
-    uint32_t *arr[3] = {a.row_start, a.item_start, a.part_start};
+    const int32_t groups = (m + 4095) / 4096;  // of four candidates per thread
+    const int32_t c0 = 4 * groups * (int32_t)threadIdx.x;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint4 v[SCAN_VEC];  // (the array's rows are padded to 256 bytes)
+#pragma unroll
+    for (int k = 0; k < SCAN_VEC; ++k) {
+        const int32_t c = c0 + 4 * k;
+        v[k] = reinterpret_cast<const uint4 *>(a.row_start)[k < groups && c < m ? c / 4 : 0];
+    }
     uint32_t s[3] = {0u, 0u, 0u};
-    const bool vec = per % 4 == 0 && per / 4 <= SCAN_VEC && c1 - c0 == per;
-    uint4 v[3][SCAN_VEC];
-    if (vec) {
-        for (int q = 0; q < 3; ++q)
-            for (int k = 0; k < SCAN_VEC; ++k)
-                if (k < per / 4) v[q][k] = reinterpret_cast<const uint4 *>(arr[q] + c0)[k];
-        for (int q = 0; q < 3; ++q)
-            for (int k = 0; k < SCAN_VEC; ++k)
-                if (k < per / 4) s[q] += v[q][k].x + v[q][k].y + v[q][k].z + v[q][k].w;
-    } else {
-        for (int q = 0; q < 3; ++q)
-            for (int32_t c = c0; c < c1; ++c) s[q] += arr[q][c];
+    const uint32_t chunk = a.chunk;
+    auto items_of = [chunk](uint32_t occ) { return (occ + chunk - 1) / chunk; };
+    auto count = [&](uint32_t occ) {
+        const uint32_t it = items_of(occ);
+        s[0] += occ;
+        s[1] += it;
+        s[2] += it > 1 ? it : 0u;
+    };
+#pragma unroll
+    for (int k = 0; k < SCAN_VEC; ++k) {
+        const int32_t c = c0 + 4 * k;
+        if (k >= groups || c >= m) v[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (c + 1 >= m) v[k].y = 0u;
+        if (c + 2 >= m) v[k].z = 0u;
+        if (c + 3 >= m) v[k].w = 0u;
+        count(v[k].x), count(v[k].y), count(v[k].z), count(v[k].w);
     }
-    for (int q = 0; q < 3; ++q) part[q][threadIdx.x] = s[q];
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t add[3];
-        for (int q = 0; q < 3; ++q) add[q] = (int)threadIdx.x >= off ? part[q][threadIdx.x - off] : 0u;
-        __syncthreads();
-        for (int q = 0; q < 3; ++q) part[q][threadIdx.x] += add[q];
-        __syncthreads();
-    }
+    uint32_t run[3];  // inclusive over the wavefront, then exclusive over all
     for (int q = 0; q < 3; ++q) {
-        uint32_t run = part[q][threadIdx.x] - s[q];
-        if (vec) {
-            for (int k = 0; k < SCAN_VEC; ++k) {
-                if (k >= per / 4) break;
-                uint4 o;
-                o.x = run, run += v[q][k].x;
-                o.y = run, run += v[q][k].y;
-                o.z = run, run += v[q][k].z;
-                o.w = run, run += v[q][k].w;
-                reinterpret_cast<uint4 *>(arr[q] + c0)[k] = o;
-            }
-        } else {
-            for (int32_t c = c0; c < c1; ++c) {
-                const uint32_t x = arr[q][c];
-                arr[q][c] = run;
-                run += x;
-            }
+        run[q] = s[q];
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(run[q], off);
+            run[q] += lane >= off ? o : 0u;
         }
-        if (threadIdx.x == 1023) arr[q][m] = part[q][1023];
+        if (lane == 63) part[q][wv] = run[q];
     }
+    __syncthreads();
+    for (int q = 0; q < 3; ++q) {
+        run[q] -= s[q];
+        for (int w = 0; w < wv; ++w) run[q] += part[q][w];
+    }
+    uint32_t *const dst[3] = {a.row_start, a.item_start, a.part_start};
+#pragma unroll
+    for (int k = 0; k < SCAN_VEC; ++k) {
+        const int32_t c = c0 + 4 * k;
+        if (k >= groups || c >= m) break;
+        const uint32_t x[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+        uint32_t o[3][4];
+        for (int u = 0; u < 4; ++u) {
+            for (int q = 0; q < 3; ++q) o[q][u] = run[q];
+            const uint32_t it = items_of(x[u]);
+            run[0] += x[u];
+            run[1] += it;
+            run[2] += it > 1 ? it : 0u;
+        }
+        for (int q = 0; q < 3; ++q) {
+            if (c + 4 <= m)
+                *reinterpret_cast<uint4 *>(dst[q] + c) = make_uint4(o[q][0], o[q][1], o[q][2], o[q][3]);
+            else
+                for (int u = 0; u < 4 && c + u < m; ++u) dst[q][c + u] = o[q][u];
+        }
+    }
+    if (threadIdx.x == 1023)  // (its candidates come last, or it has none: all sums)
+        for (int q = 0; q < 3; ++q) dst[q][m] = run[q];
+    if (threadIdx.x < OCC_QUEUES) a.tickets[threadIdx.x * TICKET_STRIDE] = 0u;
 }
 
-// Accumulation item `blockIdx.x`: a chunk of one candidate r's occurrences.
-// For an occurrence of r at position t of ballot v, every id ahead of it
-// gains the voter's weight in the LDS row (C[id][r]), and r gains it in R.
-// PACKED (unit weights): two 16-bit counts per LDS word (an item adds at
-// most OCC_CHUNK to a column).  A thread takes its occurrences B at a time
-// and, for rows read as 32-bit words, issues every row load of the batch
-// before the first LDS update, so that many loads are in flight.  The only
-// item of a row writes the row of d (d[r][y] = base + R - C[y][r], base =
-// full-ranking counts in acc or 0); an item of a heavier row writes its
-// counts to its partial row and adds its part of R to rsum[r].
-template <int MAXM, bool PACKED, typename T, int WMAX, bool PIECES, bool I32>
+// Accumulation items: chunks of one candidate r's occurrences.  For an
+// occurrence of r at position t of ballot v, every id ahead of it gains the
+// voter's weight in the LDS row (C[id][r]), and r gains it in R.  PACKED
+// (unit weights): two 16-bit counts per LDS word (an item adds at most
+// OCC_CHUNK to a column).  The only item of a row writes the row of d
+// (d[r][y] = base + R - C[y][r], base = full-ranking counts in acc or 0); an
+// item of a heavier row writes its counts to its partial row and adds its
+// part of R to rsum[r].
+//
+// Most candidates have few occurrences, so an item is a chain of dependent
+// loads (item, occurrences, ballots) and then a row of d to write, with room
+// for two to four LDS rows on a CU to hide them.  The workgroups stay: each
+// takes every gridDim-th item (heavy candidates' items come in a run and fall
+// to different workgroups), loads the next item's occurrences while it adds
+// this one's ids and the next item's first ids while it writes this one's
+// row, and clears the LDS row as it reads it out.  Ids come 16 bytes at a
+// time at any alignment, as a scattered load costs its lane the same whatever
+// its width.
+//   m = 14187, 15553 ballots of up to 150 uint16 ids:  916 -> 464 us
+//   m = 16384, 1M ballots of up to 20, int32 d:        560 -> 550
+//   m = 32768, 200000 ballots of up to 30, int32 d:   1506 -> 869 (1073 through the caches)
+//   m = 6007, 100003 ballots of up to 12 int32 ids:    114 -> 49
+// (a workgroup per item, its row found by a binary search.)
+constexpr int OCC_BATCH = 2, OCC_FLY = 4;  // occurrences per thread, pieces of ids of each in flight
+template <int MAXM, bool PACKED, typename T, bool I32>
 __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict__ d, int64_t ldd, uint32_t limit,
                                                         uint8_t *__restrict__ over_flag, int acc_zero) {
     constexpr int WORDS = PACKED ? MAXM / 2 : MAXM;
-    constexpr int B = WMAX <= 16 ? 2 : 1;  // occurrences per batch
     __shared__ __attribute__((aligned(16))) uint32_t row[WORDS];
-    __shared__ uint32_t wsum;
-    __shared__ int32_t sh_r, sh_nitems, sh_k;
-    __shared__ uint32_t sh_b, sh_e;
+    __shared__ uint32_t wsum[2], ticket;
     if (a.meta.ctr[2] != MODE_SPARSE) return;
+    const uint32_t total = __builtin_amdgcn_readfirstlane(a.item_start[a.m]), G = gridDim.x;
+    if (blockIdx.x >= total) return;
     const int32_t m = a.m;
-    const uint32_t item = blockIdx.x;
-    if (item >= a.item_start[m]) return;
-    if (threadIdx.x == 0) {
-        // the candidate whose item range holds `item` (binary search)
-        int32_t lo = 0, hi = m - 1;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (a.item_start[mid] <= item) lo = mid; else hi = mid - 1;
-        }
-        const uint32_t k = item - a.item_start[lo];
-        const uint32_t b = a.row_start[lo] + k * OCC_CHUNK;
-        sh_r = lo;
-        sh_k = (int32_t)k;
-        sh_nitems = (int32_t)(a.item_start[lo + 1] - a.item_start[lo]);
-        sh_b = b;
-        sh_e = min(a.row_start[lo + 1], b + (uint32_t)OCC_CHUNK);
-        wsum = 0;
-    }
     const int32_t words = PACKED ? (m + 1) / 2 : m;
     const int32_t words4 = (words + 3) / 4;
     uint4 *row4 = reinterpret_cast<uint4 *>(row);
     for (int32_t c = threadIdx.x; c < words4; c += 256) row4[c] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    const int32_t r = sh_r;
+    if (threadIdx.x < 2) wsum[threadIdx.x] = 0u;
+
+    using Id = typename std::conditional<I32, int32_t, uint16_t>::type;
+    constexpr int V = 16 / (int)sizeof(Id);  // ids per piece
+    const Id *ids = static_cast<const Id *>(a.ballots);
+    const int64_t last = a.n * a.L - V;  // the last piece inside the ballots (negative: less than a piece in all)
     const uint32_t tmask = (1u << a.tbits) - 1u;
-    uint32_t wpart = 0;
-    bool dup = false;
-    auto add = [&](int32_t id, uint32_t w) {
-        if (id == r) dup = true;
-        if (id < 0 || id >= m) return;
+    struct Item {
+        uint32_t r, begin, end, partial;
+    };
+    auto item_of = [](const uint4 &q) {
+        return Item{(uint32_t)__builtin_amdgcn_readfirstlane(q.x), (uint32_t)__builtin_amdgcn_readfirstlane(q.y),
+                    (uint32_t)__builtin_amdgcn_readfirstlane(q.z), (uint32_t)__builtin_amdgcn_readfirstlane(q.w)};
+    };
+    // a thread's occurrences q and q + 256 of an item, and their first ids
+    auto occ_in = [&](uint32_t (&ov)[OCC_BATCH], uint32_t q, uint32_t end) {
+#pragma unroll
+        for (int u = 0; u < OCC_BATCH; ++u) ov[u] = a.occ[min(q + 256 * u, end - 1)];
+    };
+    int64_t base[OCC_BATCH];
+    int32_t t[OCC_BATCH];
+    uint32_t w[OCC_BATCH];
+    uint4 x[OCC_BATCH][OCC_FLY];
+    auto ids_in = [&](int32_t i0) {
+#pragma unroll
+        for (int u = 0; u < OCC_BATCH; ++u)
+#pragma unroll
+            for (int f = 0; f < OCC_FLY; ++f)
+                if (i0 + V * f < t[u] && last >= 0) x[u][f] = tio::load16<Id>(ids + min(base[u] + i0 + V * f, last));
+    };
+    auto begin_ids = [&](const uint32_t (&ov)[OCC_BATCH], uint32_t q, uint32_t end) {
+#pragma unroll
+        for (int u = 0; u < OCC_BATCH; ++u) {
+            const int64_t v = ov[u] >> a.tbits;
+            base[u] = v * a.L;
+            w[u] = q + 256 * u >= end ? 0u : (PACKED ? 1u : (a.weight ? a.weight[v] : 1u));
+            t[u] = w[u] ? (int32_t)(ov[u] & tmask) : 0;
+        }
+        ids_in(0);
+    };
+    bool dup = false, over = false;
+    uint32_t r = 0;
+    auto add = [&](int32_t id, uint32_t weight) {
+        if ((uint32_t)id == r) dup = true;
+        if ((uint32_t)id >= (uint32_t)m) return;
         if (PACKED)
             atomicAdd(&row[id >> 1], 1u << ((id & 1) * 16));
         else
-            atomicAdd(&row[id], w);
+            atomicAdd(&row[id], weight);
     };
-    constexpr int WN = WMAX > 0 ? WMAX : 1;
-    if (WMAX > 0 && PIECES) {
-        // uint16 ids, rows of even length, ballots 16-byte aligned and a
-        // whole number of 16-byte pieces: a row's words (two ids each) are
-        // read as the 16-byte pieces that hold them.  A scattered load costs
-        // the load path about a cycle per lane whatever its width, so an
-        // occurrence takes about two wide loads instead of one per word.
-        constexpr int NCH = (WMAX + 3) / 4 + 1;  // pieces that hold WMAX words at any offset
-        const uint32_t *words32 = static_cast<const uint32_t *>(a.ballots);
-        const int64_t wrow = a.L / 2;
-        constexpr int PB = 2;  // occurrences per thread in flight
-        for (uint32_t q0 = sh_b + threadIdx.x; q0 < sh_e; q0 += 256 * PB) {
-            uint32_t ov[PB];
+    auto add_ids = [&](int32_t i0) {
 #pragma unroll
-            for (int u = 0; u < PB; ++u) ov[u] = q0 + 256 * u < sh_e ? a.occ[q0 + 256 * u] : 0u;
-            uint32_t f[PB][4 * NCH];
-            int32_t tt[PB], sk[PB];
+        for (int u = 0; u < OCC_BATCH; ++u)
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int64_t v = ov[u] >> a.tbits;
-                tt[u] = q0 + 256 * u < sh_e ? (int32_t)(ov[u] & tmask) : 0;
-                const int32_t nw = (tt[u] + 1) / 2;
-                const uint32_t *rw = words32 + v * wrow;
-                sk[u] = (int32_t)((reinterpret_cast<uintptr_t>(rw) >> 2) & 3);  // words before the row
-                const uint4 *rc = reinterpret_cast<const uint4 *>(rw - sk[u]);
-                const int32_t nch = (sk[u] + nw + 3) >> 2;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    uint4 x = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-                    if (c < nch) x = rc[c];
-                    f[u][4 * c] = x.x, f[u][4 * c + 1] = x.y, f[u][4 * c + 2] = x.z, f[u][4 * c + 3] = x.w;
+            for (int f = 0; f < OCC_FLY; ++f) {
+                const int32_t i = i0 + V * f;
+                if (i >= t[u]) continue;
+                if (last < 0) {
+                    for (int32_t k = i; k < min(i + V, t[u]); ++k) add(read_id<I32>(a.ballots, base[u] + k), w[u]);
+                    continue;
                 }
+                // (the ballots' last piece may start before position i: skip to it)
+                const int32_t skip = (int32_t)max(base[u] + i - last, (int64_t)0), left = t[u] - i + skip;
+                Id e[V];
+                tio::unpack<Id>(x[u][f], e);
+#pragma unroll
+                for (int k = 0; k < V; ++k)
+                    if (k >= skip && k < left) add(raw_id<I32>((uint32_t)e[k]), w[u]);
             }
+    };
+
+    Item it = item_of(a.items[blockIdx.x]), next = item_of(a.items[min(blockIdx.x + G, total - 1)]);
+    uint32_t ov[OCC_BATCH];
+    occ_in(ov, it.begin + threadIdx.x, it.end);
+    begin_ids(ov, it.begin + threadIdx.x, it.end);
+    int parity = 0;
+    uint32_t *queue = a.tickets + (blockIdx.x % OCC_QUEUES) * TICKET_STRIDE;
+    uint32_t ahead = blockIdx.x + G;  // the next item's number
+    for (uint32_t item = blockIdx.x; item < total; parity ^= 1) {
+        occ_in(ov, next.begin + threadIdx.x, next.end);
+        uint32_t drawn = 0;
+        if (threadIdx.x == 0) drawn = atomicAdd(queue, 1u);
+        __syncthreads();  // the LDS row is clear
+        r = it.r;
+        uint32_t wpart = 0;
+        for (uint32_t q = it.begin + threadIdx.x;;) {
+            int32_t longest = 0;
+            add_ids(0);
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const bool ok = q0 + 256 * u < sh_e;
-                const uint32_t w = !ok ? 0u : (PACKED ? 1u : (a.weight ? a.weight[ov[u] >> a.tbits] : 1u));
-                wpart += w;
-                // word j of the row to f[u][j]: shifts by one and by two words
-                // under masks (opaque to the compiler, which would otherwise
-                // index the array by the offset and move it to scratch memory)
-                uint32_t m1 = (sk[u] & 1) ? 0xFFFFFFFFu : 0u, m2 = (sk[u] & 2) ? 0xFFFFFFFFu : 0u;
-                asm volatile("" : "+v"(m1), "+v"(m2));
+            for (int u = 0; u < OCC_BATCH; ++u) {
+                wpart += w[u];
+                longest = max(longest, t[u]);
+            }
+            for (int32_t i0 = V * OCC_FLY; i0 < longest; i0 += V * OCC_FLY) {
+                ids_in(i0);
+                add_ids(i0);
+            }
+            q += 256 * OCC_BATCH;
+            if (q >= it.end) break;
+            uint32_t more[OCC_BATCH];
+            occ_in(more, q, it.end);
+            begin_ids(more, q, it.end);
+        }
+        if (!PACKED && wpart) atomicAdd(&wsum[parity], wpart);
+        begin_ids(ov, next.begin + threadIdx.x, next.end);
+        if (threadIdx.x == 0) ticket = 2 * G + blockIdx.x % OCC_QUEUES + OCC_QUEUES * drawn;
+        __syncthreads();
+        item = ahead;
+        ahead = ticket;  // (written again only after the next barrier)
+        const uint4 after = a.items[min(ahead, total - 1)];
+        const uint32_t R = PACKED ? it.end - it.begin : wsum[parity];
+        if (threadIdx.x == 0) wsum[parity ^ 1] = 0u;
+        if (it.partial == NO_PARTIAL) {
+            // the row's only item: d[r][y] = base + R - C[y][r]; the finish skips the row
+            const uint32_t *arow = a.acc + (int64_t)r * a.lda;
+            T *drow = d + (int64_t)r * ldd;
+            constexpr int C = 16 / (int)sizeof(T);         // columns per store
+            constexpr int CW = PACKED ? C / 2 : C;         // their LDS words
+            auto value = [&](uint32_t cnt, uint32_t full, int32_t y) -> uint32_t {
+                const uint32_t v = y == (int32_t)r ? 0u : full - cnt + R;
+                over |= v > limit;
+                return min(v, limit);
+            };
+            for (int32_t y = C * threadIdx.x; y < m; y += C * 256) {
+                uint32_t cw[CW];
+                uint32_t *rw = row + (PACKED ? y / 2 : y);
+                if (y + C <= m) {
 #pragma unroll
-                for (int j = 0; j + 1 < 4 * NCH; ++j) f[u][j] = (f[u][j] & ~m1) | (f[u][j + 1] & m1);
+                    for (int k = 0; k < CW; ++k) cw[k] = rw[k];
 #pragma unroll
-                for (int j = 0; j + 2 < 4 * NCH; ++j) f[u][j] = (f[u][j] & ~m2) | (f[u][j + 2] & m2);
+                    for (int k = 0; k < CW; ++k) rw[k] = 0u;
+                    T o[C];
 #pragma unroll
-                for (int j = 0; j < WMAX; ++j) {
-                    if (2 * j < tt[u] && w != 0) {
-                        add((int32_t)(f[u][j] & 0xFFFFu), w);
-                        if (2 * j + 1 < tt[u]) add((int32_t)(f[u][j] >> 16), w);
+                    for (int k = 0; k < C; ++k) {
+                        const uint32_t cnt = PACKED ? (cw[k / 2] >> (16 * (k & 1))) & 0xFFFFu : cw[k % CW];
+                        o[k] = (T)value(cnt, acc_zero ? 0u : arow[y + k], y + k);
                     }
+                    tio::stream16<T>(drow + y, tio::pack<T>(o));
+                } else {
+                    for (int32_t yy = y; yy < m; ++yy) {
+                        const uint32_t cnt = PACKED ? (row[yy >> 1] >> ((yy & 1) * 16)) & 0xFFFFu : row[yy];
+                        drow[yy] = (T)value(cnt, acc_zero ? 0u : arow[yy], yy);
+                    }
+                    for (int32_t k = 0; k < (PACKED ? (m - y + 1) / 2 : m - y); ++k) rw[k] = 0u;
                 }
             }
-        }
-    } else if (WMAX > 0 && a.row_vec) {
-        // uint16 ids, rows of even length read as 32-bit words (two ids each)
-        const uint32_t *words32 = static_cast<const uint32_t *>(a.ballots);
-        const int64_t wrow = a.L / 2;
-        for (uint32_t q0 = sh_b + threadIdx.x; q0 < sh_e; q0 += 256 * B) {
-            uint32_t ov[B];
-            for (int u = 0; u < B; ++u) ov[u] = q0 + 256 * u < sh_e ? a.occ[q0 + 256 * u] : 0u;
-            uint32_t wd[B][WN];
-            int32_t tt[B];
-            uint32_t ww[B];
-            for (int u = 0; u < B; ++u) {
-                const bool ok = q0 + 256 * u < sh_e;
-                const int64_t v = ov[u] >> a.tbits;
-                tt[u] = ok ? (int32_t)(ov[u] & tmask) : 0;
-                ww[u] = ok ? (PACKED ? 1u : (a.weight ? a.weight[v] : 1u)) : 0u;
-                const int32_t nw = (tt[u] + 1) / 2;
-                const uint32_t *rw = words32 + v * wrow;
-                for (int j = 0; j < WN; ++j) wd[u][j] = j < nw ? rw[j] : 0xFFFFFFFFu;
+        } else {
+            // an item of a heavier row: its partial row (same element layout as the LDS row)
+            uint4 *prow = reinterpret_cast<uint4 *>(static_cast<uint32_t *>(a.partial) +
+                                                    (int64_t)it.partial * (a.ppitch * (PACKED ? 1 : 2) / 2));
+            for (int32_t c = threadIdx.x; c < words4; c += 256) {
+                prow[c] = row4[c];
+                row4[c] = make_uint4(0u, 0u, 0u, 0u);
             }
-            for (int u = 0; u < B; ++u) {
-                wpart += ww[u];
-                if (ww[u] == 0) continue;
-                for (int j = 0; j < WN; ++j) {
-                    if (2 * j >= tt[u]) break;
-                    const uint32_t x = wd[u][j];
-                    add((int32_t)(x & 0xFFFFu), ww[u]);
-                    if (2 * j + 1 < tt[u]) add((int32_t)(x >> 16), ww[u]);
-                }
-            }
+            if (threadIdx.x == 0 && R) atomicAdd(&a.rsum[r], R);
         }
-    } else {
-        for (uint32_t q = sh_b + threadIdx.x; q < sh_e; q += 256) {
-            const uint32_t ovq = a.occ[q];
-            const int64_t v = ovq >> a.tbits;
-            const int32_t t = (int32_t)(ovq & tmask);
-            const uint32_t w = PACKED ? 1u : (a.weight ? a.weight[v] : 1u);
-            wpart += w;
-            if (w == 0) continue;
-            const int64_t base = v * a.L;
-            // sixteen ids in flight, every load unconditional (positions past t
-            // repeat the last one and are not added)
-            for (int32_t i0 = 0; i0 < t; i0 += 16) {
-                uint32_t raw[16];
-                for (int u = 0; u < 16; ++u) raw[u] = load_raw<I32>(a.ballots, base + min(i0 + u, t - 1));
-                for (int u = 0; u < 16; ++u)
-                    if (i0 + u < t) add(raw_id<I32>(raw[u]), w);
-            }
-        }
+        it = next;
+        next = item_of(after);
     }
-    if (wpart) atomicAdd(&wsum, wpart);
     if (__ballot(dup) && (threadIdx.x & 63) == 0) set_device_error(a.err, SCHULZE_EBALLOT);
-    __syncthreads();
-    if (sh_nitems == 1) {
-        // the row's only item: d[r][y] = base + R - C[y][r]; the finish skips the row
-        const uint32_t R = wsum;
-        const uint32_t *arow = a.acc + (int64_t)r * a.lda;
-        bool over = false;
-        T *drow = d + (int64_t)r * ldd;
-        for (int32_t y = 8 * threadIdx.x; y < m; y += 8 * 256) {  // eight columns per thread and step
-            uint32_t v[8];
-            for (int e = 0; e < 8; ++e) {
-                const int32_t yy = y + e;
-                v[e] = 0u;
-                if (yy >= m || yy == r) continue;
-                const uint32_t cnt = PACKED ? (row[yy >> 1] >> ((yy & 1) * 16)) & 0xFFFFu : row[yy];
-                v[e] = (acc_zero ? 0u : arow[yy]) - cnt + R;
-                if (v[e] > limit) {
-                    over = true;
-                    v[e] = limit;
-                }
-            }
-            store8<T>(drow, y, m, v);
-        }
-        // reported by the finish, after every ballot error of this launch
-        if (over) over_flag[0] = 1;
-        return;
-    }
-    // an item of a heavier row: its partial row (same element layout as the LDS row)
-    uint4 *prow = reinterpret_cast<uint4 *>(static_cast<uint32_t *>(a.partial) +
-                                            (int64_t)(a.part_start[r] + sh_k) * (a.ppitch * (PACKED ? 1 : 2) / 2));
-    for (int32_t c = threadIdx.x; c < words4; c += 256) prow[c] = row4[c];
-    if (threadIdx.x == 0 && wsum) atomicAdd(&a.rsum[r], wsum);
+    // reported by the finish, after every ballot error of this launch
+    if (over) over_flag[0] = 1;
 }
 
 // Rows the accumulation items did not finish: candidates without
@@ -1717,12 +1758,13 @@ struct MetaLayout {
 // Byte layout of WS_OCC for G bucketing workgroups, m candidates and at
 // most cap occurrences.
 // Partial rows: every item of a candidate with two or more items has one,
-// and such a candidate has more than OCC_CHUNK occurrences, so there are at
+// and such a candidate has more than its chunk of occurrences, so there are at
 // most 2 cap / OCC_CHUNK of them.
 struct OccLayout {
-    size_t hist, row_start, item_start, part_start, fin, occ, partial, total;
+    size_t hist, row_start, items, item_start, tickets, part_start, fin, occ, partial, total;
     int64_t ppitch, max_parts;
-    OccLayout(int64_t G, int32_t m, int64_t cap, size_t partial_elem) {
+    uint32_t chunk;  // occurrences per accumulation item, of at most cap, for this many workgroups
+    OccLayout(int64_t G, int32_t m, int64_t cap, size_t partial_elem, int64_t workgroups) {
         size_t o = 0;
         auto take = [&](size_t bytes) {
             size_t at = o;
@@ -1730,10 +1772,13 @@ struct OccLayout {
             return at;
         };
         ppitch = round_up(m, 8);
-        max_parts = cap > 0 ? 2 * ceil_div(cap, OCC_CHUNK) + 1 : 0;
+        chunk = (uint32_t)std::min<int64_t>(OCC_CHUNK_MAX, std::max<int64_t>(OCC_CHUNK_MIN, cap / (4 * workgroups)));
+        max_parts = cap > 0 ? 2 * ceil_div(cap, chunk) + 1 : 0;
         hist = take(sizeof(uint32_t) * (size_t)G * m);
         row_start = take(sizeof(uint32_t) * ((size_t)m + 1));
+        items = take(sizeof(uint4) * ((size_t)m + (size_t)ceil_div(cap, chunk)));
         item_start = take(sizeof(uint32_t) * ((size_t)m + 1));
+        tickets = take(sizeof(uint32_t) * OCC_QUEUES * TICKET_STRIDE);
         part_start = take(sizeof(uint32_t) * ((size_t)m + 1));
         occ = take(sizeof(uint32_t) * (size_t)cap);
         partial = take(partial_elem * (size_t)max_parts * (size_t)ppitch);
@@ -1763,45 +1808,17 @@ int occ_bucket(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 g) {
 
 // The accumulation and finish launches for the counter type T of d: packed
 // 16-bit LDS counts for unit weights, 32-bit ones otherwise; the LDS row fits
-// m; rows read as 32-bit words when the layout allows (WMAX words at most).
+// m.
 template <typename T, int MAXM, bool PACKED>
 int occ_accumulate_m(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid, T *d, int64_t ldd,
                      uint32_t limit, uint8_t *over_flag, int az) {
     const dim3 b(256);
-    if constexpr (PACKED) {
-        if (oa.row_vec == 2 && oa.L <= 32) {
-            SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                           (k_occ_accumulate<MAXM, PACKED, T, 16, true, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                          az)));
-            return SCHULZE_OK;
-        }
-        if (oa.row_vec == 2 && oa.L <= 64) {
-            SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                           (k_occ_accumulate<MAXM, PACKED, T, 32, true, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                          az)));
-            return SCHULZE_OK;
-        }
-        if (oa.row_vec && oa.L <= 32) {
-            SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                           (k_occ_accumulate<MAXM, PACKED, T, 16, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                           az)));
-            return SCHULZE_OK;
-        }
-        if (oa.row_vec && oa.L <= 64) {
-            SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                           (k_occ_accumulate<MAXM, PACKED, T, 32, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag,
-                                                                                           az)));
-            return SCHULZE_OK;
-        }
-    }
     if (oa.dtype32)
         SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                       (k_occ_accumulate<MAXM, PACKED, T, 0, false, true><<<grid, b, 0, s>>>(oa, d, ldd, limit,
-                                                                                             over_flag, az)));
+                       (k_occ_accumulate<MAXM, PACKED, T, true><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag, az)));
     else
         SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s,
-                       (k_occ_accumulate<MAXM, PACKED, T, 0, false, false><<<grid, b, 0, s>>>(oa, d, ldd, limit,
-                                                                                              over_flag, az)));
+                       (k_occ_accumulate<MAXM, PACKED, T, false><<<grid, b, 0, s>>>(oa, d, ldd, limit, over_flag, az)));
     return SCHULZE_OK;
 }
 
@@ -1809,7 +1826,6 @@ template <typename T>
 int occ_accumulate(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid, int32_t m, bool weighted, T *d,
                    int64_t ldd, uint32_t limit, uint8_t *over_flag, bool acc_zero) {
     const int az = acc_zero ? 1 : 0;
-    // rows of d 16-byte aligned: eight columns per 16-byte store (uint16) or two (int32)
     int rc;
     if (!weighted && m <= OCC_MAX_M / 2)
         rc = occ_accumulate_m<T, OCC_MAX_M / 2, true>(ctx, s, oa, grid, d, ldd, limit, over_flag, az);
@@ -1990,7 +2006,10 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     const int64_t occ_cap = n * (int64_t)L;
     const bool occ_ok = n > 0 && m <= OCC_MAX_M && occ_cap <= OCC_MAX && !ctx->legacy_pairs;
     const int64_t occ_grid = (int64_t)ctx->num_cus * (m <= OCC_MAX_M / 2 ? 2 : 1);
-    const OccLayout ol(occ_ok ? occ_grid : 0, m, occ_ok ? occ_cap : 0, voter_weight ? 4 : 2);
+    // as many accumulation workgroups as LDS rows fit the CUs (160 KB each; at most four by registers)
+    const int64_t acc_row = (m <= OCC_MAX_M / 2 ? OCC_MAX_M / 2 : OCC_MAX_M) * (voter_weight ? 4 : 2) + 256;
+    const int64_t acc_grid = ctx->num_cus * std::min<int64_t>(4, 160 * 1024 / acc_row);
+    const OccLayout ol(occ_ok ? occ_grid : 0, m, occ_ok ? occ_cap : 0, voter_weight ? 4 : 2, acc_grid);
     if (occ_ok && (rc = ws_reserve(ctx, WS_OCC, ol.total)) != SCHULZE_OK) return rc;
 
     char *mb = static_cast<char *>(ctx->ws[WS_BALLOT_META]);
@@ -2065,13 +2084,12 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
             char *ob = static_cast<char *>(ctx->ws[WS_OCC]);
             int32_t tbits = 0;
             while ((1 << tbits) < L) ++tbits;
-            const bool pieces = reinterpret_cast<uintptr_t>(ballots) % 16 == 0 && (n * L) % 8 == 0;
-            const int row_vec =
-                !dtype32 && L % 2 == 0 && reinterpret_cast<uintptr_t>(ballots) % 4 == 0 ? (pieces ? 2 : 1) : 0;
-            OccArgs oa{ballots, dtype32, L, m, n, tbits, row_vec, voter_weight, meta,
+            OccArgs oa{ballots, dtype32, L, m, n, tbits, voter_weight, meta,
                        reinterpret_cast<uint32_t *>(ob + ol.hist),
                        reinterpret_cast<uint32_t *>(ob + ol.row_start),
+                       reinterpret_cast<uint4 *>(ob + ol.items),
                        reinterpret_cast<uint32_t *>(ob + ol.item_start),
+                       reinterpret_cast<uint32_t *>(ob + ol.tickets), ol.chunk,
                        reinterpret_cast<uint32_t *>(ob + ol.part_start),
                        reinterpret_cast<int32_t *>(ob + ol.fin),
                        reinterpret_cast<uint32_t *>(ob + ol.occ),
@@ -2084,7 +2102,7 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
                            k_occ_columns<<<dim3((unsigned)ceil_div(m, 64)), dim3(64 * COL_GROUPS), 0, s>>>(
                                oa, (int32_t)occ_grid));
             SCHULZE_LAUNCH(ctx, K_COUNT_SPARSE, s, k_occ_scan<<<dim3(1), dim3(1024), 0, s>>>(oa));
-            const dim3 ig((unsigned)(m + ceil_div(occ_cap, OCC_CHUNK)));
+            const dim3 ig((unsigned)acc_grid);
             if ((rc = occ_bucket<true>(ctx, s, oa, g)) != SCHULZE_OK) return rc;
             if (d_dtype == SCHULZE_U16) {
                 if ((rc = occ_accumulate<uint16_t>(ctx, s, oa, ig, m, voter_weight != nullptr, (uint16_t *)d, ldd,

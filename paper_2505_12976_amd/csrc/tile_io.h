@@ -37,6 +37,12 @@ template <typename E>
 __device__ __forceinline__ void store16(E *p, const uint4 &v) {
     *reinterpret_cast<typename Any16<E>::type *>(p) = typename Any16<E>::type{v.x, v.y, v.z, v.w};
 }
+// The same past the caches, for an output larger than they are.
+template <typename E>
+__device__ __forceinline__ void stream16(E *p, const uint4 &v) {
+    __builtin_nontemporal_store(typename Any16<E>::type{v.x, v.y, v.z, v.w},
+                                reinterpret_cast<typename Any16<E>::type *>(p));
+}
 
 // The V elements of a 16-byte vector.
 template <typename E>
