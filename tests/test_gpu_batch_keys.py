@@ -7,7 +7,7 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 2, 31, 33, 63, 64, 65, 96, 97, 128, 129, 192, 193, 257]
+SIZES = [1, 2, 16, 17, 31, 33, 48, 49, 63, 64, 65, 96, 97, 128, 129, 192, 193, 257]
 
 
 @pytest.fixture(scope="module")
