@@ -97,7 +97,7 @@ struct Cfg {
     static constexpr int TM = B / 16;
     static constexpr int TN = B / 16;
     static constexpr int WN = TN / PER;
-    static constexpr int KC = sizeof(E) == 2 ? (B < 64 ? B : 64) : 32;  // k per LDS stage
+    static constexpr int KC = B <= 64 ? B : (sizeof(E) == 2 ? 64 : 32);  // k per LDS stage
     static constexpr int LA = KC + 16 / (int)sizeof(E);                 // padded pitches keep
     static constexpr int LB = B + 16 / (int)sizeof(E);                  // 16-byte row alignment
     static constexpr int LDS_ELEMS = B * LA + KC * LB;
@@ -306,9 +306,38 @@ __device__ inline void acc_product(Acc<E, B> &a, PA A, int64_t lda, PB Bm, int64
     E *As = lds;
     E *Bs = lds + B * LA;
     for (int kc = 0; kc < B; kc += KC) {
-        __syncthreads();
-        copy_block<E>(As, LA, A + kc, lda, B, KC);
-        copy_block<E>(Bs, LB, Bm + (int64_t)kc * ldb, ldb, KC, B);
+        if constexpr (B >= 64) {
+            // both operands' loads in flight before the barrier and the first
+            // LDS write (one round trip to memory per stage, not two)
+            constexpr int V = 16 / (int)sizeof(E), VA = KC / V, VB = B / V;
+            constexpr int NA = B * VA / 256, NB = KC * VB / 256;
+            v4u32 ra[NA], rb[NB];
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                const int v = threadIdx.x + 256 * u;
+                ra[u] = *retype<const v4u32>(A + kc + (int64_t)(v / VA) * lda + v % VA * V);
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int v = threadIdx.x + 256 * u;
+                rb[u] = *retype<const v4u32>(Bm + (int64_t)(kc + v / VB) * ldb + v % VB * V);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                const int v = threadIdx.x + 256 * u;
+                *reinterpret_cast<v4u32 *>(As + v / VA * LA + v % VA * V) = ra[u];
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int v = threadIdx.x + 256 * u;
+                *reinterpret_cast<v4u32 *>(Bs + v / VB * LB + v % VB * V) = rb[u];
+            }
+        } else {
+            __syncthreads();
+            copy_block<E>(As, LA, A + kc, lda, B, KC);
+            copy_block<E>(Bs, LB, Bm + (int64_t)kc * ldb, ldb, KC, B);
+        }
         __syncthreads();
         if constexpr (sizeof(E) == 4) {
             // four k per step: A values come as one 16-byte read per row
