@@ -167,6 +167,18 @@ __device__ inline void acc_store(const Acc<E, B> &a, DstP dst, int64_t ld) {
     }
 }
 
+// The accumulator as a row-by-row B x B tile in LDS.
+template <typename E, int B>
+__device__ inline void acc_to_lds(const Acc<E, B> &a, FW_LDS E *tile) {
+    using C = Cfg<E, B>;
+    using W = typename Lane<E>::W;
+    const int t = lane_tid(), tx = t & 15, ty = t >> 4;
+    for (int ii = 0; ii < C::TM; ++ii) {
+        FW_LDS W *row = (FW_LDS W *)(tile + (ty * C::TM + ii) * B + tx * C::TN);
+        for (int jj = 0; jj < C::WN; ++jj) row[jj] = a.c[ii][jj];
+    }
+}
+
 // Element e (0 or 1) of a 32-bit word.
 template <typename E>
 __device__ __forceinline__ E half_of(uint32_t word, int e) {
@@ -524,7 +536,7 @@ struct Diag {
     }
 };
 
-template <typename E, int B, int S, bool STAGE, typename SrcP, typename DstP>
+template <typename E, int B, int S, bool STAGE, bool PRE, typename SrcP, typename DstP>
 __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, int64_t lds_, DstP dst, int64_t ldd_,
                                                                  E *__restrict__ dst2, int64_t ldd2, E *buf) {
     using D = Diag<E, B, S>;
@@ -539,7 +551,7 @@ __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, 
     if constexpr (STAGE) {
         // through LDS: 16-byte loads of the tile, then each thread takes its
         // strided elements (few registers in flight)
-        {
+        if constexpr (!PRE) {
             constexpr int V = 16 / (int)sizeof(E);
             constexpr int VPR = B / V;
 #pragma unroll 4
@@ -547,8 +559,8 @@ __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, 
                 const int r = q / VPR, cv = q % VPR;
                 *(FW_LDS v4u32 *)(lb + r * B + cv * V) = *retype<const v4u32>(src + (int64_t)r * lds_ + cv * V);
             }
+            __syncthreads();
         }
-        __syncthreads();
         for (int a = 0; a < D::RA; ++a) {
             const FW_LDS E *row = lb + (ty + 16 * a) * B + tx;
             for (int c = 0; c < D::WC; ++c) {
@@ -611,10 +623,10 @@ __device__ __attribute__((always_inline)) inline void diag_close_body(SrcP src, 
     __syncthreads();
 }
 
-template <typename E, int B, int S, bool STAGE, typename SrcP, typename DstP>
+template <typename E, int B, int S, bool STAGE, bool PRE, typename SrcP, typename DstP>
 __device__ __attribute__((noinline)) void diag_close_call(SrcP src, int64_t lds_, DstP dst, int64_t ldd_,
                                                           E *__restrict__ dst2, int64_t ldd2, E *buf) {
-    diag_close_body<E, B, S, STAGE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
+    diag_close_body<E, B, S, STAGE, PRE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
 }
 
 // LDS elements diag_close<E, B, S, STAGE> needs (16-byte aligned): the
@@ -629,16 +641,18 @@ constexpr int diag_lds_elems() {
 // workgroups read); buf holds diag_lds_elems<E, B, S, STAGE>() elements of
 // LDS.  With STAGE the tile moves between memory and registers through LDS
 // as 16-byte vectors (src, dst and dst2 rows 16-byte aligned); without, each
-// thread reads and writes its own strided elements.  Small tiles are
+// thread reads and writes its own strided elements.  PRE (with STAGE): the
+// tile is in buf already, row by row (acc_to_lds), and src is not read.  Small tiles are
 // inlined; the larger ones are a call of their own, so that their register
 // demand is not added to the caller's.
-template <typename E, int B, int S = diag_steps<E, B>(), bool STAGE = false, typename SrcP, typename DstP>
+template <typename E, int B, int S = diag_steps<E, B>(), bool STAGE = false, bool PRE = false, typename SrcP,
+          typename DstP>
 __device__ __attribute__((always_inline)) inline void diag_close(SrcP src, int64_t lds_, DstP dst, int64_t ldd_,
                                                             E *__restrict__ dst2, int64_t ldd2, E *buf) {
     if constexpr (B >= 128)
-        diag_close_call<E, B, S, STAGE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
+        diag_close_call<E, B, S, STAGE, PRE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
     else
-        diag_close_body<E, B, S, STAGE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
+        diag_close_body<E, B, S, STAGE, PRE>(src, lds_, dst, ldd_, dst2, ldd2, buf);
 }
 
 }  // namespace fw
