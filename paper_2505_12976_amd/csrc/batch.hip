@@ -687,19 +687,7 @@ struct Stream64 {
                 v2u32{__builtin_bit_cast(uint32_t, c.c[i][0]), __builtin_bit_cast(uint32_t, c.c[i][1])};
     }
 
-    __device__ static W lo(W x, W y) {
-        if constexpr (__is_same(E, _Float16)) return __builtin_elementwise_minimum(x, y);
-        else return __builtin_elementwise_min(x, y);
-    }
-    __device__ static W hi(W x, W y) {
-        if constexpr (__is_same(E, _Float16)) return __builtin_elementwise_maximum(x, y);
-        else return __builtin_elementwise_max(x, y);
-    }
-
-    struct Step {  // four k: this thread's A rows and B columns
-        v2u32 a[4];
-        W b[4][2];
-    };
+    using Step = Step64<E>;
     __device__ static void step_in(Step &s, const FW_LDS E *As, const FW_LDS E *Bs, int k, int tx, int ty) {
         const int piece = (k >> 3) ^ ((ty & 3) << 1);
         for (int i = 0; i < 4; ++i) s.a[i] = *(const FW_LDS v2u32 *)(As + (4 * ty + i) * 64 + piece * 8 + (k & 7));
@@ -708,21 +696,6 @@ struct Stream64 {
             s.b[q][0] = b[0];
             s.b[q][1] = b[1];
         }
-    }
-    __device__ static void step(Acc<E, 64> &c, const Step &s) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t word = h ? s.a[i].y : s.a[i].x;
-                const W a0 = L::splat(half_of<E>(word, 0)), a1 = L::splat(half_of<E>(word, 1));
-                W t0[2], t1[2];
-                for (int j = 0; j < 2; ++j) {
-                    t0[j] = lo(a0, s.b[2 * h][j]);
-                    t1[j] = lo(a1, s.b[2 * h + 1][j]);
-                }
-                for (int j = 0; j < 2; ++j) c.c[i][j] = hi(hi(c.c[i][j], t0[j]), t1[j]);
-            }
     }
     // c = max(c, A (x) B); the next step's operands are read before this one's products
     __device__ static void product(Acc<E, 64> &c, const FW_LDS E *As, const FW_LDS E *Bs) {
@@ -735,13 +708,13 @@ struct Stream64 {
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0xC47F);  // lgkmcnt(4): s0 is in (a step is four LDS reads)
             __builtin_amdgcn_sched_barrier(0);
-            step(c, s0);
+            s0.add(c);
             __builtin_amdgcn_sched_barrier(0);
             step_in(s0, As, Bs, (k + 8) & 63, tx, ty);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0xC47F);
             __builtin_amdgcn_sched_barrier(0);
-            step(c, s1);
+            s1.add(c);
             __builtin_amdgcn_sched_barrier(0);
         }
     }

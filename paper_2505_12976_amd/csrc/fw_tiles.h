@@ -250,6 +250,52 @@ __device__ __forceinline__ void step4_16(Acc<E, B> &a, const v2u32 (&av)[Cfg<E, 
     }
 }
 
+// Four k of the 16-bit product with B = 64: this thread's four A rows (four k
+// each) and four B rows (its four columns), read a step ahead of their use.
+template <typename E>
+struct Step64 {
+    using L = Lane<E>;
+    using W = typename L::W;
+    v2u32 a[4];
+    W b[4][2];
+    __device__ static W lo(W x, W y) {
+        if constexpr (__is_same(E, _Float16))
+            return __builtin_elementwise_minimum(x, y);
+        else
+            return __builtin_elementwise_min(x, y);
+    }
+    __device__ static W hi(W x, W y) {
+        if constexpr (__is_same(E, _Float16))
+            return __builtin_elementwise_maximum(x, y);
+        else
+            return __builtin_elementwise_max(x, y);
+    }
+    // A rows at as (pitch lda), B rows at bs (pitch ldb)
+    __device__ void load(const FW_LDS E *as, int lda, const FW_LDS E *bs, int ldb) {
+        for (int i = 0; i < 4; ++i) a[i] = *(const FW_LDS v2u32 *)(as + i * lda);
+        for (int q = 0; q < 4; ++q) {
+            const FW_LDS W *r = (const FW_LDS W *)(bs + q * ldb);
+            b[q][0] = r[0];
+            b[q][1] = r[1];
+        }
+    }
+    __device__ void add(Acc<E, 64> &c) const {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t word = h ? a[i].y : a[i].x;
+                const W a0 = L::splat(half_of<E>(word, 0)), a1 = L::splat(half_of<E>(word, 1));
+                W t0[2], t1[2];
+                for (int j = 0; j < 2; ++j) {
+                    t0[j] = lo(a0, b[2 * h][j]);
+                    t1[j] = lo(a1, b[2 * h + 1][j]);
+                }
+                for (int j = 0; j < 2; ++j) c.c[i][j] = hi(hi(c.c[i][j], t0[j]), t1[j]);
+            }
+    }
+};
+
 // Direct-to-LDS staging of the 16-bit product with B = 128: chunks of 32 k
 // (an A chunk of B rows x 64 bytes and a B chunk of 32 rows x 256 bytes),
 // double buffered, so that the next chunk streams into LDS while the
@@ -374,6 +420,23 @@ __device__ inline void acc_product(Acc<E, B> &a, PA A, int64_t lda, PB Bm, int64
                         a.c[ii][jj] = max(max(c1, m2), m3);
                     }
                 }
+            }
+        } else if constexpr (B == 64) {
+            // the next four k's operands are read before this step's products
+            const FW_LDS E *as = (const FW_LDS E *)As + ty * TM * LA, *bs = (const FW_LDS E *)Bs + tx * TN;
+            Step64<E> s0, s1;
+            s0.load(as, LA, bs, LB);
+#pragma unroll 1
+            for (int k = 0; k < KC; k += 8) {
+                s1.load(as + k + 4, LA, bs + (k + 4) * LB, LB);
+                __builtin_amdgcn_sched_barrier(0);
+                s0.add(a);
+                __builtin_amdgcn_sched_barrier(0);
+                const int kn = (k + 8) % KC;  // (the last step reads the first again)
+                s0.load(as + kn, LA, bs + kn * LB, LB);
+                __builtin_amdgcn_sched_barrier(0);
+                s1.add(a);
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             // four k per step: A values come as one 8-byte read per row
