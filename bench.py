@@ -308,12 +308,12 @@ def bench_single(args, wl):
     count_ms = sum(kern.get(k, {}).get("ms_per_step", 0.0) for k in COUNT_KERNELS)
     bits = ctx.closure_value_bits()
     ranked = dcode == "i32" and bits == 16
-    # the persistent closure kernel: uint16 (or ranks) 1 lane-op per update
-    # (v_pk_min_u16 + v_pk_max_u16 on two columns); int32 1.5 (v_min_i32 on
-    # two k, one v_max3_i32).  An int32 closure queues both variants gated by
+    # the persistent closure kernel: uint16 (or ranks) 0.75 lane-ops per update
+    # (half-precision keys: for two k and two columns two v_pk_minimum3_f16 and
+    # one v_pk_maximum3_f16); int32 1.5 (v_min_i32 on two k, one v_max3_i32).  An int32 closure queues both variants gated by
     # the device's ranking decision; the one not taken returns at once, so the
     # kernel time per closure is the sum of both launches.
-    ops_per_update = 1.0 if bits == 16 else 1.5
+    ops_per_update = 0.75 if bits == 16 else 1.5
     persist_ms = kern.get("fw_persist", {}).get("ms_per_step", 0.0)
     roof = None
     if persist_ms > 0:
@@ -655,16 +655,20 @@ def bench_batch(args):
             bad += got != gold["elections"][e]
         oracle_equal = {"elections": E, "differing": int(bad)}
         del d_all, p_all
-    # algorithmic work: one VALU lane-op per (voter, candidate pair) of the count,
-    # one per packed max-min update of the closure
-    count_ops = float(np.sum(ns * ms * (ms - 1) / 2))
-    closure_ops = float(np.sum(ms.astype(np.float64) ** 3))
+    # algorithmic work: per 32 voters and candidate pair one VALU lane-op per
+    # bit plane of the ranks and one population count; 0.75 per max-min update
+    # of the closure (half-precision keys)
+    comparisons = float(np.sum(ns * ms * (ms - 1) / 2))
+    updates = float(np.sum(ms.astype(np.float64) ** 3))
+    planes = np.array([max(int(m) - 1, 1).bit_length() for m in ms], dtype=np.float64)
+    count_ops = float(np.sum(np.ceil(ns / 32.0) * ms * (ms - 1) / 2 * (planes + 1)))
+    closure_ops = 0.75 * updates
     work = count_ops + closure_ops
     ach = work / (kernel_ms / 1e3) / 1e12
     roof = {"bound": "alu", "kernel": "k_batch (graph replay)", "achieved": ach, "peak": VALU_LANE_OPS / 1e12,
             "unit": "Tops/s", "frac": ach / (VALU_LANE_OPS / 1e12),
             "traffic": measured_traffic("batch", "batch_mallows_E%d" % E),
-            "work": "1 lane-op per (voter, unordered pair) of the count + 1 per packed max-min update"}
+            "work": "(bit planes + 1) lane-ops per 32 voters and unordered pair of the count + 0.75 per max-min update"}
     out = {
         "metric": "elections/sec",
         "value": E / (ms_per_step / 1e3),
@@ -682,8 +686,8 @@ def bench_batch(args):
         "identical_to_per_election_calls": same,
         "equal_to_oracle": oracle_equal,
         "graph_ms": kernel_ms,
-        "count_comparisons": count_ops,
-        "closure_updates": closure_ops,
+        "count_comparisons": comparisons,
+        "closure_updates": updates,
         "closure_schedule_by_bucket": tuned,
         "closure_schedules_from_tuning_file": from_file,
         "roofline": roof,

@@ -105,7 +105,10 @@ int schulze_get_device_error(schulze_ctx *ctx, void *stream, int32_t *err_host);
  *               accumulate in 32 bits); a larger total sets SCHULZE_ERANGE.
  * d, ldd        output m x m matrix, d[x][x] = 0.
  *
- * Workspace: up to m*m*4 bytes plus about n*m*2 bytes for full rankings.
+ * Workspace: up to m*m*4 bytes for sums, about 100 MB of the dense count's
+ * partial tiles, about n*m*log2(m)/8 bytes of rank planes for full rankings,
+ * and for truncated ballots 4 bytes per listed entry plus partial rows of
+ * candidates that are listed often.
  */
 int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ballots, int ballot_dtype,
                      int64_t n, int32_t L, int32_t m, const uint32_t *voter_weight,

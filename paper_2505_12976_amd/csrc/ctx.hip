@@ -119,10 +119,13 @@ extern "C" int schulze_get_device_error(schulze_ctx *ctx, void *stream, int32_t 
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     int32_t v = 0;
-    int rc = read_words(ctx, s, {{ctx->err, 1}}, &v);
-    if (rc != SCHULZE_OK) return rc;
+    // (a copy of its own, not the context's report buffer: another thread may
+    // ask while a call on this context waits for its report)
+    if (hipMemcpyAsync(&v, ctx->err, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
+        return SCHULZE_EDEVICE;
+    if (hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
     if (v != 0) {
-        rc = fill_u32(ctx, s, (uint32_t *)ctx->err, 1, 0u);
+        int rc = fill_u32(ctx, s, (uint32_t *)ctx->err, 1, 0u);
         if (rc != SCHULZE_OK) return rc;
         if (hipStreamSynchronize(s) != hipSuccess) return SCHULZE_EDEVICE;
     }
