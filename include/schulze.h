@@ -480,8 +480,8 @@ int schulze_set_sparse_count(schulze_ctx *ctx, int mode);
  * of Section 2.1 commutes with every strictly increasing map of the weights
  * that keeps 0, so when the weights of an int32 closure with m >= 1024 take
  * at most 65535 distinct nonzero values, all below 2^24, the closure runs on
- * the ranks of the values in packed uint16 and maps the result back: same
- * output, about a third less arithmetic per update.  The decision is taken
+ * the ranks of the values as 16-bit values and maps the result back: same
+ * output, half the arithmetic per update.  The decision is taken
  * on the device (a 2 MB bitmap of the values and a count): both variants are
  * queued and the one not needed returns at once, so the call stays
  * asynchronous and can be captured in a HIP graph.  With ranking off, or

@@ -699,9 +699,10 @@ int run_closure(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_
 // the values (the max and min of mapped values are the mapped max and min),
 // and such a map can fix 0.  So when the int32 weights take at most 65535
 // distinct nonzero values, all below RANK_CAP, the closure runs on their
-// ranks (1 = smallest nonzero value) in packed uint16 -- one instruction per
-// update instead of one and a half -- and the result is mapped back through
-// the table of ranked values.  Exact; otherwise the int32 closure runs.
+// ranks (1 = smallest nonzero value) as 16-bit values -- half-precision keys
+// up to rank KEY_MAX, three quarters of a lane operation per update instead of
+// one and a half -- and the result is mapped back through the table of ranked
+// values.  Exact; otherwise the int32 closure runs.
 constexpr int32_t RANK_CAP = 1 << 24;           // values ranked below this bound
 constexpr int32_t RANK_WORDS = RANK_CAP / 32;   // bitmap words
 constexpr int32_t RANK_BLOCK = 1024;            // bitmap words per scan block
