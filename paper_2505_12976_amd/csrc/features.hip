@@ -277,7 +277,24 @@ __global__ __launch_bounds__(256) void k_feature_rows(const E *__restrict__ d, i
 // takes 64 candidates, its four wavefronts every fourth slice, and the four
 // partial results meet in LDS (a thread per candidate alone left too few
 // workgroups to keep the reads in flight).
-__global__ __launch_bounds__(256) void k_feature_reduce(int32_t m, int32_t S, RawStats part, RawStats st) {
+//
+// Each workgroup also leaves the maxima of its candidates (Copeland score,
+// largest outgoing weight, Borda score), which the normalisation gathers: a
+// pass of its own with atomics on one word each took 9 us (m = 1501) to 13
+// us (m = 32768), and a fill before it.
+struct Maxima {
+    uint32_t *cope, *out;  // one entry per workgroup of the reduction
+    unsigned long long *borda;
+};
+__device__ __forceinline__ void wave_max(uint32_t &c, uint32_t &o, unsigned long long &b) {
+    for (int off = 32; off > 0; off >>= 1) {
+        c = max(c, (uint32_t)__shfl_xor((int)c, off));
+        o = max(o, (uint32_t)__shfl_xor((int)o, off));
+        const unsigned long long q = __shfl_xor(b, off);
+        b = q > b ? q : b;
+    }
+}
+__global__ __launch_bounds__(256) void k_feature_reduce(int32_t m, int32_t S, RawStats part, RawStats st, Maxima mx) {
     __shared__ int32_t si[3][64][6];
     __shared__ unsigned long long su[3][64][3];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -302,7 +319,7 @@ __global__ __launch_bounds__(256) void k_feature_reduce(int32_t m, int32_t S, Ra
         for (int k = 0; k < 3; ++k) su[wv - 1][lane][k] = u[k];
     }
     __syncthreads();
-    if (wv != 0 || x >= m) return;
+    if (wv != 0) return;
     for (int o = 0; o < 3; ++o) {
         v[0] += si[o][lane][0];
         v[1] += si[o][lane][1];
@@ -312,6 +329,15 @@ __global__ __launch_bounds__(256) void k_feature_reduce(int32_t m, int32_t S, Ra
         v[5] = max(v[5], si[o][lane][5]);
         for (int k = 0; k < 3; ++k) u[k] += su[o][lane][k];
     }
+    uint32_t mc = x < m ? (uint32_t)v[0] : 0u, mo = x < m ? (uint32_t)v[2] : 0u;
+    unsigned long long mb = x < m ? u[0] : 0ull;
+    wave_max(mc, mo, mb);
+    if (lane == 0) {
+        mx.cope[blockIdx.x] = mc;
+        mx.out[blockIdx.x] = mo;
+        mx.borda[blockIdx.x] = mb;
+    }
+    if (x >= m) return;
     st.cope[x] = v[0];
     st.ties[x] = v[1];
     st.max_out[x] = v[2];
@@ -323,39 +349,34 @@ __global__ __launch_bounds__(256) void k_feature_reduce(int32_t m, int32_t S, Ra
     st.sum_in[x] = u[2];
 }
 
-// Maxima over candidates of the Copeland score, the largest outgoing weight
-// and the Borda score: mx[0], mx[1] (int32 as uint32) and mx[2] (64 bits at
-// mx + 2); zero on entry.
-__global__ __launch_bounds__(256) void k_feature_max(int32_t m, RawStats st, uint32_t *__restrict__ mx) {
-    __shared__ uint32_t sc, so;
-    __shared__ unsigned long long sb;
-    if (threadIdx.x == 0) {
-        sc = 0;
-        so = 0;
-        sb = 0;
+// Normalise: one thread per candidate, after the maxima of all candidates
+// from the reduction's `groups` workgroups.
+__global__ __launch_bounds__(256) void k_feature_norm(int32_t m, RawStats st, float n_voters, Maxima mx, int32_t groups,
+                                                      float *__restrict__ feat) {
+    __shared__ uint32_t sc[4], so[4];
+    __shared__ unsigned long long sb[4];
+    uint32_t mcope = 0, mout = 0;
+    unsigned long long mborda = 0;
+    for (int32_t i = threadIdx.x; i < groups; i += 256) {
+        mcope = max(mcope, mx.cope[i]);
+        mout = max(mout, mx.out[i]);
+        const unsigned long long b = mx.borda[i];
+        mborda = b > mborda ? b : mborda;
+    }
+    wave_max(mcope, mout, mborda);
+    if ((threadIdx.x & 63) == 0) {
+        sc[threadIdx.x >> 6] = mcope;
+        so[threadIdx.x >> 6] = mout;
+        sb[threadIdx.x >> 6] = mborda;
     }
     __syncthreads();
-    const int32_t x = blockIdx.x * 256 + threadIdx.x;
-    if (x < m) {
-        atomicMax(&sc, (uint32_t)st.cope[x]);
-        atomicMax(&so, (uint32_t)st.max_out[x]);
-        atomicMax(&sb, st.borda[x]);
+    for (int w = 0; w < 4; ++w) {
+        mcope = max(mcope, sc[w]);
+        mout = max(mout, so[w]);
+        mborda = sb[w] > mborda ? sb[w] : mborda;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicMax(&mx[0], sc);
-        atomicMax(&mx[1], so);
-        atomicMax(reinterpret_cast<unsigned long long *>(mx + 2), sb);
-    }
-}
-
-// Normalise: one thread per candidate.
-__global__ __launch_bounds__(256) void k_feature_norm(int32_t m, RawStats st, float n_voters,
-                                                      const uint32_t *__restrict__ mx, float *__restrict__ feat) {
     const int32_t x = blockIdx.x * 256 + threadIdx.x;
     if (x >= m) return;
-    const uint32_t mcope = mx[0], mout = mx[1];
-    const unsigned long long mborda = *reinterpret_cast<const unsigned long long *>(mx + 2);
     const float inv_m1 = m > 1 ? 1.0f / (float)(m - 1) : 0.0f;
     const float inv_n = n_voters > 0.f ? 1.0f / n_voters : 1.0f;
     float *f = feat + (int64_t)x * NF;
@@ -431,22 +452,25 @@ int run_features(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32
     size_t fin_bytes = 0, part_bytes = 0;
     (void)carve(nullptr, (size_t)m, &fin_bytes);
     (void)carve(nullptr, (size_t)m * S, &part_bytes);
-    int rc = ws_reserve(ctx, WS_FEATURES, fin_bytes + part_bytes + 256);
+    const int32_t groups = (int32_t)ceil_div(m, 64);
+    const size_t g4 = round_up(4 * (size_t)groups, 256), g8 = round_up(8 * (size_t)groups, 256);
+    int rc = ws_reserve(ctx, WS_FEATURES, fin_bytes + part_bytes + 2 * g4 + g8);
     if (rc != SCHULZE_OK) return rc;
     char *p = static_cast<char *>(ctx->ws[WS_FEATURES]);
     RawStats st = carve(p, (size_t)m, &fin_bytes);
     RawStats part = carve(p + fin_bytes, (size_t)m * S, &part_bytes);
-    uint32_t *mx = reinterpret_cast<uint32_t *>(p + fin_bytes + part_bytes);
-    if ((rc = fill_u32(ctx, s, mx, 4, 0u)) != SCHULZE_OK) return rc;
+    char *g = p + fin_bytes + part_bytes;
+    const Maxima mx{reinterpret_cast<uint32_t *>(g), reinterpret_cast<uint32_t *>(g + g4),
+                    reinterpret_cast<unsigned long long *>(g + 2 * g4)};
     rc = sb == 4   ? launch_rows<E, 4>(ctx, s, d, ldd, m, mode, part, S)
          : sb == 2 ? launch_rows<E, 2>(ctx, s, d, ldd, m, mode, part, S)
                    : launch_rows<E, 1>(ctx, s, d, ldd, m, mode, part, S);
     if (rc != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_FEATURES, s,
-                   k_feature_reduce<<<dim3((unsigned)ceil_div(m, 64)), dim3(256), 0, s>>>(m, S, part, st));
-    const dim3 vg((unsigned)ceil_div(m, 256));
-    SCHULZE_LAUNCH(ctx, K_FEATURES, s, k_feature_max<<<vg, dim3(256), 0, s>>>(m, st, mx));
-    SCHULZE_LAUNCH(ctx, K_FEATURES, s, k_feature_norm<<<vg, dim3(256), 0, s>>>(m, st, n_voters, mx, feat));
+                   k_feature_reduce<<<dim3((unsigned)groups), dim3(256), 0, s>>>(m, S, part, st, mx));
+    SCHULZE_LAUNCH(ctx, K_FEATURES, s,
+                   k_feature_norm<<<dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, s>>>(m, st, n_voters, mx, groups,
+                                                                                         feat));
     return SCHULZE_OK;
 }
 
