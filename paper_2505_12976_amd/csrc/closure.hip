@@ -466,14 +466,15 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : (B < 128 ? 2 : 1)) void k
 // m <= B: weights, closure and output of a whole small matrix in one
 // workgroup's registers and one launch, by the diagonal tile's recurrence.
 // Each launch of the other paths takes about 4.5 us on its own (m = 64:
-// three of them around a 10 us recurrence), and at B = 128 the two rounds
-// of 64-wide tiles take longer than 128 steps in registers.
-template <typename E, int B>
+// three of them around a 10 us recurrence), and two rounds of 64-wide tiles
+// take longer than 128 steps in registers.
+// C: the type it computes in (E, or int32 for uint16 values).
+template <typename E, typename C, int B>
 __global__ __launch_bounds__(256) void k_closure_small(const E *__restrict__ d, int64_t ldd, int32_t m, int mode,
                                                        E *__restrict__ p, int64_t ldp) {
-    using D = Diag<E, B>;
+    using D = Diag<C, B, 4>;
     using W = typename D::W;
-    __shared__ __attribute__((aligned(16))) E buf[D::LDS_ELEMS];
+    __shared__ __attribute__((aligned(16))) C buf[D::LDS_ELEMS];
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     W v[D::RA][D::WC];
 #pragma unroll
@@ -492,13 +493,13 @@ __global__ __launch_bounds__(256) void k_closure_small(const E *__restrict__ d, 
         }
 #pragma unroll
         for (int c = 0; c < D::WC; ++c) {
-            if constexpr (sizeof(E) == 4)
-                v[a][c] = x[c];
+            if constexpr (sizeof(C) == 4)
+                v[a][c] = (C)x[c];
             else
                 v[a][c] = W{x[2 * c], x[2 * c + 1]};
         }
     }
-    FW_LDS E *lb = (FW_LDS E *)buf;
+    FW_LDS C *lb = (FW_LDS C *)buf;
     D::template publish<0>(v, 0, lb, tx, ty);
     D::template steps<0>(v, tx, ty, lb);
 #pragma unroll
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(256) void k_closure_small(const E *__restrict__ d, 
 #pragma unroll
         for (int b = 0; b < D::CW; ++b) {
             const int32_t i = ty + 16 * a, j = tx + 16 * b;
-            if (i < m && j < m) p[(int64_t)i * ldp + j] = i == j ? (E)0 : lane_get<E>(v[a], b);
+            if (i < m && j < m) p[(int64_t)i * ldp + j] = i == j ? (E)0 : (E)lane_get<C>(v[a], b);
         }
 }
 
@@ -660,14 +661,21 @@ int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, 
     return SCHULZE_OK;
 }
 
+// The tile is m rounded up to 16, in steps of 32 from 64 on: the recurrence
+// takes a step per row of it.  16-bit tiles hold two columns per register and
+// are multiples of 32; uint16 values are closed as int32 where that is faster.
+// us, int32 / 16-bit: 16: 2.6 / -, 32: 5.2 / 4.4, 48: 9.0 / -, 64: 13.9 /
+// 12.8, 96: 31.6 / 30.0, 128: 55.5 / 114 (two rounds of 64-wide tiles and
+// their launches: 87 / 72).
 template <typename E>
 int run_closure_small(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, E *p, int64_t ldp) {
-    if (m <= 64)
-        SCHULZE_LAUNCH(ctx, K_FW_DIAG, s,
-                       (k_closure_small<E, 64><<<dim3(1), dim3(256), 0, s>>>(d, ldd, m, mode, p, ldp)));
-    else
-        SCHULZE_LAUNCH(ctx, K_FW_DIAG, s,
-                       (k_closure_small<E, 128><<<dim3(1), dim3(256), 0, s>>>(d, ldd, m, mode, p, ldp)));
+    const auto kernel = m <= 16   ? k_closure_small<E, int32_t, 16>
+                        : m <= 32 ? k_closure_small<E, E, 32>
+                        : m <= 48 ? k_closure_small<E, int32_t, 48>
+                        : m <= 64 ? k_closure_small<E, E, 64>
+                        : m <= 96 ? k_closure_small<E, E, 96>
+                                  : k_closure_small<E, int32_t, 128>;
+    SCHULZE_LAUNCH(ctx, K_FW_DIAG, s, (kernel<<<dim3(1), dim3(256), 0, s>>>(d, ldd, m, mode, p, ldp)));
     ctx->closure_bits = sizeof(E) * 8;
     return SCHULZE_OK;
 }
