@@ -8,7 +8,7 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65, 129, 131, 259, 1023, 1025, 1027, 1033]
+SIZES = [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 32, 33, 48, 49, 63, 64, 65, 96, 97, 128, 129, 131, 259, 1023, 1025, 1027, 1033]
 
 
 @pytest.fixture(scope="module")
