@@ -45,10 +45,7 @@ struct NetBf16 {
     bf16 *w1t, *w2t, *w2, *w3;
 };
 
-// With `step`, the train step's Adam counter is advanced here (one launch less).
-__global__ __launch_bounds__(256) void k_mlp_prepare(const float *__restrict__ p, NetBf16 q,
-                                                     int32_t *__restrict__ step) {
-    if (step && blockIdx.x == 0 && threadIdx.x == 0) step[0] += 1;
+__global__ __launch_bounds__(256) void k_mlp_prepare(const float *__restrict__ p, NetBf16 q) {
     for (int t = blockIdx.x * 256 + threadIdx.x; t < NH * NH; t += gridDim.x * 256) {
         const int i = t / NH, j = t % NH;
         const bf16 v = to_bf16(p[OFF_W2 + i * NH + j]);
@@ -290,11 +287,16 @@ struct BwdLds {
     float red[4][NH];
 };
 
+//
+// With `step`, the train step's Adam counter is advanced here: the launch
+// right before the one that uses it, so that a step which fails earlier leaves
+// the counter where the parameters are.
 __global__ __launch_bounds__(256) void k_mlp_bwd(const float *__restrict__ p, NetBf16 q, const float *__restrict__ X,
                                                  const float *__restrict__ dsg, int64_t M, int32_t shares,
-                                                 float *__restrict__ partial) {
+                                                 float *__restrict__ partial, int32_t *__restrict__ step) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     BwdLds &L = *reinterpret_cast<BwdLds *>(smem);
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) step[0] += 1;
     load_weights(L.f, q);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rb = wave >> 1, hi = lane >> 5, lo = lane & 31;
@@ -446,7 +448,7 @@ struct AdamArgs {
     float *p, *m1, *m2;
     float lr, b1, b2, eps;
     int32_t t_host;
-    const int32_t *t_dev;  // when given, the device counter (the train step advances it first)
+    int32_t *t_dev;  // when given, the device counter (the train step's backward advances it)
 };
 __device__ inline void adam_step(const AdamArgs &a, int k, float gk) {
     const int32_t t = a.t_dev ? *a.t_dev : a.t_host;
@@ -491,16 +493,18 @@ __global__ __launch_bounds__(64) void k_mlp_reduce(const float *__restrict__ par
 
 size_t bwd_lds_bytes() { return sizeof(BwdLds); }
 
-int prepare(schulze_ctx *ctx, hipStream_t s, const float *params, NetBf16 &q, int32_t *step = nullptr) {
-    const size_t w2b = sizeof(bf16) * NH * NH, w1b = sizeof(bf16) * NH * NF;
-    int rc = ws_reserve(ctx, WS_MLP, 2 * w2b + w1b + 256 + 256);
+constexpr size_t W2_BYTES = sizeof(bf16) * NH * NH, W1_BYTES = sizeof(bf16) * NH * NF;
+constexpr size_t PREPARED_BYTES = 2 * W2_BYTES + W1_BYTES + 256 + 256;
+
+int prepare(schulze_ctx *ctx, hipStream_t s, const float *params, NetBf16 &q) {
+    int rc = ws_reserve(ctx, WS_MLP, PREPARED_BYTES);
     if (rc != SCHULZE_OK) return rc;
     char *b = static_cast<char *>(ctx->ws[WS_MLP]);
     q.w2t = reinterpret_cast<bf16 *>(b);
-    q.w2 = reinterpret_cast<bf16 *>(b + w2b);
-    q.w1t = reinterpret_cast<bf16 *>(b + 2 * w2b);
-    q.w3 = reinterpret_cast<bf16 *>(b + 2 * w2b + w1b + 256);
-    SCHULZE_LAUNCH(ctx, K_MLP_PREP, s, k_mlp_prepare<<<dim3(16), dim3(256), 0, s>>>(params, q, step));
+    q.w2 = reinterpret_cast<bf16 *>(b + W2_BYTES);
+    q.w1t = reinterpret_cast<bf16 *>(b + 2 * W2_BYTES);
+    q.w3 = reinterpret_cast<bf16 *>(b + 2 * W2_BYTES + W1_BYTES + 256);
+    SCHULZE_LAUNCH(ctx, K_MLP_PREP, s, k_mlp_prepare<<<dim3(16), dim3(256), 0, s>>>(params, q));
     return SCHULZE_OK;
 }
 
@@ -527,21 +531,30 @@ extern "C" int schulze_mlp_forward(schulze_ctx *ctx, void *stream, const float *
 
 namespace {
 
+// What a backward over M rows needs besides its launches, before anything is
+// queued: a call that fails here has changed nothing.
+int backward_reserve(schulze_ctx *ctx, int64_t M) {
+    int rc = ws_reserve(ctx, WS_MLP, PREPARED_BYTES);
+    if (rc != SCHULZE_OK) return rc;
+    if ((rc = ws_reserve(ctx, WS_MLP_PARTIAL, sizeof(float) * (size_t)grid_for(ctx, M) * NPARAM)) != SCHULZE_OK)
+        return rc;
+    if (hipFuncSetAttribute((const void *)k_mlp_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)bwd_lds_bytes()) != hipSuccess)
+        return SCHULZE_EDEVICE;
+    return SCHULZE_OK;
+}
+
 // Backward of the prepared network (q) into grad, and its Adam step if
-// adam.p is given; arguments checked.
+// adam.p is given (adam.t_dev, if given, is advanced first); arguments
+// checked and backward_reserve done.
 int backward(schulze_ctx *ctx, hipStream_t s, const float *params, const NetBf16 &q, const float *feat, int64_t M,
              const float *dscore, float *grad, const AdamArgs &adam) {
-    int rc;
     const int shares = grid_for(ctx, M);
     const int G = std::min(shares, ctx->num_cus);
-    if ((rc = ws_reserve(ctx, WS_MLP_PARTIAL, sizeof(float) * (size_t)shares * NPARAM)) != SCHULZE_OK) return rc;
     float *partial = static_cast<float *>(ctx->ws[WS_MLP_PARTIAL]);
-    const size_t lds = bwd_lds_bytes();
-    if (hipFuncSetAttribute((const void *)k_mlp_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-        hipSuccess)
-        return SCHULZE_EDEVICE;
     SCHULZE_LAUNCH(ctx, K_MLP_BWD, s,
-                   k_mlp_bwd<<<dim3((unsigned)G), dim3(256), lds, s>>>(params, q, feat, dscore, M, shares, partial));
+                   k_mlp_bwd<<<dim3((unsigned)G), dim3(256), bwd_lds_bytes(), s>>>(params, q, feat, dscore, M, shares,
+                                                                                  partial, adam.t_dev));
     SCHULZE_LAUNCH(ctx, K_MLP_BWD, s,
                    k_mlp_reduce<<<dim3((unsigned)ceil_div(NPARAM, 64)), dim3(64), 0, s>>>(partial, shares, grad, adam));
     return SCHULZE_OK;
@@ -555,8 +568,8 @@ extern "C" int schulze_mlp_backward(schulze_ctx *ctx, void *stream, const float 
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     NetBf16 q;
-    int rc = prepare(ctx, s, params, q);
-    if (rc != SCHULZE_OK) return rc;
+    int rc = backward_reserve(ctx, M);
+    if (rc != SCHULZE_OK || (rc = prepare(ctx, s, params, q)) != SCHULZE_OK) return rc;
     return backward(ctx, s, params, q, feat, M, dscore, grad, AdamArgs{});
 }
 
@@ -595,11 +608,11 @@ extern "C" int schulze_mlp_train_step(schulze_ctx *ctx, void *stream, const schu
     // scores and their gradient live in the workspace
     const size_t vec = round_up(sizeof(float) * (size_t)b->M, 256);
     int rc = ws_reserve(ctx, WS_MLP_TRAIN, 2 * vec);
-    if (rc != SCHULZE_OK) return rc;
+    if (rc != SCHULZE_OK || (rc = backward_reserve(ctx, b->M)) != SCHULZE_OK) return rc;
     float *score = static_cast<float *>(ctx->ws[WS_MLP_TRAIN]);
     float *dscore = reinterpret_cast<float *>(static_cast<char *>(ctx->ws[WS_MLP_TRAIN]) + vec);
     NetBf16 q;
-    if ((rc = prepare(ctx, s, net->params, q, net->step)) != SCHULZE_OK) return rc;
+    if ((rc = prepare(ctx, s, net->params, q)) != SCHULZE_OK) return rc;
     SCHULZE_LAUNCH(ctx, K_MLP_FWD, s,
                    k_mlp_fwd<<<dim3((unsigned)grid_for(ctx, b->M)), dim3(256), 0, s>>>(net->params, q, b->feat, b->M,
                                                                                        score));

@@ -1,0 +1,82 @@
+"""The host side of the library's calls, on a HIP runtime that runs nothing
+(tests/fake_hip.c): what a call allocates and launches, and what is left when
+an allocation or a launch is refused.  Each test's script runs in a process of
+its own, in which that runtime is loaded first."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, random, sys
+sys.path.insert(0, sys.argv[2])
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+fake.fake_log.restype = ctypes.c_char_p
+import paper_2505_12976_amd as sz
+lib = sz.load_library()
+U16, I32, FAR = sz.U16, sz.I32, 1 << 46   # FAR: some device address, never read
+def context():
+    h = ctypes.c_void_p()
+    fake.fake_reset()
+    assert lib.schulze_create(ctypes.byref(h), 0) == 0
+    fake.fake_reset()
+    return h
+def log():
+    return fake.fake_log().decode().splitlines()
+def launched():
+    return [l.split()[1] for l in log() if l.split()[0] in ("launch", "cooperative")]
+def out(x):
+    print(json.dumps(x))
+"""
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "fake_hip.c"), "-o", so], check=True, capture_output=True)
+
+    def run(script):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + script, so, ROOT], capture_output=True, text=True,
+                           timeout=300)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+TRAIN = """
+net = sz.MlpState(FAR, FAR, FAR, FAR, FAR, 1e-3, 0.9, 0.999, 1e-8)
+batch = sz.TrainBatch(FAR, FAR, FAR, 5000, 40)
+def step(h):
+    return lib.schulze_mlp_train_step(h, None, ctypes.byref(net), ctypes.byref(batch), FAR)
+"""
+
+
+def test_train_step_that_fails_leaves_nothing_queued(fake_hip):
+    """A refused allocation (each in turn) or kernel attribute is found before
+    the first launch, so that the step counter stands still."""
+    got = fake_hip(TRAIN + """
+rows = []
+h = context()
+assert step(h) == 0
+allocations = sum(l.startswith("malloc") for l in log())
+for k in range(allocations):
+    h = context()
+    fake.fake_fail_malloc(k)
+    rows.append([step(h), launched()])
+h = context()
+fake.fake_fail_attribute(1)
+rows.append([step(h), launched()])
+out([allocations, rows])
+""")
+    allocations, rows = got
+    assert allocations >= 3
+    for rc, launches in rows[:-1]:
+        assert rc == -3 and launches == []
+    assert rows[-1] == [-4, []]
