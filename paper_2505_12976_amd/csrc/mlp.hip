@@ -206,14 +206,41 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float *__restrict__ p, Ne
 }
 
 // ------------------------------------------------------------------ loss
-// One workgroup per election e over rows [off[e], off[e+1]): softmax
-// cross-entropy with the probability mass of the winner set,
+// Softmax cross-entropy with the probability mass of the winner set, per
+// election e over rows [off[e], off[e+1]):
 //   loss_e = log sum_all exp(s) - log sum_winners exp(s),
-// ds = (softmax over all - softmax over winners, on winners) / E.
-// The exponentials of elections of up to SEG_KEEP rows are computed once, by
-// all threads, into LDS; the first wavefront adds them up (row a + lane, a +
-// lane + 64, .. per lane, then the lanes: the sums do not depend on how many
-// threads took part).  With a wavefront doing all of it, 128 elections of
+//   ds = (softmax over all - softmax over winners, on winners) / E.
+// The sums go row a + lane, a + lane + 64, .. per lane of one wavefront, then
+// over its lanes, whichever kernel runs: the results are the same bit for bit.
+__device__ inline float wave_max(float v) {
+    for (int o = 1; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
+    return v;
+}
+// one wavefront: ex(r) = exp(score[r] - max) summed over all rows and over the winners
+template <typename F>
+__device__ inline void wave_sums(const uint8_t *__restrict__ winner, int64_t a, int64_t b, F ex, float &sa, float &sw) {
+    sa = sw = 0.f;
+    for (int64_t r = a + (threadIdx.x & 63); r < b; r += 64) {
+        const float x = ex(r);
+        sa += x;
+        if (winner[r]) sw += x;
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+        sa += __shfl_xor(sa, o);
+        sw += __shfl_xor(sw, o);
+    }
+}
+__device__ inline float row_grad(float x, bool winner, float sa, float sw, float inv_e) {
+    const bool ok = sw > 0.f;
+    float g = x / sa;
+    if (winner && ok) g -= x / sw;
+    return ok ? g * inv_e : 0.f;
+}
+__device__ inline float seg_loss(float sa, float sw) { return sw > 0.f ? logf(sa) - logf(sw) : 0.f; }
+
+// Few elections: a workgroup each.  The exponentials of elections of up to
+// SEG_KEEP rows are computed once, by all threads, into LDS, and the first
+// wavefront adds them up.  With a wavefront doing all of it, 128 elections of
 // 1150 rows left half the chip idle and took 25 us, of which this 7.
 constexpr int SEG_KEEP = 8192;
 __global__ __launch_bounds__(256) void k_seg_loss(const float *__restrict__ score, const int64_t *__restrict__ off,
@@ -231,40 +258,46 @@ __global__ __launch_bounds__(256) void k_seg_loss(const float *__restrict__ scor
         if (keep) ex[r - a] = s;
         mx = fmaxf(mx, s);
     }
-    for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    mx = wave_max(mx);
     if (lane == 0) red[wave] = mx;
     __syncthreads();
     mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     if (keep)
         for (int64_t r = threadIdx.x; r < b - a; r += 256) ex[r] = expf(ex[r] - mx);
     __syncthreads();
+    auto x_of = [&](int64_t r) { return keep ? ex[r - a] : expf(score[r] - mx); };
     if (wave == 0) {
-        float sa = 0.f, sw = 0.f;
-        for (int64_t r = a + lane; r < b; r += 64) {
-            const float x = keep ? ex[r - a] : expf(score[r] - mx);
-            sa += x;
-            if (winner[r]) sw += x;
-        }
-        for (int o = 1; o < 64; o <<= 1) {
-            sa += __shfl_xor(sa, o);
-            sw += __shfl_xor(sw, o);
-        }
+        float sa, sw;
+        wave_sums(winner, a, b, x_of, sa, sw);
         if (lane == 0) {
             sums[0] = sa;
             sums[1] = sw;
         }
     }
     __syncthreads();
-    const float sa = sums[0], sw = sums[1];
+    const float sa = sums[0], sw = sums[1], inv_e = 1.0f / (float)E;
+    for (int64_t r = a + threadIdx.x; r < b; r += 256) ds[r] = row_grad(x_of(r), winner[r], sa, sw, inv_e);
+    if (threadIdx.x == 0) loss[e] = seg_loss(sa, sw);
+}
+
+// Many elections: a wavefront each, no LDS.
+__global__ __launch_bounds__(256) void k_seg_loss_many(const float *__restrict__ score,
+                                                       const int64_t *__restrict__ off,
+                                                       const uint8_t *__restrict__ winner, int32_t E,
+                                                       float *__restrict__ ds, float *__restrict__ loss) {
+    const int lane = threadIdx.x & 63;
+    const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (e >= E) return;
+    const int64_t a = off[e], b = off[e + 1];
+    float mx = -INFINITY;
+    for (int64_t r = a + lane; r < b; r += 64) mx = fmaxf(mx, score[r]);
+    mx = wave_max(mx);
+    auto x_of = [&](int64_t r) { return expf(score[r] - mx); };
+    float sa, sw;
+    wave_sums(winner, a, b, x_of, sa, sw);
     const float inv_e = 1.0f / (float)E;
-    const bool ok = sw > 0.f;
-    for (int64_t r = a + threadIdx.x; r < b; r += 256) {
-        const float x = keep ? ex[r - a] : expf(score[r] - mx);
-        float g = x / sa;
-        if (winner[r] && ok) g -= x / sw;
-        ds[r] = ok ? g * inv_e : 0.f;
-    }
-    if (threadIdx.x == 0) loss[e] = ok ? logf(sa) - logf(sw) : 0.f;
+    for (int64_t r = a + lane; r < b; r += 64) ds[r] = row_grad(x_of(r), winner[r], sa, sw, inv_e);
+    if (lane == 0) loss[e] = seg_loss(sa, sw);
 }
 
 // ------------------------------------------------------------------ backward
@@ -531,6 +564,21 @@ extern "C" int schulze_mlp_forward(schulze_ctx *ctx, void *stream, const float *
 
 namespace {
 
+// A workgroup per election while all of them stay resident together (four per
+// CU by their LDS), a wavefront each beyond.  The lengths of the elections are
+// on the device, so the rule knows their number only.
+int loss_of(schulze_ctx *ctx, hipStream_t s, const float *score, const int64_t *offsets, const uint8_t *winner,
+            int32_t E, float *dscore, float *loss) {
+    if (E <= 4 * ctx->num_cus)
+        SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
+                       k_seg_loss<<<dim3((unsigned)E), dim3(256), 0, s>>>(score, offsets, winner, E, dscore, loss));
+    else
+        SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
+                       k_seg_loss_many<<<dim3((unsigned)ceil_div(E, 4)), dim3(256), 0, s>>>(score, offsets, winner, E,
+                                                                                          dscore, loss));
+    return SCHULZE_OK;
+}
+
 // What a backward over M rows needs besides its launches, before anything is
 // queued: a call that fails here has changed nothing.
 int backward_reserve(schulze_ctx *ctx, int64_t M) {
@@ -578,10 +626,7 @@ extern "C" int schulze_mlp_loss(schulze_ctx *ctx, void *stream, const float *sco
     if (!ctx || !score || !offsets || !winner || !dscore || !loss || E < 1) return SCHULZE_EINVAL;
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
-    SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
-                   k_seg_loss<<<dim3((unsigned)E), dim3(256), 0, s>>>(score, offsets, winner, E, dscore,
-                                                                                    loss));
-    return SCHULZE_OK;
+    return loss_of(ctx, s, score, offsets, winner, E, dscore, loss);
 }
 
 extern "C" int schulze_mlp_adam(schulze_ctx *ctx, void *stream, float *params, const float *grad, float *adam_m,
@@ -616,9 +661,7 @@ extern "C" int schulze_mlp_train_step(schulze_ctx *ctx, void *stream, const schu
     SCHULZE_LAUNCH(ctx, K_MLP_FWD, s,
                    k_mlp_fwd<<<dim3((unsigned)grid_for(ctx, b->M)), dim3(256), 0, s>>>(net->params, q, b->feat, b->M,
                                                                                        score));
-    SCHULZE_LAUNCH(ctx, K_MLP_LOSS, s,
-                   k_seg_loss<<<dim3((unsigned)b->E), dim3(256), 0, s>>>(score, b->offsets, b->winner,
-                                                                                       b->E, dscore, loss));
+    if ((rc = loss_of(ctx, s, score, b->offsets, b->winner, b->E, dscore, loss)) != SCHULZE_OK) return rc;
     return backward(ctx, s, net->params, q, b->feat, b->M, dscore, net->grad,
                     AdamArgs{net->params, net->adam_m, net->adam_v, net->lr, net->beta1, net->beta2, net->eps, 0,
                              net->step});

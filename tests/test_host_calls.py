@@ -80,3 +80,21 @@ out([allocations, rows])
     for rc, launches in rows[:-1]:
         assert rc == -3 and launches == []
     assert rows[-1] == [-4, []]
+
+
+def test_loss_takes_as_many_elections_as_wavefronts(fake_hip):
+    """64 threads per election beyond the few that get a workgroup each: up to
+    2^26 - 4 elections fit one launch."""
+    got = fake_hip("""
+rows = []
+for E in (1, 1024, 1025, 1 << 24, (1 << 26) - 4):
+    h = context()
+    rc = lib.schulze_mlp_loss(h, None, FAR, FAR, FAR, E, FAR, FAR)
+    rows.append([E, rc, log()[-1]])
+out(rows)
+""")
+    for E, rc, line in got:
+        assert rc == 0, (E, line)
+        many = E > 1024
+        assert ("k_seg_loss_many" in line) == many
+        assert int(line.split()[2]) == (-(-E // 4) if many else E)
