@@ -49,7 +49,8 @@ struct Meta {
     int32_t *ctr;            // [0] full rankings [1] truncated ballots [2] route
                              // [3] |U| [4] U-space pitch [6] longest truncated
                              // ballot [7] voter weights or-ed together [8] total
-                             // weight of the full rankings (mod 2^32) [32..33] total
+                             // weight of the full rankings (mod 2^32) [9] error of a
+                             // repeated id (one-pass count) [32..33] total
                              // voter weight (64 bits) [34] its workgroups done
     unsigned long long *k2;  // NPART partial sums of k(k-1)/2 over truncated ballots
     int32_t *len;            // listed length per ballot
@@ -569,6 +570,7 @@ struct AllArgs {
     const uint32_t *weight;
     uint32_t *planes, *wplanes;
     int32_t *err;
+    int32_t *repeated;  // where a repeated id is recorded: the error word, or a word that k_weight_total reports
 };
 
 template <bool I32, int CH>
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(1024) void k_planes_all(AllArgs a) {
     __syncthreads();
     extra += planes_out<CH, 1024>(buf, cn, a.m - c0, voter_bits(live), a.bits, a.pitch,
                                   a.planes + (int64_t)g * a.bits * a.pitch + c0);
-    check_repeats(extra, &repeated, a.err);
+    check_repeats(extra, &repeated, a.repeated);
     if (a.weight && blockIdx.y == 0 && wave == 0) {
         const int v = 2 * (lane & 15) + ((lane >> 4) & 1);
         (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
@@ -693,7 +695,7 @@ __global__ __launch_bounds__(256) void k_planes_short(AllArgs a) {
     __syncthreads();
     extra += planes_out<CH, 256>(buf, cn, a.m - c0, voter_bits(live), a.bits, a.pitch,
                                  a.planes + (int64_t)g * a.bits * a.pitch + c0);
-    check_repeats(extra, &repeated, a.err);
+    check_repeats(extra, &repeated, a.repeated);
     if (a.weight && blockIdx.y == 0 && threadIdx.x < 64) {
         const int lane = threadIdx.x, v = 2 * (lane & 15) + ((lane >> 4) & 1);
         (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
@@ -1690,10 +1692,11 @@ __global__ __launch_bounds__(256) void k_count_finish(const uint32_t *__restrict
 // cannot wrap while the total stays below 2^32 (and then the finish checks
 // every count against the value type); a total of 2^32 or more sets
 // SCHULZE_ERANGE.  total and done start at zero; the last workgroup to add
-// its part decides.
+// its part decides, and then passes on an error recorded in *later, which a
+// profile with both is to report second (nullptr: none).
 __global__ __launch_bounds__(256) void k_weight_total(const uint32_t *__restrict__ w, int64_t n,
                                                       unsigned long long *total, int32_t *done, int32_t *any,
-                                                      int32_t *err) {
+                                                      const int32_t *later, int32_t *err) {
     __shared__ unsigned long long part[256];
     unsigned long long acc = 0;
     uint32_t ored = 0u;
@@ -1715,6 +1718,7 @@ __global__ __launch_bounds__(256) void k_weight_total(const uint32_t *__restrict
         if (atomicAdd(done, 1) == (int32_t)gridDim.x - 1) {
             __threadfence();
             if (atomicAdd(total, 0ull) >> 32) set_device_error(err, SCHULZE_ERANGE);
+            if (later && *later != 0) set_device_error(err, *later);
         }
     }
 }
@@ -1848,12 +1852,13 @@ int occ_accumulate(schulze_ctx *ctx, hipStream_t s, const OccArgs &oa, dim3 grid
 }
 
 // The total voter weight (counters 32 and 33, and the workgroups done in 34)
-// and the weights or-ed (7); all start at zero.
-int weight_total(schulze_ctx *ctx, hipStream_t s, const uint32_t *weight, int64_t n, int32_t *ctr) {
+// and the weights or-ed (7); all start at zero.  later: see k_weight_total.
+int weight_total(schulze_ctx *ctx, hipStream_t s, const uint32_t *weight, int64_t n, int32_t *ctr,
+                 const int32_t *later = nullptr) {
     const unsigned tg = (unsigned)std::min<int64_t>(ceil_div(n, 256), (int64_t)ctx->num_cus * 4);
     SCHULZE_LAUNCH(ctx, K_ROUTE, s,
                    k_weight_total<<<dim3(tg), dim3(256), 0, s>>>(weight, n, reinterpret_cast<unsigned long long *>(ctr + 32),
-                                                                 ctr + 34, ctr + 7, ctx->err));
+                                                                 ctr + 34, ctr + 7, later, ctx->err));
     return SCHULZE_OK;
 }
 
@@ -1905,6 +1910,7 @@ int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype3
 // most ALL_COST lane operations (65 us at 45 T/s), about what the other
 // launches would (n = 7001 weighted top-25 of m = 389: 434 us by pairs, 366 us
 // so); weights are charged as 12 bits.
+constexpr int REPEATED = 9;  // counter that holds SCHULZE_EBALLOT if a ballot lists an id twice
 constexpr double ALL_COST = 3.0e9;
 constexpr int32_t ALL_MAX_M = 4096;
 inline bool count_all_fits(int64_t n, int32_t L, int32_t m, bool weighted) {
@@ -1939,11 +1945,15 @@ int count_all(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32,
         if ((rc = ws_reserve(ctx, WS_BALLOT_META, 64 * sizeof(int32_t))) != SCHULZE_OK) return rc;
         da.meta.ctr = static_cast<int32_t *>(ctx->ws[WS_BALLOT_META]);
         if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(da.meta.ctr), 64, 0u)) != SCHULZE_OK) return rc;
-        if ((rc = weight_total(ctx, s, weight, n, da.meta.ctr)) != SCHULZE_OK) return rc;
     }
-    const AllArgs pa{ballots, (int32_t)n, L, m, pitch, bits, weight, planes, const_cast<uint32_t *>(da.wplanes), ctx->err};
+    // the first error of a profile with several: an id out of range, a total
+    // weight out of range, a repeated id, a count out of range (as the other routes')
+    int32_t *repeated = weight ? da.meta.ctr + REPEATED : ctx->err;
+    const AllArgs pa{ballots, (int32_t)n, L, m, pitch, bits, weight, planes, const_cast<uint32_t *>(da.wplanes), ctx->err,
+                     repeated};
     if ((rc = dtype32 ? planes_all<true>(ctx, s, pa, groups) : planes_all<false>(ctx, s, pa, groups)) != SCHULZE_OK)
         return rc;
+    if (weight && (rc = weight_total(ctx, s, weight, n, da.meta.ctr, repeated)) != SCHULZE_OK) return rc;
     const dim3 cg((unsigned)workers), rg((unsigned)std::min<int64_t>(64 * ntiles, (int64_t)ctx->num_cus * 8));
     if (weight)
         SCHULZE_LAUNCH(ctx, K_COUNT_DENSE, s, (k_count_bits<COUNT_ALL, true><<<cg, dim3(256), 0, s>>>(da)));
