@@ -105,10 +105,16 @@ int schulze_get_device_error(schulze_ctx *ctx, void *stream, int32_t *err_host);
  *               accumulate in 32 bits); a larger total sets SCHULZE_ERANGE.
  * d, ldd        output m x m matrix, d[x][x] = 0.
  *
- * Workspace: up to m*m*4 bytes for sums, about 100 MB of the dense count's
- * partial tiles, about n*m*log2(m)/8 bytes of rank planes for full rankings,
- * and for truncated ballots 4 bytes per listed entry plus partial rows of
- * candidates that are listed often.
+ * Workspace: up to m*m*4 bytes for sums, about n*m*log2(m)/8 bytes of rank
+ * planes for full rankings, for truncated ballots as much again but at most
+ * 1 GB (none with voter weights), and one buffer used in turn by the dense
+ * counts' partial tiles (100 MB) and the bucketed count (4 bytes per listed
+ * entry and 10 to 20 MB per thousand candidates of histograms and partial
+ * rows).  Small elections use that buffer alone.  A call sizes the workspace
+ * for every smaller one of its kind (fewer voters, candidates and listed
+ * entries; with voter_weight or without, with L >= m - 1 or below, m up to
+ * 16384 or above): such a call allocates nothing and can be captured in a HIP
+ * graph.
  */
 int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ballots, int ballot_dtype,
                      int64_t n, int32_t L, int32_t m, const uint32_t *voter_weight,

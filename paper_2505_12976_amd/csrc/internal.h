@@ -17,7 +17,6 @@ enum WsSlot {
     WS_BALLOT_META = 0,  // per-ballot listed length and class, counters
     WS_POSITIONS,        // rank planes of full rankings
     WS_TRUNC_POS,        // rank planes of truncated ballots (U space)
-    WS_PARTIAL,          // partial tiles of the bit-plane count
     WS_ACC32,            // m x m uint32 accumulator of the count
     WS_CLOSURE,          // padded closure matrix
     WS_RANK,             // ranking keys
@@ -32,7 +31,8 @@ enum WsSlot {
     WS_LEARNED_P,        // learned path: closure for the fallback
     WS_PROPAGATE,        // label propagation: weights, keys, frontiers, statuses
     WS_RANKED,           // ranked closure: value bitmap, rank tables, uint16 matrix
-    WS_OCC,              // bucketed pair counting: histograms, offsets, occurrences
+    WS_OCC,              // one after the other: partial tiles of the dense counts; the bucketed count's
+                         // histograms, offsets and occurrences; or the one-pass count's tiles and planes
     WS_MLP_TRAIN,        // train step: scores and their gradient
     WS_NUM_SLOTS
 };

@@ -1762,8 +1762,8 @@ struct MetaLayout {
 // Byte layout of WS_OCC for G bucketing workgroups, m candidates and at
 // most cap occurrences.
 // Partial rows: every item of a candidate with two or more items has one,
-// and such a candidate has more than its chunk of occurrences, so there are at
-// most 2 cap / OCC_CHUNK of them.
+// and such a candidate has more than a chunk of occurrences, so there are at
+// most 2 cap / chunk of them.
 struct OccLayout {
     size_t hist, row_start, items, item_start, tickets, part_start, fin, occ, partial, total;
     int64_t ppitch, max_parts;
@@ -1777,10 +1777,16 @@ struct OccLayout {
         };
         ppitch = round_up(m, 8);
         chunk = (uint32_t)std::min<int64_t>(OCC_CHUNK_MAX, std::max<int64_t>(OCC_CHUNK_MIN, cap / (4 * workgroups)));
-        max_parts = cap > 0 ? 2 * ceil_div(cap, chunk) + 1 : 0;
+        // room for ceil(cap / chunk) chunks, by a bound that never falls as cap
+        // grows: up to the smallest chunk's, then about 4 per workgroup, then
+        // the largest chunk's
+        const int64_t chunks = std::min(ceil_div(cap, OCC_CHUNK_MIN),
+                                        std::max(4 * workgroups + 4 * workgroups / OCC_CHUNK_MIN + 2,
+                                                 ceil_div(cap, OCC_CHUNK_MAX)));
+        max_parts = cap > 0 ? 2 * chunks + 1 : 0;
         hist = take(sizeof(uint32_t) * (size_t)G * m);
         row_start = take(sizeof(uint32_t) * ((size_t)m + 1));
-        items = take(sizeof(uint4) * ((size_t)m + (size_t)ceil_div(cap, chunk)));
+        items = take(sizeof(uint4) * ((size_t)m + (size_t)chunks));
         item_start = take(sizeof(uint32_t) * ((size_t)m + 1));
         tickets = take(sizeof(uint32_t) * OCC_QUEUES * TICKET_STRIDE);
         part_start = take(sizeof(uint32_t) * ((size_t)m + 1));
@@ -1888,7 +1894,7 @@ int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype3
     DenseArgs da{};
     da.planes = planes, da.pitch = pitch, da.bits = bits, da.m = m, da.meta = meta;
     da.acc = acc, da.lda = lda, da.rsum = rsum, da.wplanes = wplanes;
-    da.partial = static_cast<uint32_t *>(ctx->ws[WS_PARTIAL]);
+    da.partial = static_cast<uint32_t *>(ctx->ws[WS_OCC]);
     const dim3 cg((unsigned)grid), rg((unsigned)std::min<int64_t>(64 * ceil_div(pitch, CT) * ceil_div(pitch, CT),
                                                                    (int64_t)ctx->num_cus * 8));
     const int kid = FULL ? K_COUNT_DENSE : K_COUNT_TRUNC;
@@ -1919,30 +1925,50 @@ inline bool count_all_fits(int64_t n, int32_t L, int32_t m, bool weighted) {
     return (double)ceil_div(n, 32) * pitch * pitch * (rank_bits(std::min(L, m - 1)) + 2 + (weighted ? 36 : 0)) <= ALL_COST;
 }
 
+// Workspace of the one-pass count (in WS_OCC): partial tiles, planes, planes
+// of the weights.  Every part grows with n, L and m, so that the layout of a
+// call holds every smaller one's.
+struct AllLayout {
+    int64_t groups, ntiles, workers;
+    int32_t pitch, bits;
+    bool whole;  // whole tiles per workgroup; else ranges of two units or more, whose partial tiles are added up
+    size_t planes, wplanes, total;
+    AllLayout(int64_t num_cus, int64_t n, int32_t L, int32_t m, bool weighted) {
+        pitch = (int32_t)round_up(m, CT), bits = rank_bits(std::min(L, m - 1));
+        groups = ceil_div(n, 32), ntiles = (int64_t)(pitch / CT) * (pitch / CT);
+        const int64_t grid_max = num_cus * COUNT_PER_CU, ranges = std::min(grid_max, ceil_div(ntiles * groups, 2));
+        whole = 2 * ntiles >= grid_max || groups == 1;
+        workers = whole ? std::min(grid_max, ntiles) : ranges;
+        // (unused when whole, but a smaller call may not be)
+        const int64_t tiles = groups > 1 ? ranges + std::min(ntiles, grid_max / 2) : 0;
+        // a call this large may be routed, but what ALL_COST lets through has at most ALL_COST / CT words of planes
+        const size_t words = (size_t)std::min<double>((double)groups * bits * pitch, ALL_COST / CT);
+        const size_t wwords = weighted ? 32 * (size_t)std::min<double>((double)groups, ALL_COST / (CT * CT)) : 0;
+        planes = sizeof(uint32_t) * CT * CT * (size_t)tiles;
+        wplanes = planes + sizeof(uint32_t) * words;
+        total = wplanes + sizeof(uint32_t) * wwords;
+    }
+};
+
 int count_all(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype32, int64_t n, int32_t L, int32_t m,
               const uint32_t *weight, int d_dtype, void *d, int64_t ldd) {
-    const int32_t pitch = (int32_t)round_up(m, CT), bits = rank_bits(std::min(L, m - 1));
-    const int64_t groups = ceil_div(n, 32), nb = pitch / CT, ntiles = nb * nb, units = ntiles * groups;
-    const size_t plane_words = (size_t)groups * bits * pitch;
-    int rc = ws_reserve(ctx, WS_POSITIONS, sizeof(uint32_t) * (plane_words + (weight ? 32 * (size_t)groups : 0)));
+    const AllLayout al(ctx->num_cus, n, L, m, weight != nullptr);
+    const int32_t pitch = al.pitch, bits = al.bits;
+    const int64_t groups = al.groups, ntiles = al.ntiles, workers = al.workers;
+    const bool whole = al.whole;
+    int rc = ws_reserve(ctx, WS_OCC, al.total);
     if (rc != SCHULZE_OK) return rc;
-    // whole tiles per workgroup when there are enough of them; else ranges of
-    // two units or more, whose partial tiles are added up
-    const int64_t grid_max = (int64_t)ctx->num_cus * COUNT_PER_CU;
-    const bool whole = 2 * ntiles >= grid_max || groups == 1;
-    const int64_t workers = whole ? std::min(grid_max, ntiles) : std::min(grid_max, ceil_div(units, 2));
-    if (!whole && (rc = ws_reserve(ctx, WS_PARTIAL, sizeof(uint32_t) * CT * CT * (size_t)(workers + ntiles))) != SCHULZE_OK)
-        return rc;
-    uint32_t *planes = static_cast<uint32_t *>(ctx->ws[WS_POSITIONS]);
+    if (weight && (rc = ws_reserve(ctx, WS_BALLOT_META, 64 * sizeof(int32_t))) != SCHULZE_OK) return rc;
+    char *base = static_cast<char *>(ctx->ws[WS_OCC]);
+    uint32_t *planes = reinterpret_cast<uint32_t *>(base + al.planes);
     DenseArgs da{};
     da.planes = planes, da.pitch = pitch, da.bits = bits, da.m = m;
-    da.wplanes = weight ? planes + plane_words : nullptr;
-    da.partial = static_cast<uint32_t *>(ctx->ws[WS_PARTIAL]);
+    da.wplanes = weight ? reinterpret_cast<uint32_t *>(base + al.wplanes) : nullptr;
+    da.partial = reinterpret_cast<uint32_t *>(base);
     da.n = (int32_t)n, da.whole = whole;
     da.d = d, da.ldd = ldd, da.d32 = d_dtype == SCHULZE_I32, da.err = ctx->err;
     da.limit = d_dtype == SCHULZE_U16 ? 65535u : (uint32_t)INT32_MAX;
     if (weight) {
-        if ((rc = ws_reserve(ctx, WS_BALLOT_META, 64 * sizeof(int32_t))) != SCHULZE_OK) return rc;
         da.meta.ctr = static_cast<int32_t *>(ctx->ws[WS_BALLOT_META]);
         if ((rc = fill_u32(ctx, s, reinterpret_cast<uint32_t *>(da.meta.ctr), 64, 0u)) != SCHULZE_OK) return rc;
     }
@@ -2009,9 +2035,6 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     if (trunc_bytes &&
         (rc = ws_reserve(ctx, WS_TRUNC_POS, trunc_bytes)) != SCHULZE_OK)
         return rc;
-    if (n > 0 && (rc = ws_reserve(ctx, WS_PARTIAL, sizeof(uint32_t) * 2 * CT * CT * (size_t)ctx->num_cus * COUNT_PER_CU)) !=
-                     SCHULZE_OK)
-        return rc;
     // bucketed pair counting: an LDS row of counts per candidate and a bounded occurrence buffer
     const int64_t occ_cap = n * (int64_t)L;
     const bool occ_ok = n > 0 && m <= OCC_MAX_M && occ_cap <= OCC_MAX && !ctx->legacy_pairs;
@@ -2020,7 +2043,11 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     const int64_t acc_row = (m <= OCC_MAX_M / 2 ? OCC_MAX_M / 2 : OCC_MAX_M) * (voter_weight ? 4 : 2) + 256;
     const int64_t acc_grid = ctx->num_cus * std::min<int64_t>(4, 160 * 1024 / acc_row);
     const OccLayout ol(occ_ok ? occ_grid : 0, m, occ_ok ? occ_cap : 0, voter_weight ? 4 : 2, acc_grid);
-    if (occ_ok && (rc = ws_reserve(ctx, WS_OCC, ol.total)) != SCHULZE_OK) return rc;
+    // the same memory in turn: the dense counts' partial tiles, then the
+    // bucketed count's, and in a smaller call all of the one-pass count's
+    const size_t scratch = std::max({sizeof(uint32_t) * 2 * CT * CT * (size_t)ctx->num_cus * COUNT_PER_CU,
+                                     occ_ok ? ol.total : 0, AllLayout(ctx->num_cus, n, L, m, voter_weight != nullptr).total});
+    if (n > 0 && (rc = ws_reserve(ctx, WS_OCC, scratch)) != SCHULZE_OK) return rc;
 
     char *mb = static_cast<char *>(ctx->ws[WS_BALLOT_META]);
     Meta meta{reinterpret_cast<int32_t *>(mb + lay.ctr),

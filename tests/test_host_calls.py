@@ -98,3 +98,49 @@ out(rows)
         many = E > 1024
         assert ("k_seg_loss_many" in line) == many
         assert int(line.split()[2]) == (-(-E // 4) if many else E)
+
+
+def test_smaller_counts_allocate_nothing(fake_hip):
+    """A context that has made a count makes every smaller one of its kind (fewer
+    voters, shorter ballots, fewer candidates; with voter weights or without,
+    with room for full rankings or without) without a new allocation, whatever
+    kernels the smaller call takes: an eager call sizes the workspace for the
+    calls that are captured after it."""
+    got = fake_hip("""
+rng = random.Random(7)
+def log_uniform(lo, hi):
+    return int(round(lo * (hi / lo) ** rng.random()))
+def pairwise(h, n, L, m, weighted, ids):
+    assert lib.schulze_pairwise(h, None, FAR, ids, n, L, m, FAR if weighted else None, I32, 2 * FAR, m) == 0
+bad, routed = [], set()
+for trial in range(1000):
+    m, n = log_uniform(2, 20000), log_uniform(1, 200000)
+    L = m if rng.random() < 0.4 else log_uniform(1, m)
+    while n * L > 1 << 27:
+        n = max(1, n // 2)
+    weighted, ids = rng.random() < 0.4, rng.choice([U16, I32])
+    h = context()
+    pairwise(h, n, L, m, weighted, ids)
+    for smaller in range(12):
+        # (LDS rows are wider and workgroups fewer above 16384 candidates)
+        m2 = log_uniform(1, m) if m <= 16384 else rng.randint(16385, m)
+        if rng.random() < 0.3:
+            m2 = max(m2, m - rng.randint(0, 3))
+        L2 = min(L, m2) if rng.random() < 0.5 else log_uniform(1, min(L, m2))
+        if (L2 >= m2 - 1) != (L >= m - 1):
+            if L < m - 1 and m2 < 3:
+                continue
+            L2 = m2 - 2 if L < m - 1 else min(L, m2)
+        n2 = max(1, n - rng.randint(0, 3)) if rng.random() < 0.3 else log_uniform(1, n)
+        fake.fake_reset()
+        pairwise(h, n2, L2, m2, weighted, ids)
+        routed.add(any("k_route" in l for l in launched()))
+        if any(l.startswith("malloc") for l in log()):
+            bad.append([[n, L, m], [n2, L2, m2], weighted, [l for l in log() if l.startswith("malloc")]])
+            break
+    lib.schulze_destroy(h)
+out([bad, sorted(routed)])
+""")
+    bad, routed = got
+    assert routed == [False, True]
+    assert bad == []
