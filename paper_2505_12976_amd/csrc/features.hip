@@ -443,6 +443,21 @@ int feature_sb(const schulze_ctx *ctx, int32_t m) {
     return 1;
 }
 
+// Partial entries (candidates times slots) that any call of at most m
+// candidates needs: fewer tiles per super-block mean more slots, so that a
+// smaller call may need more than this one.  (The most that each super-block
+// size needs is at its largest m.)
+size_t feature_slots(const schulze_ctx *ctx, int32_t m) {
+    const int64_t tiles = ceil_div(m, 64);
+    int64_t side = 1, most = 0;  // super-blocks per side from which one size is enough
+    while (side * (side + 1) / 2 < 2 * (int64_t)ctx->num_cus) ++side;
+    for (int sb = 1; sb <= 4; sb *= 2) {
+        const int64_t t = sb == 4 ? tiles : std::min(tiles, 2 * sb * (side - 1));
+        most = std::max(most, std::min<int64_t>(m, 64 * t) * ceil_div(t, sb));
+    }
+    return (size_t)most;
+}
+
 template <typename E>
 int run_features(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, float n_voters,
                  float *feat) {
@@ -451,7 +466,7 @@ int run_features(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32
     const int32_t S = (int32_t)ceil_div(ceil_div(m, 64), sb);
     size_t fin_bytes = 0, part_bytes = 0;
     (void)carve(nullptr, (size_t)m, &fin_bytes);
-    (void)carve(nullptr, (size_t)m * S, &part_bytes);
+    (void)carve(nullptr, feature_slots(ctx, m), &part_bytes);
     const int32_t groups = (int32_t)ceil_div(m, 64);
     const size_t g4 = round_up(4 * (size_t)groups, 256), g8 = round_up(8 * (size_t)groups, 256);
     int rc = ws_reserve(ctx, WS_FEATURES, fin_bytes + part_bytes + 2 * g4 + g8);

@@ -144,3 +144,24 @@ out([bad, sorted(routed)])
     bad, routed = got
     assert routed == [False, True]
     assert bad == []
+
+
+def test_smaller_features_allocate_nothing(fake_hip):
+    got = fake_hip("""
+rng = random.Random(3)
+bad = []
+def features(h, m):
+    assert lib.schulze_features(h, None, FAR, m, m, I32, 0, 1.0, 2 * FAR) == 0
+sizes = [1, 63, 64, 65, 700, 3967, 3968, 3969, 4032, 4033, 7872, 7873, 7936, 7937, 8000, 20000, 65535]
+for m in sizes + list(range(3900, 8100, 97)):
+    h = context()
+    features(h, m)
+    fake.fake_reset()
+    for m2 in [k for k in sizes if k <= m] + [rng.randint(1, m) for _ in range(60)]:
+        features(h, m2)
+    if any(l.startswith("malloc") for l in log()):
+        bad.append([m, [l for l in log() if l.startswith("malloc")]])
+    lib.schulze_destroy(h)
+out(bad)
+""")
+    assert got == []
