@@ -28,6 +28,7 @@
 // completes and converts to the output dtype.
 #include "internal.h"
 #include "planes.h"
+#include "row_pieces.h"
 #include "tile_io.h"
 
 namespace {
@@ -42,7 +43,6 @@ constexpr int NPART = 64;         // partial sums of the pair-scattering cost
 enum { MODE_SPARSE = 0, MODE_DENSE_U = 1 };
 
 #define CNT_LDS __attribute__((address_space(3)))
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // Workspace views (WS_BALLOT_META).
 struct Meta {
@@ -98,72 +98,6 @@ __device__ inline void record_ballots(Meta meta, int nf, const int32_t *lf, int 
     for (int i = threadIdx.x; i < nf; i += blockDim.x) meta.full_src[base_f + i] = lf[i];
     for (int i = threadIdx.x; i < nt; i += blockDim.x) meta.trunc_src[base_t + i] = lt[i];
 }
-
-// Ballot rows in 16-byte pieces whatever their length and alignment: piece j
-// of a row is the j-th aligned 16 bytes that hold one of its entries, and
-// entry e of it has position j PER + e - head (outside 0 .. L-1: another
-// row's).  The few pieces that reach outside the ballot array (its first and
-// last, if the array is not aligned) are put together entry by entry.
-template <bool I32>
-struct RowPieces {
-    static constexpr int SIZE = I32 ? 4 : 2, PER = 16 / SIZE;
-    const char *lo, *hi, *at;  // the ballot array, and the row's first piece
-    int32_t head, count;
-    __device__ RowPieces(const void *ballots, int64_t n, int32_t L, int64_t row) {
-        lo = static_cast<const char *>(ballots);
-        hi = lo + n * L * SIZE;
-        const char *p = lo + row * L * SIZE;
-        at = reinterpret_cast<const char *>(reinterpret_cast<uintptr_t>(p) & ~(uintptr_t)15);
-        head = (int32_t)(p - at) / SIZE;
-        count = (head + L + PER - 1) / PER;
-    }
-    __device__ const char *piece(int32_t j) const { return at + 16 * (int64_t)min(j, count - 1); }
-    __device__ bool inside(const char *p) const { return p >= lo && p + 16 <= hi; }
-    // pieces j, j + 64, .. of a lane, in flight together
-    template <int FLY>
-    __device__ void load(v4u (&x)[FLY], int32_t j) const {
-        for (int u = 0; u < FLY; ++u) {
-            const char *p = piece(j + 64 * u);
-            x[u] = *reinterpret_cast<const v4u *>(inside(p) ? p : at + 16 * (count > 2 ? 1 : 0));
-        }
-        if (count <= 2 || !inside(at) || !inside(piece(count - 1)))
-            for (int u = 0; u < FLY; ++u) {
-                const char *p = piece(j + 64 * u);
-                if (inside(p)) continue;
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t w = 0xFFFFFFFFu;
-                    for (int h = 0; h < PER / 4; ++h) {
-                        const char *q = p + 4 * e + SIZE * h;
-                        if (q < lo || q + SIZE > hi) continue;
-                        if (I32)
-                            w = *reinterpret_cast<const uint32_t *>(q);
-                        else
-                            w = h ? (w & 0xFFFFu) | ((uint32_t)*reinterpret_cast<const uint16_t *>(q) << 16)
-                                  : (w & 0xFFFF0000u) | *reinterpret_cast<const uint16_t *>(q);
-                    }
-                    x[u][e] = w;
-                }
-            }
-    }
-    // f(position, raw id) for the row's entries of piece j
-    template <typename F>
-    __device__ void each(const v4u &x, int32_t j, int32_t L, F f) const {
-        for (int e = 0; e < PER; ++e) {
-            const int32_t t = j * PER + e - head;
-            if ((uint32_t)t < (uint32_t)L) f(t, I32 ? x[e] : (e & 1) ? x[e >> 1] >> 16 : x[e >> 1] & 0xFFFFu);
-        }
-    }
-    // the largest id of the piece, padding above all
-    __device__ static uint32_t top(const v4u &x) {
-        if constexpr (I32) return max(max(x[0], x[1]), max(x[2], x[3]));
-        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-        const uint32_t w[4] = {x[0], x[1], x[2], x[3]};
-        const us2 h = __builtin_elementwise_max(
-            __builtin_elementwise_max(__builtin_bit_cast(us2, w[0]), __builtin_bit_cast(us2, w[1])),
-            __builtin_elementwise_max(__builtin_bit_cast(us2, w[2]), __builtin_bit_cast(us2, w[3])));
-        return max((uint32_t)h.x, (uint32_t)h.y);
-    }
-};
 
 // Long rows: one wavefront per ballot, a workgroup of 16 takes `chunk`
 // ballots (at most one workgroup per CU, so that there are few
