@@ -1316,7 +1316,7 @@ __global__ __launch_bounds__(1024) void k_occ_scan(OccArgs a) {
 // occurrence of r at position t of ballot v, every id ahead of it gains the
 // voter's weight in the LDS row (C[id][r]), and r gains it in R.  PACKED
 // (unit weights): two 16-bit counts per LDS word (an item adds at most
-// OCC_CHUNK to a column).  The only item of a row writes the row of d
+// OCC_CHUNK_MAX to a column).  The only item of a row writes the row of d
 // (d[r][y] = base + R - C[y][r], base = full-ranking counts in acc or 0); an
 // item of a heavier row writes its counts to its partial row and adds its
 // part of R to rsum[r].
@@ -1324,17 +1324,28 @@ __global__ __launch_bounds__(1024) void k_occ_scan(OccArgs a) {
 // Most candidates have few occurrences, so an item is a chain of dependent
 // loads (item, occurrences, ballots) and then a row of d to write, with room
 // for two to four LDS rows on a CU to hide them.  The workgroups stay: each
-// takes every gridDim-th item (heavy candidates' items come in a run and fall
-// to different workgroups), loads the next item's occurrences while it adds
-// this one's ids and the next item's first ids while it writes this one's
-// row, and clears the LDS row as it reads it out.  Ids come 16 bytes at a
-// time at any alignment, as a scattered load costs its lane the same whatever
-// its width.
+// starts with two items and draws the others from a queue per die (heavy
+// candidates' items come in a run and fall to different workgroups), loads the
+// next item's occurrences while it adds this one's ids and the next item's
+// first ids while it writes this one's row, and clears the LDS row as it reads
+// it out.  Ids come 16 bytes at a time at any alignment, as a scattered load
+// costs its lane the same whatever its width.
 //   m = 14187, 15553 ballots of up to 150 uint16 ids:  916 -> 464 us
 //   m = 16384, 1M ballots of up to 20, int32 d:        560 -> 550
 //   m = 32768, 200000 ballots of up to 30, int32 d:   1506 -> 869 (1073 through the caches)
 //   m = 6007, 100003 ballots of up to 12 int32 ids:    114 -> 49
 // (a workgroup per item, its row found by a binary search.)
+//
+// Ballots longer than the first pieces are read one occurrence after the
+// other, the next pieces in flight while these are added.  Reading a thread's
+// two occurrences side by side kept twice as many rows live in the L2, and
+// with few wavefronts per CU (voter weights: 64 KB rows) nothing hid the wait
+// for each step.  The whole count, us, with voter weights:
+//                                        an id a load   side by side   so
+//   m = 1500, 3000 up to 1500 int32 ids      2281           3470      1820
+//   m = 1500, 3000 up to 1500 uint16 ids     2274           2500      1716
+//   m = 5000, 30000 of 150 int32 ids          866           1065       685
+//   m = 5000, 30000 of 25 int32 ids           197            169       166
 constexpr int OCC_BATCH = 2, OCC_FLY = 4;  // occurrences per thread, pieces of ids of each in flight
 template <int MAXM, bool PACKED, typename T, bool I32>
 __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict__ d, int64_t ldd, uint32_t limit,
@@ -1369,56 +1380,54 @@ __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict
 #pragma unroll
         for (int u = 0; u < OCC_BATCH; ++u) ov[u] = a.occ[min(q + 256 * u, end - 1)];
     };
-    int64_t base[OCC_BATCH];
-    int32_t t[OCC_BATCH];
-    uint32_t w[OCC_BATCH];
+    struct Occ {
+        const Id *ids;  // the ballot
+        int32_t t;      // position: so many ids are ahead
+        int32_t lim;    // position of the last piece inside the ballots, at most 2^30
+        uint32_t w;
+    };
+    Occ oc[OCC_BATCH];
     uint4 x[OCC_BATCH][OCC_FLY];
-    auto ids_in = [&](int32_t i0) {
+    auto piece = [&](const Occ &o, int32_t i) { return tio::load16<Id>(o.ids + min(i, o.lim)); };
+    auto begin_ids = [&](const uint32_t (&ov)[OCC_BATCH], uint32_t q, uint32_t end) {
+#pragma unroll
+        for (int u = 0; u < OCC_BATCH; ++u) {
+            const int64_t v = ov[u] >> a.tbits, b = v * a.L;
+            oc[u].ids = ids + b;
+            oc[u].lim = (int32_t)min(last - b, (int64_t)1 << 30);
+            oc[u].w = q + 256 * u >= end ? 0u : (PACKED ? 1u : (a.weight ? a.weight[v] : 1u));
+            oc[u].t = oc[u].w ? (int32_t)(ov[u] & tmask) : 0;
+        }
 #pragma unroll
         for (int u = 0; u < OCC_BATCH; ++u)
 #pragma unroll
             for (int f = 0; f < OCC_FLY; ++f)
-                if (i0 + V * f < t[u] && last >= 0) x[u][f] = tio::load16<Id>(ids + min(base[u] + i0 + V * f, last));
-    };
-    auto begin_ids = [&](const uint32_t (&ov)[OCC_BATCH], uint32_t q, uint32_t end) {
-#pragma unroll
-        for (int u = 0; u < OCC_BATCH; ++u) {
-            const int64_t v = ov[u] >> a.tbits;
-            base[u] = v * a.L;
-            w[u] = q + 256 * u >= end ? 0u : (PACKED ? 1u : (a.weight ? a.weight[v] : 1u));
-            t[u] = w[u] ? (int32_t)(ov[u] & tmask) : 0;
-        }
-        ids_in(0);
+                if (V * f < oc[u].t && last >= 0) x[u][f] = piece(oc[u], V * f);
     };
     bool dup = false, over = false;
     uint32_t r = 0;
-    auto add = [&](int32_t id, uint32_t weight) {
-        if ((uint32_t)id == r) dup = true;
-        if ((uint32_t)id >= (uint32_t)m) return;
-        if (PACKED)
-            atomicAdd(&row[id >> 1], 1u << ((id & 1) * 16));
-        else
-            atomicAdd(&row[id], weight);
+    auto add = [&](bool in, uint32_t id, uint32_t weight) {
+        dup |= in && id == r;
+        if (in && id < (uint32_t)m) {  // (not padding)
+            if (PACKED)
+                atomicAdd(&row[id >> 1], 1u << ((id & 1) * 16));
+            else
+                atomicAdd(&row[id], weight);
+        }
     };
-    auto add_ids = [&](int32_t i0) {
+    // the ids at positions i .. of an occurrence, from their piece
+    auto add_piece = [&](const Occ &o, int32_t i, const uint4 &xp) {
+        if (i >= o.t) return;
+        if (last < 0) {
+            for (int32_t k = i; k < min(i + V, o.t); ++k) add(true, load_raw<I32>(o.ids, k), o.w);
+            return;
+        }
+        // (the ballots' last piece may start before position i: skip to it)
+        const int32_t skip = max(i - o.lim, 0), left = o.t - i;
+        Id e[V];
+        tio::unpack<Id>(xp, e);
 #pragma unroll
-        for (int u = 0; u < OCC_BATCH; ++u)
-#pragma unroll
-            for (int f = 0; f < OCC_FLY; ++f) {
-                const int32_t i = i0 + V * f;
-                if (i >= t[u]) continue;
-                if (last < 0) {
-                    for (int32_t k = i; k < min(i + V, t[u]); ++k) add(read_id<I32>(a.ballots, base[u] + k), w[u]);
-                    continue;
-                }
-                // (the ballots' last piece may start before position i: skip to it)
-                const int32_t skip = (int32_t)max(base[u] + i - last, (int64_t)0), left = t[u] - i + skip;
-                Id e[V];
-                tio::unpack<Id>(x[u][f], e);
-#pragma unroll
-                for (int k = 0; k < V; ++k)
-                    if (k >= skip && k < left) add(raw_id<I32>((uint32_t)e[k]), w[u]);
-            }
+        for (int k = 0; k < V; ++k) add((uint32_t)(k - skip) < (uint32_t)left, (uint32_t)e[k], o.w);
     };
 
     Item it = item_of(a.items[blockIdx.x]), next = item_of(a.items[min(blockIdx.x + G, total - 1)]);
@@ -1436,16 +1445,42 @@ __global__ __launch_bounds__(256) void k_occ_accumulate(OccArgs a, T *__restrict
         r = it.r;
         uint32_t wpart = 0;
         for (uint32_t q = it.begin + threadIdx.x;;) {
-            int32_t longest = 0;
-            add_ids(0);
 #pragma unroll
             for (int u = 0; u < OCC_BATCH; ++u) {
-                wpart += w[u];
-                longest = max(longest, t[u]);
+                wpart += oc[u].w;
+#pragma unroll
+                for (int f = 0; f < OCC_FLY; ++f) add_piece(oc[u], V * f, x[u][f]);
             }
-            for (int32_t i0 = V * OCC_FLY; i0 < longest; i0 += V * OCC_FLY) {
-                ids_in(i0);
-                add_ids(i0);
+            // the rest of longer ballots, one occurrence after the other
+            constexpr int32_t STEP = V * OCC_FLY;
+#pragma unroll 1
+            for (int u = 0; u < OCC_BATCH; ++u) {
+                Occ o = oc[0];
+                if (u) o = oc[1];
+                int32_t i = STEP;
+                if (i >= o.t || last < 0) continue;
+                auto pieces_in = [&](int h, int32_t at) {
+#pragma unroll
+                    for (int f = 0; f < OCC_FLY; ++f) x[h][f] = piece(o, at + V * f);
+                };
+                auto pieces_add = [&](int h) {
+#pragma unroll
+                    for (int f = 0; f < OCC_FLY; ++f) add_piece(o, i + V * f, x[h][f]);
+                };
+                pieces_in(0, i);
+                if (o.t <= 2 * STEP) {
+                    pieces_add(0);
+                    continue;
+                }
+#pragma unroll 1
+                for (;;) {  // the next pieces in flight while these are added
+                    pieces_in(1, i + STEP);
+                    pieces_add(0);
+                    if ((i += STEP) >= o.t) break;
+                    pieces_in(0, i + STEP);
+                    pieces_add(1);
+                    if ((i += STEP) >= o.t) break;
+                }
             }
             q += 256 * OCC_BATCH;
             if (q >= it.end) break;
