@@ -383,7 +383,7 @@ struct PlaneArgs {
     Meta meta;
     const uint32_t *weight;  // nullptr: every voter counts once
     uint32_t *planes;
-    uint32_t *wplanes;  // 32 words per group
+    uint32_t *wplanes;  // WEIGHT_WORDS per group
     int32_t *err;
     int64_t n;           // ballots of the profile
 };
@@ -417,17 +417,24 @@ __device__ inline void check_repeats(int32_t extra, int32_t *total, int32_t *err
     if (threadIdx.x == 0 && *total != 0) set_device_error(err, SCHULZE_EBALLOT);
 }
 
-// One wavefront: the 32 bit planes of its lanes' weights (lanes 0 .. 31 hold
-// the voter of their bit, the others 0); returns the weights' sum.
+// One wavefront: the weights of a group's voters (lanes 0 .. 31 hold the voter
+// of their bit, the others 0) as 32 bit planes and as 32 words of digits: word
+// 4 p + j has the p-th four bits of the weights of the voters 4 i + j, i = 0 ..
+// 7.  Returns the weights' sum.
+constexpr int WEIGHT_WORDS = 64;
 __device__ inline uint32_t weight_planes(uint32_t w, uint32_t *out) {
     const int lane = threadIdx.x & 63;
-    uint32_t mine = 0u, sum = w;
+    uint32_t mine = 0u, sum = w, digits = 0u;
     for (int j = 0; j < 32; ++j) {
         const uint32_t mask = (uint32_t)__ballot((w >> j) & 1u);
         if (lane == j) mine = mask;
     }
+    for (int i = 0; i < 8; ++i) digits |= ((__shfl(w, 4 * i + (lane & 3)) >> (lane & 28)) & 15u) << (4 * i);
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane < 32) out[lane] = mine;
+    if (lane < 32) {
+        out[lane] = mine;
+        out[32 + lane] = digits;
+    }
     return sum;
 }
 
@@ -487,7 +494,8 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
     check_repeats(extra, &repeated, a.err);
     if (a.weight && c0 == 0 && wave == 0) {
         const int v = 2 * (lane & 15) + ((lane >> 4) & 1);  // the voter of bit `lane`
-        const uint32_t sum = weight_planes(lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u, a.wplanes + 32 * g);
+        const uint32_t sum = weight_planes(lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u,
+                                           a.wplanes + WEIGHT_WORDS * g);
         if (FULL && lane == 0) atomicAdd(&a.meta.ctr[8], (int32_t)sum);
     }
     __syncthreads();  // the LDS is read
@@ -572,7 +580,7 @@ __global__ __launch_bounds__(1024) void k_planes_all(AllArgs a) {
     check_repeats(extra, &repeated, a.repeated);
     if (a.weight && blockIdx.y == 0 && wave == 0) {
         const int v = 2 * (lane & 15) + ((lane >> 4) & 1);
-        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
+        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + WEIGHT_WORDS * g);
     }
 }
 
@@ -632,7 +640,7 @@ __global__ __launch_bounds__(256) void k_planes_short(AllArgs a) {
     check_repeats(extra, &repeated, a.repeated);
     if (a.weight && blockIdx.y == 0 && threadIdx.x < 64) {
         const int lane = threadIdx.x, v = 2 * (lane & 15) + ((lane >> 4) & 1);
-        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + 32 * g);
+        (void)weight_planes(lane < 32 && v < live ? a.weight[32 * g + v] : 0u, a.wplanes + WEIGHT_WORDS * g);
     }
 }
 
@@ -766,6 +774,42 @@ __device__ inline void tri_coords(int32_t t, int32_t nb, int32_t &X, int32_t &Y)
     Y = x + (t - start);
 }
 
+// acc += the masks' voters' weights times 2^shift, sixteen bits of them as the
+// digits of four bits in d: a mask is spread to one bit per digit (seven
+// operations), then four v_dot8_u32_u4 per digit and a shifted addition, 27
+// operations where bit planes take 48.
+__device__ __forceinline__ void add_digits(const Masks &lt, const uint32_t (&d)[16], int shift, uint32_t (&acc)[8][8]) {
+    uint32_t k = 0x11111111u, one = 1u, two = 2u, three = 3u;
+    asm volatile("" : "+s"(k), "+s"(one), "+s"(two), "+s"(three));  // (spread masks are not kept for the next call)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t m = lt.get(i, j);
+            const uint32_t x[4] = {m & k, (m >> one) & k, (m >> two) & k, (m >> three) & k};
+            uint32_t sum = 0u;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                uint32_t t = 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t = __builtin_amdgcn_udot8(x[q], d[4 * p + q], t, false);
+                sum += t << (4 * p);
+            }
+            acc[i][j] += sum << shift;
+            __builtin_amdgcn_sched_barrier(0);  // one mask at a time: few registers
+        }
+}
+
+// Bits of the weights that are added up as digits, sixteen at a time; the bits
+// above go plane by plane.  (Of sixteen bits or what is left, planes are fewer
+// operations up to 8.)
+__host__ __device__ inline int32_t digit_bits(int32_t bits) { return bits % 16 > 8 ? bits / 16 * 16 + 16 : bits / 16 * 16; }
+// Operations per mask for weights of so many bits.
+inline int32_t weight_ops(int32_t bits) {
+    const int32_t digits = digit_bits(bits);
+    return 27 * (digits / 16) + 3 * std::max(bits - digits, 0);
+}
+
 template <int MODE, bool WEIGHTED>
 __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
     constexpr int ROW = 2 * CT;  // LDS words per bit: the tile's rows, then its columns
@@ -886,8 +930,19 @@ __global__ __launch_bounds__(256, 3) void k_count_bits(DenseArgs a) {
         }
         if (bits & 1) lt.step(q0.x, q0.y);
         if constexpr (WEIGHTED) {
-            for (int32_t b = 0; b < wbits; ++b) {
-                const uint32_t wm = a.wplanes[32 * g + b];
+            const uint32_t *wp = a.wplanes + (int64_t)WEIGHT_WORDS * g;
+            const int32_t digits = digit_bits(wbits);
+#pragma unroll 1
+            for (int32_t b = 0; b < digits; b += 16) {
+                uint32_t d[16], any = 0u;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) any |= d[q] = __builtin_amdgcn_readfirstlane(wp[32 + b + q]);
+                if (any == 0u) continue;
+                add_digits(lt, d, b, acc);
+            }
+#pragma unroll 1
+            for (int32_t b = digits; b < wbits; ++b) {
+                const uint32_t wm = __builtin_amdgcn_readfirstlane(wp[b]);
                 if (wm == 0u) continue;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
@@ -1883,15 +1938,40 @@ int count_dense(schulze_ctx *ctx, hipStream_t s, const void *ballots, int dtype3
 // scan, the route decision and both routes' kernels (19, at about 4.5 us
 // each even where they find nothing to do).  Taken while the count costs at
 // most ALL_COST lane operations (65 us at 45 T/s), about what the other
-// launches would (n = 7001 weighted top-25 of m = 389: 434 us by pairs, 366 us
-// so); weights are charged as 12 bits.
+// launches would.
+//
+// Voter weights cost some operations more per mask (weight_ops), and how many
+// bits they have only the device knows.  Twelve planes' are charged against
+// ALL_COST; but short ballots cost the routed count little more than its
+// launches, so there the count has to win with as many bits as a total weight
+// below 2^32 allows, 33 - log2(groups) on average.  In lane operations at 37 T/s
+// the routed count is taken as 34 us (WIDE_COST; the rest of its 70 us is what
+// the one pass launches too), 1.3 ps a cell of the matrix, 8 ns a ballot and 3
+// ps for each pair that ballots of this length can list.  Counts in us, with
+// weights of 6, 16 and 32 bits (at most: their total is below 2^32):
+//                                one pass     by pairs   taken
+//   m = 1000, n =  480, top-20   53  57  69      80      one pass
+//   m = 1000, n = 1400, top-20   72  84 108      84      by pairs
+//   m =  389, n = 7001, top-25   77  93 115      85      one pass
+//   m =  128, n = 1e5,  top-10  104 117 118     130      one pass
+//   m = 2000, n =  300, top-30   66  77 107      87      by pairs
+//   m = 4096, n =   64, top-50   56  65  92     100      one pass
+//   m = 1000, n = 1400, up to 1000 places
+//                                82  94 118   92 to 700  one pass (92: all of them list 20)
 constexpr int REPEATED = 9;  // counter that holds SCHULZE_EBALLOT if a ballot lists an id twice
 constexpr double ALL_COST = 3.0e9;
+constexpr double WIDE_COST = 1.25e9, ROUTED_CELL_COST = 50.0, ROUTED_BALLOT_COST = 3.1e5, LISTED_PAIR_COST = 112.0;
 constexpr int32_t ALL_MAX_M = 4096;
 inline bool count_all_fits(int64_t n, int32_t L, int32_t m, bool weighted) {
     if (n < 1 || m > ALL_MAX_M) return false;
-    const double pitch = (double)round_up(m, CT);
-    return (double)ceil_div(n, 32) * pitch * pitch * (rank_bits(std::min(L, m - 1)) + 2 + (weighted ? 36 : 0)) <= ALL_COST;
+    const int64_t groups = ceil_div(n, 32);
+    const double pitch = (double)round_up(m, CT), work = (double)groups * pitch * pitch;
+    const int32_t ops = rank_bits(std::min(L, m - 1)) + 2;
+    if (work * (ops + (weighted ? 36 : 0)) > ALL_COST) return false;
+    if (!weighted) return true;
+    const int32_t bits = std::min(32, __builtin_clzll((uint64_t)groups) - 30);  // 33 - log2(groups)
+    return work * (ops + weight_ops(bits)) <= WIDE_COST + ROUTED_CELL_COST * m * m + ROUTED_BALLOT_COST * n +
+                                                  LISTED_PAIR_COST * 0.5 * (double)n * L * (L - 1);
 }
 
 // Workspace of the one-pass count (in WS_OCC): partial tiles, planes, planes
@@ -1912,7 +1992,7 @@ struct AllLayout {
         const int64_t tiles = groups > 1 ? ranges + std::min(ntiles, grid_max / 2) : 0;
         // a call this large may be routed, but what ALL_COST lets through has at most ALL_COST / CT words of planes
         const size_t words = (size_t)std::min<double>((double)groups * bits * pitch, ALL_COST / CT);
-        const size_t wwords = weighted ? 32 * (size_t)std::min<double>((double)groups, ALL_COST / (CT * CT)) : 0;
+        const size_t wwords = weighted ? WEIGHT_WORDS * (size_t)std::min<double>((double)groups, ALL_COST / (CT * CT)) : 0;
         planes = sizeof(uint32_t) * CT * CT * (size_t)tiles;
         wplanes = planes + sizeof(uint32_t) * words;
         total = wplanes + sizeof(uint32_t) * wwords;
@@ -1977,8 +2057,8 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     const int dtype32 = ballot_dtype == SCHULZE_I32;
-    if (!ctx->legacy_pairs && count_all_fits(n, L, m, voter_weight != nullptr))
-        return count_all(ctx, s, ballots, dtype32, n, L, m, voter_weight, d_dtype, d, ldd);
+    const bool one_pass = !ctx->legacy_pairs && count_all_fits(n, L, m, voter_weight != nullptr);
+    if (one_pass && !voter_weight) return count_all(ctx, s, ballots, dtype32, n, L, m, nullptr, d_dtype, d, ldd);
     const int32_t pitch = (int32_t)round_up(m, CT);
     const int64_t max_groups = ceil_div(n, 32);  // of 32 voters
     const bool may_have_full = L >= m - 1 && n > 0;
@@ -1990,8 +2070,8 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
             ? std::min(TRUNC_PLANES_CAP,
                        sizeof(uint32_t) * (size_t)max_groups * trunc_bits * (size_t)upitch_max)
             : 0;
-    // weights: 32 planes per group of the full rankings (weighted truncated ballots are counted by pairs)
-    const size_t weight_words = voter_weight ? 32 * (size_t)max_groups : 0;
+    // weights: planes per group of the full rankings (weighted truncated ballots are counted by pairs)
+    const size_t weight_words = voter_weight ? WEIGHT_WORDS * (size_t)max_groups : 0;
 
     const MetaLayout lay(n, m);
     int rc;
@@ -2017,6 +2097,8 @@ extern "C" int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ball
     const size_t scratch = std::max({sizeof(uint32_t) * 2 * CT * CT * (size_t)ctx->num_cus * COUNT_PER_CU,
                                      occ_ok ? ol.total : 0, AllLayout(ctx->num_cus, n, L, m, voter_weight != nullptr).total});
     if (n > 0 && (rc = ws_reserve(ctx, WS_OCC, scratch)) != SCHULZE_OK) return rc;
+    // (after the reservations: with weights a smaller call may be routed)
+    if (one_pass) return count_all(ctx, s, ballots, dtype32, n, L, m, voter_weight, d_dtype, d, ldd);
 
     char *mb = static_cast<char *>(ctx->ws[WS_BALLOT_META]);
     Meta meta{reinterpret_cast<int32_t *>(mb + lay.ctr),

@@ -165,3 +165,24 @@ for m in sizes + list(range(3900, 8100, 97)):
 out(bad)
 """)
     assert got == []
+
+
+@pytest.mark.parametrize("n,L,m,weighted,one_pass", [
+    (1000, 64, 64, False, True), (1400, 20, 1000, False, True), (20000, 25, 389, False, True),
+    (20000, 10, 2000, False, False), (300, 20, 4096, False, True), (300, 20, 4097, False, False),
+    # short weighted ballots: as many bits of weights as their total allows
+    (400, 20, 1000, True, True), (800, 20, 1000, True, False), (1400, 20, 1000, True, False),
+    (2000, 25, 389, True, True), (7001, 25, 389, True, True), (12000, 25, 389, True, False),
+    (30000, 20, 64, True, True), (100000, 10, 128, True, True), (300, 30, 2000, True, False),
+    (64, 50, 4096, True, True), (128, 50, 4096, True, False),
+    # long ones: the pairs they can list cost more
+    (1400, 1000, 1000, True, True), (3000, 389, 389, True, True), (32, 4096, 4096, True, True),
+    (30000, 256, 256, True, True), (40000, 256, 256, True, False), (1, 1, 1, True, True),
+])
+def test_route_by_size(fake_hip, n, L, m, weighted, one_pass):
+    got = fake_hip(f"""
+h = context()
+assert lib.schulze_pairwise(h, None, FAR, U16, {n}, {L}, {m}, FAR if {weighted} else None, I32, 2 * FAR, {m}) == 0
+out([any("k_route" in l for l in launched()), any("k_planes_all" in l or "k_planes_short" in l for l in launched())])
+""")
+    assert got == [not one_pass, one_pass]
