@@ -33,18 +33,22 @@ constexpr int CPL = 16;            // columns per lane
 constexpr int CB = 64 * CPL;       // columns per block
 constexpr int U = 4;               // frontier rows in flight per wavefront
 
-// Workgroups for NP problems of m candidates: one share of the frontier
-// per 32 rows of each column block (a wavefront then has two batches of a
-// full frontier), at most `cap` (the resident limit of the cooperative
-// launch).  A batch waits for memory once, a barrier costs about as much
-// whether few or many workgroups meet: learned winners at m = 1501 took 372 us
-// with shares of 256 rows, 347 of 128 and 328 of 32; winners by propagation at
-// m = 6007 459, 442 and 439.  Every column block of every problem gets at
-// least one workgroup as long as cap >= NP * ceil(m / 1024), which holds
-// for m <= 65535 and cap >= 128.
-inline int64_t grid_size(int32_t m, int np, int64_t cap) {
-    const int64_t ncb = (m + CB - 1) / CB;
-    const int64_t g = np * ncb * ((m + 31) / 32);
+// Workgroups for NP problems of m candidates: a share of the frontier per 32
+// rows of each column block, but no more than `few` workgroups altogether
+// while there is one per 256 rows, and at most `cap` (the resident limit of
+// the cooperative launch).  Every column block of every problem gets at least
+// one workgroup as long as cap >= NP * ceil(m / 1024), which holds for m <=
+// 65535 and cap >= 128.
+//
+// A batch of rows waits for memory once, so that more shares shorten a sweep
+// until the barrier costs more.  Label sweeps start from a full frontier:
+// winners by propagation at m = 6007 took 459 us with shares of 256 rows, 442
+// of 128 and 439 of 32.  Widest paths have small frontiers and many sweeps: both
+// directions of one candidate, uint16, at m = 1501 took 411, 359 and 400 us with
+// 24, 96 and 188 workgroups; at m = 4096 552, 616 and 770 with 128, 256 and 512.
+inline int64_t grid_size(int32_t m, int np, int64_t cap, int64_t few = INT64_MAX) {
+    const int64_t blocks = np * (int64_t)((m + CB - 1) / CB);
+    const int64_t g = std::max(blocks * ((m + 255) / 256), std::min(blocks * ((m + 31) / 32), few));
     return g < 1 ? 1 : (g < cap ? g : cap);
 }
 
@@ -59,10 +63,17 @@ constexpr int nvec() {
 }
 
 // Column (relative to the block) of element c of a lane's share: vector
-// k = c / V covers columns (64 k + lane) V .. + V.  In a block with fewer
-// columns inside the matrix (valid < CB) the vectors that would reach past
-// them move back to end at the last one: some columns are then taken twice,
-// with the same values, and every access is the same unconditional load.
+// k = c / V covers columns (64 k + lane) V .. + V.
+template <typename E>
+__device__ inline int32_t own_col(int lane, int c) {
+    constexpr int V = vlen<E>();
+    return ((c / V) * 64 + lane) * V + c % V;
+}
+
+// The same in a block with fewer columns inside the matrix (valid < CB): the
+// vectors that would reach past them move back to end at the last one: some
+// columns are then taken twice, with the same values, and every access is the
+// same unconditional load.
 template <typename E>
 __device__ inline int32_t lane_col(int lane, int c, int32_t valid) {
     constexpr int V = vlen<E>();
@@ -70,29 +81,67 @@ __device__ inline int32_t lane_col(int lane, int c, int32_t valid) {
     return valid >= V ? min(c0, valid - V) + c % V : min(c0 + c % V, valid - 1);
 }
 
-// The lane's 16 elements of a row (row points at the block's first column,
-// at any alignment) as 16-byte loads; a block of less than one vector takes
-// them one by one.  At m = 6007 (int32, odd pitch) the label sweeps took 167
-// us with an access per element, now 97; the widest paths of one candidate
-// at m = 1501 (uint16) 318 and 200.
+// The elements of a 16-byte vector.
 template <typename E>
+__device__ inline void unpack(const uint4 &q, uint32_t *v) {
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    if constexpr (sizeof(E) == 4) {
+        for (int u = 0; u < 4; ++u) v[u] = w[u];
+    } else {
+        for (int u = 0; u < 4; ++u) {
+            v[2 * u] = w[u] & 0xFFFFu;
+            v[2 * u + 1] = w[u] >> 16;
+        }
+    }
+}
+
+// The lane's 16 elements of one row (row points at the block's first column,
+// at any alignment).  VD: the row's length is a multiple of a vector's, and 0
+// comes for columns outside the matrix; else see lane_col.
+template <typename E, bool VD>
 __device__ inline void load_row(const E *__restrict__ row, int32_t valid, int lane, uint32_t (&v)[CPL]) {
     constexpr int V = vlen<E>();
-    if (valid >= V) {
+    uint4 q[nvec<E>()];
+    if (VD ? valid >= CB : valid >= V) {  // (uniform; the loads unconditional, so that they are in flight together)
+        for (int k = 0; k < nvec<E>(); ++k)
+            q[k] = tio::load16<E>(row + (VD ? own_col<E>(lane, k * V) : lane_col<E>(lane, k * V, valid)));
+    } else if (VD) {
         for (int k = 0; k < nvec<E>(); ++k) {
-            const uint4 q = tio::load16<E>(row + lane_col<E>(lane, k * V, valid));
-            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-            if constexpr (sizeof(E) == 4) {
-                for (int u = 0; u < 4; ++u) v[k * V + u] = w[u];
-            } else {
-                for (int u = 0; u < 4; ++u) {
-                    v[k * V + 2 * u] = w[u] & 0xFFFFu;
-                    v[k * V + 2 * u + 1] = w[u] >> 16;
-                }
-            }
+            const int32_t c = own_col<E>(lane, k * V);
+            q[k] = c < valid ? tio::load16<E>(row + c) : make_uint4(0u, 0u, 0u, 0u);
         }
     } else {
         for (int c = 0; c < CPL; ++c) v[c] = (uint32_t)row[lane_col<E>(lane, c, valid)];
+        return;
+    }
+    for (int k = 0; k < nvec<E>(); ++k) unpack<E>(q[k], &v[k * V]);
+}
+
+// The lane's 16 elements of R rows (each points at the block's first column,
+// at any alignment) as 16-byte loads; a block of less than one vector takes
+// them one by one.  All rows' loads stand in one block of code, so that they
+// are in flight together: with the choice made per row, each row was waited
+// for before the next (widest paths of one candidate, uint16, m = 32768: 1950
+// us, so 1570).  At m = 6007 (int32, odd pitch) the label sweeps took 167
+// us with an access per element, now 97; the widest paths of one candidate
+// at m = 1501 (uint16) 318 and 200.
+template <typename E, int R>
+__device__ inline void load_rows(const E *const (&row)[R], int32_t valid, int lane, uint32_t (&v)[R][CPL]) {
+    constexpr int V = vlen<E>();
+    auto vectors = [&](auto column) {
+        uint4 q[R][nvec<E>()];
+        for (int r = 0; r < R; ++r)
+            for (int k = 0; k < nvec<E>(); ++k) q[r][k] = tio::load16<E>(row[r] + column(k));
+        for (int r = 0; r < R; ++r)
+            for (int k = 0; k < nvec<E>(); ++k) unpack<E>(q[r][k], &v[r][k * V]);
+    };
+    if (valid >= CB) {  // (uniform)
+        vectors([&](int k) { return own_col<E>(lane, k * V); });
+    } else if (valid >= V) {
+        vectors([&](int k) { return lane_col<E>(lane, k * V, valid); });
+    } else {
+        for (int r = 0; r < R; ++r)
+            for (int c = 0; c < CPL; ++c) v[r][c] = (uint32_t)row[r][lane_col<E>(lane, c, valid)];
     }
 }
 
@@ -189,8 +238,9 @@ __device__ bool run(const Run<X, E, NP> &r, int32_t m, Comb comb, Accept accept)
                 // rows first, then their values and the next indices: all
                 // in flight together, one wait before the arithmetic
                 uint32_t a[U][CPL];
-                for (int u = 0; u < U; ++u)
-                    load_row<E>(A + (int64_t)(idx[u] < 0 ? 0 : idx[u]) * ld + blk0, valid, lane, a[u]);
+                const E *rows[U];
+                for (int u = 0; u < U; ++u) rows[u] = A + (int64_t)(idx[u] < 0 ? 0 : idx[u]) * ld + blk0;
+                load_rows<E, U>(rows, valid, lane, a);
                 X xi[U];
                 for (int u = 0; u < U; ++u) xi[u] = idx[u] < 0 ? (X)0 : x[idx[u] < 0 ? 0 : idx[u]];
                 load_idx(q0 + U * step, idx);

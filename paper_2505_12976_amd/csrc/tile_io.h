@@ -74,17 +74,29 @@ __device__ inline uint4 pack<uint16_t>(const uint16_t *e) {
 
 // A tile in two halves, so that the loads can be issued early and the LDS
 // written later: fetch() loads the tile at (r0, c0) of a rows x cols matrix
-// into registers (0 outside), put() writes them to LDS.
+// into registers (0 outside), put() writes them to LDS.  VEC (cols a multiple
+// of the vector length, so that a vector lies inside or outside): every tile
+// takes the same 16-byte loads, vectors outside read the tile's first row or
+// vector instead, and what lands outside the matrix is garbage that the caller
+// ignores.
 template <typename E>
 struct Regs {
     static constexpr int PER = T * (T / (16 / (int)sizeof(E))) / 256;  // 16-byte vectors per thread
     uint4 x[PER];
 };
 
-template <typename E>
+template <typename E, bool VEC = false>
 __device__ inline void fetch(Regs<E> &g, const E *__restrict__ src, int64_t ld, int32_t r0, int32_t c0, int32_t rows,
                              int32_t cols) {
     constexpr int V = 16 / (int)sizeof(E), VPR = T / V;
+    if constexpr (VEC) {
+        for (int k = 0; k < Regs<E>::PER; ++k) {
+            const int q = threadIdx.x + 256 * k;
+            const int32_t r = r0 + q / VPR, c = c0 + (q % VPR) * V;
+            g.x[k] = load16<E>(src + (int64_t)(r < rows ? r : r0) * ld + (c < cols ? c : c0));
+        }
+        return;
+    }
     if (r0 + T <= rows && c0 + T <= cols) {
         for (int k = 0; k < Regs<E>::PER; ++k) {
             const int q = threadIdx.x + 256 * k;

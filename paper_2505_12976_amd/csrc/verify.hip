@@ -241,10 +241,12 @@ __device__ __forceinline__ void check_row(const E (*A)[tio::PITCH], const E (*B)
 }
 
 // Both directions from (to) a.s over d (both problems' A = d), to the
-// fixpoint, in one cooperative launch after k_widest_init.  Three workgroups
+// fixpoint, in one cooperative launch after k_widest_init.  VD: m is a multiple
+// of the vector length, so that the tiles at the edge take vectors too (an
+// element at a time m = 300, int32, took 220 us, so 196).  Three workgroups
 // per CU (registers capped accordingly; a few spill in the gather branch):
 // 0.95 ms instead of 1.11 ms with two at m = 32768.
-template <typename E, bool MARGIN>
+template <typename E, bool MARGIN, bool VD>
 __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
     using sweep::CB;
     using sweep::CPL;
@@ -295,8 +297,8 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
             uint32_t xr = 0;
             const int xside = (threadIdx.x >> 7) & 1, xq = (threadIdx.x >> 6) & 1;
             auto fetch = [&](int32_t Xf, int32_t Yf) {
-                tio::fetch<E>(ga, d, ld, Xf * tio::T, Yf * tio::T, m, m);
-                if (Xf != Yf) tio::fetch<E>(gb, d, ld, Yf * tio::T, Xf * tio::T, m, m);
+                tio::fetch<E, VD>(ga, d, ld, Xf * tio::T, Yf * tio::T, m, m);
+                if (Xf != Yf) tio::fetch<E, VD>(gb, d, ld, Yf * tio::T, Xf * tio::T, m, m);
                 const int32_t v = (xside ? Yf : Xf) * tio::T + lane;
                 xr = v < m ? __hip_atomic_load((xq ? x1 : x0) + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
             };
@@ -352,13 +354,15 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
             const int32_t *F = R.p[gq].front[t & 1];
             const uint32_t *xq = gq ? x1 : x0;
             uint32_t best[CPL] = {};
+            // (VD: a lane's vector lies inside the block's columns or outside)
+            auto column = [&](int c) { return VD ? sweep::own_col<E>(lane, c) : sweep::lane_col<E>(lane, c, valid); };
             if (gactive) {
                 for (int32_t qi = share * 4 + wave; qi < nf; qi += 4 * shares) {
                     const int32_t v = F[qi];
                     uint32_t row[CPL], col[CPL];
-                    sweep::load_row<E>(d + (int64_t)v * ld + blk0, valid, lane, row);
+                    sweep::load_row<E, VD>(d + (int64_t)v * ld + blk0, valid, lane, row);
                     for (int c = 0; c < CPL; ++c)
-                        col[c] = (uint32_t)d[(int64_t)(blk0 + sweep::lane_col<E>(lane, c, valid)) * ld + v];
+                        col[c] = !VD || column(c) < valid ? (uint32_t)d[(int64_t)(blk0 + column(c)) * ld + v] : 0u;
                     const uint32_t xv = xq[v];
                     for (int c = 0; c < CPL; ++c) {
                         const uint32_t w = gq ? edge_weight<MARGIN>((int32_t)col[c], (int32_t)row[c])
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(256, 3) void k_check(WidestArgs<E, 2> a) {
                         best[c] = max(best[c], min(xv, w));
                     }
                 }
-                for (int c = 0; c < CPL; ++c) part[wave][sweep::lane_col<E>(lane, c, valid)] = best[c];
+                for (int c = 0; c < CPL; ++c) part[wave][column(c)] = best[c];
             }
             __syncthreads();
             uint32_t *const xg = gq ? x1 : x0;
@@ -508,7 +512,7 @@ int widest_in(schulze_ctx *ctx, hipStream_t s, const E *const (&A)[NP], const in
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_widest<E, NP, SIGNED>, 256, 0) != hipSuccess ||
         per_cu < 1)
         return SCHULZE_EDEVICE;
-    const int64_t G = sweep::grid_size(m, NP, (int64_t)ctx->num_cus * std::min(per_cu, 2));
+    const int64_t G = sweep::grid_size(m, NP, (int64_t)ctx->num_cus * std::min(per_cu, 2), 96);
     int tok = -1;
     if (timed) timing_begin(ctx, K_WIDEST, s, &tok);
     k_widest_init<E, NP><<<dim3((unsigned)std::min<int64_t>(ceil_div(m, 256), 1024)), dim3(256), 0, s>>>(a);
@@ -560,7 +564,7 @@ int verify_all(schulze_ctx *ctx, hipStream_t s, const E *w, int64_t ldw, const E
 }
 
 // The exact check of cand from d (k_check) and its verdict.
-template <typename E, bool MARGIN>
+template <typename E, bool MARGIN, bool VD>
 int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int32_t cand,
                     const float *score, E *p_from, E *p_to, int32_t *verdict, int32_t *tied) {
     int rc = ws_reserve(ctx, WS_VERIFY, widest_scratch_bytes(m, 2));
@@ -588,13 +592,13 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
     a.m = m;
     a.s = cand;
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_check<E, MARGIN>, 256, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_check<E, MARGIN, VD>, 256, 0) != hipSuccess ||
         per_cu < 1)
         return SCHULZE_EDEVICE;
     // enough workgroups for the tile pairs of the dense pass and for every
     // column block of both gather problems (cap >= 128 >= 2 ceil(m / 1024))
     const int64_t nb = ceil_div(m, 64);
-    const int64_t want = std::max<int64_t>(sweep::grid_size(m, 2, INT64_MAX), nb * (nb + 1) / 2);
+    const int64_t want = std::max<int64_t>(sweep::grid_size(m, 2, INT64_MAX, 0), nb * (nb + 1) / 2);
     const int64_t G = std::min<int64_t>((int64_t)ctx->num_cus * std::min(per_cu, 3), want);
     int tok = -1;
     timing_begin(ctx, K_WIDEST, s, &tok);
@@ -602,7 +606,7 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
     hipError_t e = hipGetLastError();
     void *args[] = {&a};
     if (e == hipSuccess)
-        e = hipLaunchCooperativeKernel((const void *)k_check<E, MARGIN>, dim3((unsigned)G), dim3(256), args, 0,
+        e = hipLaunchCooperativeKernel((const void *)k_check<E, MARGIN, VD>, dim3((unsigned)G), dim3(256), args, 0,
                                        s);
     timing_end(ctx, tok, s);
     if (e != hipSuccess) {
@@ -617,9 +621,10 @@ int check_counts_as(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, in
 template <typename E>
 int check_counts(schulze_ctx *ctx, hipStream_t s, const E *d, int64_t ldd, int32_t m, int mode, int32_t cand,
                  const float *score, E *p_from, E *p_to, int32_t *verdict, int32_t *tied) {
-    if (mode == SCHULZE_MARGIN)
-        return check_counts_as<E, true>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
-    return check_counts_as<E, false>(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
+    const auto check = m % (16 / (int)sizeof(E)) == 0
+                           ? (mode == SCHULZE_MARGIN ? check_counts_as<E, true, true> : check_counts_as<E, false, true>)
+                           : (mode == SCHULZE_MARGIN ? check_counts_as<E, true, false> : check_counts_as<E, false, false>);
+    return check(ctx, s, d, ldd, m, cand, score, p_from, p_to, verdict, tied);
 }
 
 int check_square(schulze_ctx *ctx, const void *a, int64_t ld, int32_t m, int dtype) {
