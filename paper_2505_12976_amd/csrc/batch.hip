@@ -580,17 +580,24 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
         }
     }
 
-    // completion: the workgroup that finishes the election's last count item runs its finish
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (tid == 0)
-        sh_flag = __hip_atomic_fetch_add(gmem(a.ctr) + CTR_ELEC + a.n_elec + e, 1, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT) == el.n_count - 1;
-    __syncthreads();
-    if (sh_flag) {
+    // completion: the workgroup that finishes the election's last count item
+    // runs its finish.  An election of one count item needs nothing from
+    // other workgroups: the release writes back every dirty line of the die's
+    // L2, about a microsecond that its workgroups take in turn (4096 elections
+    // of at most 10 candidates: 1249 us with it).
+    if (el.n_count > 1) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __syncthreads();
+        if (tid == 0)
+            sh_flag = __hip_atomic_fetch_add(gmem(a.ctr) + CTR_ELEC + a.n_elec + e, 1, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) == el.n_count - 1;
+        __syncthreads();
+        if (!sh_flag) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        finish(a, el, e);
+    } else {
+        __syncthreads();
     }
+    finish(a, el, e);
 }
 
 // ------------------------------------------------------------------ finish
