@@ -1669,7 +1669,8 @@ __global__ __launch_bounds__(256) void k_occ_finish(OccArgs a, T *__restrict__ d
         uint32_t v[8];
         for (int e = 0; e < 8; ++e) {
             v[e] = y + e == r ? 0u : base[e] - c[e] + R;
-            if (v[e] > limit) {
+            // (columns past m: the partial rows of 32-bit counts are written up to a multiple of 4 only)
+            if (v[e] > limit && y + e < m) {
                 over = true;
                 v[e] = limit;
             }

@@ -81,3 +81,42 @@ def test_row_lengths(ctx, L, ids, weighted, dtype):
     d = count(ctx, b, m, w, ids, dtype)
     assert ctx.device_error() == 0
     assert np.array_equal(d.cpu().numpy().astype(np.int64), oracle.pairwise(b, m, w))
+
+
+@pytest.mark.parametrize("ids,weighted,dtype", KINDS)
+@pytest.mark.parametrize("L", [9, 40, 70])
+def test_candidates_of_several_items(ctx, L, ids, weighted, dtype):
+    # items hold 1024 occurrences here (the smallest bound: few occurrences per workgroup)
+    rng = np.random.default_rng(100 + L)
+    m, n = 4500, 4300
+    many = (n, 2500, 1500, 1025, 1024)  # id c on the first many[c] ballots
+    b = np.full((n, L), -1, dtype=np.int32)
+    for i in range(n):
+        ids_i = [c for c in range(5) if i < many[c]]
+        ids_i += list(5 + rng.choice(m - 5, (L if i == 0 else rng.integers(len(ids_i), L + 1)) - len(ids_i), False))
+        b[i, :len(ids_i)] = rng.permutation(ids_i)
+    items = -(-np.bincount(b[b >= 0], minlength=m) // 1024)
+    assert list(items[:5]) == [5, 3, 2, 2, 1] and items[5:].max() == 1
+    w = rng.integers(0, 3, size=n).astype(np.uint32) if weighted else None
+    assert takes_buckets(b, m, weighted)
+    d = count(ctx, b, m, w, ids, dtype)
+    assert ctx.device_error() == 0
+    assert np.array_equal(d.cpu().numpy().astype(np.int64), oracle.pairwise(b, m, w))
+
+
+@pytest.mark.parametrize("ids,weighted,dtype", KINDS)
+@pytest.mark.parametrize("L", [9, 40, 70, 150])
+@pytest.mark.parametrize("first,second", [(0, 1), (2, 7), (0, -1), (-2, -1)])
+def test_repeated_id(ctx, L, first, second, ids, weighted, dtype):
+    import paper_2505_12976_amd as sz
+    m, n = 4500, 130
+    b = ballots(np.random.default_rng(L), n, L, m, 2)
+    w = np.ones(n, dtype=np.uint32) if weighted else None
+    b[n - 1, first] = b[n - 1, second]  # (the ballot that is full)
+    count(ctx, b, m, w, ids, dtype)
+    assert ctx.device_error() == sz.EBALLOT
+    b[n - 1, second % L:] = -1
+    assert takes_buckets(b, m, weighted)
+    d = count(ctx, b, m, w, ids, dtype)
+    assert ctx.device_error() == 0
+    assert np.array_equal(d.cpu().numpy().astype(np.int64), oracle.pairwise(b, m, w))
