@@ -186,3 +186,23 @@ assert lib.schulze_pairwise(h, None, FAR, U16, {n}, {L}, {m}, FAR if {weighted} 
 out([any("k_route" in l for l in launched()), any("k_planes_all" in l or "k_planes_short" in l for l in launched())])
 """)
     assert got == [not one_pass, one_pass]
+
+
+@pytest.mark.parametrize("m,ids,tiles", [(129, "U16", 3), (700, "U16", 11), (6200, "U16", 49), (300, "I32", 5),
+                                         (2100, "I32", 17 + 34)])
+def test_closure_when_cooperative_launches_are_refused(fake_hip, m, ids, tiles):
+    """The phased launches instead, on integers: 16-bit matrices are stored as
+    keys before the refusal is known, and go back to values first."""
+    got = fake_hip(f"""
+h = context()
+fake.fake_refuse_cooperative(1)
+assert lib.schulze_closure(h, None, FAR, {m}, {m}, {ids}, 0, 2 * FAR, {m}) == 0
+out(launched())
+""")
+    names = [next((k for k in ("k_fw_decode", "k_fw_diag", "k_fw_panel", "k_fw_rest") if k in n), None) for n in got]
+    if ids == "U16":
+        assert names == [None, None, "k_fw_decode"] + ["k_fw_diag", "k_fw_panel", "k_fw_rest"] * tiles + [None]
+        assert "k_weights" in got[1] and "k_fw_store" in got[-1]
+    else:  # (2100: the integers in tiles of 128 and the value ranks in tiles of 64, each gated)
+        assert names.count("k_fw_diag") == tiles
+        assert names.count("k_fw_decode") == (m >= 1024)
