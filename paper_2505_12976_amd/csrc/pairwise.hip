@@ -124,68 +124,68 @@ __global__ __launch_bounds__(1024) void k_scan_long(const void *__restrict__ bal
     unsigned long long k2 = 0;
     int32_t longest = 0;  // listed by a truncated ballot
     for (int64_t v0 = c0; v0 < c1; v0 += LONG_CHUNK) {
-    const int32_t here = (int32_t)min((int64_t)LONG_CHUNK, c1 - v0);
-    for (int q = wave; q < here; q += 16) {
-        const int64_t v = v0 + q;
-        const P row(ballots, n, L, v);
-        int32_t first = L, wrong = L;  // first padding entry, first id out of range
-        for (int32_t j0 = 0; j0 < row.count; j0 += 64 * FLY) {
-            v4u x[FLY];
-            row.template load<FLY>(x, j0 + lane);
-            for (int u = 0; u < FLY; ++u) {
-                const int32_t j = j0 + 64 * u + lane;
-                if (j >= row.count || P::top(x[u]) < (uint32_t)m) continue;
-                row.each(x[u], j, L, [&](int32_t t, uint32_t raw) {
-                    const int32_t id = raw_id<I32>(raw);
-                    if (id < 0)
-                        first = min(first, t);
-                    else if (id >= m)
-                        wrong = min(wrong, t);
-                });
+        const int32_t here = (int32_t)min((int64_t)LONG_CHUNK, c1 - v0);
+        for (int q = wave; q < here; q += 16) {
+            const int64_t v = v0 + q;
+            const P row(ballots, n, L, v);
+            int32_t first = L, wrong = L;  // first padding entry, first id out of range
+            for (int32_t j0 = 0; j0 < row.count; j0 += 64 * FLY) {
+                v4u x[FLY];
+                row.template load<FLY>(x, j0 + lane);
+                for (int u = 0; u < FLY; ++u) {
+                    const int32_t j = j0 + 64 * u + lane;
+                    if (j >= row.count || P::top(x[u]) < (uint32_t)m) continue;
+                    row.each(x[u], j, L, [&](int32_t t, uint32_t raw) {
+                        const int32_t id = raw_id<I32>(raw);
+                        if (id < 0)
+                            first = min(first, t);
+                        else if (id >= m)
+                            wrong = min(wrong, t);
+                    });
+                }
+                if (__ballot(first < L)) break;
             }
-            if (__ballot(first < L)) break;
-        }
-        for (int off = 32; off >= 1; off >>= 1) first = min(first, __shfl_xor(first, off));
-        const int32_t k = first;
-        bad |= wrong < k;
-        const bool trunc = k < m - 1;
-        if (trunc)
-            for (int32_t j = lane; j < row.count && j * P::PER - row.head < k; j += 64) {
-                v4u x[1];
-                row.template load<1>(x, j);
-                row.each(x[0], j, k, [&](int32_t, uint32_t raw) {
-                    const uint32_t bit = 1u << (raw & 31);
-                    if (raw < (uint32_t)m && !(seen[raw >> 5] & bit)) atomicOr(&seen[raw >> 5], bit);
-                });
+            for (int off = 32; off >= 1; off >>= 1) first = min(first, __shfl_xor(first, off));
+            const int32_t k = first;
+            bad |= wrong < k;
+            const bool trunc = k < m - 1;
+            if (trunc)
+                for (int32_t j = lane; j < row.count && j * P::PER - row.head < k; j += 64) {
+                    v4u x[1];
+                    row.template load<1>(x, j);
+                    row.each(x[0], j, k, [&](int32_t, uint32_t raw) {
+                        const uint32_t bit = 1u << (raw & 31);
+                        if (raw < (uint32_t)m && !(seen[raw >> 5] & bit)) atomicOr(&seen[raw >> 5], bit);
+                    });
+                }
+            if (lane == 0) {
+                meta.len[v] = k;
+                kind[q] = trunc ? 2 : 1;
+                if (trunc) {
+                    k2 += (unsigned long long)k * (k - 1) / 2;
+                    longest = max(longest, k);
+                }
             }
-        if (lane == 0) {
-            meta.len[v] = k;
-            kind[q] = trunc ? 2 : 1;
-            if (trunc) {
-                k2 += (unsigned long long)k * (k - 1) / 2;
-                longest = max(longest, k);
+        }
+        __syncthreads();
+        if (wave == 0) {  // the lists, in ballot order
+            int32_t a = 0, b = 0;
+            for (int q0 = 0; q0 < here; q0 += 64) {
+                const int q = q0 + lane, kq = q < here ? kind[q] : 0;
+                const uint64_t f = __ballot(kq == 1), t = __ballot(kq == 2), below = (1ull << lane) - 1ull;
+                if (kq == 1) lf[a + __popcll(f & below)] = (int32_t)(v0 + q);
+                if (kq == 2) lt[b + __popcll(t & below)] = (int32_t)(v0 + q);
+                a += __popcll(f);
+                b += __popcll(t);
+            }
+            if (lane == 0) {
+                nf = a;
+                nt = b;
             }
         }
-    }
-    __syncthreads();
-    if (wave == 0) {  // the lists, in ballot order
-        int32_t a = 0, b = 0;
-        for (int q0 = 0; q0 < here; q0 += 64) {
-            const int q = q0 + lane, kq = q < here ? kind[q] : 0;
-            const uint64_t f = __ballot(kq == 1), t = __ballot(kq == 2), below = (1ull << lane) - 1ull;
-            if (kq == 1) lf[a + __popcll(f & below)] = (int32_t)(v0 + q);
-            if (kq == 2) lt[b + __popcll(t & below)] = (int32_t)(v0 + q);
-            a += __popcll(f);
-            b += __popcll(t);
-        }
-        if (lane == 0) {
-            nf = a;
-            nt = b;
-        }
-    }
-    __syncthreads();
-    record_ballots(meta, nf, lf, nt, lt);
-    __syncthreads();  // the lists are copied
+        __syncthreads();
+        record_ballots(meta, nf, lf, nt, lt);
+        __syncthreads();  // the lists are copied
     }
     for (int32_t c = threadIdx.x; c < m; c += 1024)
         if ((seen[c >> 5] >> (c & 31)) & 1u) meta.in_u[c] = 1;
@@ -202,22 +202,18 @@ __global__ __launch_bounds__(1024) void k_scan_long(const void *__restrict__ bal
 // workgroup mean fewer list reservations on the two shared counters.)
 constexpr int SHORT_BPW = 4;
 constexpr int SHORT_ROUNDS = 4, SHORT_MAX_ROUNDS = 16;
-constexpr int32_t SEEN_BITS = 65536;
 template <bool I32>
 __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ ballots, int64_t n, int32_t L,
                                                     int32_t m, int32_t rounds, Meta meta, int32_t *err) {
     constexpr int PER_WG = 4 * SHORT_PER_WAVE * SHORT_BPW * SHORT_MAX_ROUNDS;
     __shared__ int32_t lf[PER_WG], lt[PER_WG];
     __shared__ int32_t nf, nt;
-    // candidates listed by this workgroup's truncated ballots, as bits (for
-    // m <= SEEN_BITS; else marked in meta.in_u at once): one store per
-    // candidate and workgroup at the end instead of a read of in_u at every
-    // entry, which made each step wait for memory
-    __shared__ uint32_t seen[SEEN_BITS / 32];
-    const bool use_seen = m <= SEEN_BITS;
+    // candidates listed by this workgroup's truncated ballots, as bits
+    // (m <= 65535): one store per candidate and workgroup at the end instead
+    // of a read of in_u at every entry, which made each step wait for memory
+    __shared__ uint32_t seen[65536 / 32];
     if (threadIdx.x == 0) nf = nt = 0;
-    if (use_seen)
-        for (int32_t w = threadIdx.x; w < (m + 31) / 32; w += 256) seen[w] = 0u;
+    for (int32_t w = threadIdx.x; w < (m + 31) / 32; w += 256) seen[w] = 0u;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int32_t bpw = min(SHORT_BPW, 64 / L);
@@ -249,12 +245,8 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
                 if (c[q] >= m) {
                     bad = true;
                 } else if (trunc) {
-                    if (use_seen) {
-                        const uint32_t bit = 1u << (c[q] & 31);
-                        if (!(seen[c[q] >> 5] & bit)) atomicOr(&seen[c[q] >> 5], bit);
-                    } else if (!meta.in_u[c[q]]) {  // a read first: frequent candidates are set once per cache
-                        meta.in_u[c[q]] = 1;
-                    }
+                    const uint32_t bit = 1u << (c[q] & 31);
+                    if (!(seen[c[q] >> 5] & bit)) atomicOr(&seen[c[q] >> 5], bit);
                 }
             }
             if (live && t == 0) {
@@ -272,9 +264,8 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
     for (int off = 32; off >= 1; off >>= 1) k2 += __shfl_xor(k2, off);
     if (lane == 0 && k2) atomicAdd(&meta.k2[(blockIdx.x * 4 + wave) % NPART], k2);
     __syncthreads();
-    if (use_seen)
-        for (int32_t c = threadIdx.x; c < m; c += 256)
-            if ((seen[c >> 5] >> (c & 31)) & 1u) meta.in_u[c] = 1;
+    for (int32_t c = threadIdx.x; c < m; c += 256)
+        if ((seen[c >> 5] >> (c & 31)) & 1u) meta.in_u[c] = 1;
     record_ballots(meta, nf, lf, nt, lt);
 }
 
@@ -292,30 +283,24 @@ constexpr double ATOMIC_PAIR_COST = 66.0;
 constexpr double BUCKETED_PAIR_COST = 6.0;
 
 constexpr int ROUTE_THREADS = 1024;
-constexpr int ROUTE_VEC = 4;  // 16-byte groups of flags per thread (m <= 65536)
+constexpr int ROUTE_VEC = 4;  // 16-byte groups of flags per thread
+static_assert(ROUTE_THREADS * 16 * ROUTE_VEC >= 65536, "every candidate's flag");
 __global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, int32_t short_L, Meta meta,
                                                          int64_t cap_words, double pair_cost) {
     __shared__ int32_t part[ROUTE_THREADS];
     // A thread takes consecutive flags (0 or 1 bytes; zero past m up to the
     // next 16 bytes), as ROUTE_VEC 16-byte loads issued together (a byte at
-    // a time waited for memory at every flag), else one byte at a time.
-    const bool vec = m <= ROUTE_THREADS * 16 * ROUTE_VEC;
+    // a time waited for memory at every flag).
     const int32_t groups = (m + 15) / 16;
     const int32_t gper = (groups + ROUTE_THREADS - 1) / ROUTE_THREADS;
     const int32_t g0 = (int32_t)threadIdx.x * gper;
-    const int32_t per = vec ? 16 * gper : (m + ROUTE_THREADS - 1) / ROUTE_THREADS;
-    const int32_t c0 = min(m, (int32_t)threadIdx.x * per), c1 = min(m, c0 + per);
     uint4 f[ROUTE_VEC];
     int32_t cnt = 0;
-    if (vec) {
-        const uint4 *in4 = reinterpret_cast<const uint4 *>(meta.in_u);
-        for (int k = 0; k < ROUTE_VEC; ++k) f[k] = in4[k < gper && g0 + k < groups ? g0 + k : 0];
-        for (int k = 0; k < ROUTE_VEC; ++k) {
-            if (!(k < gper && g0 + k < groups)) f[k] = make_uint4(0u, 0u, 0u, 0u);
-            cnt += __popc(f[k].x) + __popc(f[k].y) + __popc(f[k].z) + __popc(f[k].w);
-        }
-    } else {
-        for (int32_t c = c0; c < c1; ++c) cnt += meta.in_u[c] ? 1 : 0;
+    const uint4 *in4 = reinterpret_cast<const uint4 *>(meta.in_u);
+    for (int k = 0; k < ROUTE_VEC; ++k) f[k] = in4[k < gper && g0 + k < groups ? g0 + k : 0];
+    for (int k = 0; k < ROUTE_VEC; ++k) {
+        if (!(k < gper && g0 + k < groups)) f[k] = make_uint4(0u, 0u, 0u, 0u);
+        cnt += __popc(f[k].x) + __popc(f[k].y) + __popc(f[k].z) + __popc(f[k].w);
     }
     part[threadIdx.x] = cnt;
     __syncthreads();
@@ -334,16 +319,12 @@ __global__ __launch_bounds__(ROUTE_THREADS) void k_route(int32_t m, int32_t shor
             meta.umap[c] = -1;
         }
     };
-    if (vec) {
-        for (int k = 0; k < ROUTE_VEC; ++k) {
-            const uint32_t w[4] = {f[k].x, f[k].y, f[k].z, f[k].w};
-            for (int e = 0; e < 16; ++e) {
-                const int32_t c = 16 * (g0 + k) + e;
-                if (k < gper && c < m) place(c, (w[e >> 2] >> (8 * (e & 3))) & 1u);
-            }
+    for (int k = 0; k < ROUTE_VEC; ++k) {
+        const uint32_t w[4] = {f[k].x, f[k].y, f[k].z, f[k].w};
+        for (int e = 0; e < 16; ++e) {
+            const int32_t c = 16 * (g0 + k) + e;
+            if (k < gper && c < m) place(c, (w[e >> 2] >> (8 * (e & 3))) & 1u);
         }
-    } else {
-        for (int32_t c = c0; c < c1; ++c) place(c, meta.in_u[c] != 0);
     }
     if (threadIdx.x == 0) {
         const int32_t nu = part[ROUTE_THREADS - 1];
@@ -448,57 +429,57 @@ __global__ __launch_bounds__(THREADS) void k_planes(PlaneArgs a) {
     const int32_t pitch = FULL ? a.pitch : a.meta.ctr[4];
     const int32_t chunks = (pitch + CH - 1) / CH;
     for (int64_t item = blockIdx.x; item < (int64_t)(count + 31) / 32 * chunks; item += gridDim.x) {
-    const int64_t g = item / chunks;
-    const int32_t c0 = (int32_t)(item % chunks) * CH;
-    const int32_t cn = min(CH, pitch - c0);             // a multiple of 64
-    const int32_t ncols = FULL ? a.m : a.meta.ctr[3];   // real columns: candidates or U
-    const int32_t bits = FULL ? a.bits : rank_bits(a.meta.ctr[6]);
-    const int32_t *srcs = FULL ? a.meta.full_src : a.meta.trunc_src;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t live = (int32_t)min((int64_t)32, count - 32 * g);  // voters of this group
+        const int64_t g = item / chunks;
+        const int32_t c0 = (int32_t)(item % chunks) * CH;
+        const int32_t cn = min(CH, pitch - c0);             // a multiple of 64
+        const int32_t ncols = FULL ? a.m : a.meta.ctr[3];   // real columns: candidates or U
+        const int32_t bits = FULL ? a.bits : rank_bits(a.meta.ctr[6]);
+        const int32_t *srcs = FULL ? a.meta.full_src : a.meta.trunc_src;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int32_t live = (int32_t)min((int64_t)32, count - 32 * g);  // voters of this group
 
-    for (int i = threadIdx.x; i < 16 * CH; i += THREADS) {
-        const int p = i / CH;
-        buf[i] = (2 * p < live ? 0xFFFFu : 0u) | (2 * p + 1 < live ? 0xFFFF0000u : 0u);
-    }
-    if (threadIdx.x == 0) repeated = 0;
-    int32_t extra = 0;
-    __syncthreads();
-    uint16_t *half = reinterpret_cast<uint16_t *>(buf);
-    for (int v = wave; v < live; v += WAVES) {  // a wavefront per ballot
-        const int32_t src = srcs[32 * g + v];
-        const int32_t k = a.meta.len[src];
-        uint16_t *row = half + (v >> 1) * (2 * CH) + (v & 1);
-        auto place = [&](int32_t t, int32_t id) {
-            if ((uint32_t)id >= (uint32_t)a.m) return;  // reported by the scan
-            const int32_t col = (FULL ? id : a.meta.umap[id]) - c0;
-            if ((uint32_t)col >= (uint32_t)cn) return;
-            row[2 * col] = (uint16_t)t;
-            ++extra;
-        };
-        constexpr int FLY = 4;  // pieces per lane in flight
-        const RowPieces<I32> pieces(a.ballots, a.n, a.L, src);
-        const int32_t need = (pieces.head + k + pieces.PER - 1) / pieces.PER;
-        for (int32_t j0 = 0; j0 < need; j0 += 64 * FLY) {
-            v4u x[FLY];
-            pieces.template load<FLY>(x, j0 + lane);
-            for (int u = 0; u < FLY; ++u)
-                pieces.each(x[u], j0 + 64 * u + lane, k, [&](int32_t t, uint32_t raw) { place(t, (int32_t)raw); });
+        for (int i = threadIdx.x; i < 16 * CH; i += THREADS) {
+            const int p = i / CH;
+            buf[i] = (2 * p < live ? 0xFFFFu : 0u) | (2 * p + 1 < live ? 0xFFFF0000u : 0u);
         }
-    }
-    __syncthreads();
-    // the group's voters in the order of the planes' bits
-    const uint32_t voters = voter_bits(live);
-    extra += planes_out<CH, THREADS>(buf, cn, ncols - c0, voters, bits, pitch,
-                                     a.planes + g * bits * (int64_t)pitch + c0);
-    check_repeats(extra, &repeated, a.err);
-    if (a.weight && c0 == 0 && wave == 0) {
-        const int v = 2 * (lane & 15) + ((lane >> 4) & 1);  // the voter of bit `lane`
-        const uint32_t sum = weight_planes(lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u,
-                                           a.wplanes + WEIGHT_WORDS * g);
-        if (FULL && lane == 0) atomicAdd(&a.meta.ctr[8], (int32_t)sum);
-    }
-    __syncthreads();  // the LDS is read
+        if (threadIdx.x == 0) repeated = 0;
+        int32_t extra = 0;
+        __syncthreads();
+        uint16_t *half = reinterpret_cast<uint16_t *>(buf);
+        for (int v = wave; v < live; v += WAVES) {  // a wavefront per ballot
+            const int32_t src = srcs[32 * g + v];
+            const int32_t k = a.meta.len[src];
+            uint16_t *row = half + (v >> 1) * (2 * CH) + (v & 1);
+            auto place = [&](int32_t t, int32_t id) {
+                if ((uint32_t)id >= (uint32_t)a.m) return;  // reported by the scan
+                const int32_t col = (FULL ? id : a.meta.umap[id]) - c0;
+                if ((uint32_t)col >= (uint32_t)cn) return;
+                row[2 * col] = (uint16_t)t;
+                ++extra;
+            };
+            constexpr int FLY = 4;  // pieces per lane in flight
+            const RowPieces<I32> pieces(a.ballots, a.n, a.L, src);
+            const int32_t need = (pieces.head + k + pieces.PER - 1) / pieces.PER;
+            for (int32_t j0 = 0; j0 < need; j0 += 64 * FLY) {
+                v4u x[FLY];
+                pieces.template load<FLY>(x, j0 + lane);
+                for (int u = 0; u < FLY; ++u)
+                    pieces.each(x[u], j0 + 64 * u + lane, k, [&](int32_t t, uint32_t raw) { place(t, (int32_t)raw); });
+            }
+        }
+        __syncthreads();
+        // the group's voters in the order of the planes' bits
+        const uint32_t voters = voter_bits(live);
+        extra += planes_out<CH, THREADS>(buf, cn, ncols - c0, voters, bits, pitch,
+                                         a.planes + g * bits * (int64_t)pitch + c0);
+        check_repeats(extra, &repeated, a.err);
+        if (a.weight && c0 == 0 && wave == 0) {
+            const int v = 2 * (lane & 15) + ((lane >> 4) & 1);  // the voter of bit `lane`
+            const uint32_t sum = weight_planes(lane < 32 && v < live ? a.weight[srcs[32 * g + v]] : 0u,
+                                               a.wplanes + WEIGHT_WORDS * g);
+            if (FULL && lane == 0) atomicAdd(&a.meta.ctr[8], (int32_t)sum);
+        }
+        __syncthreads();  // the LDS is read
     }
 }
 
