@@ -476,7 +476,9 @@ int schulze_set_closure_tile(schulze_ctx *ctx, int tile);
  * the listed candidates of truncated ballots are too many for a dense count):
  * BUCKETED (default for m <= 32768 and n * L <= 2^27) sorts the listed
  * entries by candidate and accumulates each candidate's row of C in LDS;
- * ATOMIC adds every pair with a device-wide atomic.  Both give the same d.
+ * ATOMIC adds every pair with a device-wide atomic, and also counts small
+ * elections this way that BUCKETED takes in one pass over all candidates.
+ * Both give the same d.
  */
 enum { SCHULZE_SPARSE_BUCKETED = 0, SCHULZE_SPARSE_ATOMIC = 1 };
 int schulze_set_sparse_count(schulze_ctx *ctx, int mode);
@@ -543,7 +545,8 @@ typedef struct {
 } schulze_election;
 
 typedef struct {
-    int32_t max_range_pairs; /* 0 = automatic; else at most this many voter pairs per counting range */
+    int32_t max_range_pairs; /* 0 = automatic; else at most this many voter pairs per counting range (the
+                                plan's ranks take 16 / max_range_pairs times the memory below 16) */
     int32_t closure_only;    /* 1 = the plan only serves runs without ballots (no buffer of ranks) */
     int32_t topk;            /* 0 = no levels; k > 0: runs given a level array rank at least k candidates
                                 per election by iterated winner removal (as schulze_topk_propagate) */

@@ -50,8 +50,8 @@ constexpr int BT = 256;                          // threads per workgroup
 constexpr int STAGE_WORDS = 16384;               // count staging: two buffers of rows x cols words
 constexpr int SMEM_WORDS = STAGE_WORDS + 1024 + 64;
 constexpr int RANGE_PAIRS = 32767;         // voter pairs per count range unless the caller asks for fewer
-constexpr int64_t SCAN_WORDS = 1 << 18;    // rank-pair words staged per scan item
-constexpr int SCAN_GROUP_WORDS = 16384;    // rank-pair words staged at once by a scan
+constexpr int64_t SCAN_WORDS = 1 << 18;    // words (two voters' ranks of a candidate) per scan item
+constexpr int SCAN_GROUP_WORDS = 16384;    // words staged at once by a scan
 constexpr int SCAN_VEC = 16;              // 16-byte ballot loads in flight per thread
 constexpr int SCAN_GROUP_PAIRS = 32;      // voter pairs staged at once by a scan, at most
 constexpr int CHUNK_QUADS = 32;            // staged rows of 64 16-byte quads per count chunk
@@ -422,7 +422,7 @@ __device__ __attribute__((noinline)) void count_item(const BatchArgs &a, const B
     const int64_t g0 = (int64_t)range * el.range_groups;
     const int64_t g1 = min((el.n + gv - 1) / gv, g0 + el.range_groups);
     const uint32_t nv = (uint32_t)(min(el.n, gv * g1) - gv * g0);
-    const int32_t nrows = (int32_t)(g1 - g0) * bits;  // (at most 2^27 groups of at most 10 planes)
+    const int32_t nrows = (int32_t)(g1 - g0) * bits;  // (at most RANGE_PAIRS / group_pairs groups of at most 10 planes)
     const FW_GLOBAL uint32_t *src = gmem(a.planes + el.pos_off) + g0 * bits * pitch + c0;
     uint32_t *stage = smem;
 

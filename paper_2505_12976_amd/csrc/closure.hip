@@ -833,9 +833,9 @@ __device__ inline void pair_of(int64_t q, int32_t &I, int32_t &J) {
 // written (the ranked closure needs only their ranks; the int32 closure, if
 // the values cannot be ranked, writes its own weights).  Persistent over the
 // pairs, so that each workgroup merges its LDS bitmap once; the next pair's
-// tiles are loaded into registers while the current pair is marked (VEC:
-// 16-byte loads, d 16-byte aligned with m a multiple of 4; what they read
-// past m is ignored).
+// tiles are loaded into registers while the current pair is marked (16 bytes
+// a load whatever d's alignment; tiles that reach past m an element a load,
+// moved back inside d, with zeros past m).
 __global__ __launch_bounds__(256) void k_weights_mark(const int32_t *__restrict__ d, int64_t ldd, int32_t m,
                                                       int mode, uint32_t *__restrict__ bitmap,
                                                       int32_t *__restrict__ flags) {

@@ -275,9 +275,12 @@ __global__ __launch_bounds__(256) void k_scan_short(const void *__restrict__ bal
 // ballots, by the time each is expected to take (picoseconds, from measured
 // rates on MI355X): dense, the masks' instructions over the tiles at 45 T
 // lane operations/s and the m x m accumulator written, read and converted;
-// pair scattering, a pair's share of the bucketed accumulation (5-6 ps at
-// n = 10^6 top-20 and n = 15553 top-150) or a device-wide atomic, and d
-// written once; both have their own passes over the ballots (about 60 us).
+// pair scattering, a pair's share of the bucketed accumulation or a
+// device-wide atomic, and d written once; both have their own passes over the
+// ballots (about 60 us).  The share is what a pair took when an item's row
+// was found by a search (5-6 ps); the accumulation takes 2.4 ps at n = 10^6
+// top-20 and 2.7 ps at n = 15553 top-150, so close to the border the dense
+// route still runs where pairs would be faster.
 constexpr double DENSE_RATE = 45.0;            // lane operations per picosecond
 constexpr double ATOMIC_PAIR_COST = 66.0;
 constexpr double BUCKETED_PAIR_COST = 6.0;
@@ -1366,11 +1369,12 @@ __global__ __launch_bounds__(1024) void k_occ_scan(OccArgs a) {
 // first ids while it writes this one's row, and clears the LDS row as it reads
 // it out.  Ids come 16 bytes at a time at any alignment, as a scattered load
 // costs its lane the same whatever its width.
-//   m = 14187, 15553 ballots of up to 150 uint16 ids:  916 -> 464 us
-//   m = 16384, 1M ballots of up to 20, int32 d:        560 -> 550
-//   m = 32768, 200000 ballots of up to 30, int32 d:   1506 -> 869 (1073 through the caches)
-//   m = 6007, 100003 ballots of up to 12 int32 ids:    114 -> 49
-// (a workgroup per item, its row found by a binary search.)
+//   m = 14187, 15553 ballots of 150 uint16 ids, half cut short:  508 -> 314 us
+//   m = 16384, 1M ballots of 20 uint16 ids, int32 d:             547 -> 465
+//   m = 32768, 200000 ballots of 30 uint16 ids, int32 d:        1434 -> 824
+//   m = 6007, 100003 ballots of 12 int32 ids, int32 d:           110 -> 45
+// (before: a workgroup per item, its row found by a binary search.)  Rows of
+// d go out as streaming stores: through the caches the third took 1073.
 //
 // Ballots longer than the first pieces are read one occurrence after the
 // other, the next pieces in flight while these are added.  Reading a thread's
