@@ -14,8 +14,9 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 // last, if the array is not aligned) are put together entry by entry; in their
 // place every lane loads `spare`, the array's first piece that lies inside, so
 // that the loads stay unconditional (an array without one is read entry by
-// entry altogether).
-template <bool I32>
+// entry altogether).  LONG: rows of more than 64 entries; the row's second
+// piece lies inside the row and stands in, with no further address to keep.
+template <bool I32, bool LONG = false>
 struct RowPieces {
     static constexpr int SIZE = I32 ? 4 : 2, PER = 16 / SIZE;
     const char *lo, *hi, *at;  // the ballot array, and the row's first piece
@@ -25,11 +26,11 @@ struct RowPieces {
         lo = static_cast<const char *>(ballots);
         hi = lo + n * L * SIZE;
         const char *p = lo + row * L * SIZE;
-        at = p - (reinterpret_cast<uintptr_t>(p) & 15);
+        at = reinterpret_cast<const char *>(reinterpret_cast<uintptr_t>(p) & ~(uintptr_t)15);
         head = (int32_t)(p - at) / SIZE;
         count = (head + L + PER - 1) / PER;
-        spare = lo + (-reinterpret_cast<uintptr_t>(lo) & 15);
-        if (hi - spare < 16) spare = nullptr;
+        spare = LONG ? at + 16 : lo + (-reinterpret_cast<uintptr_t>(lo) & 15);
+        if (!LONG && hi - spare < 16) spare = nullptr;
     }
     __host__ __device__ const char *piece(int32_t j) const { return at + 16 * (int64_t)(j < count ? j : count - 1); }
     __host__ __device__ bool inside(const char *p) const { return p >= lo && p + 16 <= hi; }
@@ -38,9 +39,9 @@ struct RowPieces {
     // pieces j, j + 64, .. of a lane, in flight together
     template <int FLY>
     __host__ __device__ void load(v4u (&x)[FLY], int32_t j) const {
-        if (spare)
+        if (LONG || spare)
             for (int u = 0; u < FLY; ++u) x[u] = *reinterpret_cast<const v4u *>(source(piece(j + 64 * u)));
-        if (!spare || !inside(at) || !inside(piece(count - 1)))
+        if ((!LONG && !spare) || !inside(at) || !inside(piece(count - 1)))
             for (int u = 0; u < FLY; ++u) {
                 const char *p = piece(j + 64 * u);
                 if (inside(p)) continue;

@@ -7,9 +7,9 @@
 
 #include "../paper_2505_12976_amd/csrc/row_pieces.h"
 
-template <bool I32>
+template <bool I32, bool LONG>
 static bool check(int n, int L, int shift) {
-    using P = RowPieces<I32>;
+    using P = RowPieces<I32, LONG>;
     using Id = typename std::conditional<I32, uint32_t, uint16_t>::type;
     constexpr int FLY = 3;
     alignas(16) static Id buffer[4096];
@@ -47,14 +47,19 @@ static bool check(int n, int L, int shift) {
     return true;
 }
 
+static bool both(int n, int L, int shift) {
+    if (!check<false, false>(n, L, shift) || (L > 64 && !check<false, true>(n, L, shift))) return false;
+    return shift >= 4 || (check<true, false>(n, L, shift) && (L <= 64 || check<true, true>(n, L, shift)));
+}
+
 int main() {
     for (int n = 1; n <= 4; ++n)
         for (int L = 1; L <= 70; ++L)
             for (int shift = 0; shift < 8; ++shift)
-                if (!check<false>(n, L, shift) || (shift < 4 && !check<true>(n, L, shift))) return 1;
+                if (!both(n, L, shift)) return 1;
     for (int L : {255, 256, 257, 777})
         for (int shift = 0; shift < 8; ++shift)
-            if (!check<false>(3, L, shift) || (shift < 4 && !check<true>(3, L, shift))) return 1;
+            if (!both(3, L, shift)) return 1;
     printf("ok\n");
     return 0;
 }
