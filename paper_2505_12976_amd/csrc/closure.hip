@@ -621,9 +621,12 @@ int close_padded(schulze_ctx *ctx, hipStream_t s, E *P, int64_t ld, int32_t nb, 
             const int64_t nslots = (int64_t)nb * (2 * nb + 1);
             int32_t *flags = static_cast<int32_t *>(ctx->ws[WS_FLAGS]);
             // early panels and the two-rounds-ahead diagonal while each workgroup
-            // has few tiles per round: at most 20 (uint16) or 8 (int32); measured
-            // on one MI355X: uint16 m = 12288 66.1 -> 62.1 ms, m = 14187 112.8 ->
-            // 111.6 ms, m = 16384 146.4 -> 148 ms (hence off there)
+            // has few tiles per round: at most 20 (uint16) or 8 (int32).  The
+            // limits were drawn on packed integers (m = 16384: 146.4 without, 148
+            // ms with); the present kernels are faster with them above the limits
+            // too.  Without and with, ms, uint16: m = 8192 15.0, 13.8; 12288 47.3,
+            // 45.3; 14187 73.5, 71.4; 16384 108.9, 106.9; int32: 4096 5.40, 4.63;
+            // 6144 15.3, 13.5; 8192 34.5, 33.0
             const int32_t early = (int64_t)nb * nb <= (sizeof(E) == 2 ? 20 : 8) * G ? 1 : 0;
             PersistArgs<E> pa{P,     ld,    nb, static_cast<E *>(ctx->ws[WS_RING]), flags, flags + nslots, ctx->err,
                               (int64_t)1 << 22, early, gate, want, wide};
@@ -1074,6 +1077,9 @@ extern "C" int schulze_closure(schulze_ctx *ctx, void *stream, const void *d, in
     if (bind_device(ctx) != SCHULZE_OK) return SCHULZE_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
     const int tile = ctx->closure_tile;
+    // (borders drawn on packed integers, where they lay; now uint16 64 and 128
+    // wide take 7.3 and 8.6 ms at m = 6144, 11.4 and 10.3 at 7168; int32 4.0 and
+    // 4.6 at 4096, 14.3 and 15.4 at 6144)
     const int bu = tile ? tile : (m >= 6144 ? 128 : 64);  // uint16 tile
     const int bi = tile ? tile : (m >= 2048 ? 128 : 64);  // int32 tile
     const int32_t *di = static_cast<const int32_t *>(d);
