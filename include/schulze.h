@@ -112,9 +112,11 @@ int schulze_get_device_error(schulze_ctx *ctx, void *stream, int32_t *err_host);
  * entry and 10 to 20 MB per thousand candidates of histograms and partial
  * rows).  Small elections use that buffer alone.  A call sizes the workspace
  * for every smaller one of its kind (fewer voters, candidates and listed
- * entries; with voter_weight or without, with L >= m - 1 or below, m up to
- * 16384 or above): such a call allocates nothing and can be captured in a HIP
- * graph.
+ * entries; both with voter_weight or both without, both with L >= m - 1 or both
+ * below, m of both up to 16384 or above): such a call allocates nothing and can
+ * be captured in a HIP graph.  A captured call keeps the workspace's addresses,
+ * here and in the functions below: after a later call that needs more, capture
+ * it again.
  */
 int schulze_pairwise(schulze_ctx *ctx, void *stream, const void *ballots, int ballot_dtype,
                      int64_t n, int32_t L, int32_t m, const uint32_t *voter_weight,
